@@ -123,9 +123,17 @@ typedef struct {
     int32_t sources_per_item;  /* sources per work item: one wavefront's source range (ordered
                                   scheme, >= 64) or a range against a 4-block target group
                                   (symmetric, rounded up to a multiple of 16) */
-    int32_t pair_scheme;       /* 0: default (symmetric where the group fits, else ordered);
+    int32_t pair_scheme;       /* 0: default (d = 1 with none of targets_per_lane, sources_per_item,
+                                  jside_band_groups and kahan_span = 1 given: by modes, below; else
+                                  symmetric where the group fits, else ordered);
                                   1: every ordered pair (i, j) evaluated; 2: symmetric: each unordered
-                                  pair evaluated once, +q to i and -q to j (the kernel is odd) */
+                                  pair evaluated once, +q to i and -q to j (the kernel is odd).
+                                  By modes: the sums over all pairs as a Fourier sum over the extent of
+                                  the system's cloud, O(N) operations in double precision in every
+                                  precision mode, images and truncation below the rounding of the pair
+                                  sums; a cloud too wide for its particle count (about 170 widths b_ell
+                                  for N up to 1000, 700 from N = 4096 on) or with a non-finite particle
+                                  is summed over its ordered pairs that tick */
     int32_t graphs;            /* nonzero: each tick replays a HIP graph captured once per tick
                                   phase (tick % (h_max/h_min)); not used while profiling or with
                                   the surrogate enabled */
@@ -189,7 +197,9 @@ typedef struct {
     int32_t nonfinite;       /* non-finite particles met by the implicit solve, which follows every
                                 update and every ssm_set_state / ssm_state_refresh (sticky) */
     int32_t n_pair_items;    /* work items of the pairwise kernel per tick (phase 0): wavefronts in
-                                the ordered scheme, workgroups in the symmetric scheme */
+                                the ordered scheme, workgroups in the symmetric scheme and by modes
+                                (targets_per_lane, sources_per_item and symmetric then describe the
+                                pair kernels that such a context does not run) */
     int32_t targets_per_lane;
     int32_t sources_per_item;
     int32_t symmetric;       /* 1: symmetric pair scheme, 0: ordered pairs */
@@ -197,7 +207,8 @@ typedef struct {
     int64_t device_bytes;    /* device memory the context holds */
     /* Kernel timing (ssm_profile enabled): HIP events recorded on the context's
      * stream around the launches of the sampled ticks since the last ssm_profile. */
-    int64_t pair_launches;   /* launches of the pairwise kernel */
+    int64_t pair_launches;   /* launches of the pairwise kernel (by modes: of the mode sums, with the
+                                Brownian increments in the same launch) */
     double pair_ms;          /* their summed duration, milliseconds */
     int64_t update_launches; /* launches of the per-particle update (+ implicit solve) kernels */
     double update_ms;

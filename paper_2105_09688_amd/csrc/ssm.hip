@@ -16,6 +16,7 @@
 #include "../../include/ssm.h"
 #include "ssm_surrogate.hpp"
 #include "ssm_small.hpp"
+#include "ssm_modes.hpp"
 
 using namespace ssm;
 
@@ -215,6 +216,7 @@ struct SysHost {
     int64_t blk0, nblk;
     int64_t splits;
     int64_t steps_done;
+    int64_t mode_row0 = 0, mode_rows = 0;  // partial rows of its mode sums
     int64_t win_off = -1;  // offset of its path group's Brownian window (-1: none)
 };
 
@@ -314,6 +316,16 @@ struct ssm_ctx {
     int32_t profile_every = 1;     // bracket the launches of ticks with tick % profile_every == 0
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_pair, ev_update;
     std::vector<hipEvent_t> ev_pool;
+    // mode sums of the interaction in one dimension (ssm_modes.hpp)
+    bool modes = false;             // exact ticks use them in place of the pair kernels
+    int mode_P = 1;                 // particles per thread of a partial row
+    int64_t mode_rows = 0;          // partial rows of all systems
+    bool mode_totals = false;       // the rows are added up by k_mode_total
+    ModeItem* dmitems = nullptr;    // per phase (pair_off / pair_cnt)
+    ModeDom* dom = nullptr;         // [n_sys] the tick's domains
+    double* mode_part = nullptr;    // [mode_rows][kModeVals]
+    double* mode_tot = nullptr;     // [n_sys][kModeVals] (mode_totals)
+    double2* rng = nullptr;         // [nblk_tot] range of the scaled positions of each block
     // persistent runs of small systems (ssm_small.hpp)
     bool small_ok = false;          // eligible: ticks without surrogate, profiling or graphs use it
     SmallTile* dtiles = nullptr;    // [small_grid] workgroup -> (system, tile)
@@ -385,7 +397,8 @@ static void free_ctx(ssm_ctx* c)
     void* bufs[] = {c->x_bound ? nullptr : c->X, c->Y, c->Ys, c->Bp, c->Bpj, c->pairsum, c->psumX, c->psumY, c->dsys, c->dpair, c->dblk, c->dflags, c->dstage,
                     c->dmlp, c->surr, c->rff_part, c->mom, c->err_part, c->dsys_list, c->smean_part, c->smean,
                     c->dtick, c->dW, c->surr_res, c->dnmax, c->dred, c->dsq, c->win, c->dwin_items, c->ymean,
-                    c->jtot, c->dtiles, c->sumY, c->sumX, c->dbar};
+                    c->jtot, c->dtiles, c->sumY, c->sumX, c->dbar,
+                    c->dmitems, c->dom, c->mode_part, c->mode_tot, c->rng};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     recycle_events(c, c->ev_pair);
@@ -560,6 +573,17 @@ static void build_blk_items(const ssm_ctx* c, const std::vector<int>& systems, s
         for (int64_t b = 0; b < c->sys[s].nblk; ++b) out.push_back(BlkItem{s, (int32_t)b});
 }
 
+// The mode-sum items of the listed systems, one per partial row.
+static void build_mode_items(const ssm_ctx* c, const std::vector<int>& systems, std::vector<ModeItem>& out)
+{
+    const int64_t per = (int64_t)kBlk * c->mode_P;
+    for (int s : systems) {
+        const SysHost& S = c->sys[s];
+        for (int64_t r = 0; r < S.mode_rows; ++r)
+            out.push_back(ModeItem{s, (int32_t)(S.mode_row0 + r), (int32_t)(r * per), (int32_t)std::min<int64_t>(per, S.N - r * per)});
+    }
+}
+
 // The pair sums of phase ph's items into the partial-sum buffers: one launch,
 // or (banded j-side rows) one launch per band followed by the fold of that
 // band's rows into jtot for every stepping particle.
@@ -643,6 +667,45 @@ static ssm_status launch_window(ssm_ctx* c, int64_t t0, const int64_t* tdev)
     return SSM_OK;
 }
 
+// The tick's mode sums (d = 1): the partial rows, with the Brownian sums and
+// the means of mu^Y in the same launch, and their totals.
+template <typename T>
+static ssm_status launch_modes(ssm_ctx* c, int64_t ph, const int64_t* tdev, bool sums_only)
+{
+    const BlkItem* items = c->dblk + c->blk_off[ph];
+    const int nm = (int)c->pair_cnt[ph];
+    const int n_main = nm + (sums_only ? 0 : (int)(c->blk_cnt[ph] * c->bm_lanes));
+    const YMeanJob job{c->dsys_list + c->sys_list_off[ph],
+                       c->needs_ybar && !sums_only ? (int)c->sys_list_cnt[ph] : 0, c->psumY, c->nblk_tot, c->ymean};
+#define SSM_MODES(PV, LPV)                                                                                             \
+    hipLaunchKernelGGL((k_modes<T, PV, LPV>), dim3((unsigned)(n_main + job.n)), dim3(kBlk), 0, c->stream, nm, n_main,  \
+                       (const ModeItem*)c->dmitems + c->pair_off[ph], items, c->dsys, c->coef, c->P, (const T*)c->Ys,  \
+                       (const double2*)c->rng, c->dom, c->mode_part, c->pairsum, c->tick, tdev, (const double*)c->win, \
+                       c->dW, job)
+#define SSM_MODES_LP(LPV)                                 \
+    do {                                                  \
+        if (c->mode_P == 1) { SSM_MODES(1, LPV); }        \
+        else { SSM_MODES(4, LPV); }                       \
+    } while (0)
+    switch (c->bm_lanes) {
+        case 16: SSM_MODES_LP(16); break;
+        case 8: SSM_MODES_LP(8); break;
+        case 4: SSM_MODES_LP(4); break;
+        case 2: SSM_MODES_LP(2); break;
+        default: SSM_MODES_LP(1); break;
+    }
+#undef SSM_MODES_LP
+#undef SSM_MODES
+    HIP_TRY(hipGetLastError());
+    if (c->mode_totals) {
+        hipLaunchKernelGGL(k_mode_total, dim3((unsigned)c->sys_list_cnt[ph], 4), dim3(kBlk), 0, c->stream,
+                           c->dsys_list + c->sys_list_off[ph], c->dsys, (const ModeDom*)c->dom,
+                           (const double*)c->mode_part, c->mode_tot);
+        HIP_TRY(hipGetLastError());
+    }
+    return SSM_OK;
+}
+
 template <typename T>
 static ssm_status launch_tick(ssm_ctx* c, bool capture)
 {
@@ -676,7 +739,7 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
             e1 = take_event(c);
             if (e0) HIP_TRY(hipEventRecord(e0, c->stream));
         }
-        ssm_status st = launch_pairs<T>(c, ph);
+        ssm_status st = c->modes ? launch_modes<T>(c, ph, tdev, false) : launch_pairs<T>(c, ph);
         if (st != SSM_OK) return st;
         if (prof) {
             if (e1) HIP_TRY(hipEventRecord(e1, c->stream));
@@ -696,50 +759,59 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
             if (e0) HIP_TRY(hipEventRecord(e0, c->stream));
         }
         const BlkItem* items = c->dblk + c->blk_off[ph];
-        // Brownian sums of the step, and on exact ticks the combine of the pair
-        // partials in the same launch (k_prep)
-        const bool comb = c->has_pair && run_exact;
-        const int ncb = comb ? (int)(nb * 4) : 0;
-        const int n_main = (int)(ncb + nb * c->bm_lanes);
-        // the stepping systems' means of mu^Y, when b or sigma needs them
-        const YMeanJob job{c->dsys_list + c->sys_list_off[ph], c->needs_ybar ? (int)c->sys_list_cnt[ph] : 0,
-                           c->psumY, c->nblk_tot, c->ymean};
-        const unsigned gb = (unsigned)(n_main + job.n);
+        if (c->modes && run_exact) {
+            hipLaunchKernelGGL((k_update_modes<T>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, items, c->dsys, c->coef,
+                               c->P, c->tick, tdev, X, Y, Ys, (const ModeDom*)c->dom,
+                               (const double*)(c->mode_totals ? c->mode_tot : c->mode_part), c->mode_totals ? 1 : 0,
+                               c->pairsum, (const double*)c->dW, c->needs_ybar ? (const double*)c->ymean : nullptr,
+                               c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng);
+            HIP_TRY(hipGetLastError());
+        } else {
+            // Brownian sums of the step, and on exact ticks the combine of the pair
+            // partials in the same launch (k_prep)
+            const bool comb = c->has_pair && run_exact;
+            const int ncb = comb ? (int)(nb * 4) : 0;
+            const int n_main = (int)(ncb + nb * c->bm_lanes);
+            // the stepping systems' means of mu^Y, when b or sigma needs them
+            const YMeanJob job{c->dsys_list + c->sys_list_off[ph], c->needs_ybar ? (int)c->sys_list_cnt[ph] : 0,
+                               c->psumY, c->nblk_tot, c->ymean};
+            const unsigned gb = (unsigned)(n_main + job.n);
 #define SSM_BM(LPV)                                                                                                   \
-    if (comb) {                                                                                                       \
-        SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_prep<T, D, LPV>), dim3(gb), dim3(kBlk), 0, c->stream, ncb, n_main,    \
-                                             items, c->dsys, c->coef, c->P, (const T*)c->Bp, (const T*)c->Bpj,        \
-                                             (const double*)c->jtot, c->pairsum, c->tick, tdev, (const double*)c->win, \
-                                             c->dW, job));                                                            \
-    } else {                                                                                                          \
-        SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_brownian_sum<D, LPV, (sizeof(T) == 4)>), dim3(gb), dim3(kBlk), 0,    \
-                                             c->stream, n_main,                                                       \
-                                             items, c->dsys, c->coef, c->P, c->tick, tdev, (const double*)c->win,     \
-                                             c->dW, job));                                                            \
-    }
-        switch (c->bm_lanes) {
-            case 16: SSM_BM(16); break;
-            case 8: SSM_BM(8); break;
-            case 4: SSM_BM(4); break;
-            case 2: SSM_BM(2); break;
-            default: SSM_BM(1); break;
+        if (comb) {                                                                                                       \
+            SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_prep<T, D, LPV>), dim3(gb), dim3(kBlk), 0, c->stream, ncb, n_main,    \
+                                                 items, c->dsys, c->coef, c->P, (const T*)c->Bp, (const T*)c->Bpj,        \
+                                                 (const double*)c->jtot, c->pairsum, c->tick, tdev, (const double*)c->win, \
+                                                 c->dW, job));                                                            \
+        } else {                                                                                                          \
+            SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_brownian_sum<D, LPV, (sizeof(T) == 4)>), dim3(gb), dim3(kBlk), 0,    \
+                                                 c->stream, n_main,                                                       \
+                                                 items, c->dsys, c->coef, c->P, c->tick, tdev, (const double*)c->win,     \
+                                                 c->dW, job));                                                            \
         }
+            switch (c->bm_lanes) {
+                case 16: SSM_BM(16); break;
+                case 8: SSM_BM(8); break;
+                case 4: SSM_BM(4); break;
+                case 2: SSM_BM(2); break;
+                default: SSM_BM(1); break;
+            }
 #undef SSM_BM
-        HIP_TRY(hipGetLastError());
-        SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_update<T, D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream,
-                                             items, c->dsys, c->coef, c->P, c->tick, tdev, X, Y, Ys, c->pairsum, c->surr,
-                                             c->smean, use_surr,
-                                             make_float4((float)c->surr_gain[0], (float)c->surr_gain[1],
-                                                         (float)c->surr_gain[2], (float)c->surr_gain[3]),
-                                             (use_surr && c->surr_mode == SSM_SURR_RESIDUAL && c->surr_res_valid)
-                                                 ? c->surr_res : nullptr,
-                                             c->dW, c->needs_ybar ? (const double*)c->ymean : nullptr,
-                                             c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax));
-        HIP_TRY(hipGetLastError());
+            HIP_TRY(hipGetLastError());
+            SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_update<T, D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream,
+                                                 items, c->dsys, c->coef, c->P, c->tick, tdev, X, Y, Ys, c->pairsum, c->surr,
+                                                 c->smean, use_surr,
+                                                 make_float4((float)c->surr_gain[0], (float)c->surr_gain[1],
+                                                             (float)c->surr_gain[2], (float)c->surr_gain[3]),
+                                                 (use_surr && c->surr_mode == SSM_SURR_RESIDUAL && c->surr_res_valid)
+                                                     ? c->surr_res : nullptr,
+                                                 c->dW, c->needs_ybar ? (const double*)c->ymean : nullptr,
+                                                 c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng));
+            HIP_TRY(hipGetLastError());
+        }
         if (!c->fused) {
             SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_newton<T, D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream,
                                                  items, c->dsys, c->coef, c->P, c->tick, tdev, X, Y, Ys,
-                                                 c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax));
+                                                 c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng));
             HIP_TRY(hipGetLastError());
         }
         if (prof) {
@@ -996,10 +1068,12 @@ static ssm_status refresh_after_small(ssm_ctx* c)
     const int64_t tick_arg = c->tick - 1;
     if (c->prec == SSM_FP64) {
         SSM_DISPATCH_D(c->d, hipLaunchKernelGGL((k_ysums<double, D>), g, dim3(kBlk), 0, c->stream, items, c->dsys,
-                                                c->P, tick_arg, (const double*)c->Y, c->psumY, c->nblk_tot));
+                                                c->P, tick_arg, (const double*)c->Y, c->coef.coord_scale, c->psumY, c->nblk_tot,
+                                                c->rng));
     } else {
         SSM_DISPATCH_D(c->d, hipLaunchKernelGGL((k_ysums<float, D>), g, dim3(kBlk), 0, c->stream, items, c->dsys,
-                                                c->P, tick_arg, (const float*)c->Y, c->psumY, c->nblk_tot));
+                                                c->P, tick_arg, (const float*)c->Y, c->coef.coord_scale, c->psumY, c->nblk_tot,
+                                                c->rng));
     }
     HIP_TRY(hipGetLastError());
     c->psum_stale = false;
@@ -1017,7 +1091,7 @@ static ssm_status launch_init(ssm_ctx* c)
     HIP_TRY(hipGetLastError());
     SSM_DISPATCH_D(c->d, hipLaunchKernelGGL((k_newton<T, D>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys,
                                             c->coef, c->P, (int64_t)-1, (const int64_t*)nullptr, (const T*)c->X, (T*)c->Y, (T*)c->Ys,
-                                            c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax));
+                                            c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng));
     HIP_TRY(hipGetLastError());
     return SSM_OK;
 }
@@ -1185,6 +1259,13 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         if (cfg->pair_scheme == 2) { free_ctx(c); return fail(SSM_ERR_INVALID, "symmetric scheme: targets_per_lane too large for this d and precision (64 x R x 4 x d must be <= " + std::to_string(sym_lds_for(f64, c->d)) + ")"); }
         c->sym = false;
     }
+    // one dimension, and no tiling or scheme of the pair kernels asked for: the
+    // interaction by its modes, at every size.  FP32-compensated ticks, pair
+    // kernels against modes: N = 8191 11.7 and 9.3 us, N = 2^16 345 and 9.5 us
+    // (FP64 1300 and 9.4), 320 systems of 2^10 .. 2^16 7970 and 139 us; below
+    // that both are the launches' latency
+    c->modes = c->d == 1 && c->has_pair && !c->kpair && cfg->targets_per_lane == 0 && cfg->sources_per_item == 0 &&
+               cfg->pair_scheme == 0 && cfg->jside_band_groups == 0;
     for (int attempt = 0; attempt < 2; ++attempt) {
         std::vector<int64_t> Ns;
         for (auto& S : c->sys) Ns.push_back(S.N);
@@ -1197,7 +1278,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         // the requested bands
         c->band = 0;
         c->n_bands = 1;
-        if (c->sym) {
+        if (c->sym && !c->modes) {
             const int64_t group = 64 * (int64_t)c->R * kWaves;
             int64_t groups = 0;
             for (int64_t N : Ns) groups = std::max(groups, (N + group - 1) / group);
@@ -1228,7 +1309,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         }
         c->max_splits = 1;
         c->nb_max = 0;
-        for (int s = 0; s < (int)c->sys.size(); ++s) {
+        for (int s = 0; s < (int)c->sys.size() && !c->modes; ++s) {
             std::vector<std::pair<int64_t, PairItem>> scratch;
             int64_t nb = 0;
             c->sys[s].splits = plan_system(s, c->sys[s].N, c->R, c->sym, c->L, scratch, &nb);
@@ -1283,7 +1364,26 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         }
     }
 
+    // mode sums: a partial row per 256 particles, per 1024 where there are
+    // enough of them to fill the chip with those (256 compute units x 2 blocks)
+    if (c->modes) {
+        int64_t total = 0, reads = 0;
+        for (auto& S : c->sys) total += S.N;
+        c->mode_P = total > 2 * 256 * 1024 ? 4 : 1;
+        for (auto& S : c->sys) {
+            const int64_t rows = (S.N + kBlk * c->mode_P - 1) / (kBlk * c->mode_P);
+            S.mode_row0 = c->mode_rows;
+            S.mode_rows = rows;
+            c->mode_rows += rows;
+            reads += rows * S.nblk;
+        }
+        // every block of the update adds its system's rows; past 2^17 rows read
+        // in a tick one launch more that adds them once is cheaper
+        c->mode_totals = reads > 2 * 65536;
+    }
+
     // work lists per phase
+    std::vector<ModeItem> mitems;
     std::vector<PairItem> pairs;
     std::vector<BlkItem> blks;
     std::vector<int32_t> sys_lists;
@@ -1307,8 +1407,14 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
             if (ph % c->sys[s].stride == 0) act.push_back(s);
         c->pair_off[ph] = (int64_t)pairs.size();
         std::vector<int64_t> boff;
-        if (c->has_pair) build_pair_items(c, act, pairs, c->band > 0 ? &boff : nullptr);
-        c->pair_cnt[ph] = (int64_t)pairs.size() - c->pair_off[ph];
+        if (c->modes) {
+            c->pair_off[ph] = (int64_t)mitems.size();
+            build_mode_items(c, act, mitems);
+            c->pair_cnt[ph] = (int64_t)mitems.size() - c->pair_off[ph];
+        } else {
+            if (c->has_pair) build_pair_items(c, act, pairs, c->band > 0 ? &boff : nullptr);
+            c->pair_cnt[ph] = (int64_t)pairs.size() - c->pair_off[ph];
+        }
         c->pair_band_off.push_back(boff);
         c->blk_off[ph] = (int64_t)blks.size();
         build_blk_items(c, act, blks);
@@ -1346,6 +1452,8 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         x.sym_B = c->sym ? 64 * c->R * kWaves : 0;
         x.sym_L = c->sym ? (int32_t)c->L : 0;
         x.h = S.h;
+        x.mode_rows = (int32_t)S.mode_rows;
+        x.mode_row0 = (int32_t)S.mode_row0;
         x.win_off = S.win_off >= 0 ? S.win_off : 0;
         x.win_W = S.win_off >= 0 ? (int32_t)c->max_stride : 0;
         x.pair_scale = c->has_pair ? cfg->b_g / ((double)S.N * cf.coord_scale) : 0.0;
@@ -1355,14 +1463,22 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     ALLOC(c->X, field);
     ALLOC(c->Y, field);
     ALLOC(c->Ys, field);
-    ALLOC(c->Bp, c->has_pair ? (size_t)c->max_splits * c->d * c->P * elt(c->prec) : 0);
+    const bool direct = c->has_pair && !c->modes;
+    ALLOC(c->Bp, direct ? (size_t)c->max_splits * c->d * c->P * elt(c->prec) : 0);
     ALLOC(c->pairsum, c->has_pair ? (size_t)c->d * c->P * sizeof(double) : 0);
-    ALLOC(c->Bpj, (c->has_pair && c->sym) ? (size_t)(c->band > 0 ? c->band : c->nb_max) * c->d * c->P * elt(c->prec) : 0);
+    ALLOC(c->Bpj, (direct && c->sym) ? (size_t)(c->band > 0 ? c->band : c->nb_max) * c->d * c->P * elt(c->prec) : 0);
     if (c->band > 0) ALLOC(c->jtot, (size_t)c->d * c->P * sizeof(double));
     ALLOC(c->psumX, 2 * (size_t)(c->d + 1) * c->nblk_tot * sizeof(double));
     ALLOC(c->psumY, 2 * (size_t)c->d * c->nblk_tot * sizeof(double));
     ALLOC(c->dsys, sd.size() * sizeof(SysDev));
     ALLOC(c->dpair, std::max<size_t>(pairs.size(), 1) * sizeof(PairItem));
+    if (c->modes) {
+        ALLOC(c->dmitems, mitems.size() * sizeof(ModeItem));
+        ALLOC(c->dom, c->sys.size() * sizeof(ModeDom));
+        ALLOC(c->mode_part, (size_t)c->mode_rows * kModeVals * sizeof(double));
+        if (c->mode_totals) ALLOC(c->mode_tot, c->sys.size() * kModeVals * sizeof(double));
+        ALLOC(c->rng, (size_t)c->nblk_tot * sizeof(double2));
+    }
     ALLOC(c->dblk, blks.size() * sizeof(BlkItem));
     ALLOC(c->dflags, sizeof(Flags));
     ALLOC(c->dnmax, (size_t)c->nblk_tot * kSlotsPerBlk * sizeof(int32_t));
@@ -1388,6 +1504,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
 #undef ALLOC
     hipError_t he = hipMemcpyAsync(c->dsys, sd.data(), sd.size() * sizeof(SysDev), hipMemcpyHostToDevice, c->stream);
     if (he == hipSuccess && !pairs.empty()) he = hipMemcpyAsync(c->dpair, pairs.data(), pairs.size() * sizeof(PairItem), hipMemcpyHostToDevice, c->stream);
+    if (he == hipSuccess && !mitems.empty()) he = hipMemcpyAsync(c->dmitems, mitems.data(), mitems.size() * sizeof(ModeItem), hipMemcpyHostToDevice, c->stream);
     if (he == hipSuccess) he = hipMemcpyAsync(c->dblk, blks.data(), blks.size() * sizeof(BlkItem), hipMemcpyHostToDevice, c->stream);
     if (he == hipSuccess) he = hipMemcpyAsync(c->dsys_list, sys_lists.data(), sys_lists.size() * sizeof(int32_t), hipMemcpyHostToDevice, c->stream);
     if (he == hipSuccess && c->win_items > 0)
@@ -1477,7 +1594,7 @@ template <typename T>
 __global__ void k_moments_part(const T* __restrict__ X, int64_t P, int64_t off, int64_t N, int d,
                                const double* __restrict__ mean, double* __restrict__ part)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     for (int k = 0; k < d; ++k) {
         const double m = mean ? mean[k] : 0.0;
         double s = 0.0;
@@ -1493,7 +1610,7 @@ __global__ void k_moments_part(const T* __restrict__ X, int64_t P, int64_t off, 
 // out[k] = scale * (sum over b < nb of part[k nb + b]), one block.
 __global__ void k_red_final(const double* __restrict__ part, int nb, int d, double scale, double* __restrict__ out)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     for (int k = 0; k < d; ++k) {
         double s = 0.0;
         for (int b = threadIdx.x; b < nb; b += kBlk) s += part[k * nb + b];
@@ -1523,7 +1640,7 @@ template <typename TA, typename TB>
 __global__ void k_sqdiff_part(const TA* __restrict__ A, int64_t PA, int64_t offA, const TB* __restrict__ B, int64_t PB,
                               int64_t offB, int64_t N, int d, double* __restrict__ part)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     double s = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * kBlk + threadIdx.x; i < N; i += (int64_t)gridDim.x * kBlk)
         for (int k = 0; k < d; ++k) {
@@ -1623,14 +1740,14 @@ static ssm_status refresh_implicit(ssm_ctx* c, int32_t sys)
                                                     c->P, tick_arg, (const double*)c->X, c->psumX, c->nblk_tot));
         SSM_DISPATCH_D(c->d, hipLaunchKernelGGL((k_newton<double, D>), g, dim3(kBlk), 0, c->stream,
                                                 items, c->dsys, c->coef, c->P, tick_arg, (const int64_t*)nullptr, (const double*)c->X, (double*)c->Y,
-                                                (double*)c->Ys, c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax));
+                                                (double*)c->Ys, c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng));
     } else {
         if (!c->fused)
             SSM_DISPATCH_D(c->d, hipLaunchKernelGGL((k_xsums<float, D>), g, dim3(kBlk), 0, c->stream, items, c->dsys,
                                                     c->P, tick_arg, (const float*)c->X, c->psumX, c->nblk_tot));
         SSM_DISPATCH_D(c->d, hipLaunchKernelGGL((k_newton<float, D>), g, dim3(kBlk), 0, c->stream,
                                                 items, c->dsys, c->coef, c->P, tick_arg, (const int64_t*)nullptr, (const float*)c->X, (float*)c->Y,
-                                                (float*)c->Ys, c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax));
+                                                (float*)c->Ys, c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng));
     }
     HIP_TRY(hipGetLastError());
     return SSM_OK;
@@ -2104,6 +2221,31 @@ extern "C" ssm_status ssm_surrogate_predict(ssm_ctx* c, int32_t sys, double* out
     return ssm_sync(c);
 }
 
+// The exact pair term of every system at the current Y* into pairsum (phase 0
+// lists them all).
+template <typename T>
+static ssm_status launch_exact(ssm_ctx* c)
+{
+    const BlkItem* items = c->dblk + c->blk_off[0];
+    const unsigned nb = (unsigned)c->blk_cnt[0];
+    if (c->modes) {
+        ssm_status st = launch_modes<T>(c, 0, nullptr, true);
+        if (st != SSM_OK) return st;
+        hipLaunchKernelGGL((k_mode_eval<T>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,
+                           (const ModeDom*)c->dom, (const double*)(c->mode_totals ? c->mode_tot : c->mode_part),
+                           c->mode_totals ? 1 : 0, c->pairsum);
+        HIP_TRY(hipGetLastError());
+        return SSM_OK;
+    }
+    ssm_status st = launch_pairs<T>(c, 0);
+    if (st != SSM_OK) return st;
+    SSM_DISPATCH_D(c->d, hipLaunchKernelGGL((k_combine<T, D>), dim3(nb * 4), dim3(64 * kCombineWaves), 0, c->stream, items,
+                                            c->dsys, c->P, (const T*)c->Bp, (const T*)c->Bpj, (const double*)c->jtot,
+                                            c->pairsum));
+    HIP_TRY(hipGetLastError());
+    return SSM_OK;
+}
+
 extern "C" ssm_status ssm_surrogate_samples(ssm_ctx* c, int32_t sys, int64_t n, uint64_t seed, float* U, float* Tt)
 {
     if (!c || !U || !Tt || n < 1) return fail(SSM_ERR_INVALID, "bad argument");
@@ -2111,28 +2253,21 @@ extern "C" ssm_status ssm_surrogate_samples(ssm_ctx* c, int32_t sys, int64_t n, 
     if (!c->has_pair) return fail(SSM_ERR_STATE, "b_g is 0: no pairwise term to sample");
     ssm_status st = ensure_surrogate_buffers(c);
     if (st != SSM_OK) return st;
+    if (c->modes && c->psum_stale) {  // the blocks' ranges lag after persistent ticks
+        st = (c->prec == SSM_FP64) ? refresh_after_small<double>(c) : refresh_after_small<float>(c);
+        if (st != SSM_OK) return st;
+    }
     // exact pair sums and RFF moments of the current Y* of every system (phase-0 lists hold all)
-    const int64_t np = c->pair_cnt[0], nb = c->blk_cnt[0];
+    const int64_t nb = c->blk_cnt[0];
     const int d = c->d;
-    (void)np;
     if (c->prec == SSM_FP64) {
-        st = launch_pairs<double>(c, 0);
+        st = launch_exact<double>(c);
         if (st != SSM_OK) return st;
         SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_rff_partial<double, D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, c->dblk + c->blk_off[0], c->dsys, c->P, (const double*)c->Y, c->rff, c->rff_part));
     } else {
-        st = launch_pairs<float>(c, 0);
+        st = launch_exact<float>(c);
         if (st != SSM_OK) return st;
         SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_rff_partial<float, D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, c->dblk + c->blk_off[0], c->dsys, c->P, (const float*)c->Y, c->rff, c->rff_part));
-    }
-    HIP_TRY(hipGetLastError());
-    if (c->prec == SSM_FP64) {
-        SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_combine<double, D>), dim3((unsigned)(nb * 4)), dim3(64 * kCombineWaves), 0,
-                                             c->stream, c->dblk + c->blk_off[0], c->dsys, c->P, (const double*)c->Bp,
-                                             (const double*)c->Bpj, (const double*)c->jtot, c->pairsum));
-    } else {
-        SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_combine<float, D>), dim3((unsigned)(nb * 4)), dim3(64 * kCombineWaves), 0,
-                                             c->stream, c->dblk + c->blk_off[0], c->dsys, c->P, (const float*)c->Bp,
-                                             (const float*)c->Bpj, (const double*)c->jtot, c->pairsum));
     }
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_rff_final, dim3((unsigned)c->sys_list_cnt[0], 2 * kRff), dim3(kBlk), 0, c->stream, c->dsys_list + c->sys_list_off[0], c->dsys, c->rff_part, c->mom);

@@ -14,6 +14,8 @@
 //              the next step in the same thread;
 //   k_newton : the implicit step on its own (first step, and every step when
 //              v depends on mu^X, whose moments need the whole new cloud).
+// In one dimension the default takes k_modes and k_update_modes
+// (ssm_modes.hpp) in place of the first three.
 // A surrogate tick replaces the first two by the network's kernels
 // (ssm_surrogate.hpp) and k_brownian_sum.
 // Layout: component-major [d][P] arrays over all systems, each system starting
@@ -26,6 +28,7 @@
 namespace ssm {
 
 constexpr int kBlk = 256;      // particles per update block (and system alignment)
+constexpr int kRedLds = 2 * kBlk / 64;  // doubles of LDS of the block reductions
 constexpr int kWaves = 4;      // wavefronts per pair block
 constexpr int kUnroll = 8;     // sources per inner-loop iteration
 // Sources summed plainly (per lane and target) before a compensated add: 256
@@ -57,12 +60,12 @@ struct SysDev {
     int32_t splits;     // i-side partial sums to combine (ordered-pair scheme)
     int32_t sym_B;      // symmetric scheme: target block size (0: ordered-pair scheme)
     int32_t sym_L;      // symmetric scheme: sources per off-diagonal work item
-    int32_t pad;
+    int32_t mode_rows;  // mode sums (ssm_modes.hpp): partial rows of the system
     double h;           // time step
     double pair_scale;  // b_g / (N c): scaled pair sums -> b's pair term
     int64_t win_off;    // shared Brownian window of the system's path group (win_W > 0)
     int32_t win_W;      // ticks per window (0: the system draws its own increments)
-    int32_t pad2;
+    int32_t mode_row0;  // mode sums: its first partial row
 };
 
 struct PairItem {
@@ -285,21 +288,103 @@ __device__ __forceinline__ int64_t tick_of(const int64_t* tick_dev, int64_t tick
     return tick_dev ? *tick_dev : tick_arg;
 }
 
-// Fixed-order tree sum of one double per thread over a kBlk-thread block.
-// Returns the block total in every thread.  `red` is kBlk doubles of LDS.
+// Lane permutations within each row of 16 lanes (gfx9 DPP controls):
+// exchange with lane ^ 1 and lane ^ 2 (quad_perm), mirror within 8 and 16.
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+__device__ __forceinline__ double readlane64(double v, int lane)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// Sum over the 64 lanes of a wavefront in a fixed order; every lane gets it.
+// Within each row of 16 lanes, four DPP steps (pairs, quads, eights,
+// sixteens) leave the row's sum in all its lanes; the four row sums are then
+// read and added as (row 0 + row 1) + (row 2 + row 3).  DPP instead of LDS
+// shuffles: this sum sits on the latency chain of the update.
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v += dpp64<kDppXor1>(v);
+    v += dpp64<kDppXor2>(v);
+    v += dpp64<kDppHalfMirror>(v);
+    v += dpp64<kDppMirror>(v);
+    return (readlane64(v, 0) + readlane64(v, 16)) + (readlane64(v, 32) + readlane64(v, 48));
+}
+
+// Largest value over the lanes of a wavefront, the same way.
+__device__ __forceinline__ int wave_max(int v)
+{
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, kDppXor1, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, kDppXor2, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, kDppHalfMirror, 0xF, 0xF, false));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, kDppMirror, 0xF, 0xF, false));
+    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+
+// Fixed-order sum of one double per thread over a kBlk-thread block, in every
+// thread: each wavefront's sum, then the four of them.  Two barriers in place
+// of the ten of a tree over LDS, which were most of a block's time in the
+// kernels that end in these sums.  `red` is kBlk / 64 doubles of LDS at least.
 __device__ __forceinline__ double block_sum(double v, double* red)
 {
-    const int t = threadIdx.x;
-    red[t] = v;
+    const double w = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = w;
     __syncthreads();
-#pragma unroll
-    for (int s = kBlk / 2; s > 0; s >>= 1) {
-        if (t < s) red[t] = red[t] + red[t + s];
-        __syncthreads();
-    }
-    const double total = red[0];
+    const double total = (red[0] + red[1]) + (red[2] + red[3]);
     __syncthreads();
     return total;
+}
+
+// Lowest (a) and highest (b) value over a kBlk-thread block, in every thread.
+// `red` is 2 kBlk / 64 doubles of LDS.
+__device__ __forceinline__ void block_range(double& a, double& b, double* red)
+{
+    a = fmin(a, dpp64<kDppXor1>(a));
+    b = fmax(b, dpp64<kDppXor1>(b));
+    a = fmin(a, dpp64<kDppXor2>(a));
+    b = fmax(b, dpp64<kDppXor2>(b));
+    a = fmin(a, dpp64<kDppHalfMirror>(a));
+    b = fmax(b, dpp64<kDppHalfMirror>(b));
+    a = fmin(a, dpp64<kDppMirror>(a));
+    b = fmax(b, dpp64<kDppMirror>(b));
+    a = fmin(fmin(readlane64(a, 0), readlane64(a, 16)), fmin(readlane64(a, 32), readlane64(a, 48)));
+    b = fmax(fmax(readlane64(b, 0), readlane64(b, 16)), fmax(readlane64(b, 32), readlane64(b, 48)));
+    constexpr int kW = kBlk / 64;
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = a;
+        red[kW + (threadIdx.x >> 6)] = b;
+    }
+    __syncthreads();
+    a = fmin(fmin(red[0], red[1]), fmin(red[2], red[3]));
+    b = fmax(fmax(red[kW], red[kW + 1]), fmax(red[kW + 2], red[kW + 3]));
+    __syncthreads();
+}
+
+// Range of the scaled positions of a block's particles for the mode sums
+// (ssm_modes.hpp): one (lowest, highest) pair per update block; a non-finite
+// particle makes it infinite, so that the sums of its system run directly.
+__device__ __forceinline__ void store_range(bool valid, double ys, double2* __restrict__ rng, int64_t gb, double* red)
+{
+    double lo = valid ? ys : INFINITY, hi = valid ? ys : -INFINITY;
+    if (valid && !isfinite(ys)) {
+        lo = -INFINITY;
+        hi = INFINITY;
+    }
+    block_range(lo, hi, red);
+    if (threadIdx.x == 0) rng[gb] = make_double2(lo, hi);
 }
 
 // ---------------------------------------------------------------------------
@@ -313,7 +398,7 @@ __global__ __launch_bounds__(kBlk) void k_init(const BlkItem* __restrict__ items
                                                T* __restrict__ Ys, double* __restrict__ psumX,
                                                int64_t nblk_tot)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     const BlkItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
     const int i = it.blk * kBlk + threadIdx.x;
@@ -368,7 +453,7 @@ __device__ __forceinline__ void solve_and_store(const SysDev& S, const Coef& cf,
                                                 T* __restrict__ Y, T* __restrict__ Ys,
                                                 double* __restrict__ psumY_out, int64_t gb,
                                                 int64_t nblk_tot, Flags* flags, int32_t* __restrict__ nmax,
-                                                double* red)
+                                                double2* __restrict__ rng, double* red)
 {
     double w[D], y[D];
 #pragma unroll
@@ -422,6 +507,9 @@ __device__ __forceinline__ void solve_and_store(const SysDev& S, const Coef& cf,
         const double s = block_sum(ysum[k], red);
         if (threadIdx.x == 0) psumY_out[(int64_t)k * nblk_tot + gb] = s;
     }
+    if constexpr (D == 1) {
+        if (rng) store_range(valid, (double)(T)(cf.coord_scale * (double)(T)y[0]), rng, gb, red);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -439,9 +527,9 @@ __global__ __launch_bounds__(kBlk) void k_newton(const BlkItem* __restrict__ ite
                                                  T* __restrict__ Ys,
                                                  const double* __restrict__ psumX,
                                                  double* __restrict__ psumY, int64_t nblk_tot,
-                                                 Flags* flags, int32_t* __restrict__ nmax)
+                                                 Flags* flags, int32_t* __restrict__ nmax, double2* __restrict__ rng)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     const BlkItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
     const int64_t tick = tick_of(tick_dev, tick_arg);
@@ -466,7 +554,7 @@ __global__ __launch_bounds__(kBlk) void k_newton(const BlkItem* __restrict__ ite
         for (int k = 0; k < D; ++k) x[k] = (double)X[k * P + slot];
     }
     solve_and_store<T, D>(S, cf, valid, x, xbar, m2, slot, P, Y, Ys, pY, S.blk0 + it.blk, nblk_tot,
-                          flags, nmax, red);
+                          flags, nmax, rng, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -481,7 +569,7 @@ __global__ __launch_bounds__(kBlk) void k_xsums(const BlkItem* __restrict__ item
                                                 int64_t tick_arg, const T* __restrict__ X,
                                                 double* __restrict__ psumX, int64_t nblk_tot)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     const BlkItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
     const int64_t done = tick_arg < 0 ? 0 : tick_arg / S.stride + 1;
@@ -507,33 +595,19 @@ __global__ __launch_bounds__(kBlk) void k_xsums(const BlkItem* __restrict__ item
 }
 
 // ---------------------------------------------------------------------------
-// k_update: eq. (2.4) for the listed blocks at the tick *tick_dev (the
-// context's device tick counter), with the Brownian increments of
-// k_brownian_sum, then (fused) the implicit step (2.3) of the next step.
+// The update (2.4) of one block at step n of its system, given each thread's
+// pair term, with the Brownian increments dW; then (fused) the implicit step
+// (2.3) of the next step.  All threads of the block must call it.
 // ---------------------------------------------------------------------------
 template <typename T, int D>
-__global__ __launch_bounds__(kBlk) void k_update(const BlkItem* __restrict__ items,
-                                                 const SysDev* __restrict__ sys, Coef cf,
-                                                 int64_t P, int64_t tick_arg,
-                                                 const int64_t* __restrict__ tick_dev,
-                                                 T* __restrict__ X,
-                                                 T* __restrict__ Y, T* __restrict__ Ys,
-                                                 const double* __restrict__ pairsum,
-                                                 const float* __restrict__ surr,
-                                                 const float* __restrict__ surr_mean, int use_surr,
-                                                 float4 surr_gain, const float* __restrict__ surr_res,
-                                                 const double* __restrict__ dWbuf,
-                                                 const double* __restrict__ ymean,
-                                                 double* __restrict__ psumX,
-                                                 double* __restrict__ psumY, int64_t nblk_tot,
-                                                 Flags* flags, int32_t* __restrict__ nmax)
+__device__ __forceinline__ void update_block(const BlkItem it, const SysDev& S, const Coef& cf, int64_t P, int64_t n,
+                                             const double (&pair)[D], T* __restrict__ X, T* __restrict__ Y,
+                                             T* __restrict__ Ys, const double* __restrict__ dWbuf,
+                                             const double* __restrict__ ymean, double* __restrict__ psumX,
+                                             double* __restrict__ psumY, int64_t nblk_tot, Flags* flags,
+                                             int32_t* __restrict__ nmax, double2* __restrict__ rng, double* red)
 {
-    __shared__ double red[kBlk];
-    const BlkItem it = items[blockIdx.x];
-    const SysDev S = sys[it.sys];
-    const int64_t n = tick_of(tick_dev, tick_arg) / S.stride;  // step index of this update
-    const int par_in = (int)(n & 1);
-    const int par_out = par_in ^ 1;
+    const int par_out = (int)(n & 1) ^ 1;
     // mean of mu^Y_n, reduced by the tick's preceding launch (null: the
     // coefficients do not use it)
     double ybar[kMaxD] = {0.0, 0.0, 0.0, 0.0};
@@ -541,8 +615,6 @@ __global__ __launch_bounds__(kBlk) void k_update(const BlkItem* __restrict__ ite
 #pragma unroll
         for (int k = 0; k < D; ++k) ybar[k] = ymean[(int64_t)it.sys * kMaxD + k];
     }
-    (void)par_in;
-
     const int i = it.blk * kBlk + threadIdx.x;
     const bool valid = i < S.N;
     const int64_t slot = S.off + i;
@@ -554,18 +626,7 @@ __global__ __launch_bounds__(kBlk) void k_update(const BlkItem* __restrict__ ite
 #pragma unroll
         for (int k = 0; k < D; ++k) {
             const double y = yv[k];
-            double pair = 0.0;
-            if (use_surr) {
-                // learned surrogate of the pair term, projected to zero net force,
-                // scaled by the gain fitted at the last check and (residual mode)
-                // corrected by the particle's residual stored at the last check
-                const float gk = k == 0 ? surr_gain.x : k == 1 ? surr_gain.y : k == 2 ? surr_gain.z : surr_gain.w;
-                pair = (double)gk * ((double)surr[k * P + slot] - (double)surr_mean[(int64_t)it.sys * kMaxD + k]);
-                if (surr_res) pair += (double)surr_res[k * P + slot];
-            } else if (cf.has_pair) {
-                pair = pairsum[k * P + slot];
-            }
-            double b = cf.b_c0 * y + cf.b_lam * ybar[k] + pair;
+            double b = cf.b_c0 * y + cf.b_lam * ybar[k] + pair[k];
             if (cf.has_lin) {
                 // the linear extension b_const + b_mat y + b_mean o ybar, terms in ascending l
                 b += cf.b_const[k];
@@ -592,7 +653,7 @@ __global__ __launch_bounds__(kBlk) void k_update(const BlkItem* __restrict__ ite
     if (cf.fused) {
         const double zero[kMaxD] = {0.0, 0.0, 0.0, 0.0};
         solve_and_store<T, D>(S, cf, valid, xn, zero, 0.0, slot, P, Y, Ys,
-                              psumY + (int64_t)par_out * D * nblk_tot, gb, nblk_tot, flags, nmax, red);
+                              psumY + (int64_t)par_out * D * nblk_tot, gb, nblk_tot, flags, nmax, rng, red);
     } else {
         double* pX = psumX + (int64_t)par_out * (D + 1) * nblk_tot;
 #pragma unroll
@@ -603,6 +664,53 @@ __global__ __launch_bounds__(kBlk) void k_update(const BlkItem* __restrict__ ite
         const double s2 = block_sum(valid ? n2 : 0.0, red);
         if (threadIdx.x == 0) pX[(int64_t)D * nblk_tot + gb] = s2;
     }
+}
+
+// ---------------------------------------------------------------------------
+// k_update: eq. (2.4) for the listed blocks at the tick *tick_dev (the
+// context's device tick counter), with the pair term of k_prep or the
+// surrogate's prediction and the Brownian increments of k_brownian_sum.
+// ---------------------------------------------------------------------------
+template <typename T, int D>
+__global__ __launch_bounds__(kBlk) void k_update(const BlkItem* __restrict__ items,
+                                                 const SysDev* __restrict__ sys, Coef cf,
+                                                 int64_t P, int64_t tick_arg,
+                                                 const int64_t* __restrict__ tick_dev,
+                                                 T* __restrict__ X,
+                                                 T* __restrict__ Y, T* __restrict__ Ys,
+                                                 const double* __restrict__ pairsum,
+                                                 const float* __restrict__ surr,
+                                                 const float* __restrict__ surr_mean, int use_surr,
+                                                 float4 surr_gain, const float* __restrict__ surr_res,
+                                                 const double* __restrict__ dWbuf,
+                                                 const double* __restrict__ ymean,
+                                                 double* __restrict__ psumX,
+                                                 double* __restrict__ psumY, int64_t nblk_tot,
+                                                 Flags* flags, int32_t* __restrict__ nmax, double2* __restrict__ rng)
+{
+    __shared__ double red[kRedLds];
+    const BlkItem it = items[blockIdx.x];
+    const SysDev S = sys[it.sys];
+    const int64_t n = tick_of(tick_dev, tick_arg) / S.stride;  // step index of this update
+    const int i = it.blk * kBlk + threadIdx.x;
+    const int64_t slot = S.off + i;
+    double pair[D];
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        pair[k] = 0.0;
+        if (i >= S.N) continue;
+        if (use_surr) {
+            // learned surrogate of the pair term, projected to zero net force,
+            // scaled by the gain fitted at the last check and (residual mode)
+            // corrected by the particle's residual stored at the last check
+            const float gk = k == 0 ? surr_gain.x : k == 1 ? surr_gain.y : k == 2 ? surr_gain.z : surr_gain.w;
+            pair[k] = (double)gk * ((double)surr[k * P + slot] - (double)surr_mean[(int64_t)it.sys * kMaxD + k]);
+            if (surr_res) pair[k] += (double)surr_res[k * P + slot];
+        } else if (cf.has_pair) {
+            pair[k] = pairsum[k * P + slot];
+        }
+    }
+    update_block<T, D>(it, S, cf, P, n, pair, X, Y, Ys, dWbuf, ymean, psumX, psumY, nblk_tot, flags, nmax, rng, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -713,7 +821,7 @@ template <int D>
 __device__ __forceinline__ void ymean_block(int q, const YMeanJob& job, const SysDev* __restrict__ sys,
                                             int64_t tick_arg, const int64_t* __restrict__ tick_dev)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     const int s = job.sys_list[q];
     const SysDev S = sys[s];
     const int64_t n = tick_of(tick_dev, tick_arg) / S.stride;

@@ -1,0 +1,431 @@
+// ssm_modes.hpp -- the interaction sums in one dimension, in O(N) operations.
+//
+// In the scaled coordinate s (Ys) the pair term of particle x is
+//   K(x) = sum_j q(s_j - x),   q(z) = z 2^(-z^2) = z e^(-a z^2),  a = ln 2.
+// By Poisson summation, for every period L (k_m = 2 pi m / L),
+//   sum_p q(z + p L) = sum_{m >= 1} c_m sin(k_m z),
+//   c_m = (2 pi / L) / sqrt(4 pi a) (k_m / a) e^(-k_m^2 / (4 a)),
+// exactly.  With L = D + G, D the extent of the system's cloud, the images
+// p != 0 stay below G 2^(-G^2) for every pair, and the modes k_m > kmax below
+// 0.68 e^(-kmax^2 / (4 a)).  G and kmax are taken so that both lie under the
+// rounding of the sums they replace (mode_limits), so what is left is
+//   K(x) = sum_{m <= M} c_m (S_m cos k_m x - C_m sin k_m x),
+//   C_m + i S_m = sum_j e^(i k_m s_j)   (positions from the cloud's centre):
+// one pass over the particles for the 2 M sums and one to evaluate them,
+// M = kmax L / (2 pi), in place of N^2 / 2 exponentials.  All of it runs in
+// double precision in every precision mode.
+//
+// A cloud that is too wide for its particle count (mode_domain), or holds a
+// particle that is not finite, is summed directly in place of its modes
+// (mode_direct): every ordered pair, as the small-system kernel does, so NaN
+// and infinities spread as they do there.
+//
+// An exact tick is two launches: k_modes (the sums' partial rows; the Brownian
+// increments and the means of mu^Y, which do not depend on them, in further
+// blocks) and k_update_modes (adds the rows, evaluates, updates, solves the
+// next implicit step and leaves the new cloud's range).  At N = 2^16 a tick
+// takes 9.5 us where the symmetric pair sums alone took 345 (FP32-compensated)
+// or 1300 us (FP64); it is bound by the two dependent launches and the
+// latencies inside them, the arithmetic being about 1 us of the chip.  The domain depends on
+// the current positions only, so a resumed run equals an uninterrupted one
+// bit for bit.
+#pragma once
+
+#include "ssm_small.hpp"
+
+namespace ssm {
+
+constexpr int kModeChunk = 8;                  // modes between reductions over a wavefront
+constexpr int kModeCap = 1024;                 // modes of a system at most
+constexpr int kModeVals = 2 * kModeCap;        // doubles of a partial row: per chunk C_m x 8, S_m x 8
+constexpr double kModeAlpha = 0.69314718055994530942;  // a = ln 2
+constexpr double kTwoPi = 6.283185307179586476925286766559;
+
+// Gap G and largest wavenumber kmax of a precision: image and truncation
+// errors of one pair term, whose largest value is 0.52, below 5e-18 in FP64
+// (a twentieth of a rounding) and 1e-11 in the FP32 modes (the direct sums'
+// terms carry 3e-8 to 1e-7 there).
+struct ModeLimits {
+    double gap, kmax;
+};
+
+__host__ __device__ constexpr ModeLimits mode_limits(bool fp64) { return fp64 ? ModeLimits{7.8, 10.46} : ModeLimits{6.3, 8.35}; }
+
+// Particles [i0, i0 + n) of a system, n <= 256 P, into partial row `row`.
+struct ModeItem {
+    int32_t sys, row, i0, n;
+};
+
+// A system's domain this tick: centre, 1 / L and the number of modes, a
+// multiple of kModeChunk (0: direct sums).
+struct ModeDom {
+    double c, inv_L;
+    int32_t M, pad;
+};
+
+// The domain of the cloud between lo and hi.  The modes' cost per particle is
+// about 12 M double operations against 3 N (FP32) to 12 N (FP64) issue slots
+// of direct sums, and N / 4 keeps a wide cloud of few particles on the
+// cheaper side; below 64 modes they always are, or both are nothing beside
+// the tick's latency.
+__device__ __forceinline__ ModeDom mode_domain(double lo, double hi, int32_t N, bool fp64)
+{
+    const ModeLimits lim = mode_limits(fp64);
+    const double L = (hi - lo) + lim.gap;
+    const double m = ceil(lim.kmax / kTwoPi * L);
+    ModeDom d{0.5 * (lo + hi), 1.0 / L, 0, 0};
+    // an infinite range, or one that overflows, fails the comparison
+    if (m <= (double)min(kModeCap, max(64, N / 4))) d.M = ((int)m + kModeChunk - 1) / kModeChunk * kModeChunk;
+    return d;
+}
+
+// A system's domain from its blocks' ranges; every thread of a kBlk block gets it.
+__device__ __forceinline__ ModeDom system_domain(const SysDev& S, const double2* __restrict__ rng, bool fp64, double* red)
+{
+    double lo = INFINITY, hi = -INFINITY;
+    for (int b = threadIdx.x; b < S.nblk; b += kBlk) {
+        const double2 r = rng[S.blk0 + b];
+        lo = fmin(lo, r.x);
+        hi = fmax(hi, r.y);
+    }
+    block_range(lo, hi, red);
+    return mode_domain(lo, hi, S.N, fp64);
+}
+
+// cos and sin of 2 pi t for |t| <= 1/2: quadrant k = rint(4 t), the rest by
+// the Taylor series of sincos_angle on [-pi/4, pi/4].
+__device__ __forceinline__ void sincos_turn(double t, double* sn, double* cs)
+{
+    constexpr double sin_c[8] = {-0x1.5555555555555p-3, 0x1.1111111111111p-7, -0x1.a01a01a01a01ap-13,
+                                 0x1.71de3a556c734p-19, -0x1.ae64567f544e4p-26, 0x1.6124613a86d09p-33,
+                                 -0x1.ae7f3e733b81fp-41, 0x1.952c77030ad4ap-49};
+    constexpr double cos_c[8] = {-0x1.0000000000000p-1, 0x1.5555555555555p-5, -0x1.6c16c16c16c17p-10,
+                                 0x1.a01a01a01a01ap-16, -0x1.27e4fb7789f5cp-22, 0x1.1eed8eff8d898p-29,
+                                 -0x1.93974a8c07c9dp-37, 0x1.ae7f3e733b81fp-45};
+    const double k = rint(4.0 * t);
+    const double r = fma(k, -0.25, t) * kTwoPi;
+    const double r2 = r * r;
+    double ps = sin_c[7], pc = cos_c[7];
+#pragma unroll
+    for (int j = 6; j >= 0; --j) {
+        ps = fma(ps, r2, sin_c[j]);
+        pc = fma(pc, r2, cos_c[j]);
+    }
+    const double sr = fma(r * r2, ps, r);
+    const double cr = fma(r2, pc, 1.0);
+    const int q = (int)k & 3;
+    const double a = (q & 1) ? cr : sr;
+    const double b = (q & 1) ? sr : cr;
+    *sn = (q & 2) ? -a : a;
+    *cs = ((q + 1) & 2) ? -b : b;
+}
+
+// (re, im) = (re, im) z
+__device__ __forceinline__ void rotate(double& re, double& im, double zr, double zi)
+{
+    const double t = im * zi;
+    im = fma(re, zi, im * zr);
+    re = fma(re, zr, -t);
+}
+
+// One halving of row_scatter: lanes with `up` keep the upper H values.
+template <int CTRL, int H>
+__device__ __forceinline__ void scatter_step(double* v, bool up)
+{
+#pragma unroll
+    for (int u = 0; u < H; ++u) {
+        const double send = up ? v[u] : v[H + u];
+        const double keep = up ? v[H + u] : v[u];
+        v[u] = keep + dpp64<CTRL>(send);
+    }
+}
+
+// Sums of 16 values over each row of 16 lanes: lane l of a row gets value l.
+// Four halvings (15 adds) in place of 16 reductions of four steps each; the
+// partners of the steps (15 - l, 7 - l within eight, l ^ 2, l ^ 1) differ in
+// the bit that picks the half kept.
+__device__ __forceinline__ double row_scatter(double (&v)[16])
+{
+    const int l = threadIdx.x;
+    scatter_step<kDppMirror, 8>(v, l & 8);
+    scatter_step<kDppHalfMirror, 4>(v, l & 4);
+    scatter_step<kDppXor2, 2>(v, l & 2);
+    scatter_step<kDppXor1, 1>(v, l & 1);
+    return v[0];
+}
+
+// The direct sum of the thread's target ys over all sources of its system, in
+// tiles of kDirectTile staged in LDS (compensated within a tile in FP32, the
+// tiles' sums added in double).
+constexpr int kDirectTile = 1024;
+
+template <typename T>
+__device__ __forceinline__ double mode_direct(const SysDev& S, const T* __restrict__ Ys, T ys, T* src)
+{
+    double tot = 0.0;
+    for (int j0 = 0; j0 < S.N; j0 += kDirectTile) {
+        const int n = min(kDirectTile, S.N - j0);
+        __syncthreads();
+        for (int q = threadIdx.x; q < n; q += kBlk) src[q] = Ys[S.off + j0 + q];
+        __syncthreads();
+        const T yi[1] = {ys};
+        T out[1];
+        small_pairs<T, 1, sizeof(T) == 4>(src, 0, 0, n, yi, out);
+        tot += (double)out[0];
+    }
+    return tot;
+}
+
+// ---------------------------------------------------------------------------
+// One partial row of the mode sums: the block's particles, P per thread.
+// Wavefront rows of 16 lanes leave their sums in LDS (kRowVals at a time,
+// enough for the 64 modes that almost every cloud stays below; rows 16 doubles
+// further apart than that, so that two of them meet no bank twice), added in
+// a fixed order.  A system without modes gets its particles' direct sums here
+// instead, in pairsum: the kernel that evaluates also moves the particles.
+// ---------------------------------------------------------------------------
+constexpr int kRowVals = 128;
+constexpr int kModeRowsLds = kBlk / 16;  // rows of 16 lanes in a block
+
+template <typename T, int P>
+__device__ __forceinline__ void mode_block(const ModeItem it, const SysDev* __restrict__ sys, const T* __restrict__ Ys,
+                                           const double2* __restrict__ rng, ModeDom* __restrict__ dom,
+                                           double* __restrict__ part, double* __restrict__ pairsum)
+{
+    __shared__ __align__(32) double rows[kModeRowsLds][kRowVals + 16];
+    static_assert(sizeof(rows) >= kDirectTile * sizeof(T), "the direct sums stage their sources there");
+    __shared__ double red[kRedLds];
+    const SysDev S = sys[it.sys];
+    // the positions are on their way while the domain is reduced
+    T s[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int j = p * kBlk + (int)threadIdx.x;
+        s[p] = j < it.n ? Ys[S.off + it.i0 + j] : (T)0;
+    }
+    const ModeDom d = system_domain(S, rng, sizeof(T) == 8, red);
+    if (it.row == S.mode_row0 && threadIdx.x == 0) dom[it.sys] = d;
+    if (d.M == 0) {  // block-uniform
+#pragma unroll 1
+        for (int p = 0; p < P; ++p) {
+            const int j = p * kBlk + (int)threadIdx.x;
+            const T ys = j < it.n ? Ys[S.off + it.i0 + j] : (T)0;
+            const double K = mode_direct(S, Ys, ys, reinterpret_cast<T*>(&rows[0][0]));
+            if (j < it.n) pairsum[S.off + it.i0 + j] = K * S.pair_scale;
+        }
+        return;
+    }
+    double zr[P], zi[P], wr[P], wi[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const bool valid = p * kBlk + (int)threadIdx.x < it.n;
+        sincos_turn(((double)s[p] - d.c) * d.inv_L, &zi[p], &zr[p]);
+        wr[p] = valid ? zr[p] : 0.0;
+        wi[p] = valid ? zi[p] : 0.0;
+    }
+    double* out = part + (int64_t)it.row * kModeVals;
+    for (int v0 = 0; v0 < 2 * d.M; v0 += kRowVals) {
+        const int v1 = min(v0 + kRowVals, 2 * d.M);
+        for (int v = v0; v < v1; v += 2 * kModeChunk) {
+            double acc[2 * kModeChunk];
+#pragma unroll
+            for (int u = 0; u < kModeChunk; ++u) {
+                double c = wr[0], sn = wi[0];
+#pragma unroll
+                for (int p = 1; p < P; ++p) {
+                    c += wr[p];
+                    sn += wi[p];
+                }
+                acc[u] = c;
+                acc[kModeChunk + u] = sn;
+#pragma unroll
+                for (int p = 0; p < P; ++p) rotate(wr[p], wi[p], zr[p], zi[p]);
+            }
+            rows[threadIdx.x >> 4][v - v0 + (threadIdx.x & 15)] = row_scatter(acc);
+        }
+        __syncthreads();
+        for (int v = threadIdx.x; v < v1 - v0; v += kBlk) {
+            double t = 0.0;
+#pragma unroll
+            for (int q = 0; q < kModeRowsLds; ++q) t += rows[q][v];
+            out[v0 + v] = t;
+        }
+        if (v1 < 2 * d.M) __syncthreads();
+    }
+}
+
+// n_modes blocks of mode sums, then (up to n_main) the Brownian sums, then
+// job.n blocks of system means.
+template <typename T, int P, int LP>
+__global__ __launch_bounds__(kBlk) void k_modes(int n_modes, int n_main, const ModeItem* __restrict__ mitems,
+                                                const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
+                                                Coef cf, int64_t Pn, const T* __restrict__ Ys,
+                                                const double2* __restrict__ rng, ModeDom* __restrict__ dom,
+                                                double* __restrict__ part, double* __restrict__ pairsum,
+                                                int64_t tick_arg, const int64_t* __restrict__ tick_dev,
+                                                const double* __restrict__ win, double* __restrict__ dW, YMeanJob job)
+{
+    if ((int)blockIdx.x < n_modes)
+        mode_block<T, P>(mitems[blockIdx.x], sys, Ys, rng, dom, part, pairsum);
+    else if ((int)blockIdx.x < n_main)
+        brownian_block<1, LP, (sizeof(T) == 4)>(blockIdx.x - n_modes, items, sys, cf, Pn, tick_arg, tick_dev, win, dW);
+    else
+        ymean_block<1>(blockIdx.x - n_main, job, sys, tick_arg, tick_dev);
+}
+
+// Sum over rows [row0, row0 + nrows) of value v0 + (t & 63), in a fixed order,
+// by all threads of a block; thread t < 64 gets it.
+__device__ __forceinline__ double add_rows(const double* __restrict__ part, int64_t row0, int nrows, int v, bool in,
+                                           double (*stage)[64])
+{
+    constexpr int kW = kBlk / 64;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double a = 0.0;
+    if (in) {
+        const double* p = part + row0 * kModeVals + v;
+        int r = wave;
+        for (; r + 15 * kW < nrows; r += 16 * kW) {
+            double q[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) q[u] = p[(int64_t)(r + u * kW) * kModeVals];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) a += q[u];
+        }
+        for (; r < nrows; r += kW) a += p[(int64_t)r * kModeVals];
+    }
+    stage[wave][lane] = a;
+    __syncthreads();
+    return (stage[0][lane] + stage[1][lane]) + (stage[2][lane] + stage[3][lane]);
+}
+
+// k_mode_total: the rows of each listed system added up once, into one row of
+// `tot` per system, 16 values at a time by 16 threads each.  Launched where
+// the blocks of k_update_modes would together read many more rows than the
+// systems have.
+__global__ __launch_bounds__(kBlk) void k_mode_total(const int32_t* __restrict__ sys_list, const SysDev* __restrict__ sys,
+                                                     const ModeDom* __restrict__ dom, const double* __restrict__ part,
+                                                     double* __restrict__ tot)
+{
+    __shared__ double stage[kBlk / 16][16];
+    const int s = sys_list[blockIdx.x];
+    const SysDev S = sys[s];
+    const int V = 2 * dom[s].M;
+    const int w = threadIdx.x >> 4, l = threadIdx.x & 15;
+    for (int v0 = blockIdx.y * 16; v0 < V; v0 += gridDim.y * 16) {
+        const double* p = part + (int64_t)S.mode_row0 * kModeVals + v0 + l;
+        double a = 0.0;
+        int r = w;
+        for (; r + 7 * 16 < S.mode_rows; r += 8 * 16) {
+            double q[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) q[u] = p[(int64_t)(r + u * 16) * kModeVals];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a += q[u];
+        }
+        for (; r < S.mode_rows; r += 16) a += p[(int64_t)r * kModeVals];
+        stage[w][l] = a;
+        __syncthreads();
+        if (threadIdx.x < 16) {
+            double t = 0.0;
+#pragma unroll
+            for (int u = 0; u < kBlk / 16; ++u) t += stage[u][l];
+            tot[(int64_t)s * kModeVals + v0 + l] = t;
+        }
+        __syncthreads();
+    }
+}
+
+// The coefficients g_m = c_m (S_m + i C_m), m = 1 .. M, of a system into LDS.
+__device__ __forceinline__ void mode_coefs(const ModeDom& d, const double* __restrict__ part, int64_t row0, int nrows,
+                                           double2* g, double (*stage)[64])
+{
+    const double delta = kTwoPi * d.inv_L;
+    const double c0 = delta * 0.3388303758015525;  // 1 / sqrt(4 pi a)
+    for (int v0 = 0; v0 < 2 * d.M; v0 += 64) {
+        const int v = v0 + (int)(threadIdx.x & 63);
+        const double a = add_rows(part, row0, nrows, v, v < 2 * d.M, stage);
+        if (threadIdx.x < 64 && v < 2 * d.M) {
+            const int m = (v >> 4) * kModeChunk + (v & 7);  // from 0
+            const double k = (double)(m + 1) * delta;
+            // e^(-k^2 / (4 a)) = 2^(-k^2 / (4 a^2))
+            const double c = c0 * (k * 1.4426950408889634) * exp2_fast<double>(k * k * -0.5203422452514019);
+            double* gm = reinterpret_cast<double*>(g + m);
+            gm[(v & 8) ? 0 : 1] = c * a;
+        }
+        __syncthreads();
+    }
+}
+
+// sum_m Re(g_m z^m) at the scaled position s, by Horner's rule.
+__device__ __forceinline__ double mode_eval(const ModeDom& d, const double2* g, double s)
+{
+    double zr, zi;
+    sincos_turn((s - d.c) * d.inv_L, &zi, &zr);
+    double pr = 0.0, pi = 0.0;
+#pragma unroll 8
+    for (int m = d.M - 1; m >= 0; --m) {
+        const double2 gm = g[m];
+        const double t = fma(pr, zr, fma(-pi, zi, gm.x));
+        pi = fma(pr, zi, fma(pi, zr, gm.y));
+        pr = t;
+    }
+    return fma(pr, zr, -pi * zi);
+}
+
+// The scaled pair term of one block's particles (each thread its own), from
+// the rows of its system; stored in pairsum too, for whoever reads the exact
+// term after the tick (the surrogate's check, the training sampler).
+template <typename T>
+__device__ __forceinline__ double mode_pair(const BlkItem it, const SysDev& S, const T* __restrict__ Ys,
+                                            const ModeDom* __restrict__ dom, const double* __restrict__ part,
+                                            int totals, double* __restrict__ pairsum, double2* g, double (*stage)[64])
+{
+    const int i = it.blk * kBlk + threadIdx.x;
+    const bool valid = i < S.N;
+    const T ys = valid ? Ys[S.off + i] : (T)0;
+    const ModeDom d = dom[it.sys];
+    if (d.M == 0) return valid ? pairsum[S.off + i] : 0.0;  // block-uniform
+    mode_coefs(d, part, totals ? it.sys : S.mode_row0, totals ? 1 : S.mode_rows, g, stage);
+    const double K = valid ? mode_eval(d, g, (double)ys) * S.pair_scale : 0.0;
+    if (valid) pairsum[S.off + i] = K;
+    return K;
+}
+
+// k_update_modes: k_update with the pair term evaluated here (d = 1).
+// totals: part holds one row per system (k_mode_total).
+template <typename T>
+__global__ __launch_bounds__(kBlk) void k_update_modes(const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
+                                                       Coef cf, int64_t P, int64_t tick_arg,
+                                                       const int64_t* __restrict__ tick_dev, T* __restrict__ X,
+                                                       T* __restrict__ Y, T* Ys, const ModeDom* __restrict__ dom,
+                                                       const double* __restrict__ part, int totals,
+                                                       double* __restrict__ pairsum, const double* __restrict__ dWbuf,
+                                                       const double* __restrict__ ymean, double* __restrict__ psumX,
+                                                       double* __restrict__ psumY, int64_t nblk_tot, Flags* flags,
+                                                       int32_t* __restrict__ nmax, double2* __restrict__ rng)
+{
+    __shared__ double red[kRedLds];
+    __shared__ double stage[kBlk / 64][64];
+    __shared__ __align__(16) double2 g[kModeCap];
+    const BlkItem it = items[blockIdx.x];
+    const SysDev S = sys[it.sys];
+    const int64_t n = tick_of(tick_dev, tick_arg) / S.stride;
+    const double pair[1] = {mode_pair<T>(it, S, Ys, dom, part, totals, pairsum, g, stage)};
+    update_block<T, 1>(it, S, cf, P, n, pair, X, Y, Ys, dWbuf, ymean, psumX, psumY, nblk_tot, flags, nmax, rng, red);
+}
+
+// k_mode_eval: the pair term alone into pairsum (the training sampler).
+template <typename T>
+__global__ __launch_bounds__(kBlk) void k_mode_eval(const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
+                                                    const T* __restrict__ Ys, const ModeDom* __restrict__ dom,
+                                                    const double* __restrict__ part, int totals,
+                                                    double* __restrict__ pairsum)
+{
+    __shared__ double stage[kBlk / 64][64];
+    __shared__ __align__(16) double2 g[kModeCap];
+    const BlkItem it = items[blockIdx.x];
+    const SysDev S = sys[it.sys];
+    (void)mode_pair<T>(it, S, Ys, dom, part, totals, pairsum, g, stage);
+}
+
+}  // namespace ssm

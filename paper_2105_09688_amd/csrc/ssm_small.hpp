@@ -69,52 +69,6 @@ struct SmallArgs {
     int64_t wait_limit;      // wall-clock counts a barrier wait may take
 };
 
-// Lane permutations within each row of 16 lanes (gfx9 DPP controls):
-// exchange with lane ^ 1 and lane ^ 2 (quad_perm), mirror within 8 and 16.
-constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
-
-template <int CTRL>
-__device__ __forceinline__ double dpp64(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-__device__ __forceinline__ double readlane64(double v, int lane)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// Sum over the 64 lanes of a wavefront in a fixed order; every lane gets it.
-// Within each row of 16 lanes, four DPP steps (pairs, quads, eights,
-// sixteens) leave the row's sum in all its lanes; the four row sums are then
-// read and added as (row 0 + row 1) + (row 2 + row 3).  DPP instead of LDS
-// shuffles: this sum sits on the latency chain of the update.
-__device__ __forceinline__ double wave_sum(double v)
-{
-    v += dpp64<kDppXor1>(v);
-    v += dpp64<kDppXor2>(v);
-    v += dpp64<kDppHalfMirror>(v);
-    v += dpp64<kDppMirror>(v);
-    return (readlane64(v, 0) + readlane64(v, 16)) + (readlane64(v, 32) + readlane64(v, 48));
-}
-
-// Largest value over the lanes of a wavefront, the same way.
-__device__ __forceinline__ int wave_max(int v)
-{
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, kDppXor1, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, kDppXor2, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, kDppHalfMirror, 0xF, 0xF, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, kDppMirror, 0xF, 0xF, false));
-    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
-}
-
 // Split-phase barrier of the `members` workgroups of one system.  Arrive:
 // one release increment of the system's counter by thread 0.  Wait: until the
 // counter reaches members x epoch, then an acquire fence by thread 0 (it
@@ -579,9 +533,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_small(SmallArgs<T> a)
 template <typename T, int D>
 __global__ __launch_bounds__(kBlk) void k_ysums(const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
                                                 int64_t P, int64_t tick_arg, const T* __restrict__ Y,
-                                                double* __restrict__ psumY, int64_t nblk_tot)
+                                                double coord_scale, double* __restrict__ psumY, int64_t nblk_tot,
+                                                double2* __restrict__ rng)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     const BlkItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
     const int64_t done = tick_arg < 0 ? 0 : tick_arg / S.stride + 1;
@@ -593,6 +548,9 @@ __global__ __launch_bounds__(kBlk) void k_ysums(const BlkItem* __restrict__ item
     for (int k = 0; k < D; ++k) {
         const double s = block_sum(valid ? (double)Y[k * P + S.off + i] : 0.0, red);
         if (threadIdx.x == 0) pY[(int64_t)k * nblk_tot + gb] = s;
+    }
+    if constexpr (D == 1) {
+        if (rng) store_range(valid, (double)(T)(coord_scale * (double)Y[S.off + i]), rng, gb, red);
     }
 }
 

@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kBlk) void k_rff_final(const int32_t* __restrict__ 
                                                     const SysDev* __restrict__ sys,
                                                     const double* __restrict__ part, float* __restrict__ mom)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     const int s = sys_list[blockIdx.x];
     const SysDev S = sys[s];
     const int q = blockIdx.y;
@@ -927,7 +927,7 @@ __global__ __launch_bounds__(kBlk) void k_surr_partial(const BlkItem* __restrict
                                                        const float* __restrict__ surr,
                                                        double* __restrict__ part /*[nblk_tot][kMaxD]*/)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     const BlkItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
     const int i = it.blk * kBlk + threadIdx.x;
@@ -945,7 +945,7 @@ __global__ __launch_bounds__(kBlk) void k_surr_final(const int32_t* __restrict__
                                                      const double* __restrict__ part,
                                                      float* __restrict__ mean /*[n_sys][kMaxD]*/)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     const int s = sys_list[blockIdx.x];
     const SysDev S = sys[s];
     const int k = blockIdx.y;
@@ -971,7 +971,7 @@ __global__ __launch_bounds__(kBlk) void k_surr_err(const BlkItem* __restrict__ i
                                                    float* res, int res_read, int res_write,
                                                    double* __restrict__ err_part /*[nblk][kErrStats]*/)
 {
-    __shared__ double red[kBlk];
+    __shared__ double red[kRedLds];
     const BlkItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
     const int i = it.blk * kBlk + threadIdx.x;

@@ -6,6 +6,10 @@ context of the workload; the fastest is cached in a JSON file keyed by the
 workload shape, precision and GPU architecture ($SSM_TUNE_CACHE, default
 ~/.cache/ssm_tune.json).  Results do not depend on the tiling beyond
 floating-point summation order (tested), so any cached choice is safe.
+
+The tuner chooses among tilings of the pair kernels.  In one dimension a
+context with no tiling given sums the interaction by its modes and beats all
+of them; tiling arguments bring the pair kernels back.
 """
 from __future__ import annotations
 
