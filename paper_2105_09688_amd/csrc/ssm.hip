@@ -258,6 +258,7 @@ struct ssm_ctx {
     double* psumX = nullptr;
     double* psumY = nullptr;
     SysDev* dsys = nullptr;
+    SysDev one{};              // the system of a context of one
     PairItem* dpair = nullptr;
     BlkItem* dblk = nullptr;
     Flags* dflags = nullptr;
@@ -323,9 +324,9 @@ struct ssm_ctx {
     bool mode_totals = false;       // the rows are added up by k_mode_total
     ModeItem* dmitems = nullptr;    // per phase (pair_off / pair_cnt)
     ModeDom* dom = nullptr;         // [n_sys] the tick's domains
-    double* mode_part = nullptr;    // [mode_rows][kModeVals]
+    double* mode_part = nullptr;    // [kModeVals / 16][mode_rows][16] (mode_at)
     double* mode_tot = nullptr;     // [n_sys][kModeVals] (mode_totals)
-    double2* rng = nullptr;         // [nblk_tot] range of the scaled positions of each block
+    float2* rng = nullptr;          // [nblk_tot] range of the scaled positions of each block
     // persistent runs of small systems (ssm_small.hpp)
     bool small_ok = false;          // eligible: ticks without surrogate, profiling or graphs use it
     SmallTile* dtiles = nullptr;    // [small_grid] workgroup -> (system, tile)
@@ -677,15 +678,16 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, const int64_t* tdev, bool
     const int n_main = nm + (sums_only ? 0 : (int)(c->blk_cnt[ph] * c->bm_lanes));
     const YMeanJob job{c->dsys_list + c->sys_list_off[ph],
                        c->needs_ybar && !sums_only ? (int)c->sys_list_cnt[ph] : 0, c->psumY, c->nblk_tot, c->ymean};
-#define SSM_MODES(PV, LPV)                                                                                             \
-    hipLaunchKernelGGL((k_modes<T, PV, LPV>), dim3((unsigned)(n_main + job.n)), dim3(kBlk), 0, c->stream, nm, n_main,  \
-                       (const ModeItem*)c->dmitems + c->pair_off[ph], items, c->dsys, c->coef, c->P, (const T*)c->Ys,  \
-                       (const double2*)c->rng, c->dom, c->mode_part, c->pairsum, c->tick, tdev, (const double*)c->win, \
-                       c->dW, job)
+#define SSM_MODES(PV, LPV, ONE)                                                                                        \
+    hipLaunchKernelGGL((k_modes<T, PV, LPV, ONE>), dim3((unsigned)(n_main + job.n)), dim3(kBlk), 0, c->stream, nm, n_main,  \
+                       c->one, (const ModeItem*)c->dmitems + c->pair_off[ph], items, c->dsys, c->coef, c->P, (const T*)c->Ys,  \
+                       (const float2*)c->rng, c->dom, c->mode_part, c->mode_rows, c->pairsum, c->tick, tdev,            \
+                       (const double*)c->win, c->dW, job)
 #define SSM_MODES_LP(LPV)                                 \
     do {                                                  \
-        if (c->mode_P == 1) { SSM_MODES(1, LPV); }        \
-        else { SSM_MODES(4, LPV); }                       \
+        if (c->mode_P == 4) { SSM_MODES(4, LPV, false); } \
+        else if (c->sys.size() > 1) { SSM_MODES(1, LPV, false); } \
+        else { SSM_MODES(1, LPV, true); }                 \
     } while (0)
     switch (c->bm_lanes) {
         case 16: SSM_MODES_LP(16); break;
@@ -700,7 +702,7 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, const int64_t* tdev, bool
     if (c->mode_totals) {
         hipLaunchKernelGGL(k_mode_total, dim3((unsigned)c->sys_list_cnt[ph], 4), dim3(kBlk), 0, c->stream,
                            c->dsys_list + c->sys_list_off[ph], c->dsys, (const ModeDom*)c->dom,
-                           (const double*)c->mode_part, c->mode_tot);
+                           (const double*)c->mode_part, c->mode_rows, c->mode_tot);
         HIP_TRY(hipGetLastError());
     }
     return SSM_OK;
@@ -760,11 +762,14 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
         }
         const BlkItem* items = c->dblk + c->blk_off[ph];
         if (c->modes && run_exact) {
-            hipLaunchKernelGGL((k_update_modes<T>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, items, c->dsys, c->coef,
-                               c->P, c->tick, tdev, X, Y, Ys, (const ModeDom*)c->dom,
-                               (const double*)(c->mode_totals ? c->mode_tot : c->mode_part), c->mode_totals ? 1 : 0,
-                               c->pairsum, (const double*)c->dW, c->needs_ybar ? (const double*)c->ymean : nullptr,
-                               c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng);
+#define SSM_UPDATE_MODES(TOT, ONE, part)                                                                                  \
+    hipLaunchKernelGGL((k_update_modes<T, TOT, ONE>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, c->one, items, c->dsys,  \
+                       c->coef, c->P, c->tick, tdev, X, Y, Ys, (const ModeDom*)c->dom, (const double*)(part),           \
+                       c->mode_rows, c->pairsum, (const double*)c->dW, (const double*)c->ymean, c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng)
+            if (c->mode_totals) SSM_UPDATE_MODES(true, false, c->mode_tot);
+            else if (c->sys.size() > 1) SSM_UPDATE_MODES(false, false, c->mode_part);
+            else SSM_UPDATE_MODES(false, true, c->mode_part);
+#undef SSM_UPDATE_MODES
             HIP_TRY(hipGetLastError());
         } else {
             // Brownian sums of the step, and on exact ticks the combine of the pair
@@ -804,7 +809,7 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
                                                              (float)c->surr_gain[2], (float)c->surr_gain[3]),
                                                  (use_surr && c->surr_mode == SSM_SURR_RESIDUAL && c->surr_res_valid)
                                                      ? c->surr_res : nullptr,
-                                                 c->dW, c->needs_ybar ? (const double*)c->ymean : nullptr,
+                                                 c->dW, (const double*)c->ymean,
                                                  c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng));
             HIP_TRY(hipGetLastError());
         }
@@ -1459,6 +1464,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         x.pair_scale = c->has_pair ? cfg->b_g / ((double)S.N * cf.coord_scale) : 0.0;
         sd.push_back(x);
     }
+    c->one = sd[0];
 #define ALLOC(ptr, bytes) do { st = dev_alloc(c, (void**)&(ptr), (bytes)); if (st != SSM_OK) { free_ctx(c); return st; } } while (0)
     ALLOC(c->X, field);
     ALLOC(c->Y, field);
@@ -1477,7 +1483,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         ALLOC(c->dom, c->sys.size() * sizeof(ModeDom));
         ALLOC(c->mode_part, (size_t)c->mode_rows * kModeVals * sizeof(double));
         if (c->mode_totals) ALLOC(c->mode_tot, c->sys.size() * kModeVals * sizeof(double));
-        ALLOC(c->rng, (size_t)c->nblk_tot * sizeof(double2));
+        ALLOC(c->rng, (size_t)c->nblk_tot * sizeof(float2));
     }
     ALLOC(c->dblk, blks.size() * sizeof(BlkItem));
     ALLOC(c->dflags, sizeof(Flags));
@@ -1512,6 +1518,8 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     if (he == hipSuccess) he = hipMemsetAsync(c->dflags, 0, sizeof(Flags), c->stream);
     if (he == hipSuccess) he = hipMemsetAsync(c->dnmax, 0, (size_t)c->nblk_tot * kSlotsPerBlk * sizeof(int32_t), c->stream);
     if (he == hipSuccess) he = hipMemsetAsync(c->dtick, 0, sizeof(int64_t), c->stream);
+    // read by every update, written only where the coefficients use the means
+    if (he == hipSuccess) he = hipMemsetAsync(c->ymean, 0, c->sys.size() * kMaxD * sizeof(double), c->stream);
     if (he == hipSuccess && c->small_ok) he = hipMemcpyAsync(c->dtiles, tiles.data(), tiles.size() * sizeof(SmallTile), hipMemcpyHostToDevice, c->stream);
     if (he == hipSuccess && c->small_ok) he = hipMemsetAsync(c->dbar, 0, c->sys.size() * kBarLine * sizeof(uint64_t), c->stream);
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);  // host vectors go out of scope
@@ -2231,9 +2239,12 @@ static ssm_status launch_exact(ssm_ctx* c)
     if (c->modes) {
         ssm_status st = launch_modes<T>(c, 0, nullptr, true);
         if (st != SSM_OK) return st;
-        hipLaunchKernelGGL((k_mode_eval<T>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,
-                           (const ModeDom*)c->dom, (const double*)(c->mode_totals ? c->mode_tot : c->mode_part),
-                           c->mode_totals ? 1 : 0, c->pairsum);
+        if (c->mode_totals)
+            hipLaunchKernelGGL((k_mode_eval<T, true>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,
+                               (const ModeDom*)c->dom, (const double*)c->mode_tot, c->mode_rows, c->pairsum);
+        else
+            hipLaunchKernelGGL((k_mode_eval<T, false>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,
+                               (const ModeDom*)c->dom, (const double*)c->mode_part, c->mode_rows, c->pairsum);
         HIP_TRY(hipGetLastError());
         return SSM_OK;
     }

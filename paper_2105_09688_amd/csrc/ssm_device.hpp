@@ -187,6 +187,15 @@ __device__ __forceinline__ void normals4_f32(uint64_t seed, uint32_t tag, uint64
     }
 }
 
+// 1 / x for normal x > 0 to about 2^-47: the hardware's estimate and one
+// Newton step.  Enough for a Newton correction, whose own error is removed by
+// the next, and six instructions shorter than a correctly rounded division.
+__device__ __forceinline__ double rcp_fast(double x)
+{
+    const double r = __builtin_amdgcn_rcp(x);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
 // ---------------------------------------------------------------------------
 // Implicit step (2.3) for one particle, Lemma 4.1.  For
 //   v(c) = (rho - kappa m2) c - a |c|^2 c + lam xbar
@@ -197,12 +206,15 @@ __device__ __forceinline__ void normals4_f32(uint64_t seed, uint32_t tag, uint64
 //
 // Both |w| / alpha and cbrt(|w| / (h a)) are upper bounds of the root (q >= 0
 // there); Newton started at their minimum decreases monotonically onto the
-// root (q convex and increasing).  The bracket [lo, hi] is kept anyway: an
-// iterate that leaves it (possible only through rounding) is replaced by the
+// root (q convex and increasing).  A solve that has not stopped after
+// kPlainNewton corrections runs again with the bracket [lo, hi]: an iterate
+// that leaves it (possible only through rounding) is replaced by the
 // midpoint.  Iteration stops once a Newton correction is a few ulp.
 // Returns the iteration count, -1 if max_iter is exhausted, or -2 (y = w) if
 // w is not finite (a corrupted particle: there is no root to find).
 // ---------------------------------------------------------------------------
+constexpr int kPlainNewton = 12;  // corrections before the bracketed form takes over
+
 template <int D>
 __device__ __forceinline__ int implicit_radial(const double w[D], double alpha, double ha,
                                                int max_iter, double y[D])
@@ -217,7 +229,8 @@ __device__ __forceinline__ int implicit_radial(const double w[D], double alpha, 
         for (int k = 0; k < D; ++k) y[k] = w[k];
         return -2;
     }
-    const double nw = sqrt(nw2);
+    // |w| (one component: exactly, without the square root of its square)
+    const double nw = (D == 1) ? fabs(w[0]) : sqrt(nw2);
     if (nw == 0.0) {
 #pragma unroll
         for (int k = 0; k < D; ++k) y[k] = 0.0;
@@ -228,34 +241,58 @@ __device__ __forceinline__ int implicit_radial(const double w[D], double alpha, 
     if (ha == 0.0) {
         s = nw / alpha;
     } else {
-        double hi = fmin(nw / alpha, cbrt(nw / ha));
-        double lo = 0.0;
+        // cbrt(|w| / ha) < |w| / alpha where alpha^3 < ha |w|^2; a step of
+        // ordinary size stays on the other side, without the cube root (a
+        // third of the solve's instructions)
+        double hi = nw * rcp_fast(alpha);
+        if (alpha * alpha * alpha < ha * nw2) hi = fmin(hi, cbrt(nw / ha));
+        // Newton from there needs no bracket but for rounding: every lane of
+        // the wavefront goes through the same few corrections, without branches
+        // of its own (a tick waits for this chain of dependent operations)
         s = hi;
-        bool done = false;
-        for (iters = 1; iters <= max_iter; ++iters) {
+        bool act = true;
+        for (int it = 1; it <= min(max_iter, kPlainNewton); ++it) {
             const double s2 = s * s;
             const double q = fma(ha * s2, s, fma(alpha, s, -nw));
-            if (q == 0.0) {
-                done = true;
-                break;
-            }
-            if (q > 0.0) hi = s; else lo = s;
-            const double dq = fma(3.0 * ha, s2, alpha);
-            const double corr = q / dq;
-            if (fabs(corr) <= 0x1.0p-50 * s) {
-                s -= corr;
-                done = true;
-                break;
-            }
-            double sn = s - corr;
-            if (!(sn > lo && sn < hi)) sn = 0.5 * (lo + hi);
-            s = sn;
-            if (hi - lo <= 0x1.0p-52 * hi) {
-                done = true;
-                break;
-            }
+            const double corr = q * rcp_fast(fma(3.0 * ha, s2, alpha));
+            const bool conv = fabs(corr) <= 0x1.0p-50 * s;
+            s = act ? s - corr : s;
+            iters = act ? it : iters;
+            act = act && !conv;
+            if (__ballot(act) == 0) break;
         }
-        if (!done) iters = -1;
+        if (act) {
+            double lo = 0.0;
+            s = hi;
+            bool done = false;
+            for (iters = 1; iters <= max_iter; ++iters) {
+                const double s2 = s * s;
+                const double q = fma(ha * s2, s, fma(alpha, s, -nw));
+                if (q == 0.0) {
+                    done = true;
+                    break;
+                }
+                if (q > 0.0) hi = s; else lo = s;
+                const double corr = q * rcp_fast(fma(3.0 * ha, s2, alpha));
+                if (fabs(corr) <= 0x1.0p-50 * s) {
+                    s -= corr;
+                    done = true;
+                    break;
+                }
+                double sn = s - corr;
+                if (!(sn > lo && sn < hi)) sn = 0.5 * (lo + hi);
+                s = sn;
+                if (hi - lo <= 0x1.0p-52 * hi) {
+                    done = true;
+                    break;
+                }
+            }
+            if (!done) iters = -1;
+        }
+    }
+    if constexpr (D == 1) {
+        y[0] = copysign(s, w[0]);
+        return iters;
     }
     const double scale = s / nw;
 #pragma unroll

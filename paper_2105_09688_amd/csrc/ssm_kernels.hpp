@@ -111,7 +111,7 @@ struct Flags {
 };
 
 // Largest Newton iteration count per wavefront slot: slot gb * kSlotsPerBlk + w
-// for global block gb, wavefront w (plain stores by the owning wavefront; a
+// for global block gb, wavefront w (only its own wavefront meets it; a
 // device-wide atomic per wavefront on one address serializes across the XCDs).
 constexpr int kSlotsPerBlk = kBlk / 64;
 
@@ -348,44 +348,67 @@ __device__ __forceinline__ double block_sum(double v, double* red)
     return total;
 }
 
-// Lowest (a) and highest (b) value over a kBlk-thread block, in every thread.
-// `red` is 2 kBlk / 64 doubles of LDS.
-__device__ __forceinline__ void block_range(double& a, double& b, double* red)
+template <int CTRL>
+__device__ __forceinline__ float dpp32(float v)
 {
-    a = fmin(a, dpp64<kDppXor1>(a));
-    b = fmax(b, dpp64<kDppXor1>(b));
-    a = fmin(a, dpp64<kDppXor2>(a));
-    b = fmax(b, dpp64<kDppXor2>(b));
-    a = fmin(a, dpp64<kDppHalfMirror>(a));
-    b = fmax(b, dpp64<kDppHalfMirror>(b));
-    a = fmin(a, dpp64<kDppMirror>(a));
-    b = fmax(b, dpp64<kDppMirror>(b));
-    a = fmin(fmin(readlane64(a, 0), readlane64(a, 16)), fmin(readlane64(a, 32), readlane64(a, 48)));
-    b = fmax(fmax(readlane64(b, 0), readlane64(b, 16)), fmax(readlane64(b, 32), readlane64(b, 48)));
-    constexpr int kW = kBlk / 64;
-    if ((threadIdx.x & 63) == 0) {
-        red[threadIdx.x >> 6] = a;
-        red[kW + (threadIdx.x >> 6)] = b;
-    }
-    __syncthreads();
-    a = fmin(fmin(red[0], red[1]), fmin(red[2], red[3]));
-    b = fmax(fmax(red[kW], red[kW + 1]), fmax(red[kW + 2], red[kW + 3]));
-    __syncthreads();
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
 
-// Range of the scaled positions of a block's particles for the mode sums
-// (ssm_modes.hpp): one (lowest, highest) pair per update block; a non-finite
-// particle makes it infinite, so that the sums of its system run directly.
-__device__ __forceinline__ void store_range(bool valid, double ys, double2* __restrict__ rng, int64_t gb, double* red)
+__device__ __forceinline__ float readlane32(float v, int lane)
 {
-    double lo = valid ? ys : INFINITY, hi = valid ? ys : -INFINITY;
-    if (valid && !isfinite(ys)) {
-        lo = -INFINITY;
-        hi = INFINITY;
-    }
-    block_range(lo, hi, red);
-    if (threadIdx.x == 0) rng[gb] = make_double2(lo, hi);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
+
+// Lowest (a) and highest (b) value over a wavefront, in every lane.
+__device__ __forceinline__ void wave_range(float& a, float& b)
+{
+    a = fminf(a, dpp32<kDppXor1>(a));
+    b = fmaxf(b, dpp32<kDppXor1>(b));
+    a = fminf(a, dpp32<kDppXor2>(a));
+    b = fmaxf(b, dpp32<kDppXor2>(b));
+    a = fminf(a, dpp32<kDppHalfMirror>(a));
+    b = fmaxf(b, dpp32<kDppHalfMirror>(b));
+    a = fminf(a, dpp32<kDppMirror>(a));
+    b = fmaxf(b, dpp32<kDppMirror>(b));
+    a = fminf(fminf(readlane32(a, 0), readlane32(a, 16)), fminf(readlane32(a, 32), readlane32(a, 48)));
+    b = fmaxf(fmaxf(readlane32(b, 0), readlane32(b, 16)), fmaxf(readlane32(b, 32), readlane32(b, 48)));
+}
+
+// Range of a thread's scaled position for the mode sums (ssm_modes.hpp), as
+// floats around it; a particle that is not finite makes it infinite, so that
+// the sums of its system run directly.
+__device__ __forceinline__ float2 position_range(bool valid, double ys)
+{
+    if (!valid) return make_float2(INFINITY, -INFINITY);
+    const float f = (float)ys, e = fabsf(f) * 0x1.0p-23f + 0x1.0p-100f;
+    return isfinite(f) ? make_float2(f - e, f + e) : make_float2(-INFINITY, INFINITY);
+}
+
+// Sum of a block's values, in thread 0, and the range of its scaled positions,
+// one (lowest, highest) pair per update block, with one barrier.
+__device__ __forceinline__ double sum_and_range(bool valid, double y, double ys, float2* __restrict__ rng, int64_t gb,
+                                                double* red)
+{
+    constexpr int kW = kBlk / 64;
+    float2* redf = reinterpret_cast<float2*>(red + kW);
+    float2 r = position_range(valid, ys);
+    wave_range(r.x, r.y);
+    const double w = wave_sum(y);
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = w;
+        redf[threadIdx.x >> 6] = r;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        rng[gb] = make_float2(fminf(fminf(redf[0].x, redf[1].x), fminf(redf[2].x, redf[3].x)),
+                              fmaxf(fmaxf(redf[0].y, redf[1].y), fmaxf(redf[2].y, redf[3].y)));
+    }
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// The step that a system of stride `stride` takes at tick t (a 64-bit division
+// is about 120 instructions; most contexts have one step size).
+__device__ __forceinline__ int64_t step_of(int64_t t, int32_t stride) { return stride == 1 ? t : t / stride; }
 
 // ---------------------------------------------------------------------------
 // k_init: X_0 = x0_mean + x0_std * Z(1, i, 0, ens); zero padding; block sums
@@ -453,7 +476,7 @@ __device__ __forceinline__ void solve_and_store(const SysDev& S, const Coef& cf,
                                                 T* __restrict__ Y, T* __restrict__ Ys,
                                                 double* __restrict__ psumY_out, int64_t gb,
                                                 int64_t nblk_tot, Flags* flags, int32_t* __restrict__ nmax,
-                                                double2* __restrict__ rng, double* red)
+                                                float2* __restrict__ rng, double* red)
 {
     double w[D], y[D];
 #pragma unroll
@@ -485,14 +508,12 @@ __device__ __forceinline__ void solve_and_store(const SysDev& S, const Coef& cf,
     // any; iteration counts: the wavefront's maximum into its own slot
     const uint64_t fails = __ballot(it < 0);
     const uint64_t bad = __ballot(nonfin);
-    int itmax = it;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) itmax = max(itmax, __shfl_xor(itmax, off, 64));
+    const int itmax = wave_max(it);
     if ((threadIdx.x & 63) == 0) {
         if (fails) atomicAdd(&flags->newton_fail, (int)__popcll(fails));
         if (bad) atomicAdd(&flags->nonfinite, (int)__popcll(bad));
-        int32_t* slot = nmax + gb * kSlotsPerBlk + (threadIdx.x >> 6);
-        if (itmax > *slot) *slot = itmax;
+        // without a result: nothing waits for the old value
+        atomicMax(nmax + gb * kSlotsPerBlk + (threadIdx.x >> 6), itmax);
     }
     double ysum[D];
 #pragma unroll
@@ -502,13 +523,17 @@ __device__ __forceinline__ void solve_and_store(const SysDev& S, const Coef& cf,
         Ys[k * P + slot] = (T)(cf.coord_scale * (double)yt);
         ysum[k] = valid ? (double)yt : 0.0;
     }
+    if constexpr (D == 1) {
+        if (rng) {
+            const double s = sum_and_range(valid, ysum[0], (double)(T)(cf.coord_scale * (double)(T)y[0]), rng, gb, red);
+            if (threadIdx.x == 0) psumY_out[gb] = s;
+            return;
+        }
+    }
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         const double s = block_sum(ysum[k], red);
         if (threadIdx.x == 0) psumY_out[(int64_t)k * nblk_tot + gb] = s;
-    }
-    if constexpr (D == 1) {
-        if (rng) store_range(valid, (double)(T)(cf.coord_scale * (double)(T)y[0]), rng, gb, red);
     }
 }
 
@@ -527,7 +552,7 @@ __global__ __launch_bounds__(kBlk) void k_newton(const BlkItem* __restrict__ ite
                                                  T* __restrict__ Ys,
                                                  const double* __restrict__ psumX,
                                                  double* __restrict__ psumY, int64_t nblk_tot,
-                                                 Flags* flags, int32_t* __restrict__ nmax, double2* __restrict__ rng)
+                                                 Flags* flags, int32_t* __restrict__ nmax, float2* __restrict__ rng)
 {
     __shared__ double red[kRedLds];
     const BlkItem it = items[blockIdx.x];
@@ -594,49 +619,70 @@ __global__ __launch_bounds__(kBlk) void k_xsums(const BlkItem* __restrict__ item
     if (threadIdx.x == 0) pX[(int64_t)D * nblk_tot + gb] = s2;
 }
 
+// What the update of a thread's particle reads: Y*, the Brownian increment and
+// the mean of mu^Y (0 where the coefficients do not use it).  The kernels load
+// it before anything that waits, without branches (`slot` of a thread past the
+// system's end is the last particle's), so that it is one round trip to memory
+// with their other loads: a tick of a small cloud is a chain of those.
+template <int D>
+struct UpdateIn {
+    double y[D], dW[D], ybar[D];
+};
+
+template <typename T, int D>
+__device__ __forceinline__ UpdateIn<D> load_update(int sys, int64_t slot, int64_t P, const T* __restrict__ Y,
+                                                   const double* __restrict__ dWbuf, const double* __restrict__ ymean)
+{
+    UpdateIn<D> u;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        u.y[k] = (double)Y[k * P + slot];
+        u.dW[k] = dWbuf[k * P + slot];
+        u.ybar[k] = ymean[(int64_t)sys * kMaxD + k];
+    }
+    return u;
+}
+
+// The coefficients' cache lines fetched together, here: they lie in the
+// kernel's arguments, and each would otherwise be waited for where it is first
+// used, in the middle of the chain.
+__device__ __forceinline__ void touch_coefs(const Coef& cf)
+{
+    asm volatile("" ::"s"(cf.v_rho), "s"(cf.b_lam), "s"(cf.s0[0]), "s"(cf.s1[0]), "s"(cf.s2[0]), "s"(cf.coord_scale),
+                 "s"(cf.newton_max_iter), "s"(cf.v_cw), "s"(cf.fused));
+}
+
 // ---------------------------------------------------------------------------
 // The update (2.4) of one block at step n of its system, given each thread's
-// pair term, with the Brownian increments dW; then (fused) the implicit step
-// (2.3) of the next step.  All threads of the block must call it.
+// pair term; then (fused) the implicit step (2.3) of the next step.  All
+// threads of the block must call it.
 // ---------------------------------------------------------------------------
 template <typename T, int D>
 __device__ __forceinline__ void update_block(const BlkItem it, const SysDev& S, const Coef& cf, int64_t P, int64_t n,
-                                             const double (&pair)[D], T* __restrict__ X, T* __restrict__ Y,
-                                             T* __restrict__ Ys, const double* __restrict__ dWbuf,
-                                             const double* __restrict__ ymean, double* __restrict__ psumX,
+                                             const double (&pair)[D], const UpdateIn<D>& u, T* __restrict__ X,
+                                             T* __restrict__ Y, T* __restrict__ Ys, double* __restrict__ psumX,
                                              double* __restrict__ psumY, int64_t nblk_tot, Flags* flags,
-                                             int32_t* __restrict__ nmax, double2* __restrict__ rng, double* red)
+                                             int32_t* __restrict__ nmax, float2* __restrict__ rng, double* red)
 {
     const int par_out = (int)(n & 1) ^ 1;
-    // mean of mu^Y_n, reduced by the tick's preceding launch (null: the
-    // coefficients do not use it)
-    double ybar[kMaxD] = {0.0, 0.0, 0.0, 0.0};
-    if (ymean) {
-#pragma unroll
-        for (int k = 0; k < D; ++k) ybar[k] = ymean[(int64_t)it.sys * kMaxD + k];
-    }
     const int i = it.blk * kBlk + threadIdx.x;
     const bool valid = i < S.N;
     const int64_t slot = S.off + i;
     double xn[kMaxD] = {0.0, 0.0, 0.0, 0.0};
     if (valid) {
-        double yv[D];
-#pragma unroll
-        for (int k = 0; k < D; ++k) yv[k] = (double)Y[k * P + slot];
 #pragma unroll
         for (int k = 0; k < D; ++k) {
-            const double y = yv[k];
-            double b = cf.b_c0 * y + cf.b_lam * ybar[k] + pair[k];
+            const double y = u.y[k];
+            double b = cf.b_c0 * y + cf.b_lam * u.ybar[k] + pair[k];
             if (cf.has_lin) {
                 // the linear extension b_const + b_mat y + b_mean o ybar, terms in ascending l
                 b += cf.b_const[k];
 #pragma unroll
-                for (int l = 0; l < D; ++l) b += cf.b_mat[k * kMaxD + l] * yv[l];
-                b += cf.b_mean[k] * ybar[k];
+                for (int l = 0; l < D; ++l) b += cf.b_mat[k * kMaxD + l] * u.y[l];
+                b += cf.b_mean[k] * u.ybar[k];
             }
-            const double sig = cf.s0[k] + cf.s1[k] * y + cf.s2[k] * ybar[k];
-            const double dW = dWbuf[k * P + slot];
-            xn[k] = (y + S.h * b) + sig * dW;
+            const double sig = cf.s0[k] + cf.s1[k] * y + cf.s2[k] * u.ybar[k];
+            xn[k] = (y + S.h * b) + sig * u.dW[k];
         }
     }
     // a non-finite new state is flagged by the implicit solve that follows
@@ -686,31 +732,32 @@ __global__ __launch_bounds__(kBlk) void k_update(const BlkItem* __restrict__ ite
                                                  const double* __restrict__ ymean,
                                                  double* __restrict__ psumX,
                                                  double* __restrict__ psumY, int64_t nblk_tot,
-                                                 Flags* flags, int32_t* __restrict__ nmax, double2* __restrict__ rng)
+                                                 Flags* flags, int32_t* __restrict__ nmax, float2* __restrict__ rng)
 {
     __shared__ double red[kRedLds];
     const BlkItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
-    const int64_t n = tick_of(tick_dev, tick_arg) / S.stride;  // step index of this update
     const int i = it.blk * kBlk + threadIdx.x;
-    const int64_t slot = S.off + i;
+    const int64_t at = S.off + min(i, S.N - 1);
+    const UpdateIn<D> u = load_update<T, D>(it.sys, at, P, Y, dWbuf, ymean);
     double pair[D];
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         pair[k] = 0.0;
-        if (i >= S.N) continue;
         if (use_surr) {
             // learned surrogate of the pair term, projected to zero net force,
             // scaled by the gain fitted at the last check and (residual mode)
             // corrected by the particle's residual stored at the last check
             const float gk = k == 0 ? surr_gain.x : k == 1 ? surr_gain.y : k == 2 ? surr_gain.z : surr_gain.w;
-            pair[k] = (double)gk * ((double)surr[k * P + slot] - (double)surr_mean[(int64_t)it.sys * kMaxD + k]);
-            if (surr_res) pair[k] += (double)surr_res[k * P + slot];
+            pair[k] = (double)gk * ((double)surr[k * P + at] - (double)surr_mean[(int64_t)it.sys * kMaxD + k]);
+            if (surr_res) pair[k] += (double)surr_res[k * P + at];
         } else if (cf.has_pair) {
-            pair[k] = pairsum[k * P + slot];
+            pair[k] = pairsum[k * P + at];
         }
     }
-    update_block<T, D>(it, S, cf, P, n, pair, X, Y, Ys, dWbuf, ymean, psumX, psumY, nblk_tot, flags, nmax, rng, red);
+    touch_coefs(cf);
+    const int64_t n = step_of(tick_of(tick_dev, tick_arg), S.stride);  // step index of this update
+    update_block<T, D>(it, S, cf, P, n, pair, u, X, Y, Ys, psumX, psumY, nblk_tot, flags, nmax, rng, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -783,7 +830,7 @@ __device__ __forceinline__ void brownian_block(int vb, const BlkItem* __restrict
     const int q = threadIdx.x % LP;
     const int i = it.blk * kBlk + sub * (kBlk / LP) + threadIdx.x / LP;
     const int64_t t = tick_of(tick_dev, tick_arg);
-    const int64_t n = t / S.stride;
+    const int64_t n = step_of(t, S.stride);
     double zs[kMaxD] = {0.0, 0.0, 0.0, 0.0};
     if (i < S.N) {
         if (S.win_W > 0) {
@@ -824,7 +871,7 @@ __device__ __forceinline__ void ymean_block(int q, const YMeanJob& job, const Sy
     __shared__ double red[kRedLds];
     const int s = job.sys_list[q];
     const SysDev S = sys[s];
-    const int64_t n = tick_of(tick_dev, tick_arg) / S.stride;
+    const int64_t n = step_of(tick_of(tick_dev, tick_arg), S.stride);
     double m[kMaxD];
     system_means<D>(S, job.psumY + (int64_t)(n & 1) * D * job.nblk_tot, job.nblk_tot, D, m, red);
     if (threadIdx.x == 0)

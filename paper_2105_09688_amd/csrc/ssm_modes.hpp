@@ -37,7 +37,7 @@ namespace ssm {
 
 constexpr int kModeChunk = 8;                  // modes between reductions over a wavefront
 constexpr int kModeCap = 1024;                 // modes of a system at most
-constexpr int kModeVals = 2 * kModeCap;        // doubles of a partial row: per chunk C_m x 8, S_m x 8
+constexpr int kModeVals = 2 * kModeCap;        // values of a partial row: per chunk C_m x 8, S_m x 8
 constexpr double kModeAlpha = 0.69314718055994530942;  // a = ln 2
 constexpr double kTwoPi = 6.283185307179586476925286766559;
 
@@ -50,6 +50,16 @@ struct ModeLimits {
 };
 
 __host__ __device__ constexpr ModeLimits mode_limits(bool fp64) { return fp64 ? ModeLimits{7.8, 10.46} : ModeLimits{6.3, 8.35}; }
+
+// Value v of partial row `row` is at mode_at(row, v): the 16 values of a chunk
+// side by side, the rows of a chunk one after the other.  A system's rows are
+// then read from consecutive addresses; rows of kModeVals doubles, 16 KiB
+// apart, all met the same cache channels (the 256 rows of N = 2^16: 3.2 us of
+// k_update_modes' 8).
+__host__ __device__ constexpr int64_t mode_at(int64_t row, int v, int64_t rows)
+{
+    return ((v >> 4) * rows + row) * 16 + (v & 15);
+}
 
 // Particles [i0, i0 + n) of a system, n <= 256 P, into partial row `row`.
 struct ModeItem {
@@ -80,16 +90,20 @@ __device__ __forceinline__ ModeDom mode_domain(double lo, double hi, int32_t N, 
 }
 
 // A system's domain from its blocks' ranges; every thread of a kBlk block gets it.
-__device__ __forceinline__ ModeDom system_domain(const SysDev& S, const double2* __restrict__ rng, bool fp64, double* red)
+__device__ __forceinline__ ModeDom system_domain(const SysDev& S, const float2* __restrict__ rng, bool fp64, float2* red)
 {
-    double lo = INFINITY, hi = -INFINITY;
+    float lo = INFINITY, hi = -INFINITY;
     for (int b = threadIdx.x; b < S.nblk; b += kBlk) {
-        const double2 r = rng[S.blk0 + b];
-        lo = fmin(lo, r.x);
-        hi = fmax(hi, r.y);
+        const float2 r = rng[S.blk0 + b];
+        lo = fminf(lo, r.x);
+        hi = fmaxf(hi, r.y);
     }
-    block_range(lo, hi, red);
-    return mode_domain(lo, hi, S.N, fp64);
+    wave_range(lo, hi);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = make_float2(lo, hi);
+    __syncthreads();
+    lo = fminf(fminf(red[0].x, red[1].x), fminf(red[2].x, red[3].x));
+    hi = fmaxf(fmaxf(red[0].y, red[1].y), fmaxf(red[2].y, red[3].y));
+    return mode_domain((double)lo, (double)hi, S.N, fp64);
 }
 
 // cos and sin of 2 pi t for |t| <= 1/2: quadrant k = rint(4 t), the rest by
@@ -188,20 +202,19 @@ constexpr int kRowVals = 128;
 constexpr int kModeRowsLds = kBlk / 16;  // rows of 16 lanes in a block
 
 template <typename T, int P>
-__device__ __forceinline__ void mode_block(const ModeItem it, const SysDev* __restrict__ sys, const T* __restrict__ Ys,
-                                           const double2* __restrict__ rng, ModeDom* __restrict__ dom,
-                                           double* __restrict__ part, double* __restrict__ pairsum)
+__device__ __forceinline__ void mode_block(const ModeItem& it, const SysDev& S, const T* __restrict__ Ys,
+                                           const float2* __restrict__ rng, ModeDom* __restrict__ dom,
+                                           double* __restrict__ part, int64_t nrows_tot, double* __restrict__ pairsum)
 {
     __shared__ __align__(32) double rows[kModeRowsLds][kRowVals + 16];
     static_assert(sizeof(rows) >= kDirectTile * sizeof(T), "the direct sums stage their sources there");
-    __shared__ double red[kRedLds];
-    const SysDev S = sys[it.sys];
+    __shared__ float2 red[kBlk / 64];
     // the positions are on their way while the domain is reduced
     T s[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        const int j = p * kBlk + (int)threadIdx.x;
-        s[p] = j < it.n ? Ys[S.off + it.i0 + j] : (T)0;
+        const int j = min(p * kBlk + (int)threadIdx.x, it.n - 1);
+        s[p] = Ys[S.off + it.i0 + j];
     }
     const ModeDom d = system_domain(S, rng, sizeof(T) == 8, red);
     if (it.row == S.mode_row0 && threadIdx.x == 0) dom[it.sys] = d;
@@ -223,7 +236,6 @@ __device__ __forceinline__ void mode_block(const ModeItem it, const SysDev* __re
         wr[p] = valid ? zr[p] : 0.0;
         wi[p] = valid ? zi[p] : 0.0;
     }
-    double* out = part + (int64_t)it.row * kModeVals;
     for (int v0 = 0; v0 < 2 * d.M; v0 += kRowVals) {
         const int v1 = min(v0 + kRowVals, 2 * d.M);
         for (int v = v0; v < v1; v += 2 * kModeChunk) {
@@ -248,7 +260,7 @@ __device__ __forceinline__ void mode_block(const ModeItem it, const SysDev* __re
             double t = 0.0;
 #pragma unroll
             for (int q = 0; q < kModeRowsLds; ++q) t += rows[q][v];
-            out[v0 + v] = t;
+            part[mode_at(it.row, v0 + v, nrows_tot)] = t;
         }
         if (v1 < 2 * d.M) __syncthreads();
     }
@@ -256,46 +268,62 @@ __device__ __forceinline__ void mode_block(const ModeItem it, const SysDev* __re
 
 // n_modes blocks of mode sums, then (up to n_main) the Brownian sums, then
 // job.n blocks of system means.
-template <typename T, int P, int LP>
-__global__ __launch_bounds__(kBlk) void k_modes(int n_modes, int n_main, const ModeItem* __restrict__ mitems,
+template <typename T, int P, int LP, bool ONE>
+__global__ __launch_bounds__(kBlk) void k_modes(int n_modes, int n_main, SysDev one, const ModeItem* __restrict__ mitems,
                                                 const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
                                                 Coef cf, int64_t Pn, const T* __restrict__ Ys,
-                                                const double2* __restrict__ rng, ModeDom* __restrict__ dom,
-                                                double* __restrict__ part, double* __restrict__ pairsum,
-                                                int64_t tick_arg, const int64_t* __restrict__ tick_dev,
+                                                const float2* __restrict__ rng, ModeDom* __restrict__ dom,
+                                                double* __restrict__ part, int64_t nrows_tot,
+                                                double* __restrict__ pairsum, int64_t tick_arg, const int64_t* __restrict__ tick_dev,
                                                 const double* __restrict__ win, double* __restrict__ dW, YMeanJob job)
 {
-    if ((int)blockIdx.x < n_modes)
-        mode_block<T, P>(mitems[blockIdx.x], sys, Ys, rng, dom, part, pairsum);
-    else if ((int)blockIdx.x < n_main)
+    if ((int)blockIdx.x < n_modes) {
+        if constexpr (ONE) {
+            const int i0 = (int)blockIdx.x * kBlk * P;
+            mode_block<T, P>(ModeItem{0, (int)blockIdx.x, i0, min(kBlk * P, one.N - i0)}, one, Ys, rng, dom, part,
+                             nrows_tot, pairsum);
+        } else {
+            const ModeItem it = mitems[blockIdx.x];
+            mode_block<T, P>(it, sys[it.sys], Ys, rng, dom, part, nrows_tot, pairsum);
+        }
+    } else if ((int)blockIdx.x < n_main)
         brownian_block<1, LP, (sizeof(T) == 4)>(blockIdx.x - n_modes, items, sys, cf, Pn, tick_arg, tick_dev, win, dW);
     else
         ymean_block<1>(blockIdx.x - n_main, job, sys, tick_arg, tick_dev);
 }
 
-// Sum over rows [row0, row0 + nrows) of value v0 + (t & 63), in a fixed order,
-// by all threads of a block; thread t < 64 gets it.
-__device__ __forceinline__ double add_rows(const double* __restrict__ part, int64_t row0, int nrows, int v, bool in,
-                                           double (*stage)[64])
+// The thread's share of the sums over a system's rows of the values
+// v0 + 32 q + 2 l, + 1 (l = threadIdx.x % 16, q < 2): rows threadIdx.x / 16 +
+// 16 u.  Sixteen rows of both at a time (indexes past the end repeat the last
+// row and count nothing), so that 256 rows are one round trip to memory.
+struct RowBatch {
+    double2 v[2][16];
+};
+
+__device__ __forceinline__ RowBatch row_batch(const double* __restrict__ part, int64_t nrows_tot, const SysDev& S, int v0,
+                                              int r0)
 {
-    constexpr int kW = kBlk / 64;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    double a = 0.0;
-    if (in) {
-        const double* p = part + row0 * kModeVals + v;
-        int r = wave;
-        for (; r + 15 * kW < nrows; r += 16 * kW) {
-            double q[16];
+    RowBatch b;
 #pragma unroll
-            for (int u = 0; u < 16; ++u) q[u] = p[(int64_t)(r + u * kW) * kModeVals];
+    for (int q = 0; q < 2; ++q) {
+        const double2* p = reinterpret_cast<const double2*>(
+            part + mode_at(S.mode_row0, v0 + 32 * q + 2 * (int)(threadIdx.x & 15), nrows_tot));
 #pragma unroll
-            for (int u = 0; u < 16; ++u) a += q[u];
-        }
-        for (; r < nrows; r += kW) a += p[(int64_t)r * kModeVals];
+        for (int u = 0; u < 16; ++u) b.v[q][u] = p[(int64_t)min(r0 + 16 * u, S.mode_rows - 1) * 8];
     }
-    stage[wave][lane] = a;
-    __syncthreads();
-    return (stage[0][lane] + stage[1][lane]) + (stage[2][lane] + stage[3][lane]);
+    return b;
+}
+
+__device__ __forceinline__ void add_batch(const RowBatch& b, int r0, int nrows, double2 (&a)[2])
+{
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const bool in = r0 + 16 * u < nrows;
+            a[q].x += in ? b.v[q][u].x : 0.0;
+            a[q].y += in ? b.v[q][u].y : 0.0;
+        }
 }
 
 // k_mode_total: the rows of each listed system added up once, into one row of
@@ -304,7 +332,7 @@ __device__ __forceinline__ double add_rows(const double* __restrict__ part, int6
 // systems have.
 __global__ __launch_bounds__(kBlk) void k_mode_total(const int32_t* __restrict__ sys_list, const SysDev* __restrict__ sys,
                                                      const ModeDom* __restrict__ dom, const double* __restrict__ part,
-                                                     double* __restrict__ tot)
+                                                     int64_t nrows_tot, double* __restrict__ tot)
 {
     __shared__ double stage[kBlk / 16][16];
     const int s = sys_list[blockIdx.x];
@@ -312,17 +340,17 @@ __global__ __launch_bounds__(kBlk) void k_mode_total(const int32_t* __restrict__
     const int V = 2 * dom[s].M;
     const int w = threadIdx.x >> 4, l = threadIdx.x & 15;
     for (int v0 = blockIdx.y * 16; v0 < V; v0 += gridDim.y * 16) {
-        const double* p = part + (int64_t)S.mode_row0 * kModeVals + v0 + l;
+        const double* p = part + mode_at(S.mode_row0, v0 + l, nrows_tot);
         double a = 0.0;
         int r = w;
         for (; r + 7 * 16 < S.mode_rows; r += 8 * 16) {
             double q[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) q[u] = p[(int64_t)(r + u * 16) * kModeVals];
+            for (int u = 0; u < 8; ++u) q[u] = p[(int64_t)(r + u * 16) * 16];
 #pragma unroll
             for (int u = 0; u < 8; ++u) a += q[u];
         }
-        for (; r < S.mode_rows; r += 16) a += p[(int64_t)r * kModeVals];
+        for (; r < S.mode_rows; r += 16) a += p[(int64_t)r * 16];
         stage[w][l] = a;
         __syncthreads();
         if (threadIdx.x < 16) {
@@ -335,35 +363,55 @@ __global__ __launch_bounds__(kBlk) void k_mode_total(const int32_t* __restrict__
     }
 }
 
-// The coefficients g_m = c_m (S_m + i C_m), m = 1 .. M, of a system into LDS.
-__device__ __forceinline__ void mode_coefs(const ModeDom& d, const double* __restrict__ part, int64_t row0, int nrows,
-                                           double2* g, double (*stage)[64])
+// Value v of a system's sums, C_m or S_m, times c_m into the coefficients
+// g_m = c_m (S_m + i C_m).
+__device__ __forceinline__ void mode_coef(const ModeDom& d, int v, double sum, double2* g)
 {
     const double delta = kTwoPi * d.inv_L;
     const double c0 = delta * 0.3388303758015525;  // 1 / sqrt(4 pi a)
-    for (int v0 = 0; v0 < 2 * d.M; v0 += 64) {
-        const int v = v0 + (int)(threadIdx.x & 63);
-        const double a = add_rows(part, row0, nrows, v, v < 2 * d.M, stage);
-        if (threadIdx.x < 64 && v < 2 * d.M) {
-            const int m = (v >> 4) * kModeChunk + (v & 7);  // from 0
-            const double k = (double)(m + 1) * delta;
-            // e^(-k^2 / (4 a)) = 2^(-k^2 / (4 a^2))
-            const double c = c0 * (k * 1.4426950408889634) * exp2_fast<double>(k * k * -0.5203422452514019);
-            double* gm = reinterpret_cast<double*>(g + m);
-            gm[(v & 8) ? 0 : 1] = c * a;
+    const int m = (v >> 4) * kModeChunk + (v & 7);  // from 0
+    const double k = (double)(m + 1) * delta;
+    // e^(-k^2 / (4 a)) = 2^(-k^2 / (4 a^2))
+    const double c = c0 * (k * 1.4426950408889634) * exp2_fast<double>(k * k * -0.5203422452514019);
+    double* gm = reinterpret_cast<double*>(g + m);
+    gm[(v & 8) ? 0 : 1] = c * sum;
+}
+
+// The coefficients of a system from its rows, kCoefVals values (32 modes) a
+// round; `first` are the first round's rows, fetched before the domain is
+// known, since the rows are long enough for any.
+constexpr int kCoefVals = 64;
+
+__device__ __forceinline__ void mode_coefs(const ModeDom& d, const double* __restrict__ part, int64_t nrows_tot,
+                                           const SysDev& S, const RowBatch& first, double2* g, double (*stage)[kCoefVals])
+{
+    const int w = threadIdx.x >> 4;
+    for (int v0 = 0; v0 < 2 * d.M; v0 += kCoefVals) {
+        double2 a[2] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+        if (v0 == 0) add_batch(first, w, S.mode_rows, a);
+        for (int r0 = v0 == 0 ? w + 256 : w; r0 < S.mode_rows; r0 += 256)
+            add_batch(row_batch(part, nrows_tot, S, v0, r0), r0, S.mode_rows, a);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            *reinterpret_cast<double2*>(&stage[w][32 * q + 2 * (threadIdx.x & 15)]) = a[q];
+        __syncthreads();
+        const int v = v0 + (int)threadIdx.x;
+        if (threadIdx.x < kCoefVals && v < 2 * d.M) {
+            double t = 0.0;
+#pragma unroll
+            for (int u = 0; u < kBlk / 16; ++u) t += stage[u][threadIdx.x];
+            mode_coef(d, v, t, g);
         }
         __syncthreads();
     }
 }
 
-// sum_m Re(g_m z^m) at the scaled position s, by Horner's rule.
-__device__ __forceinline__ double mode_eval(const ModeDom& d, const double2* g, double s)
+// sum_m Re(g_m z^m) by Horner's rule.
+__device__ __forceinline__ double mode_eval(int M, const double2* g, double zr, double zi)
 {
-    double zr, zi;
-    sincos_turn((s - d.c) * d.inv_L, &zi, &zr);
     double pr = 0.0, pi = 0.0;
 #pragma unroll 8
-    for (int m = d.M - 1; m >= 0; --m) {
+    for (int m = M - 1; m >= 0; --m) {
         const double2 gm = g[m];
         const double t = fma(pr, zr, fma(-pi, zi, gm.x));
         pi = fma(pr, zi, fma(pi, zr, gm.y));
@@ -373,59 +421,88 @@ __device__ __forceinline__ double mode_eval(const ModeDom& d, const double2* g, 
 }
 
 // The scaled pair term of one block's particles (each thread its own), from
-// the rows of its system; stored in pairsum too, for whoever reads the exact
-// term after the tick (the surrogate's check, the training sampler).
-template <typename T>
+// the rows of its system (TOTALS: from the one row that k_mode_total made of
+// them; the sixteen loads in flight of the other form would cost the large
+// contexts half of their wavefronts); stored in pairsum too, for whoever reads
+// the exact term after the tick (the surrogate's check, the training sampler).
+template <bool TOTALS>
+struct ModeLds {
+    double2 g[kModeCap];
+    double stage[TOTALS ? 1 : kBlk / 16][kCoefVals];
+};
+
+template <typename T, bool TOTALS>
 __device__ __forceinline__ double mode_pair(const BlkItem it, const SysDev& S, const T* __restrict__ Ys,
                                             const ModeDom* __restrict__ dom, const double* __restrict__ part,
-                                            int totals, double* __restrict__ pairsum, double2* g, double (*stage)[64])
+                                            int64_t nrows_tot, double* __restrict__ pairsum, ModeLds<TOTALS>& lds)
 {
     const int i = it.blk * kBlk + threadIdx.x;
-    const bool valid = i < S.N;
-    const T ys = valid ? Ys[S.off + i] : (T)0;
+    const int64_t at = S.off + min(i, S.N - 1);
     const ModeDom d = dom[it.sys];
-    if (d.M == 0) return valid ? pairsum[S.off + i] : 0.0;  // block-uniform
-    mode_coefs(d, part, totals ? it.sys : S.mode_row0, totals ? 1 : S.mode_rows, g, stage);
-    const double K = valid ? mode_eval(d, g, (double)ys) * S.pair_scale : 0.0;
-    if (valid) pairsum[S.off + i] = K;
+    const T ys = Ys[at];
+    double zr, zi;
+    if constexpr (TOTALS) {
+        const double* row = part + (int64_t)it.sys * kModeVals;
+        double a = row[threadIdx.x];
+        if (d.M == 0) return pairsum[at];  // block-uniform
+        for (int v = threadIdx.x; v < 2 * d.M; v += kBlk) {
+            if (v >= kBlk) a = row[v];
+            mode_coef(d, v, a, lds.g);
+        }
+        sincos_turn(((double)ys - d.c) * d.inv_L, &zi, &zr);
+        __syncthreads();
+    } else {
+        const RowBatch first = row_batch(part, nrows_tot, S, 0, threadIdx.x >> 4);
+        if (d.M == 0) return pairsum[at];
+        sincos_turn(((double)ys - d.c) * d.inv_L, &zi, &zr);
+        mode_coefs(d, part, nrows_tot, S, first, lds.g, lds.stage);
+    }
+    const double K = mode_eval(d.M, lds.g, zr, zi) * S.pair_scale;
+    if (i < S.N) pairsum[at] = K;
     return K;
 }
 
-// k_update_modes: k_update with the pair term evaluated here (d = 1).
-// totals: part holds one row per system (k_mode_total).
-template <typename T>
-__global__ __launch_bounds__(kBlk) void k_update_modes(const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
-                                                       Coef cf, int64_t P, int64_t tick_arg,
+// k_update_modes: k_update with the pair term evaluated here (d = 1).  ONE: a
+// context of one system, passed as an argument, whose blocks are numbered by
+// blockIdx: two loads less in the chain of dependent ones.
+//
+// At N = 8191 and 2^16 (one wavefront per SIMD) the kernel is that chain.  By
+// its own clock it took 15500 cycles, of which 7700 until the rows had
+// arrived, in six waits one after the other; 2700 in the implicit solve; 1100
+// in the block's reductions.  Every load is issued before the first wait now.
+template <typename T, bool TOTALS, bool ONE>
+__global__ __launch_bounds__(kBlk) void k_update_modes(SysDev one, const BlkItem* __restrict__ items,
+                                                       const SysDev* __restrict__ sys, Coef cf, int64_t P, int64_t tick_arg,
                                                        const int64_t* __restrict__ tick_dev, T* __restrict__ X,
                                                        T* __restrict__ Y, T* Ys, const ModeDom* __restrict__ dom,
-                                                       const double* __restrict__ part, int totals,
+                                                       const double* __restrict__ part, int64_t nrows_tot,
                                                        double* __restrict__ pairsum, const double* __restrict__ dWbuf,
                                                        const double* __restrict__ ymean, double* __restrict__ psumX,
                                                        double* __restrict__ psumY, int64_t nblk_tot, Flags* flags,
-                                                       int32_t* __restrict__ nmax, double2* __restrict__ rng)
+                                                       int32_t* __restrict__ nmax, float2* __restrict__ rng)
 {
     __shared__ double red[kRedLds];
-    __shared__ double stage[kBlk / 64][64];
-    __shared__ __align__(16) double2 g[kModeCap];
-    const BlkItem it = items[blockIdx.x];
-    const SysDev S = sys[it.sys];
-    const int64_t n = tick_of(tick_dev, tick_arg) / S.stride;
-    const double pair[1] = {mode_pair<T>(it, S, Ys, dom, part, totals, pairsum, g, stage)};
-    update_block<T, 1>(it, S, cf, P, n, pair, X, Y, Ys, dWbuf, ymean, psumX, psumY, nblk_tot, flags, nmax, rng, red);
+    __shared__ __align__(16) ModeLds<TOTALS> lds;
+    const BlkItem it = ONE ? BlkItem{0, (int)blockIdx.x} : items[blockIdx.x];
+    const SysDev S = ONE ? one : sys[it.sys];
+    const int i = it.blk * kBlk + threadIdx.x;
+    const UpdateIn<1> u = load_update<T, 1>(it.sys, S.off + min(i, S.N - 1), P, Y, dWbuf, ymean);
+    touch_coefs(cf);
+    const double pair[1] = {mode_pair<T, TOTALS>(it, S, Ys, dom, part, nrows_tot, pairsum, lds)};
+    const int64_t n = step_of(tick_of(tick_dev, tick_arg), S.stride);
+    update_block<T, 1>(it, S, cf, P, n, pair, u, X, Y, Ys, psumX, psumY, nblk_tot, flags, nmax, rng, red);
 }
 
 // k_mode_eval: the pair term alone into pairsum (the training sampler).
-template <typename T>
+template <typename T, bool TOTALS>
 __global__ __launch_bounds__(kBlk) void k_mode_eval(const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
                                                     const T* __restrict__ Ys, const ModeDom* __restrict__ dom,
-                                                    const double* __restrict__ part, int totals,
+                                                    const double* __restrict__ part, int64_t nrows_tot,
                                                     double* __restrict__ pairsum)
 {
-    __shared__ double stage[kBlk / 64][64];
-    __shared__ __align__(16) double2 g[kModeCap];
+    __shared__ __align__(16) ModeLds<TOTALS> lds;
     const BlkItem it = items[blockIdx.x];
-    const SysDev S = sys[it.sys];
-    (void)mode_pair<T>(it, S, Ys, dom, part, totals, pairsum, g, stage);
+    (void)mode_pair<T, TOTALS>(it, sys[it.sys], Ys, dom, part, nrows_tot, pairsum, lds);
 }
 
 }  // namespace ssm

@@ -534,7 +534,7 @@ template <typename T, int D>
 __global__ __launch_bounds__(kBlk) void k_ysums(const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
                                                 int64_t P, int64_t tick_arg, const T* __restrict__ Y,
                                                 double coord_scale, double* __restrict__ psumY, int64_t nblk_tot,
-                                                double2* __restrict__ rng)
+                                                float2* __restrict__ rng)
 {
     __shared__ double red[kRedLds];
     const BlkItem it = items[blockIdx.x];
@@ -544,13 +544,18 @@ __global__ __launch_bounds__(kBlk) void k_ysums(const BlkItem* __restrict__ item
     const int i = it.blk * kBlk + threadIdx.x;
     const bool valid = i < S.N;
     const int64_t gb = S.blk0 + it.blk;
+    if constexpr (D == 1) {
+        if (rng) {
+            const double y = (double)Y[S.off + i];
+            const double s = sum_and_range(valid, valid ? y : 0.0, (double)(T)(coord_scale * y), rng, gb, red);
+            if (threadIdx.x == 0) pY[gb] = s;
+            return;
+        }
+    }
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         const double s = block_sum(valid ? (double)Y[k * P + S.off + i] : 0.0, red);
         if (threadIdx.x == 0) pY[(int64_t)k * nblk_tot + gb] = s;
-    }
-    if constexpr (D == 1) {
-        if (rng) store_range(valid, (double)(T)(coord_scale * (double)Y[S.off + i]), rng, gb, red);
     }
 }
 
