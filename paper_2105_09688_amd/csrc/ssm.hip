@@ -16,7 +16,7 @@
 #include "../../include/ssm.h"
 #include "ssm_surrogate.hpp"
 #include "ssm_small.hpp"
-#include "ssm_modes.hpp"
+#include "ssm_solo.hpp"
 
 using namespace ssm;
 
@@ -328,6 +328,9 @@ struct ssm_ctx {
     double* mode_tot = nullptr;     // [n_sys][kModeVals] (mode_totals)
     float2* rng = nullptr;          // [nblk_tot] range of the scaled positions of each block
     // persistent runs of small systems (ssm_small.hpp)
+    bool solo = false;              // in one workgroup per system (ssm_solo.hpp) in place of tiles
+    int64_t solo_ticks = 0;         // ticks per launch: what solo_dW holds
+    double* solo_dW = nullptr;      // [solo_ticks][P] increments of a launch
     bool small_ok = false;          // eligible: ticks without surrogate, profiling or graphs use it
     SmallTile* dtiles = nullptr;    // [small_grid] workgroup -> (system, tile)
     int64_t small_grid = 0;         // tiles of 64 particles = workgroups per launch
@@ -399,7 +402,7 @@ static void free_ctx(ssm_ctx* c)
                     c->dmlp, c->surr, c->rff_part, c->mom, c->err_part, c->dsys_list, c->smean_part, c->smean,
                     c->dtick, c->dW, c->surr_res, c->dnmax, c->dred, c->dsq, c->win, c->dwin_items, c->ymean,
                     c->jtot, c->dtiles, c->sumY, c->sumX, c->dbar,
-                    c->dmitems, c->dom, c->mode_part, c->mode_tot, c->rng};
+                    c->dmitems, c->solo_dW, c->dom, c->mode_part, c->mode_tot, c->rng};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     recycle_events(c, c->ev_pair);
@@ -1019,10 +1022,65 @@ static bool small_usable(const ssm_ctx* c)
     return c->small_ok && c->surr_check_every == 0 && !c->profiling && !c->use_graphs;
 }
 
+// Host state after n ticks in one launch.
+static ssm_status after_small(ssm_ctx* c, int64_t n)
+{
+    c->small_launches++;
+    c->small_ticks += n;
+    for (int64_t t = 0; t < n; ++t) advance_host(c);
+    c->dtick_valid = false;
+    c->psum_stale = true;
+    return SSM_OK;
+}
+
+// n ticks of every system, one workgroup each: the launch's increments, then
+// the ticks.
+template <typename T>
+static ssm_status launch_solo(ssm_ctx* c, int64_t n)
+{
+    const BlkItem* items = c->dblk + c->all_blk_off[0];
+    const dim3 gd((unsigned)(c->all_blk_cnt * c->small_lanes), (unsigned)n);
+#define SSM_DRAW(LPV)                                                                                              \
+    hipLaunchKernelGGL((k_solo_draw<LPV, (sizeof(T) == 4)>), gd, dim3(kBlk), 0, c->stream, items, c->dsys, c->coef, \
+                       c->P, c->tick, c->solo_dW)
+    switch (c->small_lanes) {
+        case 16: SSM_DRAW(16); break;
+        case 8: SSM_DRAW(8); break;
+        case 4: SSM_DRAW(4); break;
+        case 2: SSM_DRAW(2); break;
+        default: SSM_DRAW(1); break;
+    }
+#undef SSM_DRAW
+    HIP_TRY(hipGetLastError());
+    SoloArgs<T> a{c->dsys, c->coef, c->P, c->tick, n, (T*)c->X, (T*)c->Y, (T*)c->Ys, c->solo_dW, c->dflags, c->dnmax};
+    const dim3 g((unsigned)c->sys.size());
+    int64_t top = 0;
+    for (auto& S : c->sys) top = std::max(top, S.N);
+    // the fewest threads of up to four particles: each wavefront's reductions
+    // then serve 256 particles
+#define SSM_SOLO(PAIR)                                                                                           \
+    do {                                                                                                         \
+        if (top <= 256) hipLaunchKernelGGL((k_solo<T, PAIR, 256, 1>), g, dim3(256), 0, c->stream, a);            \
+        else if (top <= 512) hipLaunchKernelGGL((k_solo<T, PAIR, 256, 2>), g, dim3(256), 0, c->stream, a);       \
+        else if (top <= 1024) hipLaunchKernelGGL((k_solo<T, PAIR, 256, 4>), g, dim3(256), 0, c->stream, a);      \
+        else hipLaunchKernelGGL((k_solo<T, PAIR, 512, 4>), g, dim3(512), 0, c->stream, a);                       \
+    } while (0)
+    if (c->has_pair) SSM_SOLO(true);
+    else SSM_SOLO(false);
+#undef SSM_SOLO
+    HIP_TRY(hipGetLastError());
+    return SSM_OK;
+}
+
 // n ticks in one cooperative launch.
 template <typename T>
 static ssm_status launch_small(ssm_ctx* c, int64_t n)
 {
+    if (c->solo) {
+        ssm_status st = launch_solo<T>(c, n);
+        if (st != SSM_OK) return st;
+        return after_small(c, n);
+    }
     SmallArgs<T> a{};
     a.tiles = c->dtiles;
     a.sys = c->dsys;
@@ -1047,12 +1105,7 @@ static ssm_status launch_small(ssm_ctx* c, int64_t n)
     HIP_TRY(hipLaunchCooperativeKernel(small_kernel(c->prec, c->d), dim3((unsigned)c->small_grid), dim3(kSmallThreads),
                                        args, 0, c->stream));
     c->small_epoch += small_barriers(c->fused, n);
-    c->small_launches++;
-    c->small_ticks += n;
-    for (int64_t t = 0; t < n; ++t) advance_host(c);
-    c->dtick_valid = false;
-    c->psum_stale = true;
-    return SSM_OK;
+    return after_small(c, n);
 }
 
 // What the multi-launch path reads from earlier ticks, after persistent ticks
@@ -1337,15 +1390,19 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     if (cfg->persistent >= 0) {
         int64_t ntiles = 0;
         for (auto& S : c->sys) ntiles += (S.N + kSmallTile - 1) / kSmallTile;
-        const std::string why = small_ineligible(c, ntiles);
-        if (cfg->persistent == 1 && !why.empty()) { free_ctx(c); return fail(SSM_ERR_INVALID, "persistent = 1: " + why); }
-        // default: at most one tile per compute unit, where the estimate
-        // says the multi-launch tick is slower (bound by launch latency),
-        // unless a tiling of the multi-launch pair kernels was asked for
+        // a tiling of the multi-launch pair kernels asks for them
         const bool tiled = cfg->targets_per_lane != 0 || cfg->sources_per_item != 0 || cfg->pair_scheme != 0 ||
                            cfg->jside_band_groups != 0;
-        c->small_ok = why.empty() &&
-                      (cfg->persistent == 1 || (!tiled && ntiles <= device_cus() && small_preferred(c)));
+        int64_t top = 0;
+        for (auto& S : c->sys) top = std::max(top, S.N);
+        c->solo = cfg->persistent == 0 && c->d == 1 && !tiled && (c->modes || !c->has_pair) && top <= kSoloMax;
+        const std::string why = c->solo ? "" : small_ineligible(c, ntiles);
+        if (cfg->persistent == 1 && !why.empty()) { free_ctx(c); return fail(SSM_ERR_INVALID, "persistent = 1: " + why); }
+        // default: one-dimensional systems that a workgroup holds; else at most
+        // one tile per compute unit, where the estimate says the multi-launch
+        // tick is slower (bound by launch latency), which it is not by modes
+        c->small_ok = why.empty() && (c->solo || cfg->persistent == 1 ||
+                                      (!tiled && !c->modes && ntiles <= device_cus() && small_preferred(c)));
         if (c->small_ok) {
             for (int s = 0; s < (int)c->sys.size(); ++s) {
                 const int32_t nt = (int32_t)((c->sys[s].N + kSmallTile - 1) / kSmallTile);
@@ -1361,6 +1418,9 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
                 (void)hipGetLastError();
                 khz = 100000;  // the 100 MHz counter of gfx9
             }
+            // a launch's increments in 24 MiB (at least 16 ticks of them)
+            c->solo_ticks = std::min<int64_t>(std::max<int64_t>(((int64_t)24 << 20) / (8 * c->P), 16), kSmallTicksPerLaunch);
+            c->solo_ticks = std::min(c->solo_ticks, c->ticks_total);
             c->small_wait_limit = (int64_t)khz * 1000 * 4;  // 4 s per barrier wait
             if (const char* env = std::getenv("SSM_PERSISTENT_WAIT_US")) {
                 const long long us = std::atoll(env);
@@ -1501,7 +1561,8 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     }
     ALLOC(c->dsq, c->sys.size() * sizeof(double));
     ALLOC(c->ymean, c->sys.size() * kMaxD * sizeof(double));
-    if (c->small_ok) {
+    if (c->solo) ALLOC(c->solo_dW, (size_t)c->solo_ticks * c->P * sizeof(double));
+    if (c->small_ok && !c->solo) {
         ALLOC(c->dtiles, tiles.size() * sizeof(SmallTile));
         ALLOC(c->sumY, 2 * (size_t)c->d * c->small_grid * sizeof(double));
         ALLOC(c->sumX, (size_t)(c->d + 1) * c->small_grid * sizeof(double));
@@ -1520,8 +1581,8 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     if (he == hipSuccess) he = hipMemsetAsync(c->dtick, 0, sizeof(int64_t), c->stream);
     // read by every update, written only where the coefficients use the means
     if (he == hipSuccess) he = hipMemsetAsync(c->ymean, 0, c->sys.size() * kMaxD * sizeof(double), c->stream);
-    if (he == hipSuccess && c->small_ok) he = hipMemcpyAsync(c->dtiles, tiles.data(), tiles.size() * sizeof(SmallTile), hipMemcpyHostToDevice, c->stream);
-    if (he == hipSuccess && c->small_ok) he = hipMemsetAsync(c->dbar, 0, c->sys.size() * kBarLine * sizeof(uint64_t), c->stream);
+    if (he == hipSuccess && c->small_ok && !c->solo) he = hipMemcpyAsync(c->dtiles, tiles.data(), tiles.size() * sizeof(SmallTile), hipMemcpyHostToDevice, c->stream);
+    if (he == hipSuccess && c->small_ok && !c->solo) he = hipMemsetAsync(c->dbar, 0, c->sys.size() * kBarLine * sizeof(uint64_t), c->stream);
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);  // host vectors go out of scope
     if (he != hipSuccess) { std::string m = hipGetErrorString(he); free_ctx(c); return fail(SSM_ERR_HIP, "upload: " + m); }
 
@@ -1543,7 +1604,7 @@ extern "C" ssm_status ssm_step(ssm_ctx* c, int64_t n_ticks)
         // does not hold the GPU for an unbounded time (a run split over
         // launches equals one launch bit for bit)
         for (int64_t done = 0; done < n_ticks;) {
-            const int64_t n = std::min<int64_t>(n_ticks - done, kSmallTicksPerLaunch);
+            const int64_t n = std::min<int64_t>(n_ticks - done, c->solo ? c->solo_ticks : kSmallTicksPerLaunch);
             ssm_status st = (c->prec == SSM_FP64) ? launch_small<double>(c, n) : launch_small<float>(c, n);
             if (st != SSM_OK) return st;
             done += n;

@@ -215,89 +215,153 @@ __device__ __forceinline__ double rcp_fast(double x)
 // ---------------------------------------------------------------------------
 constexpr int kPlainNewton = 12;  // corrections before the bracketed form takes over
 
+// The bracketed form: s from hi, iterations counted; -1 if max_iter is exhausted.
+__device__ __forceinline__ int newton_bracketed(double nw, double alpha, double ha, int max_iter, double hi, double* root)
+{
+    double lo = 0.0, s = hi;
+    int iters;
+    bool done = false;
+    for (iters = 1; iters <= max_iter; ++iters) {
+        const double s2 = s * s;
+        const double q = fma(ha * s2, s, fma(alpha, s, -nw));
+        if (q == 0.0) {
+            done = true;
+            break;
+        }
+        if (q > 0.0) hi = s; else lo = s;
+        const double corr = q * rcp_fast(fma(3.0 * ha, s2, alpha));
+        if (fabs(corr) <= 0x1.0p-50 * s) {
+            s -= corr;
+            done = true;
+            break;
+        }
+        double sn = s - corr;
+        if (!(sn > lo && sn < hi)) sn = 0.5 * (lo + hi);
+        s = sn;
+        if (hi - lo <= 0x1.0p-52 * hi) {
+            done = true;
+            break;
+        }
+    }
+    *root = s;
+    return done ? iters : -1;
+}
+
+// The roots s of ha s^3 + alpha s = nw (nw >= 0, with its square nw2) of P
+// particles; live[p] = false: nothing to solve (it[p], s[p] stay).
+//
+// Newton from the smaller upper bound needs no bracket but for rounding, so
+// every lane of the wavefront goes through the same few corrections, without
+// branches of its own and the P particles' chains of dependent operations side
+// by side (a tick of a small system waits for these chains).
+template <int P>
+__device__ __forceinline__ void newton_roots(const double (&nw)[P], const double (&nw2)[P], bool (&live)[P], double alpha,
+                                             double ha, int max_iter, double (&s)[P], int (&it)[P])
+{
+    double hi[P];
+    bool act[P];
+    const double alpha3 = alpha * alpha * alpha;
+    bool any = false;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        // cbrt(nw / ha) < nw / alpha where alpha^3 < ha nw^2; a step of ordinary
+        // size stays on the other side, without the cube root (a third of the
+        // solve's instructions)
+        hi[p] = nw[p] * rcp_fast(alpha);
+        if (live[p] && alpha3 < ha * nw2[p]) hi[p] = fmin(hi[p], cbrt(nw[p] / ha));
+        act[p] = live[p];
+        if (live[p]) s[p] = hi[p];
+        any = any || act[p];
+    }
+    for (int k = 1; k <= min(max_iter, kPlainNewton); ++k) {
+        if (__ballot(any) == 0) break;
+        any = false;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const double s2 = s[p] * s[p];
+            const double q = fma(ha * s2, s[p], fma(alpha, s[p], -nw[p]));
+            const double corr = q * rcp_fast(fma(3.0 * ha, s2, alpha));
+            const bool conv = fabs(corr) <= 0x1.0p-50 * s[p];
+            s[p] = act[p] ? s[p] - corr : s[p];
+            it[p] = act[p] ? k : it[p];
+            act[p] = act[p] && !conv;
+            any = any || act[p];
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (act[p]) it[p] = newton_bracketed(nw[p], alpha, ha, max_iter, hi[p], &s[p]);
+}
+
+// The implicit step of P particles in one dimension (see implicit_radial):
+// it[p] iterations, -1 or -2 as there.
+template <int P>
+__device__ __forceinline__ void implicit_scalar(const double (&w)[P], double alpha, double ha, int max_iter, double (&y)[P],
+                                                int (&it)[P])
+{
+    double nw[P], nw2[P], s[P];
+    bool live[P], fin[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        nw[p] = fabs(w[p]);
+        nw2[p] = w[p] * w[p];
+        fin[p] = isfinite(nw2[p]);
+        live[p] = fin[p] && nw[p] != 0.0;
+        it[p] = 0;
+        s[p] = 0.0;
+    }
+    if (ha == 0.0) {
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            if (live[p]) s[p] = nw[p] / alpha;
+    } else {
+        newton_roots<P>(nw, nw2, live, alpha, ha, max_iter, s, it);
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        // a NaN or infinite coordinate is passed through
+        y[p] = fin[p] ? copysign(s[p], w[p]) : w[p];
+        if (!fin[p]) it[p] = -2;
+    }
+}
+
 template <int D>
 __device__ __forceinline__ int implicit_radial(const double w[D], double alpha, double ha,
                                                int max_iter, double y[D])
 {
-    double nw2 = 0.0;
+    if constexpr (D == 1) {
+        const double w1[1] = {w[0]};
+        double y1[1];
+        int it[1];
+        implicit_scalar<1>(w1, alpha, ha, max_iter, y1, it);
+        y[0] = y1[0];
+        return it[0];
+    }
+    double nw2[1] = {0.0};
 #pragma unroll
-    for (int k = 0; k < D; ++k) nw2 = fma(w[k], w[k], nw2);
-    if (!isfinite(nw2)) {
+    for (int k = 0; k < D; ++k) nw2[0] = fma(w[k], w[k], nw2[0]);
+    if (!isfinite(nw2[0])) {
         // NaN or infinite coordinates (an overflowing |w|^2 of finite ones is
         // far outside any state the scheme reaches): passed through, flagged
 #pragma unroll
         for (int k = 0; k < D; ++k) y[k] = w[k];
         return -2;
     }
-    // |w| (one component: exactly, without the square root of its square)
-    const double nw = (D == 1) ? fabs(w[0]) : sqrt(nw2);
-    if (nw == 0.0) {
+    const double nw[1] = {sqrt(nw2[0])};
+    if (nw[0] == 0.0) {
 #pragma unroll
         for (int k = 0; k < D; ++k) y[k] = 0.0;
         return 0;
     }
-    double s;
-    int iters = 0;
-    if (ha == 0.0) {
-        s = nw / alpha;
-    } else {
-        // cbrt(|w| / ha) < |w| / alpha where alpha^3 < ha |w|^2; a step of
-        // ordinary size stays on the other side, without the cube root (a
-        // third of the solve's instructions)
-        double hi = nw * rcp_fast(alpha);
-        if (alpha * alpha * alpha < ha * nw2) hi = fmin(hi, cbrt(nw / ha));
-        // Newton from there needs no bracket but for rounding: every lane of
-        // the wavefront goes through the same few corrections, without branches
-        // of its own (a tick waits for this chain of dependent operations)
-        s = hi;
-        bool act = true;
-        for (int it = 1; it <= min(max_iter, kPlainNewton); ++it) {
-            const double s2 = s * s;
-            const double q = fma(ha * s2, s, fma(alpha, s, -nw));
-            const double corr = q * rcp_fast(fma(3.0 * ha, s2, alpha));
-            const bool conv = fabs(corr) <= 0x1.0p-50 * s;
-            s = act ? s - corr : s;
-            iters = act ? it : iters;
-            act = act && !conv;
-            if (__ballot(act) == 0) break;
-        }
-        if (act) {
-            double lo = 0.0;
-            s = hi;
-            bool done = false;
-            for (iters = 1; iters <= max_iter; ++iters) {
-                const double s2 = s * s;
-                const double q = fma(ha * s2, s, fma(alpha, s, -nw));
-                if (q == 0.0) {
-                    done = true;
-                    break;
-                }
-                if (q > 0.0) hi = s; else lo = s;
-                const double corr = q * rcp_fast(fma(3.0 * ha, s2, alpha));
-                if (fabs(corr) <= 0x1.0p-50 * s) {
-                    s -= corr;
-                    done = true;
-                    break;
-                }
-                double sn = s - corr;
-                if (!(sn > lo && sn < hi)) sn = 0.5 * (lo + hi);
-                s = sn;
-                if (hi - lo <= 0x1.0p-52 * hi) {
-                    done = true;
-                    break;
-                }
-            }
-            if (!done) iters = -1;
-        }
-    }
-    if constexpr (D == 1) {
-        y[0] = copysign(s, w[0]);
-        return iters;
-    }
-    const double scale = s / nw;
+    double s[1] = {0.0};
+    int iters[1] = {0};
+    bool live[1] = {true};
+    if (ha == 0.0) s[0] = nw[0] / alpha;
+    else newton_roots<1>(nw, nw2, live, alpha, ha, max_iter, s, iters);
+    const double scale = s[0] / nw[0];
 #pragma unroll
     for (int k = 0; k < D; ++k) y[k] = w[k] * scale;
-    return iters;
+    return iters[0];
 }
 
 }  // namespace ssm

@@ -168,6 +168,37 @@ __device__ __forceinline__ double row_scatter(double (&v)[16])
     return v[0];
 }
 
+// The next kModeChunk modes of a thread's P particles: their current powers w
+// added up and moved on by z, and the 16 sums over each row of lanes (C_m x 8,
+// S_m x 8) left in lanes 0 .. 15 of it.
+template <int P>
+__device__ __forceinline__ double mode_chunk(double (&wr)[P], double (&wi)[P], const double (&zr)[P], const double (&zi)[P])
+{
+    double acc[2 * kModeChunk];
+#pragma unroll
+    for (int u = 0; u < kModeChunk; ++u) {
+        double c = wr[0], sn = wi[0];
+#pragma unroll
+        for (int p = 1; p < P; ++p) {
+            c += wr[p];
+            sn += wi[p];
+        }
+        acc[u] = c;
+        acc[kModeChunk + u] = sn;
+#pragma unroll
+        for (int p = 0; p < P; ++p) rotate(wr[p], wi[p], zr[p], zi[p]);
+    }
+    return row_scatter(acc);
+}
+
+// p = p z + g
+__device__ __forceinline__ void horner(double& pr, double& pi, double zr, double zi, const double2 g)
+{
+    const double t = fma(pr, zr, fma(-pi, zi, g.x));
+    pi = fma(pr, zi, fma(pi, zr, g.y));
+    pr = t;
+}
+
 // The direct sum of the thread's target ys over all sources of its system, in
 // tiles of kDirectTile staged in LDS (compensated within a tile in FP32, the
 // tiles' sums added in double).
@@ -239,21 +270,7 @@ __device__ __forceinline__ void mode_block(const ModeItem& it, const SysDev& S, 
     for (int v0 = 0; v0 < 2 * d.M; v0 += kRowVals) {
         const int v1 = min(v0 + kRowVals, 2 * d.M);
         for (int v = v0; v < v1; v += 2 * kModeChunk) {
-            double acc[2 * kModeChunk];
-#pragma unroll
-            for (int u = 0; u < kModeChunk; ++u) {
-                double c = wr[0], sn = wi[0];
-#pragma unroll
-                for (int p = 1; p < P; ++p) {
-                    c += wr[p];
-                    sn += wi[p];
-                }
-                acc[u] = c;
-                acc[kModeChunk + u] = sn;
-#pragma unroll
-                for (int p = 0; p < P; ++p) rotate(wr[p], wi[p], zr[p], zi[p]);
-            }
-            rows[threadIdx.x >> 4][v - v0 + (threadIdx.x & 15)] = row_scatter(acc);
+            rows[threadIdx.x >> 4][v - v0 + (threadIdx.x & 15)] = mode_chunk<P>(wr, wi, zr, zi);
         }
         __syncthreads();
         for (int v = threadIdx.x; v < v1 - v0; v += kBlk) {
@@ -411,12 +428,7 @@ __device__ __forceinline__ double mode_eval(int M, const double2* g, double zr, 
 {
     double pr = 0.0, pi = 0.0;
 #pragma unroll 8
-    for (int m = M - 1; m >= 0; --m) {
-        const double2 gm = g[m];
-        const double t = fma(pr, zr, fma(-pi, zi, gm.x));
-        pi = fma(pr, zi, fma(pi, zr, gm.y));
-        pr = t;
-    }
+    for (int m = M - 1; m >= 0; --m) horner(pr, pi, zr, zi, g[m]);
     return fma(pr, zr, -pi * zi);
 }
 
