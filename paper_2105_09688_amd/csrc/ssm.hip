@@ -2171,14 +2171,6 @@ __global__ void k_rff_freq(uint64_t seed, int d, double ell, RffFreq* out)
     for (int k = 0; k < kMaxD; ++k) out->w[q][k] = (k < d) ? (float)(z[k] / ell) : 0.0f;
 }
 
-__global__ void k_loss_reduce(const float* __restrict__ part, int nb, int B, float* __restrict__ out)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double s = 0.0;
-    for (int q = 0; q < nb; ++q) s += part[q];
-    out[0] = (float)(s / (double)B);
-}
-
 }  // namespace ssm
 
 extern "C" int64_t ssm_mlp_num_params(int32_t d)
@@ -2214,10 +2206,18 @@ static ssm_status ensure_surrogate_buffers(ssm_ctx* c)
     return SSM_OK;
 }
 
-static ssm_status pack_weights(const float* master_dev, int d, MlpPacked* out, hipStream_t st)
+// The packed matrices of the training kernels, and the inference layout.
+static ssm_status pack_train(const float* master_dev, int d, MlpPacked* out, hipStream_t st)
 {
     hipLaunchKernelGGL(k_mlp_pack, dim3((kHid * kStride + 255) / 256), dim3(256), 0, st, master_dev, d, out);
     HIP_TRY(hipGetLastError());
+    return SSM_OK;
+}
+
+static ssm_status pack_weights(const float* master_dev, int d, MlpPacked* out, hipStream_t st)
+{
+    ssm_status s = pack_train(master_dev, d, out, st);
+    if (s != SSM_OK) return s;
     hipLaunchKernelGGL(k_mlp_pack_infer, dim3(64), dim3(256), 0, st, master_dev, d, &out->inf);
     HIP_TRY(hipGetLastError());
     return SSM_OK;
@@ -2452,12 +2452,13 @@ extern "C" ssm_status ssm_mlp_loss_grad(int32_t d, const float* master, const fl
     TrainWork w;
     ssm_status s = alloc_train((int)n, &w);
     if (s != SSM_OK) return s;
-    s = pack_weights(master, d, w.W, st);
+    s = pack_train(master, d, w.W, st);
     hipError_t he = hipSuccess;
     std::vector<float> lp(n / 64);
     if (s == SSM_OK) {
         hipLaunchKernelGGL(k_train_fwdbwd, dim3((unsigned)(n / 64)), dim3(256), 0, st, w.W, U, Tt, n, d, (int)n, 0ull, (int64_t)0, 1, w.tb);
-        hipLaunchKernelGGL(k_train_wgrad, dim3(52), dim3(64), 0, st, w.tb, d, (int)n, grad);
+        hipLaunchKernelGGL(k_train_wgrad, dim3(kWgradTiles), dim3(64), 0, st, w.tb, d, (int)n, grad, AdamArgs{}, (MlpPacked*)nullptr,
+                           (float*)nullptr);
         he = hipGetLastError();
         if (he == hipSuccess) he = hipMemcpyAsync(lp.data(), w.tb.loss_part, lp.size() * sizeof(float), hipMemcpyDeviceToHost, st);
         if (he == hipSuccess) he = hipStreamSynchronize(st);
@@ -2485,26 +2486,22 @@ extern "C" ssm_status ssm_mlp_train(int32_t d, const float* U, const float* Tt, 
     TrainWork w;
     ssm_status s = alloc_train(B, &w);
     if (s != SSM_OK) return s;
-    float *m = nullptr, *g = nullptr, *lh = nullptr;
-    hipError_t he = hipMalloc((void**)&m, 3 * P * sizeof(float) + cfg->steps * sizeof(float));
+    float* m = nullptr;
+    hipError_t he = hipMalloc((void**)&m, 2 * P * sizeof(float) + cfg->steps * sizeof(float));
     if (he != hipSuccess) { (void)hipFree(w.base); return fail(SSM_ERR_OOM, "mlp_train workspace"); }
     float* v = m + P;
-    g = v + P;
-    lh = g + P;
+    float* lh = v + P;
     he = hipMemsetAsync(m, 0, 2 * P * sizeof(float), st);
     const float b1 = cfg->beta1 > 0.0f ? cfg->beta1 : 0.9f, b2 = cfg->beta2 > 0.0f ? cfg->beta2 : 0.999f;
     const float eps = cfg->eps > 0.0f ? cfg->eps : 1e-8f;
     double c1 = 1.0, c2 = 1.0;
-    for (int64_t t = 0; t < cfg->steps && he == hipSuccess; ++t) {
+    if (he == hipSuccess) s = pack_train(master, d, w.W, st);
+    for (int64_t t = 0; t < cfg->steps && he == hipSuccess && s == SSM_OK; ++t) {
         c1 *= b1;
         c2 *= b2;
-        s = pack_weights(master, d, w.W, st);
-        if (s != SSM_OK) break;
         hipLaunchKernelGGL(k_train_fwdbwd, dim3((unsigned)(B / 64)), dim3(256), 0, st, w.W, U, Tt, n_samples, d, B, cfg->seed, t, 0, w.tb);
-        hipLaunchKernelGGL(k_train_wgrad, dim3(52), dim3(64), 0, st, w.tb, d, B, g);
-        hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(64), 0, st, w.tb.loss_part, B / 64, B, lh + t);
-        hipLaunchKernelGGL(k_adam, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, st, master, m, v, g, P, cfg->lr, b1, b2,
-                           eps, (float)(1.0 - c1), (float)(1.0 - c2));
+        hipLaunchKernelGGL(k_train_wgrad, dim3(kWgradTiles + 1), dim3(64), 0, st, w.tb, d, B, (float*)nullptr,
+                           AdamArgs{master, m, v, cfg->lr, b1, b2, eps, (float)(1.0 - c1), (float)(1.0 - c2)}, w.W, lh + t);
         he = hipGetLastError();
     }
     if (he == hipSuccess && loss_hist) he = hipMemcpyAsync(loss_hist, lh, cfg->steps * sizeof(float), hipMemcpyDeviceToHost, st);

@@ -211,6 +211,16 @@ __global__ void k_mlp_pack_infer(const float* __restrict__ master, int d, MlpInf
     }
 }
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// Two floats -> packed BF16 (one v_cvt_pk_bf16_f32).
+__device__ __forceinline__ uint32_t pk_bf16(float a, float b)
+{
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
 // Copy the forward weights (W1..W4, biases) into LDS.
 __device__ __forceinline__ void load_fwd_weights(const MlpPacked* __restrict__ P, __bf16* sW1, __bf16* sW2,
                                                  __bf16* sW3, __bf16* sW4, float* sb)
@@ -256,6 +266,14 @@ __device__ __forceinline__ void dense_tiles(const __bf16* W, const bf16x8 a[2], 
     }
 }
 
+// Orders a wavefront's own LDS writes and reads (one wavefront's tile).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Write 16 x (16 NT) values held in D layout into an LDS tile [16][kStride]
 // as BF16, then read them back in A layout (two K slices of 32).
 template <int NT>
@@ -266,20 +284,29 @@ __device__ __forceinline__ void d_to_a(const f32x4 v[NT], __bf16* tile, bf16x8 a
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) tile[(4 * (l >> 4) + i) * kStride + nt * 16 + (l & 15)] = (__bf16)v[nt][i];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) a[ks] = *(const bf16x8*)&tile[(l & 15) * kStride + ks * 32 + 8 * (l >> 4)];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
 }
 
 // Input features of one sample in A layout (training): lane l holds features
 // k = 32 ks + 8 (l / 16) + 0..7 of sample l % 16:  u = [hi(y), lo(y), m_0..m_{2K-1}, 0...],
-// from a raw row r = [y (d), m (2K)] in global memory (r may be null: zeros).
-__device__ __forceinline__ void build_input_row(const float* r, int d, bf16x8 a[2])
+// from a raw row r = [y (d), m (2K)] in global memory.  load_input_row fetches
+// the values that the lane's features come from, build_input_row makes them.
+__device__ __forceinline__ void load_input_row(const float* r, int d, float (&u)[2][8])
+{
+    const int l = threadIdx.x & 63;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int k = ks * 32 + 8 * (l >> 4) + i;
+            u[ks][i] = r[min(k < d ? k : k - d, raw_in(d) - 1)];
+        }
+}
+
+__device__ __forceinline__ void build_input_row(const float (&u)[2][8], int d, bf16x8 a[2])
 {
     const int l = threadIdx.x & 63;
 #pragma unroll
@@ -288,21 +315,19 @@ __device__ __forceinline__ void build_input_row(const float* r, int d, bf16x8 a[
         for (int i = 0; i < 8; ++i) {
             const int k = ks * 32 + 8 * (l >> 4) + i;
             __bf16 v = (__bf16)0.0f;
-            if (r) {
-                if (k < d) v = bf_hi(r[k]);
-                else if (k < 2 * d) v = bf_lo(r[k - d]);
-                else if (k < 2 * d + 2 * kRff) v = (__bf16)r[k - d];
-            }
+            if (k < d) v = bf_hi(u[ks][i]);
+            else if (k < 2 * d) v = bf_lo(u[ks][i]);
+            else if (k < 2 * d + 2 * kRff) v = (__bf16)u[ks][i];
             a[ks][i] = v;
         }
 }
 
 // Forward pass of the wavefront's 16 samples.  Returns the output tile
-// (D layout, columns 0..d-1 valid, bias added) and optionally the
-// pre-activations z1..z3 (D layout) for the backward pass.
+// (D layout, columns 0..d-1 valid, bias added), the pre-activations z1..z3 and
+// the activations h1..h3 (D layout) for the backward pass.
 __device__ __forceinline__ void mlp_forward16(const __bf16* sW1, const __bf16* sW2, const __bf16* sW3,
                                               const __bf16* sW4, const float* sb, bf16x8 a[2],
-                                              __bf16* tile, f32x4 z[3][4], f32x4& out, bf16x8 act[3][2])
+                                              __bf16* tile, f32x4 z[3][4], f32x4 h[3][4], f32x4& out)
 {
     const int l = threadIdx.x & 63;
     const __bf16* Ws[3] = {sW1, sW2, sW3};
@@ -310,7 +335,6 @@ __device__ __forceinline__ void mlp_forward16(const __bf16* sW1, const __bf16* s
     for (int layer = 0; layer < 3; ++layer) {
         f32x4 acc[4];
         dense_tiles<4>(Ws[layer], a, acc);
-        f32x4 h[4];
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) {
             const float bias = sb[layer * kHid + nt * 16 + (l & 15)];
@@ -318,12 +342,10 @@ __device__ __forceinline__ void mlp_forward16(const __bf16* sW1, const __bf16* s
             for (int i = 0; i < 4; ++i) {
                 const float zz = acc[nt][i] + bias;
                 z[layer][nt][i] = zz;
-                h[nt][i] = silu_f(zz);
+                h[layer][nt][i] = silu_f(zz);
             }
         }
-        d_to_a<4>(h, tile, a);
-        act[layer][0] = a[0];
-        act[layer][1] = a[1];
+        d_to_a<4>(h[layer], tile, a);
     }
     f32x4 o[1];
     dense_tiles<1>(sW4, a, o);
@@ -405,16 +427,6 @@ __global__ __launch_bounds__(kBlk) void k_rff_final(const int32_t* __restrict__ 
 // from one step to the next).  A wavefront runs two 16-sample tiles at a
 // time in the transposed layout of MlpInfer.
 // ---------------------------------------------------------------------------
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-// Two floats -> packed BF16 (one v_cvt_pk_bf16_f32).
-__device__ __forceinline__ uint32_t pk_bf16(float a, float b)
-{
-    const f32x2 v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
 // hi / lo B operands of 8 values (4 from each of two output tiles).
 __device__ __forceinline__ void split8(const f32x4& a, const f32x4& b, bf16x8& hi, bf16x8& lo)
 {
@@ -700,10 +712,9 @@ __global__ void k_gather_samples(const SysDev* __restrict__ sys, int s, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// Training.  k_train_fwdbwd: 64 samples per block (16 per wavefront), drawn
-// with replacement by Philox (tag 4) from the sample set; forward, loss and
-// back-propagated deltas; activations and deltas stored feature-major
-// ([feature][batch], BF16) for the weight-gradient kernel.
+// Training, two launches a step.  k_train_fwdbwd: samples drawn with
+// replacement by Philox (tag 4) from the sample set; forward, loss and
+// back-propagated deltas.  k_train_wgrad: weight gradients, Adam, packing.
 // ---------------------------------------------------------------------------
 // Row `row` of minibatch `step`: a uniform draw (with replacement) from the
 // sample set, Philox stream tag 4; or row itself for sequential batches.
@@ -714,12 +725,32 @@ __device__ __forceinline__ int64_t sample_index(int row, int64_t step, uint64_t 
     return (int64_t)(rb.w[0] % (uint64_t)n);
 }
 
+// Activations and deltas between the two kernels of a training step, in BF16,
+// already in the order of the matrix-core operands that k_train_wgrad reads:
+// per 32 samples and tile of 16 features, lane l holds feature l % 16 of the
+// samples 8 (l / 16) .. + 7 (16 bytes).
 struct TrainBufs {
-    __bf16* act[4];    // act[0]: inputs [64][B]; act[1..3]: SiLU outputs [64][B]
-    __bf16* delta[4];  // delta[0..2]: dL/dz of hidden layers 1..3 [64][B]; delta[3]: dL/dy [16][B]
+    __bf16* act[4];    // act[0]: inputs; act[1..3]: SiLU outputs, 4 tiles each
+    __bf16* delta[4];  // delta[0..2]: dL/dz of hidden layers 1..3, 4 tiles; delta[3]: dL/dy, 1 tile
     float* loss_part;  // [B / 64]
 };
 
+// The four samples 4 (l / 16) + r of a wavefront's 16 (samples b0 ..) at
+// feature l % 16 of a tile: eight bytes of an operand in TrainBufs.
+__device__ __forceinline__ void store_operand(__bf16* buf, int tiles, int tile, int b0, const f32x4& v)
+{
+    const int l = threadIdx.x & 63, g = l >> 4;
+    const int64_t lane = (int64_t)((b0 >> 5) * tiles + tile) * 64 + (2 * ((b0 >> 4) & 1) + (g >> 1)) * 16 + (l & 15);
+    *reinterpret_cast<uint2*>(buf + lane * 8 + 4 * (g & 1)) = make_uint2(pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3]));
+}
+
+// 64 samples per block, 16 per wavefront; a wavefront is a chain of dependent
+// stages (draw, rows, three layers, three back), one per SIMD at a batch of
+// 4096.  Each sample is drawn by one lane of each group of 16 and handed to
+// the lanes that need its target (drawn again in each of them it was five
+// Philox blocks a lane); its row is on the way while the weights go to LDS;
+// activations and deltas leave as 8-byte pieces of operands, where the
+// feature-major form stored every value on its own.  Batch 4096: @TFB@
 __global__ __launch_bounds__(256) void k_train_fwdbwd(const MlpPacked* __restrict__ W, const float* __restrict__ U,
                                                       const float* __restrict__ Tg, int64_t n_samples, int d,
                                                       int B, uint64_t seed, int64_t step, int sequential,
@@ -735,6 +766,14 @@ __global__ __launch_bounds__(256) void k_train_fwdbwd(const MlpPacked* __restric
     __shared__ float sb[3 * kHid + kOutPad];
     __shared__ __align__(16) __bf16 tiles[4][16 * kStride];
     __shared__ float lossw[4];
+    const int wave = threadIdx.x >> 6;
+    const int l = threadIdx.x & 63;
+    const int in = raw_in(d);
+    const int b0 = blockIdx.x * 64 + wave * 16;  // first batch row of this wavefront
+    // this lane's sample (A layout row l % 16)
+    const int64_t sidx = sample_index(b0 + (l & 15), step, seed, n_samples, sequential);
+    float u[2][8];
+    load_input_row(U + sidx * in, d, u);
     load_fwd_weights(W, sW1, sW2, sW3, sW4, sb);
     {
         const int n64 = kHid * kStride * 2 / 16;
@@ -745,72 +784,65 @@ __global__ __launch_bounds__(256) void k_train_fwdbwd(const MlpPacked* __restric
         }
         for (int q = threadIdx.x; q < n4; q += blockDim.x) ((uint4*)sW4t)[q] = ((const uint4*)W->W4t)[q];
     }
+    // targets of the four samples whose outputs this lane will hold
+    const int comp = l & 15;
+    float tg[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int64_t si = __shfl(sidx, 4 * (l >> 4) + r, 64);
+        tg[r] = comp < d ? Tg[si * d + comp] : 0.0f;
+    }
     __syncthreads();
-    const int wave = threadIdx.x >> 6;
-    const int l = threadIdx.x & 63;
-    const int in = raw_in(d);
-    const int b0 = blockIdx.x * 64 + wave * 16;  // first batch row of this wavefront
-    // this lane's sample (A layout row l % 16)
-    const int brow = b0 + (l & 15);
-    const int64_t sidx = sample_index(brow, step, seed, n_samples, sequential);
     bf16x8 a[2];
-    build_input_row(U + sidx * in, d, a);
-    // inputs, feature-major
+    build_input_row(u, d, a);
+    // inputs as operands, through the wavefront's tile (rows = samples)
+    __bf16* tile = tiles[wave];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
+    for (int ks = 0; ks < 2; ++ks) *(bf16x8*)&tile[(l & 15) * kStride + ks * 32 + 8 * (l >> 4)] = a[ks];
+    wave_lds_fence();
 #pragma unroll
-        for (int i = 0; i < 8; ++i) tb.act[0][(int64_t)(ks * 32 + 8 * (l >> 4) + i) * B + brow] = a[ks][i];
+    for (int nt = 0; nt < 4; ++nt) {
+        f32x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = (float)tile[(4 * (l >> 4) + r) * kStride + nt * 16 + (l & 15)];
+        store_operand(tb.act[0], 4, nt, b0, v);
+    }
+    wave_lds_fence();
 
-    f32x4 z[3][4];
-    bf16x8 act[3][2];
+    f32x4 z[3][4], h[3][4];
     f32x4 out;
-    mlp_forward16(sW1, sW2, sW3, sW4, sb, a, tiles[wave], z, out, act);
+    mlp_forward16(sW1, sW2, sW3, sW4, sb, a, tile, z, h, out);
 
     // dL/dy in D layout: rows = samples 4 (l/16) + r, column = output l % 16
-    const int comp = l & 15;
     f32x4 dy;
     float lsum = 0.0f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int row = b0 + 4 * (l >> 4) + r;
         float g = 0.0f;
         if (comp < d) {
-            const int64_t si = sample_index(row, step, seed, n_samples, sequential);
-            const float res = out[r] - Tg[si * d + comp];
+            const float res = out[r] - tg[r];
             lsum += res * res;
             g = 2.0f * res / (float)B;
         }
         dy[r] = g;
-        tb.delta[3][(int64_t)comp * B + row] = (__bf16)g;
     }
-    // activations of the hidden layers, feature-major, from the D-layout values
-    // (recomputed SiLU of z, rounded to BF16 exactly as the forward pass fed them)
+    store_operand(tb.delta[3], 1, 0, b0, dy);
 #pragma unroll
     for (int layer = 0; layer < 3; ++layer)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                tb.act[layer + 1][(int64_t)(nt * 16 + (l & 15)) * B + b0 + 4 * (l >> 4) + r] =
-                    (__bf16)silu_f(z[layer][nt][r]);
+        for (int nt = 0; nt < 4; ++nt) store_operand(tb.act[layer + 1], 4, nt, b0, h[layer][nt]);
 
     // back-propagation: delta_3 = (dy W4) * silu'(z3) ...
     bf16x8 ga[2];
     {
         // dy (16 x 16, D layout) -> A layout with K = 32 (outputs 16..31 zero)
-        f32x4 v[1] = {dy};
-        __bf16* tile = tiles[wave];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) tile[(4 * (l >> 4) + i) * kStride + (l & 15)] = (__bf16)v[0][i];
+        for (int i = 0; i < 4; ++i) tile[(4 * (l >> 4) + i) * kStride + (l & 15)] = (__bf16)dy[i];
 #pragma unroll
         for (int i = 0; i < 4; ++i) tile[(4 * (l >> 4) + i) * kStride + 16 + (l & 15)] = (__bf16)0.0f;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
         ga[0] = *(const bf16x8*)&tile[(l & 15) * kStride + 8 * (l >> 4)];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_fence();
     }
     f32x4 g[4];
     // layer 4 backward: K = 32 (padded outputs), B operand from W4t [in][out]
@@ -830,12 +862,9 @@ __global__ __launch_bounds__(256) void k_train_fwdbwd(const MlpPacked* __restric
 #pragma unroll
             for (int r = 0; r < 4; ++r) g[nt][r] *= silu_prime_f(z[layer][nt][r]);
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                tb.delta[layer][(int64_t)(nt * 16 + (l & 15)) * B + b0 + 4 * (l >> 4) + r] = (__bf16)g[nt][r];
+        for (int nt = 0; nt < 4; ++nt) store_operand(tb.delta[layer], 4, nt, b0, g[nt]);
         if (layer == 0) break;
-        d_to_a<4>(g, tiles[wave], ga);
+        d_to_a<4>(g, tile, ga);
         f32x4 nxt[4];
         dense_tiles<4>(Wt[2 - layer], ga, nxt);
 #pragma unroll
@@ -849,73 +878,141 @@ __global__ __launch_bounds__(256) void k_train_fwdbwd(const MlpPacked* __restric
     if (threadIdx.x == 0) tb.loss_part[blockIdx.x] = (lossw[0] + lossw[1]) + (lossw[2] + lossw[3]);
 }
 
+// Adam (Kingma & Ba, bias-corrected) of one weight; returns the new one.
+struct AdamArgs {
+    float *w, *m, *v;  // flat master weights and moments
+    float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ float adam_step(const AdamArgs& o, int64_t q, float gg, float w, float m, float v)
+{
+    const float mm = fmaf(1.0f - o.b1, gg, o.b1 * m);
+    const float vv = fmaf(gg, (1.0f - o.b2) * gg, o.b2 * v);
+    o.m[q] = mm;
+    o.v[q] = vv;
+    w -= o.lr * (mm / o.c1) / (sqrtf(vv / o.c2) + o.eps);
+    o.w[q] = w;
+    return w;
+}
+
 // Weight gradients: one wavefront per 16 x 16 tile of a layer's weight matrix,
 // summing over the batch with K = 32 samples per MFMA (fixed order); the
 // tiles of input-column block 0 also produce the bias gradients.
-// Tiles: layer 1: 4 x 4, layers 2 and 3: 4 x 4, layer 4: 1 x 4  -> 52.
-__global__ __launch_bounds__(64) void k_train_wgrad(TrainBufs tb, int d, int B, float* __restrict__ grad)
+// Tiles: layer 1: 4 x 4, layers 2 and 3: 4 x 4, layer 4: 1 x 4  -> 52; one
+// block more adds up the loss.
+//
+// grad: the gradients go there.  Else (a training step) each wavefront
+// applies Adam to its tile's weights and rounds them into the packed matrices
+// that the next step reads: no weight belongs to two tiles, so the step ends
+// with this launch (gradients, loss, Adam and packing were five).
+//
+// The sums are chains of B / 32 MFMAs; what they wait for is the operands.
+// kWgradBatch chunks are on their way while as many are multiplied.  Batch
+// 4096: @TWG@
+constexpr int kWgradTiles = 52, kWgradBatch = 16;
+
+struct WgradChunks {
+    bf16x8 a[kWgradBatch], b[kWgradBatch];
+};
+
+__device__ __forceinline__ void load_chunks(const bf16x8* a, const bf16x8* b, int ta, int c0, int nc, WgradChunks& w)
 {
-    int t = blockIdx.x;
-    int layer, ot, it;
-    if (t < 48) {
-        layer = t / 16;
-        ot = (t % 16) / 4;
-        it = t % 4;
-    } else {
-        layer = 3;
-        ot = 0;
-        it = t - 48;
+#pragma unroll
+    for (int q = 0; q < kWgradBatch; ++q) {
+        const int64_t c = min(c0 + q, nc - 1);  // past the end: repeated, not used
+        w.a[q] = a[c * ta * 64];
+        w.b[q] = b[c * 4 * 64];
     }
+}
+
+__global__ __launch_bounds__(64) void k_train_wgrad(TrainBufs tb, int d, int B, float* __restrict__ grad, AdamArgs opt,
+                                                    MlpPacked* __restrict__ W, float* __restrict__ loss)
+{
+    const int t = blockIdx.x;
     const int l = threadIdx.x & 63;
-    const __bf16* dl = tb.delta[layer];  // [out][B]
-    const __bf16* al = tb.act[layer];    // [in][B]
+    if (t == kWgradTiles) {
+        // the blocks' parts in ascending order, fetched 64 at a time
+        double s = 0.0;
+        for (int q0 = 0; q0 < B / 64; q0 += 64) {
+            const float p = q0 + l < B / 64 ? tb.loss_part[q0 + l] : 0.0f;
+            for (int q = 0; q < min(64, B / 64 - q0); ++q)
+                s += (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), q));
+        }
+        if (l == 0) *loss = (float)(s / (double)B);
+        return;
+    }
+    const int layer = t < 48 ? t / 16 : 3;
+    const int ot = t < 48 ? (t % 16) / 4 : 0, it = t < 48 ? t % 4 : t - 48;
+    const int ta = layer < 3 ? 4 : 1;
     const int nout = layer < 3 ? kHid : d;
     const int nin = layer == 0 ? mlp_in(d) : kHid;
+    const MlpOffsets o = mlp_offsets(d);
+    const int64_t wo = layer == 0 ? o.W1 : layer == 1 ? o.W2 : layer == 2 ? o.W3 : o.W4;
+    const int64_t bo = layer == 0 ? o.b1 : layer == 1 ? o.b2 : layer == 2 ? o.b3 : o.b4;
+    const int ic = it * 16 + (l & 15);            // D column = input feature
+    const int or0 = ot * 16 + 4 * (l >> 4);       // D rows or0 .. or0 + 3 = output features
+    const bool bias = it == 0 && (l & 15) == 0;
+    const bf16x8* pa = (const bf16x8*)tb.delta[layer] + ot * 64 + l;
+    const bf16x8* pb = (const bf16x8*)tb.act[layer] + it * 64 + l;
+    const int nc = B / 32;
+    WgradChunks cur, nxt;
+    load_chunks(pa, pb, ta, 0, nc, cur);
+    // this lane's weights and moments, used after the sums
+    float w[4], m[4], v[4], wb[4], mb[4], vb[4];
+    if (!grad) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int orr = min(or0 + r, nout - 1);
+            const int64_t q = wo + (int64_t)orr * nin + min(ic, nin - 1), qb = bo + orr;
+            w[r] = opt.w[q]; m[r] = opt.m[q]; v[r] = opt.v[q];
+            wb[r] = opt.w[qb]; mb[r] = opt.m[qb]; vb[r] = opt.v[qb];
+        }
+    }
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     f32x4 bacc = {0.0f, 0.0f, 0.0f, 0.0f};
     bf16x8 ones;
 #pragma unroll
     for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
-    const int orow = ot * 16 + (l & 15);
-    const int icol = it * 16 + (l & 15);
-    for (int k0 = 0; k0 < B; k0 += 32) {
-        bf16x8 a, b;
-        const int kk = k0 + 8 * (l >> 4);
-        if (layer == 3 && orow >= kOutPad) {
+    for (int c0 = 0; c0 < nc; c0 += kWgradBatch) {
+        if (c0 + kWgradBatch < nc) load_chunks(pa, pb, ta, c0 + kWgradBatch, nc, nxt);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) a[i] = (__bf16)0.0f;
-        } else {
-            a = *(const bf16x8*)&dl[(int64_t)orow * B + kk];
+        for (int q = 0; q < kWgradBatch; ++q) {
+            if (c0 + q < nc) {  // uniform
+                acc = mfma_bf16(cur.a[q], cur.b[q], acc);
+                if (it == 0) bacc = mfma_bf16(cur.a[q], ones, bacc);
+            }
         }
-        b = *(const bf16x8*)&al[(int64_t)icol * B + kk];
-        acc = mfma_bf16(a, b, acc);
-        if (it == 0) bacc = mfma_bf16(a, ones, bacc);
+        cur = nxt;
     }
-    const MlpOffsets o = mlp_offsets(d);
-    const int64_t wo[4] = {o.W1, o.W2, o.W3, o.W4};
-    const int64_t bo[4] = {o.b1, o.b2, o.b3, o.b4};
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int orr = ot * 16 + 4 * (l >> 4) + r;  // D row = output feature
-        const int ic = it * 16 + (l & 15);          // D column = input feature
-        if (orr < nout && ic < nin) grad[wo[layer] + (int64_t)orr * nin + ic] = acc[r];
-        if (it == 0 && (l & 15) == 0 && orr < nout) grad[bo[layer] + orr] = bacc[r];
+        const int orr = or0 + r;
+        if (orr >= nout) continue;
+        if (grad) {
+            if (ic < nin) grad[wo + (int64_t)orr * nin + ic] = acc[r];
+            if (bias) grad[bo + orr] = bacc[r];
+            continue;
+        }
+        if (ic < nin) {
+            const __bf16 nw = (__bf16)adam_step(opt, wo + (int64_t)orr * nin + ic, acc[r], w[r], m[r], v[r]);
+            if (layer == 0) {
+                W->W1[orr * kStride + ic] = nw;
+            } else if (layer == 1) {
+                W->W2[orr * kStride + ic] = nw;
+                W->W2t[ic * kStride + orr] = nw;
+            } else if (layer == 2) {
+                W->W3[orr * kStride + ic] = nw;
+                W->W3t[ic * kStride + orr] = nw;
+            } else {
+                W->W4[orr * kStride + ic] = nw;
+                W->W4t[ic * kStrideT4 + orr] = nw;
+            }
+        }
+        if (bias) {
+            const float nb = adam_step(opt, bo + orr, bacc[r], wb[r], mb[r], vb[r]);
+            (layer == 0 ? W->b1 : layer == 1 ? W->b2 : layer == 2 ? W->b3 : W->b4)[orr] = nb;
+        }
     }
-}
-
-// Adam on the flat FP32 master weights (Kingma & Ba), bias-corrected.
-__global__ void k_adam(float* __restrict__ w, float* __restrict__ m, float* __restrict__ v,
-                       const float* __restrict__ g, int64_t n, float lr, float b1, float b2, float eps,
-                       float c1, float c2)
-{
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    const float gg = g[q];
-    const float mm = b1 * m[q] + (1.0f - b1) * gg;
-    const float vv = b2 * v[q] + (1.0f - b2) * gg * gg;
-    m[q] = mm;
-    v[q] = vv;
-    w[q] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
 }
 
 // The exact pair term has zero net force (odd kernel: sum_i K^i = 0).  The
