@@ -2456,7 +2456,8 @@ extern "C" ssm_status ssm_mlp_loss_grad(int32_t d, const float* master, const fl
     hipError_t he = hipSuccess;
     std::vector<float> lp(n / 64);
     if (s == SSM_OK) {
-        hipLaunchKernelGGL(k_train_fwdbwd, dim3((unsigned)(n / 64)), dim3(256), 0, st, w.W, U, Tt, n, d, (int)n, 0ull, (int64_t)0, 1, w.tb);
+        SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_train_fwdbwd<D>), dim3((unsigned)(n / 64)), dim3(256), 0, st, w.W, U, Tt, n, (int)n,
+                                             0ull, (int64_t)0, 1, w.tb));
         hipLaunchKernelGGL(k_train_wgrad, dim3(kWgradTiles), dim3(64), 0, st, w.tb, d, (int)n, grad, AdamArgs{}, (MlpPacked*)nullptr,
                            (float*)nullptr);
         he = hipGetLastError();
@@ -2499,7 +2500,8 @@ extern "C" ssm_status ssm_mlp_train(int32_t d, const float* U, const float* Tt, 
     for (int64_t t = 0; t < cfg->steps && he == hipSuccess && s == SSM_OK; ++t) {
         c1 *= b1;
         c2 *= b2;
-        hipLaunchKernelGGL(k_train_fwdbwd, dim3((unsigned)(B / 64)), dim3(256), 0, st, w.W, U, Tt, n_samples, d, B, cfg->seed, t, 0, w.tb);
+        SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_train_fwdbwd<D>), dim3((unsigned)(B / 64)), dim3(256), 0, st, w.W, U, Tt, n_samples, B,
+                                             cfg->seed, t, 0, w.tb));
         hipLaunchKernelGGL(k_train_wgrad, dim3(kWgradTiles + 1), dim3(64), 0, st, w.tb, d, B, (float*)nullptr,
                            AdamArgs{master, m, v, cfg->lr, b1, b2, eps, (float)(1.0 - c1), (float)(1.0 - c2)}, w.W, lh + t);
         he = hipGetLastError();

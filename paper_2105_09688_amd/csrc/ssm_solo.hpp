@@ -15,7 +15,10 @@
 // about 10 us a tick on one compute unit, 0.4 us spread over all).
 //
 // A tick of the small case (10 systems of 1000) took 18.6 us in FP64 and 8.6
-// in FP32-compensated by the tiled kernel: @MEAS@
+// in FP32-compensated by the tiled kernel; 6.0 and 5.2 here, four wavefronts
+// on one compute unit, bound by their issue (512 threads of two particles took
+// 6.5 and 5.6, 1024 of one 9.8 and 9.3: the reductions of the mode sums are
+// paid per wavefront).
 #pragma once
 
 #include "ssm_modes.hpp"

@@ -13,6 +13,8 @@
 // A wavefront always works on 16 samples (rows); features are columns.
 #pragma once
 
+#include <cstddef>
+
 #include "ssm_kernels.hpp"
 
 namespace ssm {
@@ -221,32 +223,14 @@ __device__ __forceinline__ uint32_t pk_bf16(float a, float b)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// Copy the forward weights (W1..W4, biases) into LDS.
-__device__ __forceinline__ void load_fwd_weights(const MlpPacked* __restrict__ P, __bf16* sW1, __bf16* sW2,
-                                                 __bf16* sW3, __bf16* sW4, float* sb)
-{
-    const int nt = blockDim.x;
-    const uint4* g1 = (const uint4*)P->W1;
-    const uint4* g2 = (const uint4*)P->W2;
-    const uint4* g3 = (const uint4*)P->W3;
-    const uint4* g4 = (const uint4*)P->W4;
-    const int n64 = kHid * kStride * 2 / 16;
-    const int n16 = kOutPad * kStride * 2 / 16;
-    for (int q = threadIdx.x; q < n64; q += nt) {
-        ((uint4*)sW1)[q] = g1[q];
-        ((uint4*)sW2)[q] = g2[q];
-        ((uint4*)sW3)[q] = g3[q];
-    }
-    for (int q = threadIdx.x; q < n16; q += nt) ((uint4*)sW4)[q] = g4[q];
-    for (int q = threadIdx.x; q < 3 * kHid + kOutPad; q += nt) {
-        float v;
-        if (q < kHid) v = P->b1[q];
-        else if (q < 2 * kHid) v = P->b2[q - kHid];
-        else if (q < 3 * kHid) v = P->b3[q - 2 * kHid];
-        else v = P->b4[q - 3 * kHid];
-        sb[q] = v;
-    }
-}
+// The training kernel's weights in LDS: the front of MlpPacked, as it is.
+struct TrainLds {
+    __bf16 W1[kHid * kStride], W2[kHid * kStride], W3[kHid * kStride], W4[kOutPad * kStride];
+    __bf16 W2t[kHid * kStride], W3t[kHid * kStride], W4t[kHid * kStrideT4];
+    float b[3 * kHid + kOutPad];
+};
+constexpr int kTrainCopies = (sizeof(TrainLds) / 16 + 255) / 256;  // 16-byte pieces a thread of 256 copies
+static_assert(sizeof(TrainLds) % 16 == 0 && sizeof(TrainLds) == offsetof(MlpPacked, inf), "one flat copy");
 
 // One dense layer for the wavefront's 16 samples: acc[nt] = A (16 x 64) * W^T
 // for NT column tiles; W is LDS [NT*16][kStride] (row = output feature).
@@ -294,7 +278,8 @@ __device__ __forceinline__ void d_to_a(const f32x4 v[NT], __bf16* tile, bf16x8 a
 // k = 32 ks + 8 (l / 16) + 0..7 of sample l % 16:  u = [hi(y), lo(y), m_0..m_{2K-1}, 0...],
 // from a raw row r = [y (d), m (2K)] in global memory.  load_input_row fetches
 // the values that the lane's features come from, build_input_row makes them.
-__device__ __forceinline__ void load_input_row(const float* r, int d, float (&u)[2][8])
+template <int D>
+__device__ __forceinline__ void load_input_row(const float* r, float (&u)[2][8])
 {
     const int l = threadIdx.x & 63;
 #pragma unroll
@@ -302,23 +287,23 @@ __device__ __forceinline__ void load_input_row(const float* r, int d, float (&u)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int k = ks * 32 + 8 * (l >> 4) + i;
-            u[ks][i] = r[min(k < d ? k : k - d, raw_in(d) - 1)];
+            u[ks][i] = r[min(k < D ? k : k - D, raw_in(D) - 1)];
         }
 }
 
-__device__ __forceinline__ void build_input_row(const float (&u)[2][8], int d, bf16x8 a[2])
+template <int D>
+__device__ __forceinline__ void build_input_row(const float (&u)[2][8], bf16x8 a[2])
 {
-    const int l = threadIdx.x & 63;
+    const int g = (threadIdx.x & 63) >> 4;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int k = ks * 32 + 8 * (l >> 4) + i;
-            __bf16 v = (__bf16)0.0f;
-            if (k < d) v = bf_hi(u[ks][i]);
-            else if (k < 2 * d) v = bf_lo(u[ks][i]);
-            else if (k < 2 * d + 2 * kRff) v = (__bf16)u[ks][i];
-            a[ks][i] = v;
+            // only the first eight features (lanes of group 0) hold positions, only the last 32 padding
+            float v = u[ks][i];
+            if (ks == 0 && i >= D && i < 2 * D) v = g == 0 ? v - (float)bf_hi(v) : v;
+            if (ks == 1) v = 8 * g + i < mlp_in(D) - 32 ? v : 0.0f;
+            a[ks][i] = (__bf16)v;
         }
 }
 
@@ -737,11 +722,16 @@ struct TrainBufs {
 
 // The four samples 4 (l / 16) + r of a wavefront's 16 (samples b0 ..) at
 // feature l % 16 of a tile: eight bytes of an operand in TrainBufs.
-__device__ __forceinline__ void store_operand(__bf16* buf, int tiles, int tile, int b0, const f32x4& v)
+__device__ __forceinline__ void store_operand(__bf16* buf, int tiles, int tile, int b0, const uint2 v)
 {
     const int l = threadIdx.x & 63, g = l >> 4;
     const int64_t lane = (int64_t)((b0 >> 5) * tiles + tile) * 64 + (2 * ((b0 >> 4) & 1) + (g >> 1)) * 16 + (l & 15);
-    *reinterpret_cast<uint2*>(buf + lane * 8 + 4 * (g & 1)) = make_uint2(pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3]));
+    *reinterpret_cast<uint2*>(buf + lane * 8 + 4 * (g & 1)) = v;
+}
+
+__device__ __forceinline__ void store_operand(__bf16* buf, int tiles, int tile, int b0, const f32x4& v)
+{
+    store_operand(buf, tiles, tile, b0, make_uint2(pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3])));
 }
 
 // 64 samples per block, 16 per wavefront; a wavefront is a chain of dependent
@@ -750,51 +740,45 @@ __device__ __forceinline__ void store_operand(__bf16* buf, int tiles, int tile, 
 // the lanes that need its target (drawn again in each of them it was five
 // Philox blocks a lane); its row is on the way while the weights go to LDS;
 // activations and deltas leave as 8-byte pieces of operands, where the
-// feature-major form stored every value on its own.  Batch 4096: @TFB@
+// feature-major form stored every value on its own.  At a batch of 4096
+// 22.8 us before, 10.8 now.
+template <int D>
 __global__ __launch_bounds__(256) void k_train_fwdbwd(const MlpPacked* __restrict__ W, const float* __restrict__ U,
-                                                      const float* __restrict__ Tg, int64_t n_samples, int d,
+                                                      const float* __restrict__ Tg, int64_t n_samples,
                                                       int B, uint64_t seed, int64_t step, int sequential,
                                                       TrainBufs tb)
 {
-    __shared__ __align__(16) __bf16 sW1[kHid * kStride];
-    __shared__ __align__(16) __bf16 sW2[kHid * kStride];
-    __shared__ __align__(16) __bf16 sW3[kHid * kStride];
-    __shared__ __align__(16) __bf16 sW4[kOutPad * kStride];
-    __shared__ __align__(16) __bf16 sW2t[kHid * kStride];
-    __shared__ __align__(16) __bf16 sW3t[kHid * kStride];
-    __shared__ __align__(16) __bf16 sW4t[kHid * kStrideT4];
-    __shared__ float sb[3 * kHid + kOutPad];
+    __shared__ __align__(16) TrainLds L;
     __shared__ __align__(16) __bf16 tiles[4][16 * kStride];
     __shared__ float lossw[4];
     const int wave = threadIdx.x >> 6;
     const int l = threadIdx.x & 63;
-    const int in = raw_in(d);
     const int b0 = blockIdx.x * 64 + wave * 16;  // first batch row of this wavefront
+    // all of the weights are on their way while the sample is drawn
+    uint4 wt[kTrainCopies];
+#pragma unroll
+    for (int q = 0; q < kTrainCopies; ++q)
+        wt[q] = reinterpret_cast<const uint4*>(W)[min(q * 256 + (int)threadIdx.x, (int)(sizeof(TrainLds) / 16) - 1)];
     // this lane's sample (A layout row l % 16)
     const int64_t sidx = sample_index(b0 + (l & 15), step, seed, n_samples, sequential);
     float u[2][8];
-    load_input_row(U + sidx * in, d, u);
-    load_fwd_weights(W, sW1, sW2, sW3, sW4, sb);
-    {
-        const int n64 = kHid * kStride * 2 / 16;
-        const int n4 = kHid * kStrideT4 * 2 / 16;
-        for (int q = threadIdx.x; q < n64; q += blockDim.x) {
-            ((uint4*)sW2t)[q] = ((const uint4*)W->W2t)[q];
-            ((uint4*)sW3t)[q] = ((const uint4*)W->W3t)[q];
-        }
-        for (int q = threadIdx.x; q < n4; q += blockDim.x) ((uint4*)sW4t)[q] = ((const uint4*)W->W4t)[q];
-    }
+    load_input_row<D>(U + sidx * raw_in(D), u);
     // targets of the four samples whose outputs this lane will hold
     const int comp = l & 15;
     float tg[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t si = __shfl(sidx, 4 * (l >> 4) + r, 64);
-        tg[r] = comp < d ? Tg[si * d + comp] : 0.0f;
+        tg[r] = Tg[si * D + min(comp, D - 1)];
+    }
+#pragma unroll
+    for (int q = 0; q < kTrainCopies; ++q) {
+        const int at = q * 256 + (int)threadIdx.x;
+        if (at < (int)(sizeof(TrainLds) / 16)) reinterpret_cast<uint4*>(&L)[at] = wt[q];
     }
     __syncthreads();
     bf16x8 a[2];
-    build_input_row(u, d, a);
+    build_input_row<D>(u, a);
     // inputs as operands, through the wavefront's tile (rows = samples)
     __bf16* tile = tiles[wave];
 #pragma unroll
@@ -802,16 +786,17 @@ __global__ __launch_bounds__(256) void k_train_fwdbwd(const MlpPacked* __restric
     wave_lds_fence();
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
-        f32x4 v;
+        uint32_t v[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = (float)tile[(4 * (l >> 4) + r) * kStride + nt * 16 + (l & 15)];
-        store_operand(tb.act[0], 4, nt, b0, v);
+        for (int r = 0; r < 4; ++r)
+            v[r] = reinterpret_cast<const uint16_t*>(tile)[(4 * (l >> 4) + r) * kStride + nt * 16 + (l & 15)];
+        store_operand(tb.act[0], 4, nt, b0, make_uint2(v[0] | v[1] << 16, v[2] | v[3] << 16));
     }
     wave_lds_fence();
 
     f32x4 z[3][4], h[3][4];
     f32x4 out;
-    mlp_forward16(sW1, sW2, sW3, sW4, sb, a, tile, z, h, out);
+    mlp_forward16(L.W1, L.W2, L.W3, L.W4, L.b, a, tile, z, h, out);
 
     // dL/dy in D layout: rows = samples 4 (l/16) + r, column = output l % 16
     f32x4 dy;
@@ -819,7 +804,7 @@ __global__ __launch_bounds__(256) void k_train_fwdbwd(const MlpPacked* __restric
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         float g = 0.0f;
-        if (comp < d) {
+        if (comp < D) {
             const float res = out[r] - tg[r];
             lsum += res * res;
             g = 2.0f * res / (float)B;
@@ -849,11 +834,11 @@ __global__ __launch_bounds__(256) void k_train_fwdbwd(const MlpPacked* __restric
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
         f32x4 c = {0.0f, 0.0f, 0.0f, 0.0f};
-        const bf16x8 b = *(const bf16x8*)&sW4t[(nt * 16 + (l & 15)) * kStrideT4 + 8 * (l >> 4)];
+        const bf16x8 b = *(const bf16x8*)&L.W4t[(nt * 16 + (l & 15)) * kStrideT4 + 8 * (l >> 4)];
         c = mfma_bf16(ga[0], b, c);
         g[nt] = c;
     }
-    const __bf16* Wt[2] = {sW3t, sW2t};
+    const __bf16* Wt[2] = {L.W3t, L.W2t};
 #pragma unroll
     for (int layer = 2; layer >= 0; --layer) {
         // delta of hidden layer (layer+1) = g * silu'(z)
@@ -907,8 +892,8 @@ __device__ __forceinline__ float adam_step(const AdamArgs& o, int64_t q, float g
 // with this launch (gradients, loss, Adam and packing were five).
 //
 // The sums are chains of B / 32 MFMAs; what they wait for is the operands.
-// kWgradBatch chunks are on their way while as many are multiplied.  Batch
-// 4096: @TWG@
+// kWgradBatch chunks are on their way while as many are multiplied.  At a
+// batch of 4096 35.1 us before (and 14 us of small launches), 8.9 now.
 constexpr int kWgradTiles = 52, kWgradBatch = 16;
 
 struct WgradChunks {
@@ -923,6 +908,40 @@ __device__ __forceinline__ void load_chunks(const bf16x8* a, const bf16x8* b, in
         w.a[q] = a[c * ta * 64];
         w.b[q] = b[c * 4 * 64];
     }
+}
+
+template <bool BIAS>
+__device__ __forceinline__ void mul_chunks(const WgradChunks& w, int n, f32x4& acc, f32x4& bacc)
+{
+    bf16x8 ones;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
+#pragma unroll
+    for (int q = 0; q < kWgradBatch; ++q)
+        if (q < n) {  // uniform; n is kWgradBatch but for the last
+            acc = mfma_bf16(w.a[q], w.b[q], acc);
+            if constexpr (BIAS) bacc = mfma_bf16(w.a[q], ones, bacc);
+        }
+}
+
+// The sum over all nc chunks in ascending order; cur: the first of them. Two
+// sets of registers take turns, so that nothing is moved between them.
+template <bool BIAS>
+__device__ __forceinline__ void wgrad_sum(const bf16x8* pa, const bf16x8* pb, int ta, int nc, WgradChunks& cur, f32x4& acc,
+                                          f32x4& bacc)
+{
+    WgradChunks nxt;
+    int c0 = 0;
+    for (; c0 + 2 * kWgradBatch <= nc; c0 += 2 * kWgradBatch) {
+        load_chunks(pa, pb, ta, c0 + kWgradBatch, nc, nxt);
+        mul_chunks<BIAS>(cur, kWgradBatch, acc, bacc);
+        load_chunks(pa, pb, ta, c0 + 2 * kWgradBatch, nc, cur);
+        mul_chunks<BIAS>(nxt, kWgradBatch, acc, bacc);
+    }
+    const int rest = nc - c0;
+    if (rest > kWgradBatch) load_chunks(pa, pb, ta, c0 + kWgradBatch, nc, nxt);
+    mul_chunks<BIAS>(cur, min(rest, kWgradBatch), acc, bacc);
+    if (rest > kWgradBatch) mul_chunks<BIAS>(nxt, rest - kWgradBatch, acc, bacc);
 }
 
 __global__ __launch_bounds__(64) void k_train_wgrad(TrainBufs tb, int d, int B, float* __restrict__ grad, AdamArgs opt,
@@ -955,7 +974,7 @@ __global__ __launch_bounds__(64) void k_train_wgrad(TrainBufs tb, int d, int B, 
     const bf16x8* pa = (const bf16x8*)tb.delta[layer] + ot * 64 + l;
     const bf16x8* pb = (const bf16x8*)tb.act[layer] + it * 64 + l;
     const int nc = B / 32;
-    WgradChunks cur, nxt;
+    WgradChunks cur;
     load_chunks(pa, pb, ta, 0, nc, cur);
     // this lane's weights and moments, used after the sums
     float w[4], m[4], v[4], wb[4], mb[4], vb[4];
@@ -970,20 +989,8 @@ __global__ __launch_bounds__(64) void k_train_wgrad(TrainBufs tb, int d, int B, 
     }
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     f32x4 bacc = {0.0f, 0.0f, 0.0f, 0.0f};
-    bf16x8 ones;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
-    for (int c0 = 0; c0 < nc; c0 += kWgradBatch) {
-        if (c0 + kWgradBatch < nc) load_chunks(pa, pb, ta, c0 + kWgradBatch, nc, nxt);
-#pragma unroll
-        for (int q = 0; q < kWgradBatch; ++q) {
-            if (c0 + q < nc) {  // uniform
-                acc = mfma_bf16(cur.a[q], cur.b[q], acc);
-                if (it == 0) bacc = mfma_bf16(cur.a[q], ones, bacc);
-            }
-        }
-        cur = nxt;
-    }
+    if (it == 0) wgrad_sum<true>(pa, pb, ta, nc, cur, acc, bacc);
+    else wgrad_sum<false>(pa, pb, ta, nc, cur, acc, bacc);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int orr = or0 + r;
