@@ -312,6 +312,11 @@ struct ssm_ctx {
     int win_lanes = 1;          // lanes per particle in k_bm_window
     bool use_graphs = false;
     std::vector<hipGraphExec_t> phase_graph;
+    // graphs of several ticks of a one-dimensional context (graph_choice)
+    hipGraphExec_t tick_graph[3] = {nullptr, nullptr, nullptr};
+    hipStream_t cap_stream = nullptr;
+    int64_t multi_ticks = 0;       // ticks launched one by one
+    bool no_tick_graph = false;    // a capture failed
     // kernel timing: event pairs recorded around launches while profiling
     bool profiling = false;
     int32_t profile_every = 1;     // bracket the launches of ticks with tick % profile_every == 0
@@ -394,6 +399,8 @@ static ssm_status dev_alloc(ssm_ctx* c, void** p, size_t bytes)
     return SSM_OK;
 }
 
+static void drop_graphs(ssm_ctx* c);
+
 static void free_ctx(ssm_ctx* c)
 {
     if (!c) return;
@@ -408,8 +415,8 @@ static void free_ctx(ssm_ctx* c)
     recycle_events(c, c->ev_pair);
     recycle_events(c, c->ev_update);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
-    for (hipGraphExec_t g : c->phase_graph)
-        if (g) (void)hipGraphExecDestroy(g);
+    drop_graphs(c);
+    if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }
@@ -674,7 +681,7 @@ static ssm_status launch_window(ssm_ctx* c, int64_t t0, const int64_t* tdev)
 // The tick's mode sums (d = 1): the partial rows, with the Brownian sums and
 // the means of mu^Y in the same launch, and their totals.
 template <typename T>
-static ssm_status launch_modes(ssm_ctx* c, int64_t ph, const int64_t* tdev, bool sums_only)
+static ssm_status launch_modes(ssm_ctx* c, int64_t ph, int64_t targ, const int64_t* tdev, bool sums_only)
 {
     const BlkItem* items = c->dblk + c->blk_off[ph];
     const int nm = (int)c->pair_cnt[ph];
@@ -684,7 +691,7 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, const int64_t* tdev, bool
 #define SSM_MODES(PV, LPV, ONE)                                                                                        \
     hipLaunchKernelGGL((k_modes<T, PV, LPV, ONE>), dim3((unsigned)(n_main + job.n)), dim3(kBlk), 0, c->stream, nm, n_main,  \
                        c->one, (const ModeItem*)c->dmitems + c->pair_off[ph], items, c->dsys, c->coef, c->P, (const T*)c->Ys,  \
-                       (const float2*)c->rng, c->dom, c->mode_part, c->mode_rows, c->pairsum, c->tick, tdev,            \
+                       (const float2*)c->rng, c->dom, c->mode_part, c->mode_rows, c->pairsum, targ, tdev,               \
                        (const double*)c->win, c->dW, job)
 #define SSM_MODES_LP(LPV)                                 \
     do {                                                  \
@@ -712,12 +719,12 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, const int64_t* tdev, bool
 }
 
 template <typename T>
-static ssm_status launch_tick(ssm_ctx* c, bool capture)
+static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
 {
-    // eager launches pass the tick by value; a captured tick reads (and at its
-    // end advances) the device counter so that the graph can be replayed
-    const int64_t* tdev = capture ? c->dtick : nullptr;
-    const int64_t ph = c->tick % c->max_stride;
+    // eager launches pass the tick by value; the tick `off` of a captured graph
+    // adds its place to the device counter, so that the graph can be replayed
+    const int64_t targ = tdev ? off : c->tick;
+    const int64_t ph = (c->tick + off) % c->max_stride;
     const int64_t np = c->pair_cnt[ph], nb = c->blk_cnt[ph];
     T* X = (T*)c->X;
     T* Y = (T*)c->Y;
@@ -734,7 +741,7 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
     const bool run_surr = surr_on && (check || !c->surr_fallback);
     const bool prof = c->profiling && c->tick % c->profile_every == 0;
     if (ph == 0 && c->win_items > 0 && nb > 0) {
-        ssm_status st = launch_window<T>(c, c->tick, tdev);
+        ssm_status st = launch_window<T>(c, targ, tdev);
         if (st != SSM_OK) return st;
     }
     if (c->has_pair && np > 0 && run_exact) {
@@ -744,7 +751,7 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
             e1 = take_event(c);
             if (e0) HIP_TRY(hipEventRecord(e0, c->stream));
         }
-        ssm_status st = c->modes ? launch_modes<T>(c, ph, tdev, false) : launch_pairs<T>(c, ph);
+        ssm_status st = c->modes ? launch_modes<T>(c, ph, targ, tdev, false) : launch_pairs<T>(c, ph);
         if (st != SSM_OK) return st;
         if (prof) {
             if (e1) HIP_TRY(hipEventRecord(e1, c->stream));
@@ -767,7 +774,7 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
         if (c->modes && run_exact) {
 #define SSM_UPDATE_MODES(TOT, ONE, part)                                                                                  \
     hipLaunchKernelGGL((k_update_modes<T, TOT, ONE>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, c->one, items, c->dsys,  \
-                       c->coef, c->P, c->tick, tdev, X, Y, Ys, (const ModeDom*)c->dom, (const double*)(part),           \
+                       c->coef, c->P, targ, tdev, X, Y, Ys, (const ModeDom*)c->dom, (const double*)(part),           \
                        c->mode_rows, c->pairsum, (const double*)c->dW, (const double*)c->ymean, c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng)
             if (c->mode_totals) SSM_UPDATE_MODES(true, false, c->mode_tot);
             else if (c->sys.size() > 1) SSM_UPDATE_MODES(false, false, c->mode_part);
@@ -788,12 +795,12 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
         if (comb) {                                                                                                       \
             SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_prep<T, D, LPV>), dim3(gb), dim3(kBlk), 0, c->stream, ncb, n_main,    \
                                                  items, c->dsys, c->coef, c->P, (const T*)c->Bp, (const T*)c->Bpj,        \
-                                                 (const double*)c->jtot, c->pairsum, c->tick, tdev, (const double*)c->win, \
+                                                 (const double*)c->jtot, c->pairsum, targ, tdev, (const double*)c->win, \
                                                  c->dW, job));                                                            \
         } else {                                                                                                          \
             SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_brownian_sum<D, LPV, (sizeof(T) == 4)>), dim3(gb), dim3(kBlk), 0,    \
                                                  c->stream, n_main,                                                       \
-                                                 items, c->dsys, c->coef, c->P, c->tick, tdev, (const double*)c->win,     \
+                                                 items, c->dsys, c->coef, c->P, targ, tdev, (const double*)c->win,     \
                                                  c->dW, job));                                                            \
         }
             switch (c->bm_lanes) {
@@ -806,7 +813,7 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
 #undef SSM_BM
             HIP_TRY(hipGetLastError());
             SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_update<T, D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream,
-                                                 items, c->dsys, c->coef, c->P, c->tick, tdev, X, Y, Ys, c->pairsum, c->surr,
+                                                 items, c->dsys, c->coef, c->P, targ, tdev, X, Y, Ys, c->pairsum, c->surr,
                                                  c->smean, use_surr,
                                                  make_float4((float)c->surr_gain[0], (float)c->surr_gain[1],
                                                              (float)c->surr_gain[2], (float)c->surr_gain[3]),
@@ -818,7 +825,7 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
         }
         if (!c->fused) {
             SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_newton<T, D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream,
-                                                 items, c->dsys, c->coef, c->P, c->tick, tdev, X, Y, Ys,
+                                                 items, c->dsys, c->coef, c->P, targ, tdev, X, Y, Ys,
                                                  c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng));
             HIP_TRY(hipGetLastError());
         }
@@ -835,10 +842,6 @@ static ssm_status launch_tick(ssm_ctx* c, bool capture)
         SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_surr_err<T, D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, items,
                                              c->dsys, c->P, c->pairsum, c->surr, c->smean, c->surr_res,
                                              (resid && c->surr_res_valid) ? 1 : 0, resid ? 1 : 0, c->err_part));
-        HIP_TRY(hipGetLastError());
-    }
-    if (capture) {
-        hipLaunchKernelGGL(k_tick_advance, dim3(1), dim3(64), 0, c->stream, c->dtick);
         HIP_TRY(hipGetLastError());
     }
     if (surr_on) {
@@ -896,46 +899,119 @@ static void advance_host(ssm_ctx* c)
     c->tick++;
 }
 
-// One tick: eager launches, or (graphs on, no profiling, no surrogate) the
-// replay of this phase's captured graph.
+// The graph of the n ticks from the context's current one (their phases are
+// part of it), captured on a stream of the library's own: the context's may be
+// the caller's, with work of other threads on it.
 template <typename T>
-static ssm_status run_tick(ssm_ctx* c)
+static ssm_status capture_ticks(ssm_ctx* c, int64_t n, hipGraphExec_t* out)
 {
+    if (!c->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
+    hipGraph_t g = nullptr;
+    HIP_TRY(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
+    hipStream_t own = c->stream;
+    c->stream = c->cap_stream;
+    ssm_status st = SSM_OK;
+    for (int64_t k = 0; k < n && st == SSM_OK; ++k) st = launch_tick<T>(c, c->dtick, k);
+    if (st == SSM_OK) {
+        hipLaunchKernelGGL(k_tick_advance, dim3(1), dim3(64), 0, c->stream, c->dtick, n);
+        if (hipGetLastError() != hipSuccess) st = fail(SSM_ERR_HIP, "graph capture: tick counter");
+    }
+    c->stream = own;
+    hipError_t he = hipStreamEndCapture(c->cap_stream, &g);
+    if (st != SSM_OK) {
+        if (g) (void)hipGraphDestroy(g);
+        return st;
+    }
+    if (he != hipSuccess) return fail(SSM_ERR_HIP, std::string("graph capture: ") + hipGetErrorString(he));
+    he = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(g);
+    if (he != hipSuccess) return fail(SSM_ERR_HIP, std::string("graph instantiate: ") + hipGetErrorString(he));
+    return SSM_OK;
+}
+
+template <typename T>
+static ssm_status replay_ticks(ssm_ctx* c, int64_t n, hipGraphExec_t ex)
+{
+    if (!c->dtick_valid) {  // the device counter lags after eager ticks
+        hipLaunchKernelGGL(k_tick_set, dim3(1), dim3(64), 0, c->stream, c->dtick, c->tick);
+        HIP_TRY(hipGetLastError());
+        c->dtick_valid = true;
+    }
+    HIP_TRY(hipGraphLaunch(ex, c->stream));
+    for (int64_t k = 0; k < n; ++k) advance_host(c);
+    return SSM_OK;
+}
+
+// Ticks that leave as one graph where n are left to do: the host's time for a
+// launch (2.7 to 4 us of it) and not the kernels' bounds small and medium
+// one-dimensional contexts whose ticks are two short launches; a graph costs
+// about 14 us and 0.2 us a node (measured: 8 nodes 1.7 us each, 32 nodes 0.4).
+// So from 4 ticks on, in whole periods of the step sizes, for contexts that
+// have taken kGraphAfter ticks (a graph takes some 100 us to make, which short
+// runs would not get back).  0: launch by launch.
+static constexpr int64_t kGraphAfter = 64;
+static constexpr int64_t kGraphTicks[3] = {16, 8, 4};
+
+static int graph_choice(ssm_ctx* c, int64_t n)
+{
+    if (!c->modes || c->no_tick_graph || c->use_graphs || c->profiling || c->surr_check_every != 0 ||
+        c->multi_ticks < kGraphAfter || c->tick % c->max_stride != 0)
+        return -1;
+    // a caller that captures the context's stream gets the launches
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return -1;
+    }
+    for (int q = 0; q < 3; ++q)
+        if (kGraphTicks[q] % c->max_stride == 0 && kGraphTicks[q] <= n) return q;
+    return -1;
+}
+
+// The next ticks of at most n: a graph of several, one tick launch by launch,
+// or (graphs on, no profiling, no surrogate) the replay of its phase's graph.
+template <typename T>
+static ssm_status run_ticks(ssm_ctx* c, int64_t n, int64_t* done)
+{
+    const int q = graph_choice(c, n);
+    if (q >= 0) {
+        if (!c->tick_graph[q] && capture_ticks<T>(c, kGraphTicks[q], &c->tick_graph[q]) != SSM_OK) {
+            (void)hipGetLastError();
+            c->no_tick_graph = true;
+        }
+        if (c->tick_graph[q]) {
+            *done = kGraphTicks[q];
+            return replay_ticks<T>(c, kGraphTicks[q], c->tick_graph[q]);
+        }
+    }
+    *done = 1;
     const bool graph_ok = c->use_graphs && !c->profiling && c->surr_check_every == 0;
     if (!graph_ok) {
-        ssm_status st = launch_tick<T>(c, false);
+        ssm_status st = launch_tick<T>(c, nullptr, 0);
         if (st != SSM_OK) return st;
         advance_host(c);
+        c->multi_ticks++;
         c->dtick_valid = false;
         return SSM_OK;
     }
-    const int64_t ph = c->tick % c->max_stride;
-    if (!c->dtick_valid) {
-        // the device counter lags after eager ticks: set it (value copied at the call)
-        const int64_t t = c->tick;
-        HIP_TRY(hipMemcpyAsync(c->dtick, &t, sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));
-        c->dtick_valid = true;
+    hipGraphExec_t& ex = c->phase_graph[c->tick % c->max_stride];
+    if (!ex) {
+        ssm_status st = capture_ticks<T>(c, 1, &ex);
+        if (st != SSM_OK) return st;
     }
-    if (!c->phase_graph[ph]) {
-        hipGraph_t g = nullptr;
-        HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-        ssm_status st = launch_tick<T>(c, true);
-        hipError_t he = hipStreamEndCapture(c->stream, &g);
-        if (st != SSM_OK) {
-            if (g) (void)hipGraphDestroy(g);
-            return st;
-        }
-        if (he != hipSuccess) return fail(SSM_ERR_HIP, std::string("graph capture: ") + hipGetErrorString(he));
-        hipGraphExec_t ex = nullptr;
-        he = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-        (void)hipGraphDestroy(g);
-        if (he != hipSuccess) return fail(SSM_ERR_HIP, std::string("graph instantiate: ") + hipGetErrorString(he));
-        c->phase_graph[ph] = ex;
+    return replay_ticks<T>(c, 1, ex);
+}
+
+static void drop_graphs(ssm_ctx* c)
+{
+    for (auto& g : c->phase_graph) {
+        if (g) (void)hipGraphExecDestroy(g);
+        g = nullptr;
     }
-    HIP_TRY(hipGraphLaunch(c->phase_graph[ph], c->stream));
-    advance_host(c);
-    return SSM_OK;
+    for (auto& g : c->tick_graph) {
+        if (g) (void)hipGraphExecDestroy(g);
+        g = nullptr;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1615,9 +1691,11 @@ extern "C" ssm_status ssm_step(ssm_ctx* c, int64_t n_ticks)
         ssm_status st = (c->prec == SSM_FP64) ? refresh_after_small<double>(c) : refresh_after_small<float>(c);
         if (st != SSM_OK) return st;
     }
-    for (int64_t t = 0; t < n_ticks; ++t) {
-        ssm_status st = (c->prec == SSM_FP64) ? run_tick<double>(c) : run_tick<float>(c);
+    for (int64_t t = 0; t < n_ticks;) {
+        int64_t done = 0;
+        ssm_status st = (c->prec == SSM_FP64) ? run_ticks<double>(c, n_ticks - t, &done) : run_ticks<float>(c, n_ticks - t, &done);
         if (st != SSM_OK) return st;
+        t += done;
     }
     return SSM_OK;
 }
@@ -1903,12 +1981,7 @@ extern "C" ssm_status ssm_bind_state(ssm_ctx* c, void* dev, size_t bytes)
     }
     c->X = dev;
     c->x_bound = true;
-    // captured tick graphs hold the old address
-    for (auto& g : c->phase_graph)
-        if (g) {
-            (void)hipGraphExecDestroy(g);
-            g = nullptr;
-        }
+    drop_graphs(c);  // they hold the old address
     return ssm_sync(c);
 }
 
@@ -2298,7 +2371,7 @@ static ssm_status launch_exact(ssm_ctx* c)
     const BlkItem* items = c->dblk + c->blk_off[0];
     const unsigned nb = (unsigned)c->blk_cnt[0];
     if (c->modes) {
-        ssm_status st = launch_modes<T>(c, 0, nullptr, true);
+        ssm_status st = launch_modes<T>(c, 0, c->tick, nullptr, true);
         if (st != SSM_OK) return st;
         if (c->mode_totals)
             hipLaunchKernelGGL((k_mode_eval<T, true>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,

@@ -281,11 +281,11 @@ __global__ __launch_bounds__(64 * kCombineWaves) void k_combine(const BlkItem* _
     combine_block<PT, D>(blockIdx.x, items, sys, P, Bp, Bpj, jtot, out, part);
 }
 
-// The tick a per-tick kernel works on: the context's device counter when
-// given (graph replays), else the value passed at launch.
+// The tick a per-tick kernel works on: the value passed at launch, or, in a
+// captured tick, the context's device counter plus the tick's place in its graph.
 __device__ __forceinline__ int64_t tick_of(const int64_t* tick_dev, int64_t tick_arg)
 {
-    return tick_dev ? *tick_dev : tick_arg;
+    return tick_dev ? *tick_dev + tick_arg : tick_arg;
 }
 
 // Lane permutations within each row of 16 lanes (gfx9 DPP controls):
@@ -949,10 +949,16 @@ __global__ __launch_bounds__(kBlk) void k_prep(int n_combine, int n_main, const 
         ymean_block<D>(blockIdx.x - n_main, job, sys, tick_arg, tick_dev);
 }
 
-// Advance the context's device tick counter (last launch of every tick).
-__global__ void k_tick_advance(int64_t* tick_dev)
+// The context's device tick counter moved by n ticks (last launch of a graph),
+// or set to t after ticks that ran without it.
+__global__ void k_tick_advance(int64_t* tick_dev, int64_t n)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *tick_dev += 1;
+    if (threadIdx.x == 0 && blockIdx.x == 0) *tick_dev += n;
+}
+
+__global__ void k_tick_set(int64_t* tick_dev, int64_t t)
+{
+    if (threadIdx.x == 0 && blockIdx.x == 0) *tick_dev = t;
 }
 
 // ---------------------------------------------------------------------------

@@ -139,3 +139,59 @@ def test_sampler_after_persistent_ticks():
     near = np.abs(Y[0][at] - U[:, 0].cpu().numpy()) <= 1e-6
     assert near.mean() > 0.4
     assert np.max(np.abs(K[0][at] - T[:, 0].cpu().numpy())[near]) <= 1e-6
+
+
+@pytest.mark.parametrize("case", ["one", "strides"])
+def test_graphs_of_several_ticks_are_the_launches(case):
+    """Past 64 ticks a context's longer step calls leave as graphs of 4, 8 or
+    16 ticks; steps of one tick never do.  Both runs are equal bit for bit,
+    with reads and moments between replays, ticks left over (the device tick
+    counter is set again), a state moved to another step and a newly bound
+    state buffer (the graphs are made again)."""
+    w = (_w([3000], steps=400) if case == "one" else
+         W.batched(n_ens=2, levels=(5, 6, 7), h_fine=2.0 ** -9, sizes=[3000, 300]))
+    w["T"] = 400 * max(s[2] for s in w["systems"])
+    with _ssm(w, "fp32_kahan", persistent=-1) as a, _ssm(w, "fp32_kahan", persistent=-1) as b:
+        def same(note):
+            for k in range(len(w["systems"])):
+                assert np.array_equal(a.state(k), b.state(k)), (note, k)
+
+        def both(n):
+            for _ in range(n):
+                a.step(1)
+            b.step(n)
+
+        for n in (64, 4, 4, 8, 16, 10, 12, 32, 7, 1, 60):
+            both(n)
+            same(n)
+            assert np.array_equal(a.moments(0)[0], b.moments(0)[0])
+        for s in (a, b):
+            for k, (N, e, h) in enumerate(w["systems"]):
+                s.set_state(k, s.state(k), step=round(64 * max(x[2] for x in w["systems"]) / h))
+        both(36)
+        same("moved")
+        buf = b.bind_state()
+        both(20)
+        same("bound")
+        assert buf.shape[0] == 1
+
+
+def test_graphs_stay_out_of_a_callers_capture(torch_cuda):
+    """A context on a stream that the caller is capturing launches tick by
+    tick into the capture, also past 64 ticks; the caller's graph then takes
+    the same four ticks as a context without it."""
+    torch = torch_cuda
+    w = _w([3000], steps=200)
+    st = torch.cuda.Stream()
+    with _ssm(w, "fp64", persistent=-1, stream=st) as a, _ssm(w, "fp64", persistent=-1) as b:
+        a.step(80)
+        b.step(80)
+        a.sync()
+        X = a.state(0)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            a.step(4)
+        g.replay()
+        torch.cuda.synchronize()
+        b.step(4)
+        assert np.array_equal(a.state(0), b.state(0)) and not np.array_equal(a.state(0), X)
