@@ -303,7 +303,7 @@ struct ssm_ctx {
     double* dW = nullptr;  // [d][P] Brownian increments of the current tick
     bool needs_ybar = false;   // b or sigma uses the mean of mu^Y
     double* ymean = nullptr;   // [n_sys][kMaxD] mean of mu^Y of the current step (k_prep / k_brownian_sum)
-    int bm_lanes = 1;      // lanes per particle in k_brownian_sum
+    std::vector<int> bm_lanes;  // per phase: lanes per particle in k_brownian_sum
     // shared Brownian windows of path groups (systems of one ensemble and size)
     double* win = nullptr;      // [groups][max_stride][d][N_g] per-tick normal sums
     BlkItem* dwin_items = nullptr;
@@ -685,7 +685,7 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, int64_t targ, const int64
 {
     const BlkItem* items = c->dblk + c->blk_off[ph];
     const int nm = (int)c->pair_cnt[ph];
-    const int n_main = nm + (sums_only ? 0 : (int)(c->blk_cnt[ph] * c->bm_lanes));
+    const int n_main = nm + (sums_only ? 0 : (int)(c->blk_cnt[ph] * c->bm_lanes[ph]));
     const YMeanJob job{c->dsys_list + c->sys_list_off[ph],
                        c->needs_ybar && !sums_only ? (int)c->sys_list_cnt[ph] : 0, c->psumY, c->nblk_tot, c->ymean};
 #define SSM_MODES(PV, LPV, ONE)                                                                                        \
@@ -699,7 +699,7 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, int64_t targ, const int64
         else if (c->sys.size() > 1) { SSM_MODES(1, LPV, false); } \
         else { SSM_MODES(1, LPV, true); }                 \
     } while (0)
-    switch (c->bm_lanes) {
+    switch (c->bm_lanes[ph]) {
         case 16: SSM_MODES_LP(16); break;
         case 8: SSM_MODES_LP(8); break;
         case 4: SSM_MODES_LP(4); break;
@@ -786,7 +786,7 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
             // partials in the same launch (k_prep)
             const bool comb = c->has_pair && run_exact;
             const int ncb = comb ? (int)(nb * 4) : 0;
-            const int n_main = (int)(ncb + nb * c->bm_lanes);
+            const int n_main = (int)(ncb + nb * c->bm_lanes[ph]);
             // the stepping systems' means of mu^Y, when b or sigma needs them
             const YMeanJob job{c->dsys_list + c->sys_list_off[ph], c->needs_ybar ? (int)c->sys_list_cnt[ph] : 0,
                                c->psumY, c->nblk_tot, c->ymean};
@@ -803,7 +803,7 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
                                                  items, c->dsys, c->coef, c->P, targ, tdev, (const double*)c->win,     \
                                                  c->dW, job));                                                            \
         }
-            switch (c->bm_lanes) {
+            switch (c->bm_lanes[ph]) {
                 case 16: SSM_BM(16); break;
                 case 8: SSM_BM(8); break;
                 case 4: SSM_BM(4); break;
@@ -1265,6 +1265,18 @@ static ssm_status validate(const ssm_config* cfg)
     return SSM_OK;
 }
 
+// Lanes per particle of a draw of `blocks` Philox blocks (or entries) each: as
+// many as there are blocks, up to 16, so that a small cloud fills the chip; one
+// lane where the particles do that (2^19 lanes are 8 wavefronts per SIMD).  A
+// block's number is then the same in a whole wavefront, and the generator's
+// products that depend on it alone are made once in scalar registers: 8 of 80.
+static int draw_lanes(int64_t blocks, int64_t particles)
+{
+    int lanes = blocks >= 16 ? 16 : blocks >= 8 ? 8 : blocks >= 4 ? 4 : blocks >= 2 ? 2 : 1;
+    while (lanes > 1 && particles * lanes > ((int64_t)1 << 19)) lanes /= 2;
+    return lanes;
+}
+
 // Largest j-side partial-sum buffer the symmetric scheme may take: 40 % of the
 // device's free memory, or 32 GiB if the runtime cannot say.
 static double jside_cap()
@@ -1368,8 +1380,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
             win_doubles += c->max_stride * (int64_t)cfg->d * R0.N;
         }
         is_int_ratio(h_min, cfg->h_fine, &c->r_min);
-        const int64_t wb = (c->r_min * cfg->d + 3) / 4;
-        c->win_lanes = wb >= 16 ? 16 : wb >= 8 ? 8 : wb >= 4 ? 4 : wb >= 2 ? 2 : 1;
+        c->win_lanes = draw_lanes((c->r_min * cfg->d + 3) / 4, win_doubles / cfg->d);
     }
     c->win_items = (int64_t)win_items.size();
     is_int_ratio(cfg->T, h_min, &c->ticks_total);
@@ -1488,7 +1499,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
             c->small_grid = (int64_t)tiles.size();
             int64_t bmax = 1;
             for (auto& S : c->sys) bmax = std::max<int64_t>(bmax, (S.r * c->d + 3) / 4);
-            c->small_lanes = bmax >= 16 ? 16 : bmax >= 8 ? 8 : bmax >= 4 ? 4 : bmax >= 2 ? 2 : 1;
+            c->small_lanes = draw_lanes(bmax, 0);
             int dev = 0, khz = 0;
             if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0) {
                 (void)hipGetLastError();
@@ -1528,14 +1539,6 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     std::vector<PairItem> pairs;
     std::vector<BlkItem> blks;
     std::vector<int32_t> sys_lists;
-    {
-        // per step and particle: about r d / 4 Philox blocks, or (path groups)
-        // `stride` window entries, four per lane
-        int64_t bmax = 1;
-        for (auto& S : c->sys)
-            bmax = std::max<int64_t>(bmax, S.win_off >= 0 ? (S.stride + 3) / 4 : (S.r * c->d + 3) / 4);
-        c->bm_lanes = bmax >= 16 ? 16 : bmax >= 8 ? 8 : bmax >= 4 ? 4 : bmax >= 2 ? 2 : 1;
-    }
     c->phase_graph.assign(c->max_stride, nullptr);
     c->use_graphs = cfg->graphs != 0;
     c->pair_off.resize(c->max_stride);
@@ -1546,6 +1549,15 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         std::vector<int> act;
         for (int s = 0; s < (int)c->sys.size(); ++s)
             if (ph % c->sys[s].stride == 0) act.push_back(s);
+        // per step and particle: about r d / 4 Philox blocks, or (path groups)
+        // `stride` window entries, four per lane; over the systems of this phase
+        int64_t bmax = 1, np = 0;
+        for (int s : act) {
+            const SysHost& S = c->sys[s];
+            bmax = std::max<int64_t>(bmax, S.win_off >= 0 ? (S.stride + 3) / 4 : (S.r * c->d + 3) / 4);
+            np += S.N;
+        }
+        c->bm_lanes.push_back(draw_lanes(bmax, np));
         c->pair_off[ph] = (int64_t)pairs.size();
         std::vector<int64_t> boff;
         if (c->modes) {

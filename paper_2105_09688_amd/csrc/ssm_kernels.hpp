@@ -769,19 +769,21 @@ __global__ __launch_bounds__(kBlk) void k_update(const BlkItem* __restrict__ ite
 // b = b_first, b_first + stride, ... (a lane's share), per component.
 // ---------------------------------------------------------------------------
 // F32: the FP32 transform (the FP32 precision modes); the sums stay in double.
-template <int D, bool F32 = false>
-__device__ __forceinline__ void stream_sum(uint64_t seed, uint64_t i, uint64_t e, uint64_t q0, uint64_t q1,
+// A 32-bit particle index I leaves the generator's first product with it two of
+// its four partial products.
+template <int D, bool F32 = false, typename I = uint64_t>
+__device__ __forceinline__ void stream_sum(uint64_t seed, I i, uint64_t e, uint64_t q0, uint64_t q1,
                                            uint64_t b_first, uint64_t stride, double zs[kMaxD])
 {
     for (uint64_t b = b_first; b * 4 < q1; b += stride) {
         double z[kMaxD];
         if constexpr (F32) {
             float zf[4];
-            normals4_f32(seed, 0u, i, b, e, zf);
+            normals4_f32(seed, 0u, (uint64_t)i, b, e, zf);
 #pragma unroll
             for (int s = 0; s < 4; ++s) z[s] = (double)zf[s];
         } else {
-            normals(seed, 0u, i, b, e, 4, z);
+            normals(seed, 0u, (uint64_t)i, b, e, 4, z);
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -842,7 +844,7 @@ __device__ __forceinline__ void brownian_block(int vb, const BlkItem* __restrict
         } else {
             const uint64_t q0 = (uint64_t)n * (uint64_t)S.r * D;
             const uint64_t q1 = q0 + (uint64_t)S.r * D;
-            stream_sum<D, F32>(cf.seed, (uint64_t)i, (uint64_t)S.ens, q0, q1, q0 / 4 + q, LP, zs);
+            stream_sum<D, F32>(cf.seed, (uint32_t)i, (uint64_t)S.ens, q0, q1, q0 / 4 + q, LP, zs);
         }
     }
     lane_butterfly<LP, D>(zs);
@@ -917,7 +919,7 @@ __global__ __launch_bounds__(kBlk) void k_bm_window(const BlkItem* __restrict__ 
     if (i < S.N) {
         const uint64_t q0 = (uint64_t)t * (uint64_t)r_min * D;
         const uint64_t q1 = q0 + (uint64_t)r_min * D;
-        stream_sum<D, F32>(cf.seed, (uint64_t)i, (uint64_t)S.ens, q0, q1, q0 / 4 + q, LP, zs);
+        stream_sum<D, F32>(cf.seed, (uint32_t)i, (uint64_t)S.ens, q0, q1, q0 / 4 + q, LP, zs);
     }
     lane_butterfly<LP, D>(zs);
     if (q == 0 && i < S.N) {

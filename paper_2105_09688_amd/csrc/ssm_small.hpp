@@ -210,7 +210,7 @@ __device__ __forceinline__ void small_brownian(const SysDev& S, const Coef& cf, 
         if (i < S.N) {
             const uint64_t q0 = (uint64_t)n * (uint64_t)S.r * D;
             const uint64_t q1 = q0 + (uint64_t)S.r * D;
-            stream_sum<D, F32>(cf.seed, (uint64_t)i, (uint64_t)S.ens, q0, q1, q0 / 4 + q, LP, zs);
+            stream_sum<D, F32>(cf.seed, (uint32_t)i, (uint64_t)S.ens, q0, q1, q0 / 4 + q, LP, zs);
         }
         lane_butterfly<LP, D>(zs);
         if (q == 0)

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kBlk) void k_solo_draw(const BlkItem* __restrict__ 
     double zs[kMaxD] = {0.0, 0.0, 0.0, 0.0};
     if (i < S.N) {
         const uint64_t q0 = (uint64_t)step_of(t, S.stride) * (uint64_t)S.r;
-        stream_sum<1, F32>(cf.seed, (uint64_t)i, (uint64_t)S.ens, q0, q0 + (uint64_t)S.r, q0 / 4 + q, LP, zs);
+        stream_sum<1, F32>(cf.seed, (uint32_t)i, (uint64_t)S.ens, q0, q0 + (uint64_t)S.r, q0 / 4 + q, LP, zs);
     }
     lane_butterfly<LP, 1>(zs);
     if (q == 0 && i < S.N) dW[(int64_t)blockIdx.y * P + S.off + i] = cf.sqrt_hf * zs[0];
