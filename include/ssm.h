@@ -124,8 +124,9 @@ typedef struct {
                                   scheme, >= 64) or a range against a 4-block target group
                                   (symmetric, rounded up to a multiple of 16) */
     int32_t pair_scheme;       /* 0: default (d = 1 with none of targets_per_lane, sources_per_item,
-                                  jside_band_groups and kahan_span = 1 given: by modes, below; else
-                                  symmetric where the group fits, else ordered);
+                                  jside_band_groups and kahan_span = 1 given: by modes, below; d = 3
+                                  likewise with one system of 24000 particles or more: by a grid,
+                                  below; else symmetric where the group fits, else ordered);
                                   1: every ordered pair (i, j) evaluated; 2: symmetric: each unordered
                                   pair evaluated once, +q to i and -q to j (the kernel is odd).
                                   By modes: the sums over all pairs as a Fourier sum over the extent of
@@ -133,10 +134,21 @@ typedef struct {
                                   precision mode, images and truncation below the rounding of the pair
                                   sums; a cloud too wide for its particle count (about 170 widths b_ell
                                   for N up to 1000, 700 from N = 4096 on) or with a non-finite particle
-                                  is summed over its ordered pairs that tick */
+                                  is summed over its ordered pairs that tick.
+                                  By a grid: the sums over all pairs by a window function, a grid over
+                                  the cloud's extent and convolutions along its axes, O(N) operations
+                                  in double precision in every precision mode; error against the exact
+                                  sums 1e-15 of their size in FP64, 5e-9 in the FP32 modes (a direct
+                                  FP32 sum: 2e-8).  A cloud too wide for the grid (30 widths b_ell along
+                                  an axis or 27 along all three in FP64, 42 and 31 in the FP32 modes)
+                                  or with a non-finite particle takes the pair kernels that tick.  It holds 60 MB more
+                                  device memory (117 in FP64); without room for them the pair kernels
+                                  are taken */
     int32_t graphs;            /* nonzero: each tick replays a HIP graph captured once per tick
                                   phase (tick % (h_max/h_min)); not used while profiling or with
-                                  the surrogate enabled */
+                                  the surrogate enabled.  0: contexts by modes still launch 4, 8 or
+                                  16 ticks of an ssm_step call as one graph once they have taken 64,
+                                  unless the caller is capturing the stream */
     /* Coefficient extensions (zero: off), see "Coefficients" above. */
     int32_t v_componentwise;   /* nonzero: component-wise cubic -v_ak[k] y_k^3 (v_a unused) */
     int32_t kahan_span;        /* SSM_FP32_KAHAN only: 0 -> plain sums over 256 sources between
@@ -167,6 +179,10 @@ typedef struct {
      * to 4) elements of the precision within 32 KiB per system, the
      * compensated-sum default (kahan_span = 0) and co-resident workgroups for
      * every 64 particles.
+     * With 0 below, contexts of one dimension whose systems have at most 2048
+     * particles each, summed by modes or without a pair term, take an ordinary
+     * launch in its place: one workgroup per system, no barrier between
+     * workgroups, the increments drawn by a launch before it.
      * Ticks with the surrogate enabled, with profiling or with graphs run the
      * multi-launch path.  Every barrier wait is bounded (4 s; the environment
      * variable SSM_PERSISTENT_WAIT_US, read by ssm_init, sets another limit
@@ -208,7 +224,8 @@ typedef struct {
     /* Kernel timing (ssm_profile enabled): HIP events recorded on the context's
      * stream around the launches of the sampled ticks since the last ssm_profile. */
     int64_t pair_launches;   /* launches of the pairwise kernel (by modes: of the mode sums, with the
-                                Brownian increments in the same launch) */
+                                Brownian increments in the same launch; by a grid: of its eight
+                                kernels and the pairwise kernel, which returns at once) */
     double pair_ms;          /* their summed duration, milliseconds */
     int64_t update_launches; /* launches of the per-particle update (+ implicit solve) kernels */
     double update_ms;
@@ -222,8 +239,9 @@ typedef struct {
     double surr_gain[SSM_MAX_D]; /* per-component gain fitted at the last check */
     /* persistent runs of small systems (ssm_config.persistent) */
     int32_t persistent;          /* 1: eligible (ticks without surrogate, profiling or graphs use it) */
-    int32_t persistent_tiles;    /* workgroups of a persistent launch (64 particles each) */
-    int64_t persistent_launches; /* cooperative launches so far */
+    int32_t persistent_tiles;    /* tiles of 64 particles: the workgroups of a cooperative launch (one
+                                    per system instead where ssm_config.persistent says so) */
+    int64_t persistent_launches; /* persistent launches so far */
     int64_t persistent_ticks;    /* ticks they ran */
     int64_t surr_rechecks;       /* checks made during a fallback (ssm_surrogate_recheck) */
 } ssm_info_t;

@@ -17,6 +17,7 @@
 #include "ssm_surrogate.hpp"
 #include "ssm_small.hpp"
 #include "ssm_solo.hpp"
+#include "ssm_grid.hpp"
 
 using namespace ssm;
 
@@ -332,6 +333,9 @@ struct ssm_ctx {
     double* mode_part = nullptr;    // [kModeVals / 16][mode_rows][16] (mode_at)
     double* mode_tot = nullptr;     // [n_sys][kModeVals] (mode_totals)
     float2* rng = nullptr;          // [nblk_tot] range of the scaled positions of each block
+    bool grid = false;              // d = 3: exact ticks by the grid where the cloud fits it (ssm_grid.hpp)
+    GridArgs ga{};
+    void* grid_buf = nullptr;       // its buffers
     // persistent runs of small systems (ssm_small.hpp)
     bool solo = false;              // in one workgroup per system (ssm_solo.hpp) in place of tiles
     int64_t solo_ticks = 0;         // ticks per launch: what solo_dW holds
@@ -409,7 +413,7 @@ static void free_ctx(ssm_ctx* c)
                     c->dmlp, c->surr, c->rff_part, c->mom, c->err_part, c->dsys_list, c->smean_part, c->smean,
                     c->dtick, c->dW, c->surr_res, c->dnmax, c->dred, c->dsq, c->win, c->dwin_items, c->ymean,
                     c->jtot, c->dtiles, c->sumY, c->sumX, c->dbar,
-                    c->dmitems, c->solo_dW, c->dom, c->mode_part, c->mode_tot, c->rng};
+                    c->dmitems, c->solo_dW, c->dom, c->mode_part, c->mode_tot, c->rng, c->grid_buf};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     recycle_events(c, c->ev_pair);
@@ -595,6 +599,84 @@ static void build_mode_items(const ssm_ctx* c, const std::vector<int>& systems, 
     }
 }
 
+static int device_cus();
+
+// The grid's sums into pairsum, where the cloud fits the grid; else nothing but
+// the mark that the pair kernels are to make them.
+template <typename T>
+static ssm_status launch_grid(ssm_ctx* c)
+{
+    typedef GridWin<T> Win;
+    const GridArgs& g = c->ga;
+    const T* Ys = (const T*)c->Ys;
+    const int nrange = (int)std::min<int64_t>(kGridRange, (g.N + kBlk - 1) / kBlk);
+    const dim3 per((unsigned)((g.N + kBlk * kGridPer - 1) / (kBlk * kGridPer)));
+    const int64_t chunks = g.N / Win::chunk + kGridBins;  // at most
+    // workgroups as many as a compute unit's LDS holds at once
+    const int cus = device_cus();
+    const dim3 spread((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 4 : 2) * cus));
+    const dim3 gather((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 2 : 1) * cus));
+    const dim3 conv((unsigned)(4 * cus));
+    hipLaunchKernelGGL(k_grid_range<T>, dim3((unsigned)nrange), dim3(kBlk), 0, c->stream, g, Ys);
+    hipLaunchKernelGGL(k_grid_bin<T>, per, dim3(kBlk), 0, c->stream, g, nrange, Ys);
+    hipLaunchKernelGGL(k_grid_scatter<T>, per, dim3(kBlk), 0, c->stream, g, Ys);
+    hipLaunchKernelGGL(k_grid_spread<T>, spread, dim3(Win::wg), 0, c->stream, g);
+    hipLaunchKernelGGL(k_grid_conv<0>, conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
+    hipLaunchKernelGGL(k_grid_conv<1>, conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
+    hipLaunchKernelGGL(k_grid_conv<2>, conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
+    hipLaunchKernelGGL(k_grid_gather<T>, gather, dim3(Win::gather_wg), 0, c->stream, g, Win::nodes);
+    HIP_TRY(hipGetLastError());
+    return SSM_OK;
+}
+
+// Buffers of the grid's sums; without memory for them the pair kernels stay.
+template <typename T>
+static bool grid_setup(ssm_ctx* c)
+{
+    typedef GridWin<T> Win;
+    static const std::vector<double> tab = grid_table(Win::W, Win::step, Win::beta);
+    GridArgs& g = c->ga;
+    const int64_t N = c->sys[0].N;
+    g.P = c->P;
+    g.off = c->one.off;
+    g.N = (int32_t)N;
+    g.qb = std::min(50, 62 - (int)std::ceil(std::log2((double)N)));
+    g.scale = c->one.pair_scale;
+    g.out = c->pairsum;
+    g.sys = c->dsys;
+    // one allocation, a part per buffer
+    size_t at = 0;
+    auto part = [&at](size_t bytes) {
+        const size_t here = at;
+        at += (bytes + 255) / 256 * 256;
+        return here;
+    };
+    const size_t range = part(kGridRange * 6 * sizeof(double)), dom = part(sizeof(GridDom)),
+                 count = part(kGridBins * sizeof(uint32_t)), key = part(N * sizeof(int2)), rec = part(N * sizeof(GridRec)),
+                 chunks = part((N / Win::chunk + kGridBins) * sizeof(GridChunk)),
+                 grid = part(Win::nodes * sizeof(unsigned long long)), A = part(3 * Win::nodes * sizeof(double)),
+                 B = part(3 * Win::nodes * sizeof(double)), dtab = part(tab.size() * sizeof(double));
+    char* base = nullptr;
+    if (dev_alloc(c, (void**)&base, at) != SSM_OK) {
+        (void)hipGetLastError();
+        return false;
+    }
+    c->grid_buf = base;
+    g.range = (double*)(base + range);
+    g.dom = (GridDom*)(base + dom);
+    g.count = (uint32_t*)(base + count);
+    g.key = (int2*)(base + key);
+    g.rec = (GridRec*)(base + rec);
+    g.chunks = (GridChunk*)(base + chunks);
+    g.grid = (unsigned long long*)(base + grid);
+    g.A = (double*)(base + A);
+    g.B = (double*)(base + B);
+    g.tab = (const double*)(base + dtab);
+    return hipMemcpyAsync(base + dtab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice, c->stream) == hipSuccess &&
+           hipMemsetAsync(g.count, 0, kGridBins * sizeof(uint32_t), c->stream) == hipSuccess &&
+           hipMemsetAsync(g.grid, 0, Win::nodes * sizeof(unsigned long long), c->stream) == hipSuccess;
+}
+
 // The pair sums of phase ph's items into the partial-sum buffers: one launch,
 // or (banded j-side rows) one launch per band followed by the fold of that
 // band's rows into jtot for every stepping particle.
@@ -604,6 +686,10 @@ static ssm_status launch_pairs(ssm_ctx* c, int64_t ph)
     const int d = c->d;
     const int64_t np = c->pair_cnt[ph];
     const PairItem* items = c->dpair + c->pair_off[ph];
+    if (c->grid) {
+        ssm_status st = launch_grid<T>(c);
+        if (st != SSM_OK) return st;
+    }
     if (c->band == 0) {
         const dim3 grid((unsigned)(c->sym ? np : (np + kWaves - 1) / kWaves));
         launch_pair<T>(d, c->R, c->prec == SSM_FP32_KAHAN, grid, c->stream, items, (int)np, c->dsys, (const T*)c->Ys,
@@ -1411,6 +1497,12 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     // that both are the launches' latency
     c->modes = c->d == 1 && c->has_pair && !c->kpair && cfg->targets_per_lane == 0 && cfg->sources_per_item == 0 &&
                cfg->pair_scheme == 0 && cfg->jside_band_groups == 0;
+    // one system in three dimensions by way of a grid, from the size on where
+    // that is faster.  A tick, pair kernels against grid: FP32 N = 16384 93 and
+    // 145 us, 24000 162 and 149, 2^18 14.1 ms and 325 us; FP64 N = 16384 203 and
+    // 197 us, 24000 367 and 232, 50021 1450 and 265
+    c->grid = c->d == 3 && c->has_pair && !c->kpair && c->sys.size() == 1 && c->sys[0].N >= 24000 && cfg->targets_per_lane == 0 &&
+              cfg->sources_per_item == 0 && cfg->pair_scheme == 0 && cfg->jside_band_groups == 0;
     for (int attempt = 0; attempt < 2; ++attempt) {
         std::vector<int64_t> Ns;
         for (auto& S : c->sys) Ns.push_back(S.N);
@@ -1671,6 +1763,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     if (he == hipSuccess) he = hipMemsetAsync(c->ymean, 0, c->sys.size() * kMaxD * sizeof(double), c->stream);
     if (he == hipSuccess && c->small_ok && !c->solo) he = hipMemcpyAsync(c->dtiles, tiles.data(), tiles.size() * sizeof(SmallTile), hipMemcpyHostToDevice, c->stream);
     if (he == hipSuccess && c->small_ok && !c->solo) he = hipMemsetAsync(c->dbar, 0, c->sys.size() * kBarLine * sizeof(uint64_t), c->stream);
+    if (he == hipSuccess && c->grid) c->grid = c->prec == SSM_FP64 ? grid_setup<double>(c) : grid_setup<float>(c);
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);  // host vectors go out of scope
     if (he != hipSuccess) { std::string m = hipGetErrorString(he); free_ctx(c); return fail(SSM_ERR_HIP, "upload: " + m); }
 

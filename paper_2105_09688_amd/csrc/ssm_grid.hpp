@@ -1,0 +1,614 @@
+// ssm_grid.hpp -- the interaction sums of one large system in three
+// dimensions, by way of a grid, in O(N) operations.
+//
+// In the scaled coordinates s (Ys) the pair term of particle i is
+//   K_i = sum_j (s_j - s_i) 2^(-|s_j - s_i|^2) = grad Phi(s_i) / (2 a),
+//   Phi(x) = sum_j e^(-a |x - s_j|^2),  a = ln 2.
+// On a grid of spacing g, and with a window psi of W nodes,
+//   e^(-a x^2) = sum_u sum_v psi(x - u) t(u - v) psi(v)      per dimension,
+//   t^(k) = G^(k) g / psi^(k)^2 on |k| <= pi / g   (G the Gaussian, ^ Fourier),
+// up to the window's aliases and what the Gaussian has beyond pi / g.  So K is
+//   spread : psi of every particle onto the grid,
+//   convolve: with t along two axes and with t' / (2 a) along the third (three
+//             components), and
+//   gather : the three fields with psi at every particle,
+// W^3 nodes a particle each way in place of N pairs.  psi is the window
+// e^(beta (sqrt(1 - z^2) - 1)), |z| <= 1 (Barnett, Magland, af Klinteberg, "A
+// parallel nonuniform fast Fourier transform library based on an exponential
+// of semicircle kernel", SIAM J. Sci. Comput. 41, 2019).
+//
+// All of it is in double precision in every precision mode.  Node values are
+// added up as 64-bit integers in units of 2^-qb: integer sums do not depend on
+// their order, so runs stay bitwise reproducible with atomic additions, and
+// a resumed run equals an uninterrupted one.
+//
+// A cloud that is too wide for the grid, or holds a particle that is not
+// finite, is summed by the pair kernels as before: k_grid_bin marks in SysDev
+// which of the two the tick takes, and the other's kernels return at once.
+#pragma once
+
+#include "ssm_kernels.hpp"
+
+#include <cmath>
+#include <vector>
+
+namespace ssm {
+
+constexpr int kGridCell = 8;     // nodes of a bin along each axis
+constexpr int kGridAxis = 128;   // first nodes along an axis at most: 16 bins
+constexpr int kGridBins = (kGridAxis / kGridCell) * (kGridAxis / kGridCell) * (kGridAxis / kGridCell);
+constexpr int kGridTab = 144;    // offsets of the convolution tables: more than kGridAxis + W
+constexpr int kGridRange = 256;  // blocks of k_grid_range at most
+constexpr int kGridPer = 4;      // particles per thread of k_grid_bin and k_grid_scatter
+constexpr double kGridAlpha = 0.69314718055994530942;  // a = ln 2
+
+// Window and spacing of a precision.  Error of K against the exact sums,
+// relative to its root mean square (one dimension, normal cloud): FP64 1.1e-15,
+// FP32 modes 4.6e-9 (the direct FP32 terms carry 2e-8 and their plain sums 5e-7).
+template <typename T>
+struct GridWin;
+template <>
+struct GridWin<float> {
+    static constexpr int W = 8;
+    static constexpr double step = 0.28, beta = 2.55 * 8;
+    static constexpr int group = 8;    // lanes per particle of k_grid_gather
+    static constexpr int chunk = 256;  // particles of a bin that a workgroup takes at a time
+    static constexpr int wg = 256, gather_wg = 512;
+    static constexpr int64_t nodes = 1 << 20;
+};
+template <>
+struct GridWin<double> {
+    static constexpr int W = 14;
+    static constexpr double step = 0.2, beta = 2.6 * 14;
+    static constexpr int group = 16;
+    static constexpr int chunk = 128;
+    static constexpr int wg = 512, gather_wg = 1024;
+    static constexpr int64_t nodes = 1 << 21;
+};
+
+// The tick's grid: lowest coordinates, nodes and bins along each axis, chunks.
+struct GridDom {
+    double lo[3];
+    int32_t n[3], nb[3];
+    int32_t use;      // 0: the pair kernels take the tick
+    int32_t nchunks;
+};
+
+struct GridRec {      // a particle in its bin's order
+    double v[3];      // (s - lo) / step
+    int64_t i;
+};
+
+struct GridChunk {
+    int32_t start, len, bin, pad;
+};
+
+struct GridArgs {
+    int64_t P, off;                 // component stride and first slot of the system
+    int32_t N, qb;                  // particles; unit 2^-qb of the node sums
+    double scale;                   // pair_scale
+    double* range;                  // [kGridRange][6]
+    GridDom* dom;
+    SysDev* sys;
+    uint32_t* count;                // [kGridBins], zero between ticks
+    int2* key;                      // [N] bin and place in it
+    GridRec* rec;                   // [N]
+    GridChunk* chunks;
+    unsigned long long* grid;       // [nodes], zero between ticks
+    double *A, *B;                  // [3][nodes] each
+    const double* tab;              // [2][2 kGridTab]: t and t' / (2 a) at offsets -kGridTab ..
+    double* out;                    // pairsum
+};
+
+// ---------------------------------------------------------------------------
+// Host: t and t' / (2 a) at the grid's offsets.  Gauss-Legendre panels in long
+// double; psi's integral in z = sin(theta), where it is smooth.
+// ---------------------------------------------------------------------------
+inline std::vector<double> grid_table(int W, double step, double beta)
+{
+    typedef long double L;
+    const L pi = 3.14159265358979323846264338327950288L, a = 0.693147180559945309417232121458176568L;
+    constexpr int G = 20, panels = 12, n = G * panels;
+    L gx[G], gw[G];
+    for (int i = 0; i < G; ++i) {
+        L x = std::cos(pi * (i + 0.75L) / (G + 0.5L)), dp = 0;
+        for (int it = 0; it < 50; ++it) {
+            L p0 = 1, p1 = x;
+            for (int k = 2; k <= G; ++k) {
+                const L p2 = ((2 * k - 1) * x * p1 - (k - 1) * p0) / k;
+                p0 = p1;
+                p1 = p2;
+            }
+            dp = G * (x * p1 - p0) / (x * x - 1);
+            const L dx = p1 / dp;
+            x -= dx;
+            if (std::fabs(dx) < 1e-19L) break;
+        }
+        gx[i] = x;
+        gw[i] = 2 / ((1 - x * x) * dp * dp);
+    }
+    std::vector<L> X(n), Wt(n);  // nodes of [0, 1]
+    for (int p = 0; p < panels; ++p)
+        for (int i = 0; i < G; ++i) {
+            X[p * G + i] = (p + 0.5L * (gx[i] + 1)) / panels;
+            Wt[p * G + i] = 0.5L * gw[i] / panels;
+        }
+    const L hw = (L)W * (L)step / 2, kmax = pi / (L)step;
+    std::vector<L> zq(n), pq(n);
+    for (int q = 0; q < n; ++q) {  // even in theta: twice the half range
+        const L th = X[q] * pi / 2, c = std::cos(th);
+        zq[q] = std::sin(th) * hw;
+        pq[q] = std::exp((L)beta * (c - 1)) * c * Wt[q] * (pi / 2) * hw * 2;
+    }
+    std::vector<L> t(kGridTab, 0), td(kGridTab, 0);
+    for (int q = 0; q < n; ++q) {
+        const L k = X[q] * kmax;
+        L ph = 0;
+        for (int u = 0; u < n; ++u) ph += pq[u] * std::cos(k * zq[u]);
+        const L th = std::sqrt(pi / a) * std::exp(-k * k / (4 * a)) * (L)step / (ph * ph) * Wt[q] * kmax * (L)step / pi;
+        const L c1 = std::cos(k * (L)step), s1 = std::sin(k * (L)step);
+        L c = 1, s = 0;
+        for (int m = 0; m < kGridTab; ++m) {
+            t[m] += th * c;
+            td[m] -= th * k * s / (2 * a);
+            const L cn = c * c1 - s * s1;
+            s = s * c1 + c * s1;
+            c = cn;
+        }
+    }
+    std::vector<double> tab(4 * kGridTab, 0.0);
+    for (int m = 0; m < kGridTab; ++m) {
+        tab[kGridTab + m] = (double)t[m];
+        tab[3 * kGridTab + m] = (double)td[m];
+        if (m > 0) {
+            tab[kGridTab - m] = (double)t[m];
+            tab[3 * kGridTab - m] = -(double)td[m];
+        }
+    }
+    return tab;
+}
+
+// ---------------------------------------------------------------------------
+// k_grid_range: the cloud's extent, a row per block.  A coordinate that is not
+// finite leaves -infinity as its lower end.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ double wave_min_f64(double v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
+    return v;
+}
+
+// lo[3], -hi[3] of a block's threads, in all of wavefront 0 .. (kBlk / 64 wavefronts)
+__device__ __forceinline__ void block_min6(double (&m)[6], double (*part)[6])
+{
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) m[k] = wave_min_f64(m[k]);
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) part[wave][k] = m[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 6; ++k) m[k] = fmin(fmin(part[0][k], part[1][k]), fmin(part[2][k], part[3][k]));
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlk) void k_grid_range(GridArgs g, const T* __restrict__ Ys)
+{
+    __shared__ double part[kBlk / 64][6];
+    double m[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) m[k] = INFINITY;
+    for (int i = blockIdx.x * kBlk + threadIdx.x; i < g.N; i += gridDim.x * kBlk)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double x = (double)Ys[k * g.P + g.off + i];
+            const bool ok = fabs(x) < INFINITY;
+            m[k] = fmin(m[k], ok ? x : -INFINITY);
+            m[k + 3] = fmin(m[k + 3], ok ? -x : -INFINITY);
+        }
+    block_min6(m, part);
+    if (threadIdx.x < 6) {
+        double v = m[0];
+#pragma unroll
+        for (int k = 1; k < 6; ++k) v = (int)threadIdx.x == k ? m[k] : v;
+        g.range[blockIdx.x * 6 + threadIdx.x] = v;
+    }
+}
+
+// The tick's grid from the blocks' ranges: the same in every block.
+template <typename T>
+__device__ __forceinline__ GridDom grid_domain(const GridArgs& g, int nrange, double (*part)[6])
+{
+    constexpr int W = GridWin<T>::W;
+    double m[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) m[k] = (int)threadIdx.x < nrange ? g.range[threadIdx.x * 6 + k] : INFINITY;
+    block_min6(m, part);
+    GridDom d;
+    d.use = 1;
+    d.nchunks = 0;
+    int64_t nodes = 1;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        d.lo[k] = m[k];
+        const double e = ceil((-m[k + 3] - m[k]) * (1.0 / GridWin<T>::step));
+        const bool fits = e < (double)kGridAxis;  // false for NaN and infinities
+        const int cells = fits ? (int)e + 1 : 1;
+        if (!fits) d.use = 0;
+        d.n[k] = cells + W - 1;
+        d.nb[k] = (cells + kGridCell - 1) / kGridCell;
+        nodes *= d.n[k];
+    }
+    if (nodes > GridWin<T>::nodes) d.use = 0;
+    return d;
+}
+
+// ---------------------------------------------------------------------------
+// k_grid_bin: the particles' bins and their places in them.  A block counts
+// 1024 particles in LDS and takes its places in each bin with one addition.
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(kBlk) void k_grid_bin(GridArgs g, int nrange, const T* __restrict__ Ys)
+{
+    __shared__ double part[kBlk / 64][6];
+    __shared__ uint32_t hist[kGridBins];
+    const int i0 = blockIdx.x * (kBlk * kGridPer) + threadIdx.x;
+    double s[kGridPer][3];
+#pragma unroll
+    for (int u = 0; u < kGridPer; ++u)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) s[u][k] = (double)Ys[k * g.P + g.off + min(i0 + u * kBlk, g.N - 1)];
+    const GridDom d = grid_domain<T>(g, nrange, part);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *g.dom = d;
+        g.sys->by_grid = d.use;
+    }
+    if (!d.use) return;
+    const int bins = d.nb[0] * d.nb[1] * d.nb[2];
+    for (int b = threadIdx.x; b < bins; b += kBlk) hist[b] = 0;
+    __syncthreads();
+    int bin[kGridPer], place[kGridPer];
+#pragma unroll
+    for (int u = 0; u < kGridPer; ++u) {
+        int c[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c[k] = (int)ceil((s[u][k] - d.lo[k]) * (1.0 / GridWin<T>::step)) / kGridCell;
+        bin[u] = (c[0] * d.nb[1] + c[1]) * d.nb[2] + c[2];
+        if (i0 + u * kBlk < g.N) place[u] = (int)atomicAdd(&hist[bin[u]], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < bins; b += kBlk) {
+        const uint32_t c = hist[b];
+        if (c) hist[b] = atomicAdd(&g.count[b], c);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kGridPer; ++u)
+        if (i0 + u * kBlk < g.N) g.key[i0 + u * kBlk] = make_int2(bin[u], place[u] + (int)hist[bin[u]]);
+}
+
+// Exclusive sums of v over the block's threads; *total: their sum.
+__device__ __forceinline__ int block_scan(int v, int* wsum, int* total)
+{
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o);
+        if (lane >= o) x += y;
+    }
+    __syncthreads();
+    if (lane == 63) wsum[wave] = x;
+    __syncthreads();
+    int base = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < kBlk / 64; ++w) {
+        if (w < wave) base += wsum[w];
+        tot += wsum[w];
+    }
+    *total = tot;
+    return base + x - v;
+}
+
+// ---------------------------------------------------------------------------
+// k_grid_scatter: the particles in the order of their bins, and (block 0) the
+// list of chunks: at most GridWin::chunk particles of one bin each.
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(kBlk) void k_grid_scatter(GridArgs g, const T* __restrict__ Ys)
+{
+    constexpr int kRun = kGridBins / kBlk, C = GridWin<T>::chunk;
+    __shared__ int start[kGridBins];
+    __shared__ int wsum[kBlk / 64];
+    const GridDom d = *g.dom;
+    if (!d.use) return;
+    const int bins = d.nb[0] * d.nb[1] * d.nb[2];
+    int c[kRun], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kRun; ++q) {
+        const int b = threadIdx.x * kRun + q;
+        c[q] = b < bins ? (int)g.count[b] : 0;
+        sum += c[q];
+    }
+    int total;
+    int at = block_scan(sum, wsum, &total);
+    int nch = 0;
+#pragma unroll
+    for (int q = 0; q < kRun; ++q) {
+        start[threadIdx.x * kRun + q] = at;
+        at += c[q];
+        nch += (c[q] + C - 1) / C;
+    }
+    if (blockIdx.x == 0) {
+        int ch = block_scan(nch, wsum, &total);
+        for (int q = 0; q < kRun; ++q) {
+            const int b = threadIdx.x * kRun + q;
+            for (int a = 0; a < c[q]; a += C) g.chunks[ch++] = GridChunk{start[b] + a, min(C, c[q] - a), b, 0};
+        }
+        if (threadIdx.x == 0) g.dom->nchunks = total;
+    }
+    __syncthreads();
+    const int i0 = blockIdx.x * (kBlk * kGridPer) + threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < kGridPer; ++u) {
+        const int i = i0 + u * kBlk;
+        if (i >= g.N) break;
+        const int2 k = g.key[i];
+        GridRec r;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) r.v[a] = ((double)Ys[a * g.P + g.off + i] - d.lo[a]) * (1.0 / GridWin<T>::step);
+        r.i = i;
+        g.rec[start[k.x] + k.y] = r;
+    }
+}
+
+// psi at node m of a particle's W, f in [0, 1) the first node's distance.
+template <typename T>
+__device__ __forceinline__ double grid_psi(int m, double f)
+{
+    constexpr int W = GridWin<T>::W;
+    constexpr double b = GridWin<T>::beta * 1.44269504088896340736;
+    const double z = ((double)(m - W / 2) + f) * (2.0 / W);
+    return exp2_fast(fma(b, sqrt(fmax(fma(-z, z, 1.0), 0.0)), -b));
+}
+
+// A bin's nodes in LDS: kGridCell + W - 1 along each axis.  W = 8: rows of 16,
+// odd ones turned by 8, so that the 8 x 8 nodes of a wavefront meet every bank
+// equally often.
+template <typename T>
+struct GridTile {
+    static constexpr int E = kGridCell + GridWin<T>::W - 1;
+    static constexpr int pitch = GridWin<T>::W == 8 ? 16 : E;
+    static constexpr int size = E * E * pitch;
+    static __device__ __forceinline__ int at(int x, int y, int z)
+    {
+        const int row = x * E + y;
+        return row * pitch + (pitch == 16 ? (z ^ ((y & 1) << 3)) : z);
+    }
+};
+
+// Weights of `n` particles from rec into w, 3 W (+ pad) each, by the threads t, t + nt, ...
+template <typename T, int PITCH>
+__device__ __forceinline__ void grid_weights(const GridRec* __restrict__ rec, int n, double* w, int t, int nt)
+{
+    constexpr int W = GridWin<T>::W;
+    for (int q = t; q < n * 3 * W; q += nt) {
+        const int p = q / (3 * W), r = q - p * (3 * W), a = r / W, m = r - a * W;
+        const double v = rec[p].v[a];
+        w[p * PITCH + r] = grid_psi<T>(m, ceil(v) - v);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_grid_spread: a workgroup adds a chunk's particles into its bin's nodes in
+// LDS, a wavefront one particle at a time (lanes: y and z), then into the grid.
+// A value is rounded to units of 2^-qb by adding 1.5 2^(52 - qb), whose own
+// bits are taken off again.  Bound by LDS atomics: W^3 / 64 a particle.
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
+{
+    constexpr int W = GridWin<T>::W, WG = GridWin<T>::wg, PB = W == 8 ? 8 : 2, R = (W * W + 63) / 64;
+    typedef GridTile<T> Tile;
+    constexpr int E = Tile::E;
+    __shared__ unsigned long long tile[Tile::size];
+    __shared__ double wts[WG / 64][PB * 3 * W];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const GridDom d = *g.dom;
+    if (!d.use) return;
+    const double magic = ldexp(1.5, 52 - g.qb);
+    const unsigned long long mbits = (unsigned long long)__double_as_longlong(magic);
+    double* w = wts[wave];
+    for (int ch = blockIdx.x; ch < d.nchunks; ch += gridDim.x) {
+        const GridChunk c = g.chunks[ch];
+        const int bx = c.bin / (d.nb[1] * d.nb[2]), by = c.bin / d.nb[2] % d.nb[1], bz = c.bin % d.nb[2];
+        for (int q = threadIdx.x; q < Tile::size; q += WG) tile[q] = 0;
+        __syncthreads();
+        for (int p0 = wave * PB; p0 < c.len; p0 += WG / 64 * PB) {
+            const GridRec* __restrict__ rec = g.rec + c.start + p0;
+            const int n = min(PB, c.len - p0);
+            grid_weights<T, 3 * W>(rec, n, w, lane, 64);
+            wave_lds_fence();
+            for (int p = 0; p < n; ++p) {
+                const int x0 = (int)ceil(rec[p].v[0]) - bx * kGridCell;
+                const int y0 = (int)ceil(rec[p].v[1]) - by * kGridCell;
+                const int z0 = (int)ceil(rec[p].v[2]) - bz * kGridCell;
+                double wyz[R];
+                int at[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int q = lane + 64 * r, y = q / W, z = q - y * W;
+                    const bool in = q < W * W;
+                    wyz[r] = in ? w[p * 3 * W + W + y] * w[p * 3 * W + 2 * W + z] : 0.0;
+                    at[r] = Tile::at(x0, y0 + (in ? y : 0), z0 + (in ? z : 0));
+                }
+#pragma unroll
+                for (int x = 0; x < W; ++x) {
+                    const double wx = w[p * 3 * W + x];
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        if (64 * (r + 1) <= W * W || lane + 64 * r < W * W)
+                            atomicAdd(&tile[at[r] + x * E * Tile::pitch],
+                                      (unsigned long long)__double_as_longlong(fma(wx, wyz[r], magic)) - mbits);
+                }
+            }
+            wave_lds_fence();
+        }
+        __syncthreads();
+        for (int q = threadIdx.x; q < E * E * E; q += WG) {
+            const int x = q / (E * E), y = q / E % E, z = q % E;
+            const unsigned long long v = tile[Tile::at(x, y, z)];
+            if (v) {  // nodes outside the grid hold nothing
+                const int64_t node = ((int64_t)(bx * kGridCell + x) * d.n[1] + by * kGridCell + y) * d.n[2] + bz * kGridCell + z;
+                atomicAdd(&g.grid[node], v);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_grid_conv: one axis, the slowest of its input, which becomes the fastest
+// of its output; three launches come back to the grid's own order.  A thread
+// makes 4 outputs along the axis for one line; table values are wave-uniform.
+//   pass 0: grid -> A = {t, t'}     pass 1: A -> B = {tt, tt', t't}
+//   pass 2: B -> A = {t't t, t t' t, t t t'}, the three components' fields
+// Pass 1 also clears the grid and the bins' counts for the next tick.
+// ---------------------------------------------------------------------------
+template <int PASS>
+__global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
+{
+    constexpr int R = 4, U = 4, NIN = PASS + 1, NOUT = PASS == 0 ? 2 : 3;
+    const GridDom d = *g.dom;
+    if (!d.use) return;
+    const int n = d.n[PASS], inner = d.n[(PASS + 1) % 3] * d.n[(PASS + 2) % 3];
+    const double* __restrict__ in = PASS == 1 ? g.A : g.B;
+    const unsigned long long* __restrict__ raw = g.grid;
+    double* __restrict__ out = PASS == 1 ? g.B : g.A;
+    const double unit = ldexp(1.0, -g.qb);
+    const int lines = (inner + kBlk - 1) / kBlk, work = lines * ((n + R - 1) / R);
+    for (int it = blockIdx.x; it < work; it += gridDim.x) {
+        const int a0 = it / lines * R;
+        const int q = it % lines * kBlk + threadIdx.x;
+        const int qc = min(q, inner - 1);
+        const double* __restrict__ t = g.tab + kGridTab + a0;
+        const double* __restrict__ td = t + 2 * kGridTab;
+        double acc[NOUT][R];
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o)
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[o][r] = 0.0;
+        auto load = [&](int f, int b) -> double {
+            const int64_t at = (int64_t)b * inner + qc;
+            if constexpr (PASS == 0) return (double)(long long)raw[at];
+            else return in[f * nodes + at];
+        };
+        auto add = [&](const double (&x)[NIN], int b) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const double tv = t[r - b], dv = td[r - b];
+                if constexpr (PASS == 0) {
+                    acc[0][r] = fma(tv, x[0], acc[0][r]);
+                    acc[1][r] = fma(dv, x[0], acc[1][r]);
+                } else if constexpr (PASS == 1) {
+                    acc[0][r] = fma(tv, x[0], acc[0][r]);
+                    acc[1][r] = fma(dv, x[0], acc[1][r]);
+                    acc[2][r] = fma(tv, x[1], acc[2][r]);
+                } else {
+                    acc[0][r] = fma(tv, x[2], acc[0][r]);
+                    acc[1][r] = fma(tv, x[1], acc[1][r]);
+                    acc[2][r] = fma(dv, x[0], acc[2][r]);
+                }
+            }
+        };
+        int b = 0;
+        for (; b + U <= n; b += U) {
+            double x[U][NIN];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int f = 0; f < NIN; ++f) x[u][f] = load(f, b + u);
+#pragma unroll
+            for (int u = 0; u < U; ++u) add(x[u], b + u);
+        }
+        for (; b < n; ++b) {
+            double x[NIN];
+#pragma unroll
+            for (int f = 0; f < NIN; ++f) x[f] = load(f, b);
+            add(x, b);
+        }
+        if (q < inner)
+#pragma unroll
+            for (int o = 0; o < NOUT; ++o)
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+                    if (a0 + r < n) out[o * nodes + (int64_t)q * n + a0 + r] = PASS == 0 ? acc[o][r] * unit : acc[o][r];
+    }
+    if constexpr (PASS == 1) {
+        const int64_t used = (int64_t)n * inner;
+        for (int64_t q = (int64_t)blockIdx.x * kBlk + threadIdx.x; q < used; q += (int64_t)gridDim.x * kBlk) g.grid[q] = 0;
+        const int bins = d.nb[0] * d.nb[1] * d.nb[2];
+        for (int q = blockIdx.x * kBlk + threadIdx.x; q < bins; q += gridDim.x * kBlk) g.count[q] = 0;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_grid_gather: the pair term of a chunk's particles from their bin's nodes.
+// The nodes of one field at a time in LDS; `group` lanes per particle, one
+// for each z.  Bound by LDS reads: 3 W^2 a lane.
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(GridWin<T>::gather_wg) void k_grid_gather(GridArgs g, int64_t nodes)
+{
+    constexpr int W = GridWin<T>::W, WG = GridWin<T>::gather_wg, GR = GridWin<T>::group, C = GridWin<T>::chunk;
+    constexpr int WP = 3 * W + 1;
+    typedef GridTile<T> Tile;
+    constexpr int E = Tile::E;
+    __shared__ double tile[Tile::size];
+    __shared__ double wts[C * WP];
+    const GridDom d = *g.dom;
+    if (!d.use) return;
+    const int z = threadIdx.x & (GR - 1), slot = threadIdx.x / GR;
+    const int zc = min(z, W - 1);
+    for (int ch = blockIdx.x; ch < d.nchunks; ch += gridDim.x) {
+        const GridChunk c = g.chunks[ch];
+        const int ox = c.bin / (d.nb[1] * d.nb[2]) * kGridCell, oy = c.bin / d.nb[2] % d.nb[1] * kGridCell,
+                  oz = c.bin % d.nb[2] * kGridCell;
+        const GridRec* __restrict__ rec = g.rec + c.start;
+        grid_weights<T, WP>(rec, c.len, wts, threadIdx.x, WG);
+#pragma unroll 1
+        for (int f = 0; f < 3; ++f) {
+            const double* __restrict__ F = g.A + f * nodes;
+            for (int q = threadIdx.x; q < E * E * E; q += WG) {
+                const int x = q / (E * E), y = q / E % E, zz = q % E;
+                const bool in = ox + x < d.n[0] && oy + y < d.n[1] && oz + zz < d.n[2];
+                tile[Tile::at(x, y, zz)] = in ? F[((int64_t)(ox + x) * d.n[1] + oy + y) * d.n[2] + oz + zz] : 0.0;
+            }
+            __syncthreads();
+            for (int p = slot; p < c.len; p += WG / GR) {
+                const GridRec r = rec[p];
+                const int x0 = (int)ceil(r.v[0]) - ox, y0 = (int)ceil(r.v[1]) - oy, z0 = (int)ceil(r.v[2]) - oz + zc;
+                const double* w = wts + p * WP;
+                double acc = 0.0;
+#pragma unroll 2
+                for (int x = 0; x < W; ++x) {
+                    double s = 0.0;
+#pragma unroll
+                    for (int y = 0; y < W; ++y) s = fma(w[W + y], tile[Tile::at(x0 + x, y0 + y, z0)], s);
+                    acc = fma(w[x], s, acc);
+                }
+                acc = z < W ? acc * w[2 * W + zc] : 0.0;
+                acc += dpp64<kDppXor1>(acc);
+                acc += dpp64<kDppXor2>(acc);
+                acc += dpp64<kDppHalfMirror>(acc);
+                if (GR == 16) acc += dpp64<kDppMirror>(acc);
+                if (z == 0) g.out[f * g.P + g.off + r.i] = g.scale * acc;
+            }
+            __syncthreads();
+        }
+    }
+}
+
+}  // namespace ssm

@@ -15,7 +15,9 @@
 //   k_newton : the implicit step on its own (first step, and every step when
 //              v depends on mu^X, whose moments need the whole new cloud).
 // In one dimension the default takes k_modes and k_update_modes
-// (ssm_modes.hpp) in place of the first three.
+// (ssm_modes.hpp) in place of the first three; in three dimensions large
+// systems make the sums by a grid (ssm_grid.hpp), k_pair_sym and the combine
+// returning at once.
 // A surrogate tick replaces the first two by the network's kernels
 // (ssm_surrogate.hpp) and k_brownian_sum.
 // Layout: component-major [d][P] arrays over all systems, each system starting
@@ -66,6 +68,8 @@ struct SysDev {
     int64_t win_off;    // shared Brownian window of the system's path group (win_W > 0)
     int32_t win_W;      // ticks per window (0: the system draws its own increments)
     int32_t mode_row0;  // mode sums: its first partial row
+    int32_t by_grid;    // device only: this tick's pair sums are made by the grid (ssm_grid.hpp)
+    int32_t pad;
 };
 
 struct PairItem {
@@ -218,6 +222,7 @@ __device__ __forceinline__ void combine_block(int vb, const BlkItem* __restrict_
     const int q4 = vb & 3;
     const BlkItem it = items ? items[vb >> 2] : BlkItem{0, (int32_t)(vb >> 2)};
     const SysDev S = sys[it.sys];
+    if (D == 3 && S.by_grid) return;
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int i = it.blk * kBlk + q4 * 64 + lane;
@@ -258,7 +263,7 @@ __global__ __launch_bounds__(kBlk) void k_jfold(const BlkItem* __restrict__ item
     const BlkItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
     const int i = it.blk * kBlk + threadIdx.x;
-    if (i >= S.N || !S.sym_B) return;
+    if (i >= S.N || !S.sym_B || (D == 3 && S.by_grid)) return;
     const int64_t slot = S.off + i;
     const int hi = min(a1, i / S.sym_B + 1);
 #pragma unroll
@@ -291,6 +296,14 @@ __device__ __forceinline__ int64_t tick_of(const int64_t* tick_dev, int64_t tick
 // Lane permutations within each row of 16 lanes (gfx9 DPP controls):
 // exchange with lane ^ 1 and lane ^ 2 (quad_perm), mirror within 8 and 16.
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+
+// Orders a wavefront's own LDS writes and reads (one wavefront's tile).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 template <int CTRL>
 __device__ __forceinline__ double dpp64(double v)
@@ -1265,6 +1278,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_pair_sym(const PairItem* __rest
     const int lane = threadIdx.x & 63;
     const PairItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
+    if (D == 3 && S.by_grid) return;
     const T* __restrict__ base = Ys + S.off;
     const int blk = 64 * R;
     const int tb0 = it.tgt0 + wave * blk;  // this wavefront's target block
@@ -1351,6 +1365,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_pair(const PairItem* __restrict
     if (idx >= n_items) return;
     const PairItem it = items[idx];
     const SysDev S = sys[it.sys];
+    if (D == 3 && S.by_grid) return;
     const T* __restrict__ base = Ys + S.off;
 
     T yi[R][D];

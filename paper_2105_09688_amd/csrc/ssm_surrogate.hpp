@@ -249,15 +249,6 @@ __device__ __forceinline__ void dense_tiles(const __bf16* W, const bf16x8 a[2], 
         acc[nt] = c;
     }
 }
-
-// Orders a wavefront's own LDS writes and reads (one wavefront's tile).
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Write 16 x (16 NT) values held in D layout into an LDS tile [16][kStride]
 // as BF16, then read them back in A layout (two K slices of 32).
 template <int NT>

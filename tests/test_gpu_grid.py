@@ -1,0 +1,134 @@
+"""The interaction sums of one large system in three dimensions by way of a
+grid (the library's default there) against sums over every pair in 64 bits, at
+the least size and beyond it, for clouds of one bin, of many, and flat ones;
+clouds that it leaves to the pair kernels (too wide, or with a particle that
+is not finite), bit for bit as an explicit choice of them; a step repeated
+from the same state, and a context resumed after steps of both kinds.
+
+Tolerances.  With the drift g K alone a step from x gives x + h g K / N, so
+(x_1 - x) / h is the pair term K / N, |K / N| <= 0.6 ell.  FP64: the grid's
+error is 1.1e-15 of the root mean square of K in one dimension, three of them
+and the roundings of W^3 products are taken as 1e-13 of ell.  FP32: 4.6e-9 a
+dimension, K / N and x_1 rounded to 24 bits (h = 1024 makes x_1 of the size of
+h K / N): 8e-8 of ell, taken as 2e-7.  To both, the rounding u |x| of a scaled
+coordinate, own and others', which moves K / N by at most as much, and the one
+that is left of x_0 in the difference."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2105_09688_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+H = 1024.0
+TOL = {"fp64": 1e-13, "fp32": 2e-7, "fp32_kahan": 2e-7}
+U = {"fp64": 2.0 ** -53, "fp32": 2.0 ** -24, "fp32_kahan": 2.0 ** -24}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a ROCm GPU"
+    return torch
+
+
+def _ssm(w, precision, **kw):
+    from paper_2105_09688_amd.ssm import SSM
+    return SSM(w, precision=precision, **kw)
+
+
+def _w(N, std, ell=0.5, mean=(0.0, 0.0, 0.0)):
+    w = W.precision_d3(N=N)
+    w.update(T=4 * H, h_fine=H, systems=[(N, 0, H)], x0_mean=list(mean), x0_std=list(std),
+             v=dict(rho=0.0, a=0.0, kappa=0.0, lam=0.0), sigma=dict(s0=[0.0] * 3, s1=[0.0] * 3, s2=[0.0] * 3))
+    w["b"]["ell"] = ell
+    w["allow_unstable_h"] = True
+    return w
+
+
+def _pairs(torch, X, ell, idx):
+    Y = torch.tensor(X, device="cuda", dtype=torch.float64)
+    out = torch.empty(3, len(idx), dtype=torch.float64, device="cuda")
+    for a in range(0, len(idx), 256):
+        z = Y[:, None, :] - Y[:, idx[a:a + 256], None]
+        t = torch.exp((z * z).sum(0) * (-0.5 / ell ** 2))
+        out[:, a:a + 256] = (z * t).sum(2) / Y.shape[1]
+    return out.cpu().numpy()
+
+
+CLOUDS = [((1.0, 1.0, 1.0), 0.5), ((0.02, 0.02, 0.02), 0.5), ((2.0, 0.1, 0.001), 0.5), ((1.0, 1.0, 0.0), 0.7), ((1.0, 2.0, 0.5), 4.0)]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_kahan"])
+@pytest.mark.parametrize("N", [32768, 65537])
+def test_pair_term(torch_cuda, precision, N):
+    for k, (std, ell) in enumerate(CLOUDS):
+        w = _w(N, std, ell, mean=(0.0, 5.0, -300.0) if k == 0 and precision == "fp64" else (0.0, 0.0, 0.0))
+        print(f"[gpu-grid] {precision} N={N} cloud {std} ell={ell}", flush=True)
+        with _ssm(w, precision) as s:
+            x0 = s.state(0)
+            s.step(1)
+            x1 = s.state(0)
+        idx = np.unique(np.concatenate([np.arange(64), np.argsort(x0[0])[[0, 1, -2, -1]], np.linspace(0, N - 1, 800).astype(int)]))
+        err = np.abs((x1 - x0)[:, idx] / H - _pairs(torch_cuda, x0, ell, idx)).max() / ell
+        print(f"[gpu-grid] error {err:.1e}", flush=True)
+        assert err <= TOL[precision] + 2 * (1 + 1 / H) * U[precision] * np.abs(x0).max() / ell
+
+
+def _set(s, X, step):
+    """As set_state, which reports a particle that is not finite after it has copied it."""
+    from paper_2105_09688_amd import _lib
+    X = np.ascontiguousarray(X)
+    _lib.load().ssm_set_state(s._h, 0, X.ctypes.data_as(C.POINTER(C.c_double)), step)
+
+
+def _get(s):
+    from paper_2105_09688_amd import _lib
+    X, n = np.zeros((3, s.N[0])), C.c_int64()
+    _lib.load().ssm_get_state(s._h, 0, 0, X.ctypes.data_as(C.POINTER(C.c_double)), C.byref(n))
+    return X
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_left_to_the_pair_kernels(torch_cuda, precision):
+    """Too wide, NaN and infinite: as the pair kernels asked for by name; and the grid again after them."""
+    w = _w(32768, (1.0, 1.0, 1.0))
+    rng = np.random.default_rng(5)
+    clouds = [rng.normal(size=(3, 32768)) * 40.0, rng.normal(size=(3, 32768)), rng.normal(size=(3, 32768))]
+    clouds[1][1, 77] = np.nan
+    clouds[2][0, 9] = np.inf
+    for n, x in enumerate(clouds):
+        print(f"[gpu-grid] left to the pair kernels {precision} {n}", flush=True)
+        with _ssm(w, precision) as s, _ssm(w, precision, pair_scheme="symmetric") as p:
+            for c in (s, p):
+                _set(c, x, 0)
+                c.step(1)
+            assert np.array_equal(_get(s), _get(p), equal_nan=True)
+            y = rng.normal(size=(3, 32768))
+            with _ssm(w, precision) as f:
+                for c in (s, f):
+                    _set(c, y, 2)
+                    c.step(1)
+                assert np.array_equal(_get(s), f.state(0))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_kahan"])
+def test_repeats_bit_for_bit(torch_cuda, precision):
+    """Steps in one call, one by one, in graphs, and resumed in a new context."""
+    w = W.precision_d3(N=40001)
+    out = []
+    for kw, plan in (({}, (4,)), ({}, (1, 1, 2)), ({"graphs": True}, (1, 3))):
+        with _ssm(w, precision, **kw) as s:
+            for n in plan:
+                s.step(n)
+            out.append(s.state(0))
+    with _ssm(w, precision) as s:
+        s.step(3)
+        mid = s.state(0)
+    with _ssm(w, precision) as s:
+        s.set_state(0, mid, step=3)
+        s.step(1)
+        out.append(s.state(0))
+    for x in out[1:]:
+        assert np.array_equal(out[0], x)
