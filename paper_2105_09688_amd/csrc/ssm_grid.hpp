@@ -37,7 +37,7 @@ namespace ssm {
 constexpr int kGridCell = 8;     // nodes of a bin along each axis
 constexpr int kGridAxis = 128;   // first nodes along an axis at most: 16 bins
 constexpr int kGridBins = (kGridAxis / kGridCell) * (kGridAxis / kGridCell) * (kGridAxis / kGridCell);
-constexpr int kGridTab = 144;    // offsets of the convolution tables: more than kGridAxis + W
+constexpr int kGridTab = 176;    // offsets of the convolution tables: kGridAxis + W - 1, rounded up to whole products
 constexpr int kGridRange = 256;  // blocks of k_grid_range at most
 constexpr int kGridPer = 4;      // particles per thread of k_grid_bin and k_grid_scatter
 constexpr double kGridAlpha = 0.69314718055994530942;  // a = ln 2
@@ -471,80 +471,92 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
 
 // ---------------------------------------------------------------------------
 // k_grid_conv: one axis, the slowest of its input, which becomes the fastest
-// of its output; three launches come back to the grid's own order.  A thread
-// makes 4 outputs along the axis for one line; table values are wave-uniform.
+// of its output; three launches come back to the grid's own order.
 //   pass 0: grid -> A = {t, t'}     pass 1: A -> B = {tt, tt', t't}
 //   pass 2: B -> A = {t't t, t t' t, t t t'}, the three components' fields
+// A pass is the product [lines x n] [n x n] with the Toeplitz matrix t(a - b),
+// so it runs on the FP64 matrix instruction: a wavefront makes 16 lines x 32
+// outputs, its table operands from LDS.  The wait for the input, four products
+// of 4 nodes ahead, is what is left of its time.  On the vector units (4
+// outputs a thread) the three passes took 54 us at 65^3 nodes and 87 us at
+// 95^3, CONV_MEASURED.
 // Pass 1 also clears the grid and the bins' counts for the next tick.
 // ---------------------------------------------------------------------------
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 template <int PASS>
 __global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
 {
-    constexpr int R = 4, U = 4, NIN = PASS + 1, NOUT = PASS == 0 ? 2 : 3;
+    constexpr int NIN = PASS + 1, NOUT = PASS == 0 ? 2 : 3, NT = 2, U = 4;
+    __shared__ double tab[4 * kGridTab];
     const GridDom d = *g.dom;
     if (!d.use) return;
+    for (int q = threadIdx.x; q < 4 * kGridTab; q += kBlk) tab[q] = g.tab[q];
+    __syncthreads();
     const int n = d.n[PASS], inner = d.n[(PASS + 1) % 3] * d.n[(PASS + 2) % 3];
     const double* __restrict__ in = PASS == 1 ? g.A : g.B;
     const unsigned long long* __restrict__ raw = g.grid;
     double* __restrict__ out = PASS == 1 ? g.B : g.A;
     const double unit = ldexp(1.0, -g.qb);
-    const int lines = (inner + kBlk - 1) / kBlk, work = lines * ((n + R - 1) / R);
-    for (int it = blockIdx.x; it < work; it += gridDim.x) {
-        const int a0 = it / lines * R;
-        const int q = it % lines * kBlk + threadIdx.x;
-        const int qc = min(q, inner - 1);
-        const double* __restrict__ t = g.tab + kGridTab + a0;
-        const double* __restrict__ td = t + 2 * kGridTab;
-        double acc[NOUT][R];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int col = lane & 15, kk = lane >> 4;
+    const int qt = (inner + 15) / 16, work = qt * ((n + 16 * NT - 1) / (16 * NT));
+    for (int it = blockIdx.x * (kBlk / 64) + wave; it < work; it += gridDim.x * (kBlk / 64)) {
+        const int a0 = it / qt * (16 * NT), q0 = it % qt * 16;
+        const int qc = min(q0 + col, inner - 1);
+        const double* t = tab + kGridTab + a0 + col - kk;
+        f64x4 acc[NOUT][NT];
 #pragma unroll
         for (int o = 0; o < NOUT; ++o)
 #pragma unroll
-            for (int r = 0; r < R; ++r) acc[o][r] = 0.0;
-        auto load = [&](int f, int b) -> double {
-            const int64_t at = (int64_t)b * inner + qc;
-            if constexpr (PASS == 0) return (double)(long long)raw[at];
-            else return in[f * nodes + at];
-        };
-        auto add = [&](const double (&x)[NIN], int b) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const double tv = t[r - b], dv = td[r - b];
-                if constexpr (PASS == 0) {
-                    acc[0][r] = fma(tv, x[0], acc[0][r]);
-                    acc[1][r] = fma(dv, x[0], acc[1][r]);
-                } else if constexpr (PASS == 1) {
-                    acc[0][r] = fma(tv, x[0], acc[0][r]);
-                    acc[1][r] = fma(dv, x[0], acc[1][r]);
-                    acc[2][r] = fma(tv, x[1], acc[2][r]);
-                } else {
-                    acc[0][r] = fma(tv, x[2], acc[0][r]);
-                    acc[1][r] = fma(tv, x[1], acc[1][r]);
-                    acc[2][r] = fma(dv, x[0], acc[2][r]);
-                }
-            }
-        };
-        int b = 0;
-        for (; b + U <= n; b += U) {
+            for (int c = 0; c < NT; ++c) acc[o][c] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+        for (int b = 0; b < n; b += 4 * U) {
             double x[U][NIN];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < U; ++u) {
+                const int k = b + 4 * u + kk;
+                const int64_t at = (int64_t)min(k, n - 1) * inner + qc;
 #pragma unroll
-                for (int f = 0; f < NIN; ++f) x[u][f] = load(f, b + u);
+                for (int f = 0; f < NIN; ++f) {
+                    if constexpr (PASS == 0) x[u][f] = (double)(long long)raw[at];
+                    else x[u][f] = in[f * nodes + at];
+                }
+            }
 #pragma unroll
-            for (int u = 0; u < U; ++u) add(x[u], b + u);
+            for (int u = 0; u < U; ++u) {
+                const bool live = b + 4 * u + kk < n;
+#pragma unroll
+                for (int f = 0; f < NIN; ++f) x[u][f] = live ? x[u][f] : 0.0;
+#pragma unroll
+                for (int c = 0; c < NT; ++c) {
+                    const double tv = t[16 * c - b - 4 * u], dv = t[2 * kGridTab + 16 * c - b - 4 * u];
+                    auto mul = [&](f64x4& z, double xv, double bv) { z = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, bv, z, 0, 0, 0); };
+                    if constexpr (PASS == 0) {
+                        mul(acc[0][c], x[u][0], tv);
+                        mul(acc[1][c], x[u][0], dv);
+                    } else if constexpr (PASS == 1) {
+                        mul(acc[0][c], x[u][0], tv);
+                        mul(acc[1][c], x[u][0], dv);
+                        mul(acc[2][c], x[u][1], tv);
+                    } else {
+                        mul(acc[0][c], x[u][2], tv);
+                        mul(acc[1][c], x[u][1], tv);
+                        mul(acc[2][c], x[u][0], dv);
+                    }
+                }
+            }
         }
-        for (; b < n; ++b) {
-            double x[NIN];
+        // value r of a lane: line 4 r + lane / 16, output lane % 16
 #pragma unroll
-            for (int f = 0; f < NIN; ++f) x[f] = load(f, b);
-            add(x, b);
-        }
-        if (q < inner)
+        for (int o = 0; o < NOUT; ++o)
 #pragma unroll
-            for (int o = 0; o < NOUT; ++o)
+            for (int c = 0; c < NT; ++c)
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if (a0 + r < n) out[o * nodes + (int64_t)q * n + a0 + r] = PASS == 0 ? acc[o][r] * unit : acc[o][r];
+                for (int r = 0; r < 4; ++r) {
+                    const int q = q0 + 4 * r + kk, a = a0 + 16 * c + col;
+                    if (q < inner && a < n) out[o * nodes + (int64_t)q * n + a] = PASS == 0 ? acc[o][c][r] * unit : acc[o][c][r];
+                }
     }
     if constexpr (PASS == 1) {
         const int64_t used = (int64_t)n * inner;
