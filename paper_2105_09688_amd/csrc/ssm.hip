@@ -614,8 +614,8 @@ static ssm_status launch_grid(ssm_ctx* c)
     const int64_t chunks = g.N / Win::chunk + kGridBins;  // at most
     // workgroups as many as a compute unit's LDS holds at once
     const int cus = device_cus();
-    const dim3 spread((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 4 : 2) * cus));
-    const dim3 gather((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 2 : 1) * cus));
+    const dim3 spread((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 3 : 2) * cus));
+    const dim3 gather((unsigned)std::min<int64_t>(chunks, cus));
     const dim3 conv((unsigned)(4 * cus));
     hipLaunchKernelGGL(k_grid_range<T>, dim3((unsigned)nrange), dim3(kBlk), 0, c->stream, g, Ys);
     hipLaunchKernelGGL(k_grid_bin<T>, per, dim3(kBlk), 0, c->stream, g, nrange, Ys);
@@ -624,7 +624,8 @@ static ssm_status launch_grid(ssm_ctx* c)
     hipLaunchKernelGGL(k_grid_conv<0>, conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
     hipLaunchKernelGGL(k_grid_conv<1>, conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
     hipLaunchKernelGGL(k_grid_conv<2>, conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
-    hipLaunchKernelGGL(k_grid_gather<T>, gather, dim3(Win::gather_wg), 0, c->stream, g, Win::nodes);
+    if constexpr (Win::W == 8) hipLaunchKernelGGL(k_grid_gather8, gather, dim3(Win::gather_wg), 0, c->stream, g, Win::nodes);
+    else hipLaunchKernelGGL(k_grid_gather14, gather, dim3(Win::gather_wg), 0, c->stream, g, Win::nodes);
     HIP_TRY(hipGetLastError());
     return SSM_OK;
 }
@@ -640,7 +641,7 @@ static bool grid_setup(ssm_ctx* c)
     g.P = c->P;
     g.off = c->one.off;
     g.N = (int32_t)N;
-    g.qb = std::min(50, 62 - (int)std::ceil(std::log2((double)N)));
+    g.qb = std::min(Win::unit, 62 - (int)std::ceil(std::log2((double)N)));
     g.scale = c->one.pair_scale;
     g.out = c->pairsum;
     g.sys = c->dsys;

@@ -52,9 +52,10 @@ struct GridWin<float> {
     static constexpr int W = 8;
     static constexpr double step = 0.28, beta = 2.55 * 8;
     static constexpr int group = 8;    // lanes per particle of k_grid_gather
-    static constexpr int chunk = 256;  // particles of a bin that a workgroup takes at a time
-    static constexpr int wg = 256, gather_wg = 512;
+    static constexpr int chunk = 512;  // particles of a bin that a workgroup takes at a time
+    static constexpr int wg = 512, gather_wg = 1024;
     static constexpr int64_t nodes = 1 << 20;
+    static constexpr int unit = 42;    // node sums in units of 2^-unit at most
 };
 template <>
 struct GridWin<double> {
@@ -64,6 +65,7 @@ struct GridWin<double> {
     static constexpr int chunk = 128;
     static constexpr int wg = 512, gather_wg = 1024;
     static constexpr int64_t nodes = 1 << 21;
+    static constexpr int unit = 50;
 };
 
 // The tick's grid: lowest coordinates, nodes and bins along each axis, chunks.
@@ -76,7 +78,8 @@ struct GridDom {
 
 struct GridRec {      // a particle in its bin's order
     double v[3];      // (s - lo) / step
-    int64_t i;
+    int32_t i;
+    int32_t cell;     // its first node's place in the bin: x | y << 4 | z << 8
 };
 
 struct GridChunk {
@@ -360,6 +363,9 @@ __global__ __launch_bounds__(kBlk) void k_grid_scatter(GridArgs g, const T* __re
 #pragma unroll
         for (int a = 0; a < 3; ++a) r.v[a] = ((double)Ys[a * g.P + g.off + i] - d.lo[a]) * (1.0 / GridWin<T>::step);
         r.i = i;
+        r.cell = 0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) r.cell |= ((int)ceil(r.v[a]) % kGridCell) << (4 * a);
         g.rec[start[k.x] + k.y] = r;
     }
 }
@@ -410,7 +416,7 @@ __device__ __forceinline__ void grid_weights(const GridRec* __restrict__ rec, in
 template <typename T>
 __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
 {
-    constexpr int W = GridWin<T>::W, WG = GridWin<T>::wg, PB = W == 8 ? 8 : 2, R = (W * W + 63) / 64;
+    constexpr int W = GridWin<T>::W, WG = GridWin<T>::wg, PB = W == 8 ? 8 : 2, Z = W == 8 ? 8 : 16, R = (W * Z + 63) / 64;
     typedef GridTile<T> Tile;
     constexpr int E = Tile::E;
     __shared__ unsigned long long tile[Tile::size];
@@ -418,8 +424,11 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const GridDom d = *g.dom;
     if (!d.use) return;
-    const double magic = ldexp(1.5, 52 - g.qb);
-    const unsigned long long mbits = (unsigned long long)__double_as_longlong(magic);
+    // at W = 8 the added bits stay in: a power of two, they are above bit 51, and
+    // a chunk's sum of a node is below 2^51 (GridWin::unit)
+    const double magic = ldexp(W == 8 ? 1.0 : 1.5, 52 - g.qb);
+    const unsigned long long mbits = W == 8 ? 0 : (unsigned long long)__double_as_longlong(magic);
+    constexpr unsigned long long keep = W == 8 ? (1ull << 52) - 1 : ~0ull;
     double* w = wts[wave];
     for (int ch = blockIdx.x; ch < d.nchunks; ch += gridDim.x) {
         const GridChunk c = g.chunks[ch];
@@ -429,18 +438,18 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
         for (int p0 = wave * PB; p0 < c.len; p0 += WG / 64 * PB) {
             const GridRec* __restrict__ rec = g.rec + c.start + p0;
             const int n = min(PB, c.len - p0);
+            const int cells = rec[min(lane, n - 1)].cell;
             grid_weights<T, 3 * W>(rec, n, w, lane, 64);
             wave_lds_fence();
             for (int p = 0; p < n; ++p) {
-                const int x0 = (int)ceil(rec[p].v[0]) - bx * kGridCell;
-                const int y0 = (int)ceil(rec[p].v[1]) - by * kGridCell;
-                const int z0 = (int)ceil(rec[p].v[2]) - bz * kGridCell;
+                const int cell = __builtin_amdgcn_readlane(cells, p);
+                const int x0 = cell & 15, y0 = (cell >> 4) & 15, z0 = cell >> 8;
                 double wyz[R];
                 int at[R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const int q = lane + 64 * r, y = q / W, z = q - y * W;
-                    const bool in = q < W * W;
+                    const int y = lane / Z + 64 / Z * r, z = lane % Z;
+                    const bool in = y < W && z < W;
                     wyz[r] = in ? w[p * 3 * W + W + y] * w[p * 3 * W + 2 * W + z] : 0.0;
                     at[r] = Tile::at(x0, y0 + (in ? y : 0), z0 + (in ? z : 0));
                 }
@@ -449,7 +458,7 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
                     const double wx = w[p * 3 * W + x];
 #pragma unroll
                     for (int r = 0; r < R; ++r)
-                        if (64 * (r + 1) <= W * W || lane + 64 * r < W * W)
+                        if (Z == W || (lane / Z + 64 / Z * r < W && lane % Z < W))
                             atomicAdd(&tile[at[r] + x * E * Tile::pitch],
                                       (unsigned long long)__double_as_longlong(fma(wx, wyz[r], magic)) - mbits);
                 }
@@ -459,7 +468,7 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
         __syncthreads();
         for (int q = threadIdx.x; q < E * E * E; q += WG) {
             const int x = q / (E * E), y = q / E % E, z = q % E;
-            const unsigned long long v = tile[Tile::at(x, y, z)];
+            const unsigned long long v = tile[Tile::at(x, y, z)] & keep;
             if (v) {  // nodes outside the grid hold nothing
                 const int64_t node = ((int64_t)(bx * kGridCell + x) * d.n[1] + by * kGridCell + y) * d.n[2] + bz * kGridCell + z;
                 atomicAdd(&g.grid[node], v);
@@ -479,7 +488,7 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
 // outputs, its table operands from LDS.  The wait for the input, four products
 // of 4 nodes ahead, is what is left of its time.  On the vector units (4
 // outputs a thread) the three passes took 54 us at 65^3 nodes and 87 us at
-// 95^3, CONV_MEASURED.
+// 95^3, on it 24 and 33 us.
 // Pass 1 also clears the grid and the bins' counts for the next tick.
 // ---------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -567,58 +576,183 @@ __global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
 }
 
 // ---------------------------------------------------------------------------
-// k_grid_gather: the pair term of a chunk's particles from their bin's nodes.
-// The nodes of one field at a time in LDS; `group` lanes per particle, one
-// for each z.  Bound by LDS reads: 3 W^2 a lane.
+// k_grid_gather: the pair term of a chunk's particles from the three fields at
+// their bin's nodes, `group` lanes per particle, one for each z.  The nodes
+// are staged through LDS, the next ones read into registers meanwhile.
+//
+// W = 8: all fields at once, {F0, F1} of a node and {F2(x), F2(x + 1)} side by
+// side.  A particle's 16 lanes are 8 z of two neighbouring rows, and rows of
+// 16 nodes, odd ones turned by 8, put them on all 64 banks once; they are the
+// lanes that a 16-byte LDS read serves together (of a half wavefront the quads
+// 0, 3, 5, 6 and 1, 2, 4, 7).  N = 2^18: GATHER8_MEASURED
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(GridWin<T>::gather_wg) void k_grid_gather(GridArgs g, int64_t nodes)
+template <int W, int WG, int E>
+struct GridNodes {  // which nodes of the grid a thread stages
+    static constexpr int per = (E * E * E + WG - 1) / WG;
+    int at[per];    // -1: outside the grid
+    __device__ __forceinline__ void set(const GridDom& d, int bin)
+    {
+        const int ox = bin / (d.nb[1] * d.nb[2]) * kGridCell, oy = bin / d.nb[2] % d.nb[1] * kGridCell, oz = bin % d.nb[2] * kGridCell;
+#pragma unroll
+        for (int u = 0; u < per; ++u) {
+            const int q = threadIdx.x + u * WG, x = q / (E * E), y = q / E % E, z = q % E;
+            const bool in = ox + x < d.n[0] && oy + y < d.n[1] && oz + z < d.n[2] && q < E * E * E;
+            at[u] = in ? ((ox + x) * d.n[1] + oy + y) * d.n[2] + oz + z : -1;
+        }
+    }
+    __device__ __forceinline__ double load(const double* __restrict__ F, int u) const
+    {
+        const double v = F[max(at[u], 0)];
+        return at[u] < 0 ? 0.0 : v;
+    }
+};
+
+__global__ __launch_bounds__(GridWin<float>::gather_wg) void k_grid_gather8(GridArgs g, int64_t nodes)
 {
-    constexpr int W = GridWin<T>::W, WG = GridWin<T>::gather_wg, GR = GridWin<T>::group, C = GridWin<T>::chunk;
-    constexpr int WP = 3 * W + 1;
-    typedef GridTile<T> Tile;
-    constexpr int E = Tile::E;
-    __shared__ double tile[Tile::size];
-    __shared__ double wts[C * WP];
+    constexpr int W = 8, WG = GridWin<float>::gather_wg, E = kGridCell + W - 1, SP = 18, ROW = 16;
+    __shared__ double2 t01[E * E * ROW];
+    __shared__ double2 t2[E * E * ROW];
+    __shared__ double stage[WG / 64][4 * SP];
     const GridDom d = *g.dom;
-    if (!d.use) return;
+    if (!d.use || (int)blockIdx.x >= d.nchunks) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int quad = lane >> 2, odd = (quad >> 2) & 1;
+    const int z = (quad & 2) * 2 + (lane & 3), grp = (__popc(quad & 7) & 1) + 2 * (lane >> 5);
+    double* __restrict__ st = stage[wave] + grp * SP;
+    GridNodes<W, WG, E> nd;
+    double next[nd.per][3];
+    GridChunk c = g.chunks[blockIdx.x];
+    nd.set(d, c.bin);
+#pragma unroll
+    for (int u = 0; u < nd.per; ++u)
+#pragma unroll
+        for (int f = 0; f < 3; ++f) next[u][f] = nd.load(g.A + f * nodes, u);
+    for (int ch = blockIdx.x; ch < d.nchunks; ch += gridDim.x) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < nd.per; ++u) {
+            const int q = threadIdx.x + u * WG;
+            if (q < E * E * E) {
+                const int row = q / E, at = row * ROW + ((q - row * E) ^ ((row % E & 1) << 3));
+                t01[at] = make_double2(next[u][0], next[u][1]);
+                t2[at].x = next[u][2];
+                if (row >= E) t2[at - E * ROW].y = next[u][2];
+            }
+        }
+        __syncthreads();
+        const GridRec* __restrict__ rec = g.rec + c.start;
+        const int len = c.len;
+        if (ch + (int)gridDim.x < d.nchunks) {
+            c = g.chunks[ch + gridDim.x];
+            nd.set(d, c.bin);
+#pragma unroll
+            for (int u = 0; u < nd.per; ++u)
+#pragma unroll
+                for (int f = 0; f < 3; ++f) next[u][f] = nd.load(g.A + f * nodes, u);
+        }
+        for (int p0 = wave * 4; p0 < len; p0 += WG / 16) {
+            const GridRec r = rec[min(p0 + grp, len - 1)];
+            double wx[W], wy[W / 2];
+            wave_lds_fence();
+            const double vxy = odd ? r.v[1] : r.v[0];
+            st[odd ? W + (z & 1) * 4 + z / 2 : z] = grid_psi<float>(z, ceil(vxy) - vxy);  // wx, then wy: even ones, odd ones
+            const double wz = grid_psi<float>(z, ceil(r.v[2]) - r.v[2]);
+            const int y0 = ((r.cell >> 4) & 15) + odd;
+            const int base = ((r.cell & 15) * E + y0) * ROW + (((r.cell >> 8) + z) ^ ((y0 & 1) << 3));
+            wave_lds_fence();
+#pragma unroll
+            for (int m = 0; m < W; ++m) wx[m] = st[m];
+#pragma unroll
+            for (int m = 0; m < W / 2; ++m) wy[m] = st[W + 4 * odd + m];
+            double acc[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+            for (int x = 0; x < W; x += 2) {
+                double s[2][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
+#pragma unroll
+                for (int y = 0; y < W / 2; ++y) {
+                    const double2 a = t01[base + (x * E + 2 * y) * ROW], b = t01[base + ((x + 1) * E + 2 * y) * ROW],
+                                  e = t2[base + (x * E + 2 * y) * ROW];
+                    s[0][0] = fma(wy[y], a.x, s[0][0]);
+                    s[0][1] = fma(wy[y], a.y, s[0][1]);
+                    s[0][2] = fma(wy[y], e.x, s[0][2]);
+                    s[1][0] = fma(wy[y], b.x, s[1][0]);
+                    s[1][1] = fma(wy[y], b.y, s[1][1]);
+                    s[1][2] = fma(wy[y], e.y, s[1][2]);
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) acc[k] = fma(wx[x + 1], s[1][k], fma(wx[x], s[0][k], acc[k]));
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                acc[k] *= wz;
+                acc[k] += dpp64<kDppXor1>(acc[k]);
+                acc[k] += dpp64<kDppXor2>(acc[k]);
+                acc[k] += dpp64<kDppMirror>(acc[k]);  // the quad of the other four z
+                acc[k] += __shfl_xor(acc[k], 20);     // the other rows
+            }
+            if (!odd && z < 3 && p0 + grp < len)
+                g.out[z * g.P + g.off + r.i] = g.scale * (z == 0 ? acc[0] : z == 1 ? acc[1] : acc[2]);
+        }
+    }
+}
+
+// W = 14: a field at a time (three are more than the LDS holds); 14 of 16
+// lanes, whose rows of 14 nodes meet the banks evenly.  GATHER14_MEASURED
+__global__ __launch_bounds__(GridWin<double>::gather_wg) void k_grid_gather14(GridArgs g, int64_t nodes)
+{
+    typedef GridWin<double> Win;
+    constexpr int W = Win::W, WG = Win::gather_wg, GR = Win::group, WP = 3 * W + 1, E = kGridCell + W - 1;
+    __shared__ double tile[E * E * E];
+    __shared__ double wts[Win::chunk * WP];
+    const GridDom d = *g.dom;
+    if (!d.use || (int)blockIdx.x >= d.nchunks) return;
     const int z = threadIdx.x & (GR - 1), slot = threadIdx.x / GR;
     const int zc = min(z, W - 1);
+    GridNodes<W, WG, E> nd;
+    double next[nd.per];
+    nd.set(d, g.chunks[blockIdx.x].bin);
+#pragma unroll
+    for (int u = 0; u < nd.per; ++u) next[u] = nd.load(g.A, u);
     for (int ch = blockIdx.x; ch < d.nchunks; ch += gridDim.x) {
         const GridChunk c = g.chunks[ch];
-        const int ox = c.bin / (d.nb[1] * d.nb[2]) * kGridCell, oy = c.bin / d.nb[2] % d.nb[1] * kGridCell,
-                  oz = c.bin % d.nb[2] * kGridCell;
         const GridRec* __restrict__ rec = g.rec + c.start;
-        grid_weights<T, WP>(rec, c.len, wts, threadIdx.x, WG);
 #pragma unroll 1
         for (int f = 0; f < 3; ++f) {
-            const double* __restrict__ F = g.A + f * nodes;
-            for (int q = threadIdx.x; q < E * E * E; q += WG) {
-                const int x = q / (E * E), y = q / E % E, zz = q % E;
-                const bool in = ox + x < d.n[0] && oy + y < d.n[1] && oz + zz < d.n[2];
-                tile[Tile::at(x, y, zz)] = in ? F[((int64_t)(ox + x) * d.n[1] + oy + y) * d.n[2] + oz + zz] : 0.0;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < nd.per; ++u)
+                if (threadIdx.x + u * WG < E * E * E) tile[threadIdx.x + u * WG] = next[u];
+            const double* __restrict__ F = g.A + (f + 1) * nodes;
+            bool more = true;
+            if (f == 2) {
+                F = g.A;
+                more = ch + (int)gridDim.x < d.nchunks;
+                if (more) nd.set(d, g.chunks[ch + gridDim.x].bin);
             }
+            if (more)
+#pragma unroll
+                for (int u = 0; u < nd.per; ++u) next[u] = nd.load(F, u);
+            if (f == 0) grid_weights<double, WP>(rec, c.len, wts, threadIdx.x, WG);
             __syncthreads();
             for (int p = slot; p < c.len; p += WG / GR) {
                 const GridRec r = rec[p];
-                const int x0 = (int)ceil(r.v[0]) - ox, y0 = (int)ceil(r.v[1]) - oy, z0 = (int)ceil(r.v[2]) - oz + zc;
+                const int base = ((r.cell & 15) * E + ((r.cell >> 4) & 15)) * E + (r.cell >> 8) + zc;
                 const double* w = wts + p * WP;
                 double acc = 0.0;
 #pragma unroll 2
                 for (int x = 0; x < W; ++x) {
                     double s = 0.0;
 #pragma unroll
-                    for (int y = 0; y < W; ++y) s = fma(w[W + y], tile[Tile::at(x0 + x, y0 + y, z0)], s);
+                    for (int y = 0; y < W; ++y) s = fma(w[W + y], tile[base + (x * E + y) * E], s);
                     acc = fma(w[x], s, acc);
                 }
                 acc = z < W ? acc * w[2 * W + zc] : 0.0;
                 acc += dpp64<kDppXor1>(acc);
                 acc += dpp64<kDppXor2>(acc);
                 acc += dpp64<kDppHalfMirror>(acc);
-                if (GR == 16) acc += dpp64<kDppMirror>(acc);
+                acc += dpp64<kDppMirror>(acc);
                 if (z == 0) g.out[f * g.P + g.off + r.i] = g.scale * acc;
             }
-            __syncthreads();
         }
     }
 }
