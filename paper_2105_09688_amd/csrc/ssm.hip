@@ -333,7 +333,8 @@ struct ssm_ctx {
     double* mode_part = nullptr;    // [kModeVals / 16][mode_rows][16] (mode_at)
     double* mode_tot = nullptr;     // [n_sys][kModeVals] (mode_totals)
     float2* rng = nullptr;          // [nblk_tot] range of the scaled positions of each block
-    bool grid = false;              // d = 3: exact ticks by the grid where the cloud fits it (ssm_grid.hpp)
+    bool grid_ok = false;           // one large system in two or three dimensions
+    bool grid = false;              // exact ticks by the grid where the cloud fits it (ssm_grid.hpp)
     GridArgs ga{};
     void* grid_buf = nullptr;       // its buffers
     // persistent runs of small systems (ssm_small.hpp)
@@ -641,6 +642,7 @@ static bool grid_setup(ssm_ctx* c)
     g.P = c->P;
     g.off = c->one.off;
     g.N = (int32_t)N;
+    g.dim = c->d;
     g.qb = std::min(Win::unit, 62 - (int)std::ceil(std::log2((double)N)));
     g.scale = c->one.pair_scale;
     g.out = c->pairsum;
@@ -1500,10 +1502,14 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
                cfg->pair_scheme == 0 && cfg->jside_band_groups == 0;
     // one system in three dimensions by way of a grid, from the size on where
     // that is faster.  A tick, pair kernels against grid: FP32 N = 16384 93 and
-    // 145 us, 24000 162 and 149, 2^18 14.1 ms and 325 us; FP64 N = 16384 203 and
-    // 197 us, 24000 367 and 232, 50021 1450 and 265
-    c->grid = c->d == 3 && c->has_pair && !c->kpair && c->sys.size() == 1 && c->sys[0].N >= 24000 && cfg->targets_per_lane == 0 &&
-              cfg->sources_per_item == 0 && cfg->pair_scheme == 0 && cfg->jside_band_groups == 0;
+    // 145 us, 24000 162 and 149, 2^18 14.1 ms and 250 us; FP64 N = 16384 203 and
+    // 197 us, 24000 367 and 232, 50021 1450 and 230.  In two dimensions where
+    // the context has a surrogate, for its checks (N = 2^16: 614 us of pair
+    // kernels, 100 us); without one the pair kernels stay there, as the exact
+    // method that the surrogate's gain is held against
+    c->grid_ok = c->has_pair && !c->kpair && c->sys.size() == 1 && cfg->targets_per_lane == 0 && cfg->sources_per_item == 0 &&
+                 cfg->pair_scheme == 0 && cfg->jside_band_groups == 0 &&
+                 ((c->d == 3 && c->sys[0].N >= 24000) || (c->d == 2 && c->sys[0].N >= 32768));
     for (int attempt = 0; attempt < 2; ++attempt) {
         std::vector<int64_t> Ns;
         for (auto& S : c->sys) Ns.push_back(S.N);
@@ -1764,7 +1770,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     if (he == hipSuccess) he = hipMemsetAsync(c->ymean, 0, c->sys.size() * kMaxD * sizeof(double), c->stream);
     if (he == hipSuccess && c->small_ok && !c->solo) he = hipMemcpyAsync(c->dtiles, tiles.data(), tiles.size() * sizeof(SmallTile), hipMemcpyHostToDevice, c->stream);
     if (he == hipSuccess && c->small_ok && !c->solo) he = hipMemsetAsync(c->dbar, 0, c->sys.size() * kBarLine * sizeof(uint64_t), c->stream);
-    if (he == hipSuccess && c->grid) c->grid = c->prec == SSM_FP64 ? grid_setup<double>(c) : grid_setup<float>(c);
+    if (he == hipSuccess && c->grid_ok && c->d == 3) c->grid = c->prec == SSM_FP64 ? grid_setup<double>(c) : grid_setup<float>(c);
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);  // host vectors go out of scope
     if (he != hipSuccess) { std::string m = hipGetErrorString(he); free_ctx(c); return fail(SSM_ERR_HIP, "upload: " + m); }
 
@@ -2380,6 +2386,11 @@ static ssm_status ensure_surrogate_buffers(ssm_ctx* c)
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
     (void)hipFree(dfq);
     if (he != hipSuccess) return fail(SSM_ERR_HIP, std::string("rff frequencies: ") + hipGetErrorString(he));
+    if (c->grid_ok && !c->grid && c->d == 2) {
+        c->grid = c->prec == SSM_FP64 ? grid_setup<double>(c) : grid_setup<float>(c);
+        drop_graphs(c);  // their ticks do not have the grid's launches
+        HIP_TRY(hipStreamSynchronize(c->stream));
+    }
     ALLOC2(c->dmlp, sizeof(MlpPacked));
 #undef ALLOC2
     return SSM_OK;

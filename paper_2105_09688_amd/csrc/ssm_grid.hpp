@@ -1,4 +1,4 @@
-// ssm_grid.hpp -- the interaction sums of one large system in three
+// ssm_grid.hpp -- the interaction sums of one large system in three (or two)
 // dimensions, by way of a grid, in O(N) operations.
 //
 // In the scaled coordinates s (Ys) the pair term of particle i is
@@ -16,6 +16,9 @@
 // e^(beta (sqrt(1 - z^2) - 1)), |z| <= 1 (Barnett, Magland, af Klinteberg, "A
 // parallel nonuniform fast Fourier transform library based on an exponential
 // of semicircle kernel", SIAM J. Sci. Comput. 41, 2019).
+//
+// Two dimensions are taken as a third coordinate of 0: that makes 8 times (FP64
+// 14 times) the nodes a particle needs, on sums that are bound by their launches.
 //
 // All of it is in double precision in every precision mode.  Node values are
 // added up as 64-bit integers in units of 2^-qb: integer sums do not depend on
@@ -89,6 +92,7 @@ struct GridChunk {
 struct GridArgs {
     int64_t P, off;                 // component stride and first slot of the system
     int32_t N, qb;                  // particles; unit 2^-qb of the node sums
+    int32_t dim;                    // 3, or 2: the third coordinate is 0
     double scale;                   // pair_scale
     double* range;                  // [kGridRange][6]
     GridDom* dom;
@@ -206,7 +210,7 @@ __global__ __launch_bounds__(kBlk) void k_grid_range(GridArgs g, const T* __rest
     for (int i = blockIdx.x * kBlk + threadIdx.x; i < g.N; i += gridDim.x * kBlk)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const double x = (double)Ys[k * g.P + g.off + i];
+            const double x = k < g.dim ? (double)Ys[k * g.P + g.off + i] : 0.0;
             const bool ok = fabs(x) < INFINITY;
             m[k] = fmin(m[k], ok ? x : -INFINITY);
             m[k + 3] = fmin(m[k + 3], ok ? -x : -INFINITY);
@@ -262,7 +266,7 @@ __global__ __launch_bounds__(kBlk) void k_grid_bin(GridArgs g, int nrange, const
 #pragma unroll
     for (int u = 0; u < kGridPer; ++u)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) s[u][k] = (double)Ys[k * g.P + g.off + min(i0 + u * kBlk, g.N - 1)];
+        for (int k = 0; k < 3; ++k) s[u][k] = k < g.dim ? (double)Ys[k * g.P + g.off + min(i0 + u * kBlk, g.N - 1)] : 0.0;
     const GridDom d = grid_domain<T>(g, nrange, part);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *g.dom = d;
@@ -361,7 +365,7 @@ __global__ __launch_bounds__(kBlk) void k_grid_scatter(GridArgs g, const T* __re
         const int2 k = g.key[i];
         GridRec r;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) r.v[a] = ((double)Ys[a * g.P + g.off + i] - d.lo[a]) * (1.0 / GridWin<T>::step);
+        for (int a = 0; a < 3; ++a) r.v[a] = a < g.dim ? ((double)Ys[a * g.P + g.off + i] - d.lo[a]) * (1.0 / GridWin<T>::step) : 0.0;
         r.i = i;
         r.cell = 0;
 #pragma unroll
@@ -584,7 +588,9 @@ __global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
 // side.  A particle's 16 lanes are 8 z of two neighbouring rows, and rows of
 // 16 nodes, odd ones turned by 8, put them on all 64 banks once; they are the
 // lanes that a 16-byte LDS read serves together (of a half wavefront the quads
-// 0, 3, 5, 6 and 1, 2, 4, 7).  N = 2^18: GATHER8_MEASURED
+// 0, 3, 5, 6 and 1, 2, 4, 7).  N = 2^18: 140 us before (a
+// field at a time in single doubles, 8 lanes a particle: 43 % of the LDS cycles
+// were conflicts), 82 us
 // ---------------------------------------------------------------------------
 template <int W, int WG, int E>
 struct GridNodes {  // which nodes of the grid a thread stages
@@ -690,14 +696,16 @@ __global__ __launch_bounds__(GridWin<float>::gather_wg) void k_grid_gather8(Grid
                 acc[k] += dpp64<kDppMirror>(acc[k]);  // the quad of the other four z
                 acc[k] += __shfl_xor(acc[k], 20);     // the other rows
             }
-            if (!odd && z < 3 && p0 + grp < len)
+            if (!odd && z < g.dim && p0 + grp < len)
                 g.out[z * g.P + g.off + r.i] = g.scale * (z == 0 ? acc[0] : z == 1 ? acc[1] : acc[2]);
         }
     }
 }
 
 // W = 14: a field at a time (three are more than the LDS holds); 14 of 16
-// lanes, whose rows of 14 nodes meet the banks evenly.  GATHER14_MEASURED
+// lanes, whose rows of 14 nodes meet the banks evenly.  N = 50021: 130 us
+// of a 230 us tick, half of it LDS reads (two fields side by side as above
+// halved those and took longer, 147 us: no room to read ahead)
 __global__ __launch_bounds__(GridWin<double>::gather_wg) void k_grid_gather14(GridArgs g, int64_t nodes)
 {
     typedef GridWin<double> Win;
@@ -717,14 +725,14 @@ __global__ __launch_bounds__(GridWin<double>::gather_wg) void k_grid_gather14(Gr
         const GridChunk c = g.chunks[ch];
         const GridRec* __restrict__ rec = g.rec + c.start;
 #pragma unroll 1
-        for (int f = 0; f < 3; ++f) {
+        for (int f = 0; f < g.dim; ++f) {
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < nd.per; ++u)
                 if (threadIdx.x + u * WG < E * E * E) tile[threadIdx.x + u * WG] = next[u];
             const double* __restrict__ F = g.A + (f + 1) * nodes;
             bool more = true;
-            if (f == 2) {
+            if (f == g.dim - 1) {
                 F = g.A;
                 more = ch + (int)gridDim.x < d.nchunks;
                 if (more) nd.set(d, g.chunks[ch + gridDim.x].bin);

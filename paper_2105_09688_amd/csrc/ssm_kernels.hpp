@@ -222,7 +222,7 @@ __device__ __forceinline__ void combine_block(int vb, const BlkItem* __restrict_
     const int q4 = vb & 3;
     const BlkItem it = items ? items[vb >> 2] : BlkItem{0, (int32_t)(vb >> 2)};
     const SysDev S = sys[it.sys];
-    if (D == 3 && S.by_grid) return;
+    if ((D == 2 || D == 3) && S.by_grid) return;
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int i = it.blk * kBlk + q4 * 64 + lane;
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(kBlk) void k_jfold(const BlkItem* __restrict__ item
     const BlkItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
     const int i = it.blk * kBlk + threadIdx.x;
-    if (i >= S.N || !S.sym_B || (D == 3 && S.by_grid)) return;
+    if (i >= S.N || !S.sym_B || ((D == 2 || D == 3) && S.by_grid)) return;
     const int64_t slot = S.off + i;
     const int hi = min(a1, i / S.sym_B + 1);
 #pragma unroll
@@ -1278,7 +1278,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_pair_sym(const PairItem* __rest
     const int lane = threadIdx.x & 63;
     const PairItem it = items[blockIdx.x];
     const SysDev S = sys[it.sys];
-    if (D == 3 && S.by_grid) return;
+    if ((D == 2 || D == 3) && S.by_grid) return;
     const T* __restrict__ base = Ys + S.off;
     const int blk = 64 * R;
     const int tb0 = it.tgt0 + wave * blk;  // this wavefront's target block
@@ -1365,7 +1365,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_pair(const PairItem* __restrict
     if (idx >= n_items) return;
     const PairItem it = items[idx];
     const SysDev S = sys[it.sys];
-    if (D == 3 && S.by_grid) return;
+    if ((D == 2 || D == 3) && S.by_grid) return;
     const T* __restrict__ base = Ys + S.off;
 
     T yi[R][D];

@@ -1,5 +1,5 @@
 """The interaction sums of one large system in three dimensions by way of a
-grid (the library's default there) against sums over every pair in 64 bits, at
+grid (the library's default there, and in two dimensions with a surrogate) against sums over every pair in 64 bits, at
 the least size and beyond it, for clouds of one bin, of many, and flat ones;
 clouds that it leaves to the pair kernels (too wide, or with a particle that
 is not finite), bit for bit as an explicit choice of them; a step repeated
@@ -49,7 +49,7 @@ def _w(N, std, ell=0.5, mean=(0.0, 0.0, 0.0)):
 
 def _pairs(torch, X, ell, idx):
     Y = torch.tensor(X, device="cuda", dtype=torch.float64)
-    out = torch.empty(3, len(idx), dtype=torch.float64, device="cuda")
+    out = torch.empty(len(X), len(idx), dtype=torch.float64, device="cuda")
     for a in range(0, len(idx), 256):
         z = Y[:, None, :] - Y[:, idx[a:a + 256], None]
         t = torch.exp((z * z).sum(0) * (-0.5 / ell ** 2))
@@ -61,7 +61,7 @@ CLOUDS = [((1.0, 1.0, 1.0), 0.5), ((0.02, 0.02, 0.02), 0.5), ((2.0, 0.1, 0.001),
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32_kahan"])
-@pytest.mark.parametrize("N", [32768, 65537])
+@pytest.mark.parametrize("N", [24000, 65537])
 def test_pair_term(torch_cuda, precision, N):
     for k, (std, ell) in enumerate(CLOUDS):
         w = _w(N, std, ell, mean=(0.0, 5.0, -300.0) if k == 0 and precision == "fp64" else (0.0, 0.0, 0.0))
@@ -111,6 +111,31 @@ def test_left_to_the_pair_kernels(torch_cuda, precision):
                     _set(c, y, 2)
                     c.step(1)
                 assert np.array_equal(_get(s), f.state(0))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("graphs", [False, True])
+def test_two_dimensions(torch_cuda, precision, graphs):
+    """A context takes the grid once it has a surrogate, its captured ticks too."""
+    from paper_2105_09688_amd.ssm import mlp_init
+    N, ell = 32769, 0.6
+    w = _w(N, (1.0, 1.0, 1.0), ell)
+    w.update(d=2, x0_mean=[0.0, 2.0], x0_std=[1.0, 0.3], sigma=dict(s0=[0.0] * 2, s1=[0.0] * 2, s2=[0.0] * 2))
+    out = []
+    with _ssm(w, precision, graphs=graphs) as s:
+        x0 = s.state(0)
+        for load in (False, True):
+            if load:
+                s.surrogate_load(mlp_init(2, seed=1))
+            s.set_state(0, x0, step=0)
+            s.step(1)
+            out.append(s.state(0))
+    assert not np.array_equal(*out)  # two ways, to the same result:
+    idx = np.linspace(0, N - 1, 800).astype(int)
+    ref = _pairs(torch_cuda, x0, ell, idx)
+    err = [np.abs((x1 - x0)[:, idx] / H - ref).max() / ell for x1 in out]
+    print(f"[gpu-grid] two dimensions {precision}: pair kernels {err[0]:.1e}, grid {err[1]:.1e}", flush=True)
+    assert err[1] <= TOL[precision] + 2 * (1 + 1 / H) * U[precision] * np.abs(x0).max() / ell
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32_kahan"])
