@@ -718,14 +718,34 @@ static ssm_status launch_pairs(ssm_ctx* c, int64_t ph)
     return SSM_OK;
 }
 
+// The network's prediction; with_draws: with the tick's Brownian sums and means
+// of mu^Y in the launch of its moments.
 template <typename T>
-static ssm_status launch_surrogate(ssm_ctx* c, int64_t ph)
+static ssm_status launch_surrogate(ssm_ctx* c, int64_t ph, bool with_draws, int64_t targ, const int64_t* tdev)
 {
     const int d = c->d;
     const BlkItem* items = c->dblk + c->blk_off[ph];
     const int64_t nb = c->blk_cnt[ph];
-    SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_rff_partial<T, D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, items,
-                                         c->dsys, c->P, (const T*)c->Y, c->rff, c->rff_part));
+    if (with_draws) {
+        const int n_main = (int)(nb + nb * c->bm_lanes[ph]);
+        const YMeanJob job{c->dsys_list + c->sys_list_off[ph], c->needs_ybar ? (int)c->sys_list_cnt[ph] : 0, c->psumY, c->nblk_tot,
+                           c->ymean};
+#define SSM_RFF(LPV)                                                                                                  \
+    SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_rff_prep<T, D, LPV>), dim3((unsigned)(n_main + job.n)), dim3(kBlk), 0, c->stream, \
+                                         (int)nb, n_main, items, c->dsys, c->coef, c->P, (const T*)c->Y, c->rff, c->rff_part, \
+                                         targ, tdev, (const double*)c->win, c->dW, job))
+        switch (c->bm_lanes[ph]) {
+            case 16: SSM_RFF(16); break;
+            case 8: SSM_RFF(8); break;
+            case 4: SSM_RFF(4); break;
+            case 2: SSM_RFF(2); break;
+            default: SSM_RFF(1); break;
+        }
+#undef SSM_RFF
+    } else {
+        SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_rff_partial<T, D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, items,
+                                             c->dsys, c->P, (const T*)c->Y, c->rff, c->rff_part));
+    }
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_rff_final, dim3((unsigned)c->sys_list_cnt[ph], 2 * kRff), dim3(kBlk), 0, c->stream,
                        c->dsys_list + c->sys_list_off[ph], c->dsys, c->rff_part, c->mom);
@@ -734,10 +754,7 @@ static ssm_status launch_surrogate(ssm_ctx* c, int64_t ph)
     // 71.8 us at N = 2^20 against 75.6 us with 2048 workgroups of two blocks each
     const unsigned grid = (unsigned)std::min<int64_t>(nb, 1 << 20);
     SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_mlp_infer<T, D>), dim3(grid), dim3(256), 0, c->stream, items, (int)nb,
-                                         c->dsys, c->P, (const T*)c->Y, c->mom, c->dmlp, c->surr));
-    HIP_TRY(hipGetLastError());
-    SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_surr_partial<D>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, items,
-                                         c->dsys, c->P, c->surr, c->smean_part));
+                                         c->dsys, c->P, (const T*)c->Y, c->mom, c->dmlp, c->surr, c->smean_part));
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_surr_final, dim3((unsigned)c->sys_list_cnt[ph], d), dim3(kBlk), 0, c->stream,
                        c->dsys_list + c->sys_list_off[ph], c->dsys, c->smean_part, c->smean);
@@ -848,7 +865,7 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
         }
     }
     if (run_surr && nb > 0) {
-        ssm_status st = launch_surrogate<T>(c, ph);
+        ssm_status st = launch_surrogate<T>(c, ph, !run_exact, targ, tdev);
         if (st != SSM_OK) return st;
     }
     const int use_surr = (run_surr && !check) ? 1 : 0;
@@ -861,10 +878,11 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
         }
         const BlkItem* items = c->dblk + c->blk_off[ph];
         if (c->modes && run_exact) {
-#define SSM_UPDATE_MODES(TOT, ONE, part)                                                                                  \
-    hipLaunchKernelGGL((k_update_modes<T, TOT, ONE>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, c->one, items, c->dsys,  \
-                       c->coef, c->P, targ, tdev, X, Y, Ys, (const ModeDom*)c->dom, (const double*)(part),           \
-                       c->mode_rows, c->pairsum, (const double*)c->dW, (const double*)c->ymean, c->psumX, c->psumY, c->nblk_tot, c->dflags, c->dnmax, c->rng)
+#define SSM_UPDATE_MODES(TOT, ONE, part)                                                                              \
+    hipLaunchKernelGGL((k_update_modes<T, TOT, ONE>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, c->one, items,      \
+                       c->dsys, c->coef, c->P, targ, tdev, X, Y, Ys, (const ModeDom*)c->dom, (const double*)(part),      \
+                       c->mode_rows, c->pairsum, (const double*)c->dW, (const double*)c->ymean, c->psumX, c->psumY,      \
+                       c->nblk_tot, c->dflags, c->dnmax, c->rng)
             if (c->mode_totals) SSM_UPDATE_MODES(true, false, c->mode_tot);
             else if (c->sys.size() > 1) SSM_UPDATE_MODES(false, false, c->mode_part);
             else SSM_UPDATE_MODES(false, true, c->mode_part);
@@ -872,7 +890,8 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
             HIP_TRY(hipGetLastError());
         } else {
             // Brownian sums of the step, and on exact ticks the combine of the pair
-            // partials in the same launch (k_prep)
+            // partials in the same launch (k_prep); network ticks have drawn them
+            // beside their moments
             const bool comb = c->has_pair && run_exact;
             const int ncb = comb ? (int)(nb * 4) : 0;
             const int n_main = (int)(ncb + nb * c->bm_lanes[ph]);
@@ -880,24 +899,25 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
             const YMeanJob job{c->dsys_list + c->sys_list_off[ph], c->needs_ybar ? (int)c->sys_list_cnt[ph] : 0,
                                c->psumY, c->nblk_tot, c->ymean};
             const unsigned gb = (unsigned)(n_main + job.n);
-#define SSM_BM(LPV)                                                                                                   \
-        if (comb) {                                                                                                       \
-            SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_prep<T, D, LPV>), dim3(gb), dim3(kBlk), 0, c->stream, ncb, n_main,    \
-                                                 items, c->dsys, c->coef, c->P, (const T*)c->Bp, (const T*)c->Bpj,        \
-                                                 (const double*)c->jtot, c->pairsum, targ, tdev, (const double*)c->win, \
-                                                 c->dW, job));                                                            \
-        } else {                                                                                                          \
-            SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_brownian_sum<D, LPV, (sizeof(T) == 4)>), dim3(gb), dim3(kBlk), 0,    \
-                                                 c->stream, n_main,                                                       \
-                                                 items, c->dsys, c->coef, c->P, targ, tdev, (const double*)c->win,     \
-                                                 c->dW, job));                                                            \
-        }
-            switch (c->bm_lanes[ph]) {
-                case 16: SSM_BM(16); break;
-                case 8: SSM_BM(8); break;
-                case 4: SSM_BM(4); break;
-                case 2: SSM_BM(2); break;
-                default: SSM_BM(1); break;
+#define SSM_BM(LPV)                                                                                                       \
+    if (comb) {                                                                                                           \
+        SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_prep<T, D, LPV>), dim3(gb), dim3(kBlk), 0, c->stream, ncb, n_main, items, \
+                                             c->dsys, c->coef, c->P, (const T*)c->Bp, (const T*)c->Bpj,                   \
+                                             (const double*)c->jtot, c->pairsum, targ, tdev, (const double*)c->win,       \
+                                             c->dW, job));                                                                \
+    } else {                                                                                                              \
+        SSM_DISPATCH_D(d, hipLaunchKernelGGL((k_brownian_sum<D, LPV, (sizeof(T) == 4)>), dim3(gb), dim3(kBlk), 0,         \
+                                             c->stream, n_main, items, c->dsys, c->coef, c->P, targ, tdev,                \
+                                             (const double*)c->win, c->dW, job));                                         \
+    }
+            if (comb || !run_surr) {
+                switch (c->bm_lanes[ph]) {
+                    case 16: SSM_BM(16); break;
+                    case 8: SSM_BM(8); break;
+                    case 4: SSM_BM(4); break;
+                    case 2: SSM_BM(2); break;
+                    default: SSM_BM(1); break;
+                }
             }
 #undef SSM_BM
             HIP_TRY(hipGetLastError());
@@ -2467,7 +2487,8 @@ extern "C" ssm_status ssm_surrogate_predict(ssm_ctx* c, int32_t sys, double* out
     if (sys < 0 || sys >= (int32_t)c->sys.size()) return fail(SSM_ERR_INVALID, "sys out of range");
     if (!c->surr_loaded) return fail(SSM_ERR_STATE, "load surrogate weights first");
     // the tick's own launches (phase 0 lists every system) on the current Y*
-    ssm_status st = (c->prec == SSM_FP64) ? launch_surrogate<double>(c, 0) : launch_surrogate<float>(c, 0);
+    ssm_status st = (c->prec == SSM_FP64) ? launch_surrogate<double>(c, 0, false, 0, nullptr)
+                                             : launch_surrogate<float>(c, 0, false, 0, nullptr);
     if (st != SSM_OK) return st;
     const SysHost& S = c->sys[sys];
     hipLaunchKernelGGL(k_gather<float>, dim3((unsigned)((S.N + kBlk - 1) / kBlk)), dim3(kBlk), 0, c->stream,

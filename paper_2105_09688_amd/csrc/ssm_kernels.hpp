@@ -336,6 +336,32 @@ __device__ __forceinline__ double wave_sum(double v)
     return (readlane64(v, 0) + readlane64(v, 16)) + (readlane64(v, 32) + readlane64(v, 48));
 }
 
+// One halving of row_scatter: lanes with `up` keep the upper H values.
+template <int CTRL, int H>
+__device__ __forceinline__ void scatter_step(double* v, bool up)
+{
+#pragma unroll
+    for (int u = 0; u < H; ++u) {
+        const double send = up ? v[u] : v[H + u];
+        const double keep = up ? v[H + u] : v[u];
+        v[u] = keep + dpp64<CTRL>(send);
+    }
+}
+
+// Sums of 16 values over each row of 16 lanes: lane l of a row gets value l.
+// Four halvings (15 adds) in place of 16 reductions of four steps each; the
+// partners of the steps (15 - l, 7 - l within eight, l ^ 2, l ^ 1) differ in
+// the bit that picks the half kept.
+__device__ __forceinline__ double row_scatter(double (&v)[16])
+{
+    const int l = threadIdx.x;
+    scatter_step<kDppMirror, 8>(v, l & 8);
+    scatter_step<kDppHalfMirror, 4>(v, l & 4);
+    scatter_step<kDppXor2, 2>(v, l & 2);
+    scatter_step<kDppXor1, 1>(v, l & 1);
+    return v[0];
+}
+
 // Largest value over the lanes of a wavefront, the same way.
 __device__ __forceinline__ int wave_max(int v)
 {

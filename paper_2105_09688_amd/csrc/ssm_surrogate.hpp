@@ -331,27 +331,31 @@ __device__ __forceinline__ void mlp_forward16(const __bf16* sW1, const __bf16* s
 }
 
 // ---------------------------------------------------------------------------
-// RFF moments: per-block sums of cos / sin(omega_k . y) (FP32 within a block,
-// FP64 partials), then one block per system reduces its partials in order.
+// RFF moments: per-block sums of cos / sin(omega_k . y), FP32 terms added in
+// double, then one block per (system, moment) adds its partials in order.  A
+// wavefront's 32 sums are left by two reduce-scatters over its rows of lanes
+// (256 values per moment one after the other in 32 threads took 19 us at
+// N = 2^20; with the draws in further blocks 69 us of two launches are 63).
 // ---------------------------------------------------------------------------
 struct RffFreq {
     float w[kRff][kMaxD];  // omega_k (already divided by ell)
 };
 
 template <typename T, int D>
-__global__ __launch_bounds__(kBlk) void k_rff_partial(const BlkItem* __restrict__ items,
-                                                      const SysDev* __restrict__ sys, int64_t P,
-                                                      const T* __restrict__ Y, RffFreq fq,
-                                                      double* __restrict__ part /*[nblk_tot][2K]*/)
+__device__ __forceinline__ void rff_block(int vb, const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
+                                          int64_t P, const T* __restrict__ Y, const RffFreq& fq,
+                                          double* __restrict__ part /*[nblk_tot][2K]*/)
 {
-    __shared__ float red[2 * kRff][kBlk + 1];
-    const BlkItem it = items[blockIdx.x];
+    static_assert(kRff == 16, "a row of lanes per kind of moment");
+    __shared__ double red[kBlk / 64][2 * kRff];
+    const BlkItem it = items[vb];
     const SysDev S = sys[it.sys];
     const int i = it.blk * kBlk + threadIdx.x;
     const bool valid = i < S.N;
     float y[D];
 #pragma unroll
     for (int k = 0; k < D; ++k) y[k] = valid ? (float)Y[k * P + S.off + i] : 0.0f;
+    double c[kRff], s[kRff];
 #pragma unroll
     for (int q = 0; q < kRff; ++q) {
         float ph = 0.0f;
@@ -359,15 +363,45 @@ __global__ __launch_bounds__(kBlk) void k_rff_partial(const BlkItem* __restrict_
         for (int k = 0; k < D; ++k) ph = fmaf(fq.w[q][k], y[k], ph);
         float sn, cs;
         __sincosf(ph, &sn, &cs);
-        red[q][threadIdx.x] = valid ? cs : 0.0f;
-        red[kRff + q][threadIdx.x] = valid ? sn : 0.0f;
+        c[q] = valid ? (double)cs : 0.0;
+        s[q] = valid ? (double)sn : 0.0;
     }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double cv = row_scatter(c), sv = row_scatter(s);
+    cv += __shfl_xor(cv, 16);
+    sv += __shfl_xor(sv, 16);
+    cv += __shfl_xor(cv, 32);
+    sv += __shfl_xor(sv, 32);
+    if (lane < 2 * kRff) red[wave][lane] = lane < kRff ? cv : sv;
     __syncthreads();
-    if (threadIdx.x < 2 * kRff) {
-        double s = 0.0;
-        for (int t = 0; t < kBlk; ++t) s += (double)red[threadIdx.x][t];
-        part[(int64_t)(S.blk0 + it.blk) * (2 * kRff) + threadIdx.x] = s;
-    }
+    if (threadIdx.x < 2 * kRff)
+        part[(int64_t)(S.blk0 + it.blk) * (2 * kRff) + threadIdx.x] =
+            (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(kBlk) void k_rff_partial(const BlkItem* __restrict__ items,
+                                                      const SysDev* __restrict__ sys, int64_t P,
+                                                      const T* __restrict__ Y, RffFreq fq, double* __restrict__ part)
+{
+    rff_block<T, D>(blockIdx.x, items, sys, P, Y, fq, part);
+}
+
+// A network tick's moments and, in further blocks, what else does not depend
+// on the network: the Brownian sums and the means of mu^Y.
+template <typename T, int D, int LP>
+__global__ __launch_bounds__(kBlk) void k_rff_prep(int n_rff, int n_main, const BlkItem* __restrict__ items,
+                                                   const SysDev* __restrict__ sys, Coef cf, int64_t P,
+                                                   const T* __restrict__ Y, RffFreq fq, double* __restrict__ part,
+                                                   int64_t tick_arg, const int64_t* __restrict__ tick_dev,
+                                                   const double* __restrict__ win, double* __restrict__ dW, YMeanJob job)
+{
+    if ((int)blockIdx.x < n_rff)
+        rff_block<T, D>(blockIdx.x, items, sys, P, Y, fq, part);
+    else if ((int)blockIdx.x < n_main)
+        brownian_block<D, LP, (sizeof(T) == 4)>(blockIdx.x - n_rff, items, sys, cf, P, tick_arg, tick_dev, win, dW);
+    else
+        ymean_block<D>(blockIdx.x - n_main, job, sys, tick_arg, tick_dev);
 }
 
 // Sum over a system's block partials part[(blk0 + b) * stride + q], b < nblk:
@@ -576,10 +610,12 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void k_mlp_infer(const BlkItem* __restrict__ items, int n_items,
                                                    const SysDev* __restrict__ sys, int64_t P,
                                                    const T* __restrict__ Y, const float* __restrict__ mom,
-                                                   const MlpPacked* __restrict__ W, float* __restrict__ surr)
+                                                   const MlpPacked* __restrict__ W, float* __restrict__ surr,
+                                                   double* __restrict__ part /*[nblk_tot][kMaxD]*/)
 {
     __shared__ InferLds L;
     __shared__ __align__(16) float c1s[kHid];
+    __shared__ double red[4][D];
     load_infer(W, L);
     const int wave = threadIdx.x >> 6;
     const int l = threadIdx.x & 63;
@@ -593,6 +629,9 @@ __global__ __launch_bounds__(256) void k_mlp_infer(const BlkItem* __restrict__ i
             cur_sys = it.sys;
         }
         __syncthreads();
+        double tot[D];
+#pragma unroll
+        for (int k = 0; k < D; ++k) tot[k] = 0.0;
 #pragma unroll 1
         for (int tp = 0; tp < 2; ++tp) {
             const int i0 = it.blk * kBlk + (4 * wave + 2 * tp) * 16;
@@ -614,10 +653,26 @@ __global__ __launch_bounds__(256) void k_mlp_infer(const BlkItem* __restrict__ i
                     const int i = i0 + 16 * t + l;
                     if (i < S.N)
 #pragma unroll
-                        for (int k = 0; k < D; ++k) surr[(int64_t)k * P + S.off + i] = out[t][k];
+                        for (int k = 0; k < D; ++k) {
+                            surr[(int64_t)k * P + S.off + i] = out[t][k];
+                            tot[k] += (double)out[t][k];
+                        }
                 }
             }
         }
+        // the block's sums, for the mean that the tick takes off (k_surr_final)
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            tot[k] += dpp64<kDppXor1>(tot[k]);
+            tot[k] += dpp64<kDppXor2>(tot[k]);
+            tot[k] += dpp64<kDppHalfMirror>(tot[k]);
+            tot[k] += dpp64<kDppMirror>(tot[k]);
+            if (l == 0) red[wave][k] = tot[k];
+        }
+        __syncthreads();
+        if (threadIdx.x < D)
+            part[(int64_t)(S.blk0 + it.blk) * kMaxD + threadIdx.x] =
+                (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
     }
 }
 
@@ -1014,26 +1069,8 @@ __global__ __launch_bounds__(64) void k_train_wgrad(TrainBufs tb, int d, int B, 
 }
 
 // The exact pair term has zero net force (odd kernel: sum_i K^i = 0).  The
-// surrogate is projected onto that constraint: block sums of its outputs,
-// then per-system means that k_update / k_surr_err subtract.
-template <int D>
-__global__ __launch_bounds__(kBlk) void k_surr_partial(const BlkItem* __restrict__ items,
-                                                       const SysDev* __restrict__ sys, int64_t P,
-                                                       const float* __restrict__ surr,
-                                                       double* __restrict__ part /*[nblk_tot][kMaxD]*/)
-{
-    __shared__ double red[kRedLds];
-    const BlkItem it = items[blockIdx.x];
-    const SysDev S = sys[it.sys];
-    const int i = it.blk * kBlk + threadIdx.x;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-        const double v = (i < S.N) ? (double)surr[k * P + S.off + i] : 0.0;
-        const double t = block_sum(v, red);
-        if (threadIdx.x == 0) part[(int64_t)(S.blk0 + it.blk) * kMaxD + k] = t;
-    }
-}
-
+// surrogate is projected onto that constraint: block sums of its outputs
+// (k_mlp_infer), then per-system means that k_update / k_surr_err subtract.
 // grid (listed systems, d), kBlk threads
 __global__ __launch_bounds__(kBlk) void k_surr_final(const int32_t* __restrict__ sys_list,
                                                      const SysDev* __restrict__ sys,
