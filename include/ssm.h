@@ -147,9 +147,10 @@ typedef struct {
                                   are taken */
     int32_t graphs;            /* nonzero: each tick replays a HIP graph captured once per tick
                                   phase (tick % (h_max/h_min)); not used while profiling or with
-                                  the surrogate enabled.  0: contexts by modes still launch 4, 8 or
-                                  16 ticks of an ssm_step call as one graph once they have taken 64,
-                                  unless the caller is capturing the stream */
+                                  the surrogate enabled.  0: contexts by modes, and network ticks
+                                  of the surrogate in residual mode, still launch 4, 8 or 16 ticks of
+                                  an ssm_step call as one graph once the context has taken 64, unless
+                                  the caller is capturing the stream */
     /* Coefficient extensions (zero: off), see "Coefficients" above. */
     int32_t v_componentwise;   /* nonzero: component-wise cubic -v_ak[k] y_k^3 (v_a unused) */
     int32_t kahan_span;        /* SSM_FP32_KAHAN only: 0 -> plain sums over 256 sources between

@@ -315,6 +315,8 @@ struct ssm_ctx {
     std::vector<hipGraphExec_t> phase_graph;
     // graphs of several ticks of a one-dimensional context (graph_choice)
     hipGraphExec_t tick_graph[3] = {nullptr, nullptr, nullptr};
+    hipGraphExec_t net_graph[3] = {nullptr, nullptr, nullptr};  // and of several network ticks
+    bool net_graph_res = false;    // those add the residuals
     hipStream_t cap_stream = nullptr;
     int64_t multi_ticks = 0;       // ticks launched one by one
     bool no_tick_graph = false;    // a capture failed
@@ -1020,7 +1022,9 @@ static ssm_status capture_ticks(ssm_ctx* c, int64_t n, hipGraphExec_t* out)
     hipStream_t own = c->stream;
     c->stream = c->cap_stream;
     ssm_status st = SSM_OK;
+    const int64_t surr_ticks = c->surr_ticks;
     for (int64_t k = 0; k < n && st == SSM_OK; ++k) st = launch_tick<T>(c, c->dtick, k);
+    c->surr_ticks = surr_ticks;  // none has run
     if (st == SSM_OK) {
         hipLaunchKernelGGL(k_tick_advance, dim3(1), dim3(64), 0, c->stream, c->dtick, n);
         if (hipGetLastError() != hipSuccess) st = fail(SSM_ERR_HIP, "graph capture: tick counter");
@@ -1048,6 +1052,7 @@ static ssm_status replay_ticks(ssm_ctx* c, int64_t n, hipGraphExec_t ex)
     }
     HIP_TRY(hipGraphLaunch(ex, c->stream));
     for (int64_t k = 0; k < n; ++k) advance_host(c);
+    if (c->surr_check_every > 0) c->surr_ticks += n;
     return SSM_OK;
 }
 
@@ -1057,15 +1062,25 @@ static ssm_status replay_ticks(ssm_ctx* c, int64_t n, hipGraphExec_t ex)
 // about 14 us and 0.2 us a node (measured: 8 nodes 1.7 us each, 32 nodes 0.4).
 // So from 4 ticks on, in whole periods of the step sizes, for contexts that
 // have taken kGraphAfter ticks (a graph takes some 100 us to make, which short
-// runs would not get back).  0: launch by launch.
+// runs would not get back).  The network ticks up to the next check likewise,
+// five launches each, while what they carry in their arguments stays: no fitted
+// gains (residual mode), with residuals or without.  -1: launch by launch.
+// One check and 15 network ticks, N = 2^16, three contexts in turn: 472 us and 317
 static constexpr int64_t kGraphAfter = 64;
 static constexpr int64_t kGraphTicks[3] = {16, 8, 4};
 
 static int graph_choice(ssm_ctx* c, int64_t n)
 {
-    if (!c->modes || c->no_tick_graph || c->use_graphs || c->profiling || c->surr_check_every != 0 ||
-        c->multi_ticks < kGraphAfter || c->tick % c->max_stride != 0)
+    if (c->no_tick_graph || c->use_graphs || c->profiling || c->multi_ticks < kGraphAfter || c->tick % c->max_stride != 0) return -1;
+    if (c->surr_check_every > 0 && c->has_pair) {
+        const int64_t since = c->tick % c->surr_check_every;
+        if (since == 0 || c->surr_fallback || c->surr_mode != SSM_SURR_RESIDUAL) return -1;
+        for (int k = 0; k < c->d; ++k)
+            if (c->surr_gain[k] != 1.0) return -1;
+        n = std::min(n, c->surr_check_every - since);
+    } else if (!c->modes) {
         return -1;
+    }
     // a caller that captures the context's stream gets the launches
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
@@ -1084,13 +1099,22 @@ static ssm_status run_ticks(ssm_ctx* c, int64_t n, int64_t* done)
 {
     const int q = graph_choice(c, n);
     if (q >= 0) {
-        if (!c->tick_graph[q] && capture_ticks<T>(c, kGraphTicks[q], &c->tick_graph[q]) != SSM_OK) {
+        const bool net = c->surr_check_every > 0 && c->has_pair;
+        if (net && c->net_graph_res != c->surr_res_valid) {
+            for (auto& g : c->net_graph) {
+                if (g) (void)hipGraphExecDestroy(g);
+                g = nullptr;
+            }
+            c->net_graph_res = c->surr_res_valid;
+        }
+        hipGraphExec_t& ex = net ? c->net_graph[q] : c->tick_graph[q];
+        if (!ex && capture_ticks<T>(c, kGraphTicks[q], &ex) != SSM_OK) {
             (void)hipGetLastError();
             c->no_tick_graph = true;
         }
-        if (c->tick_graph[q]) {
+        if (ex) {
             *done = kGraphTicks[q];
-            return replay_ticks<T>(c, kGraphTicks[q], c->tick_graph[q]);
+            return replay_ticks<T>(c, kGraphTicks[q], ex);
         }
     }
     *done = 1;
@@ -1117,10 +1141,11 @@ static void drop_graphs(ssm_ctx* c)
         if (g) (void)hipGraphExecDestroy(g);
         g = nullptr;
     }
-    for (auto& g : c->tick_graph) {
-        if (g) (void)hipGraphExecDestroy(g);
-        g = nullptr;
-    }
+    for (auto* set : {c->tick_graph, c->net_graph})
+        for (int q = 0; q < 3; ++q) {
+            if (set[q]) (void)hipGraphExecDestroy(set[q]);
+            set[q] = nullptr;
+        }
 }
 
 // ---------------------------------------------------------------------------
