@@ -682,6 +682,16 @@ static bool grid_setup(ssm_ctx* c)
            hipMemsetAsync(g.grid, 0, Win::nodes * sizeof(unsigned long long), c->stream) == hipSuccess;
 }
 
+// The grid in two dimensions, from a context's first check (or training rows)
+// on: runs without one do not pay for its buffers.  Both synchronize anyway.
+static void grid_for_checks(ssm_ctx* c)
+{
+    if (!c->grid_ok || c->grid || c->d != 2) return;
+    c->grid_ok = false;  // tried
+    c->grid = c->prec == SSM_FP64 ? grid_setup<double>(c) : grid_setup<float>(c);
+    drop_graphs(c);  // their ticks do not have the grid's launches
+}
+
 // The pair sums of phase ph's items into the partial-sum buffers: one launch,
 // or (banded j-side rows) one launch per band followed by the fold of that
 // band's rows into jtot for every stepping particle.
@@ -859,6 +869,7 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
             e1 = take_event(c);
             if (e0) HIP_TRY(hipEventRecord(e0, c->stream));
         }
+        if (check) grid_for_checks(c);
         ssm_status st = c->modes ? launch_modes<T>(c, ph, targ, tdev, false) : launch_pairs<T>(c, ph);
         if (st != SSM_OK) return st;
         if (prof) {
@@ -2431,11 +2442,6 @@ static ssm_status ensure_surrogate_buffers(ssm_ctx* c)
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);
     (void)hipFree(dfq);
     if (he != hipSuccess) return fail(SSM_ERR_HIP, std::string("rff frequencies: ") + hipGetErrorString(he));
-    if (c->grid_ok && !c->grid && c->d == 2) {
-        c->grid = c->prec == SSM_FP64 ? grid_setup<double>(c) : grid_setup<float>(c);
-        drop_graphs(c);  // their ticks do not have the grid's launches
-        HIP_TRY(hipStreamSynchronize(c->stream));
-    }
     ALLOC2(c->dmlp, sizeof(MlpPacked));
 #undef ALLOC2
     return SSM_OK;
@@ -2565,6 +2571,7 @@ extern "C" ssm_status ssm_surrogate_samples(ssm_ctx* c, int32_t sys, int64_t n, 
         st = (c->prec == SSM_FP64) ? refresh_after_small<double>(c) : refresh_after_small<float>(c);
         if (st != SSM_OK) return st;
     }
+    grid_for_checks(c);
     // exact pair sums and RFF moments of the current Y* of every system (phase-0 lists hold all)
     const int64_t nb = c->blk_cnt[0];
     const int d = c->d;

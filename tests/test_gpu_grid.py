@@ -116,7 +116,7 @@ def test_left_to_the_pair_kernels(torch_cuda, precision):
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
 @pytest.mark.parametrize("graphs", [False, True])
 def test_two_dimensions(torch_cuda, precision, graphs):
-    """A context takes the grid once it has a surrogate, its captured ticks too."""
+    """A context takes the grid from its first check on, then in its captured ticks too."""
     from paper_2105_09688_amd.ssm import mlp_init
     N, ell = 32769, 0.6
     w = _w(N, (1.0, 1.0, 1.0), ell)
@@ -124,12 +124,14 @@ def test_two_dimensions(torch_cuda, precision, graphs):
     out = []
     with _ssm(w, precision, graphs=graphs) as s:
         x0 = s.state(0)
-        for load in (False, True):
-            if load:
-                s.surrogate_load(mlp_init(2, seed=1))
+        s.surrogate_load(mlp_init(2, seed=1))
+        for every in (0, 16, 0):  # an exact tick, a check, an exact tick
+            s.surrogate_enable(check_every=every, tol=1e9, mode="residual")
             s.set_state(0, x0, step=0)
             s.step(1)
             out.append(s.state(0))
+    assert np.array_equal(out[1], out[2])
+    out.pop()
     assert not np.array_equal(*out)  # two ways, to the same result:
     idx = np.linspace(0, N - 1, 800).astype(int)
     ref = _pairs(torch_cuda, x0, ell, idx)
