@@ -618,7 +618,7 @@ static ssm_status launch_grid(ssm_ctx* c)
     // workgroups as many as a compute unit's LDS holds at once
     const int cus = device_cus();
     const dim3 spread((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 3 : 2) * cus));
-    const dim3 gather((unsigned)std::min<int64_t>(chunks, cus));
+    const dim3 gather((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 1 : 2) * cus));
     const dim3 conv((unsigned)(4 * cus));
     hipLaunchKernelGGL(k_grid_range<T>, dim3((unsigned)nrange), dim3(kBlk), 0, c->stream, g, Ys);
     hipLaunchKernelGGL(k_grid_bin<T>, per, dim3(kBlk), 0, c->stream, g, nrange, Ys);

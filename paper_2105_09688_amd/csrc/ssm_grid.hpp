@@ -66,7 +66,7 @@ struct GridWin<double> {
     static constexpr double step = 0.2, beta = 2.6 * 14;
     static constexpr int group = 16;
     static constexpr int chunk = 128;
-    static constexpr int wg = 512, gather_wg = 1024;
+    static constexpr int wg = 512, gather_wg = 512;
     static constexpr int64_t nodes = 1 << 21;
     static constexpr int unit = 50;
 };
@@ -702,64 +702,83 @@ __global__ __launch_bounds__(GridWin<float>::gather_wg) void k_grid_gather8(Grid
     }
 }
 
-// W = 14: a field at a time (three are more than the LDS holds); 14 of 16
-// lanes, whose rows of 14 nodes meet the banks evenly.  N = 50021: 130 us
-// of a 230 us tick, half of it LDS reads (two fields side by side as above
-// halved those and took longer, 147 us: no room to read ahead)
-__global__ __launch_bounds__(GridWin<double>::gather_wg) void k_grid_gather14(GridArgs g, int64_t nodes)
+// W = 14: a field at a time in 74 KB, so that two workgroups share a compute
+// unit, one staging nodes while the other reads them.  A lane keeps its three
+// weights of each of its particles.  N = 50021: 122 us of a
+// 230 us tick, bound by LDS reads (60 %) and unequal chunks; one workgroup of
+// 1024 threads with the nodes read ahead 130, two fields side by side in one 147
+__global__ __launch_bounds__(GridWin<double>::gather_wg, 4) void k_grid_gather14(GridArgs g, int64_t nodes)
 {
     typedef GridWin<double> Win;
-    constexpr int W = Win::W, WG = Win::gather_wg, GR = Win::group, WP = 3 * W + 1, E = kGridCell + W - 1;
+    constexpr int W = Win::W, WG = Win::gather_wg, E = kGridCell + W - 1, SP = 2 * W + 2, Q = Win::chunk / (WG / 16);
     __shared__ double tile[E * E * E];
-    __shared__ double wts[Win::chunk * WP];
+    __shared__ double stage[WG / 64][4 * SP];
     const GridDom d = *g.dom;
-    if (!d.use || (int)blockIdx.x >= d.nchunks) return;
-    const int z = threadIdx.x & (GR - 1), slot = threadIdx.x / GR;
-    const int zc = min(z, W - 1);
-    GridNodes<W, WG, E> nd;
-    double next[nd.per];
-    nd.set(d, g.chunks[blockIdx.x].bin);
-#pragma unroll
-    for (int u = 0; u < nd.per; ++u) next[u] = nd.load(g.A, u);
+    if (!d.use) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int z = lane & 15, grp = lane >> 4, zc = min(z, W - 1);
+    const int tx = threadIdx.x / (E * E), ty = threadIdx.x / E % E, tz = threadIdx.x % E;
+    double* __restrict__ st = stage[wave] + grp * SP;
     for (int ch = blockIdx.x; ch < d.nchunks; ch += gridDim.x) {
         const GridChunk c = g.chunks[ch];
-        const GridRec* __restrict__ rec = g.rec + c.start;
+        const GridRec* __restrict__ rec = g.rec + c.start + wave * 4;
+        const int len = c.len - wave * 4;  // particles from this wavefront's first on
+        const int ox = c.bin / (d.nb[1] * d.nb[2]) * kGridCell, oy = c.bin / d.nb[2] % d.nb[1] * kGridCell,
+                  oz = c.bin % d.nb[2] * kGridCell;
+        double w[Q][3];
+        int base[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            if (q * (WG / 16) >= len) break;
+            const GridRec r = rec[min(q * (WG / 16) + grp, len - 1)];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) w[q][a] = grid_psi<double>(zc, ceil(r.v[a]) - r.v[a]);
+            base[q] = ((r.cell & 15) * E + ((r.cell >> 4) & 15)) * E + (r.cell >> 8) + zc;
+        }
 #pragma unroll 1
         for (int f = 0; f < g.dim; ++f) {
+            const double* __restrict__ F = g.A + f * nodes;
             __syncthreads();
-#pragma unroll
-            for (int u = 0; u < nd.per; ++u)
-                if (threadIdx.x + u * WG < E * E * E) tile[threadIdx.x + u * WG] = next[u];
-            const double* __restrict__ F = g.A + (f + 1) * nodes;
-            bool more = true;
-            if (f == g.dim - 1) {
-                F = g.A;
-                more = ch + (int)gridDim.x < d.nchunks;
-                if (more) nd.set(d, g.chunks[ch + gridDim.x].bin);
+            // node t of the tile, then t + WG, ...: x, y and z move on by WG's digits
+            int x = tx, y = ty, zz = tz;
+#pragma unroll 5
+            for (int t = threadIdx.x; t < E * E * E; t += WG) {
+                const bool in = ox + x < d.n[0] && oy + y < d.n[1] && oz + zz < d.n[2];
+                const double v = F[in ? ((ox + x) * d.n[1] + oy + y) * d.n[2] + oz + zz : 0];
+                tile[t] = in ? v : 0.0;
+                zz += WG % E;
+                y += WG / E % E + (zz >= E);
+                zz -= zz >= E ? E : 0;
+                x += WG / (E * E) + (y >= E);
+                y -= y >= E ? E : 0;
             }
-            if (more)
-#pragma unroll
-                for (int u = 0; u < nd.per; ++u) next[u] = nd.load(F, u);
-            if (f == 0) grid_weights<double, WP>(rec, c.len, wts, threadIdx.x, WG);
             __syncthreads();
-            for (int p = slot; p < c.len; p += WG / GR) {
-                const GridRec r = rec[p];
-                const int base = ((r.cell & 15) * E + ((r.cell >> 4) & 15)) * E + (r.cell >> 8) + zc;
-                const double* w = wts + p * WP;
-                double acc = 0.0;
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const int p = q * (WG / 16) + grp;
+                if (q * (WG / 16) >= len) break;
+                wave_lds_fence();
+                if (z < W) {
+                    st[z] = w[q][0];
+                    st[W + z] = w[q][1];
+                }
+                wave_lds_fence();
+                double wy[W], acc = 0.0;
+#pragma unroll
+                for (int m = 0; m < W; ++m) wy[m] = st[W + m];
 #pragma unroll 2
                 for (int x = 0; x < W; ++x) {
                     double s = 0.0;
 #pragma unroll
-                    for (int y = 0; y < W; ++y) s = fma(w[W + y], tile[base + (x * E + y) * E], s);
-                    acc = fma(w[x], s, acc);
+                    for (int y = 0; y < W; ++y) s = fma(wy[y], tile[base[q] + (x * E + y) * E], s);
+                    acc = fma(st[x], s, acc);
                 }
-                acc = z < W ? acc * w[2 * W + zc] : 0.0;
+                acc = z < W ? acc * w[q][2] : 0.0;
                 acc += dpp64<kDppXor1>(acc);
                 acc += dpp64<kDppXor2>(acc);
                 acc += dpp64<kDppHalfMirror>(acc);
                 acc += dpp64<kDppMirror>(acc);
-                if (z == 0) g.out[f * g.P + g.off + r.i] = g.scale * acc;
+                if (z == 0 && p < len) g.out[f * g.P + g.off + rec[p].i] = g.scale * acc;
             }
         }
     }

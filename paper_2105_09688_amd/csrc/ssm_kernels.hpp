@@ -19,7 +19,7 @@
 // systems make the sums by a grid (ssm_grid.hpp), k_pair_sym and the combine
 // returning at once.
 // A surrogate tick replaces the first two by the network's kernels
-// (ssm_surrogate.hpp) and k_brownian_sum.
+// (ssm_surrogate.hpp), the Brownian increments in one of their launches.
 // Layout: component-major [d][P] arrays over all systems, each system starting
 // at a multiple of kBlk particles (padding slots are zero and never read as
 // sources).
