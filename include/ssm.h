@@ -125,8 +125,8 @@ typedef struct {
                                   (symmetric, rounded up to a multiple of 16) */
     int32_t pair_scheme;       /* 0: default (d = 1 with none of targets_per_lane, sources_per_item,
                                   jside_band_groups and kahan_span = 1 given: by modes, below; d = 3
-                                  likewise with one system of 24000 particles or more, and d = 2 with
-                                  one of 32768 or more from its first surrogate check or samples on: by
+                                  likewise with one system of 20000 particles or more, and d = 2 with
+                                  one of 24000 or more from its first surrogate check or samples on: by
                                   a grid, below; else symmetric where the group fits, else ordered);
                                   1: every ordered pair (i, j) evaluated; 2: symmetric: each unordered
                                   pair evaluated once, +q to i and -q to j (the kernel is odd).

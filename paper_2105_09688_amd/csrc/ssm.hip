@@ -1557,15 +1557,16 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     c->modes = c->d == 1 && c->has_pair && !c->kpair && cfg->targets_per_lane == 0 && cfg->sources_per_item == 0 &&
                cfg->pair_scheme == 0 && cfg->jside_band_groups == 0;
     // one system in three dimensions by way of a grid, from the size on where
-    // that is faster.  A tick, pair kernels against grid: FP32 N = 16384 93 and
-    // 145 us, 24000 162 and 149, 2^18 14.1 ms and 250 us; FP64 N = 16384 203 and
-    // 197 us, 24000 367 and 232, 50021 1450 and 230.  In two dimensions where
-    // the context has a surrogate, for its checks (N = 2^16: 614 us of pair
-    // kernels, 100 us); without one the pair kernels stay there, as the exact
-    // method that the surrogate's gain is held against
+    // that is faster.  A tick, pair kernels against grid: FP32 N = 16384 91 and
+    // 105 us, 20000 119 and 106, 2^18 14.1 ms and 225 us; FP64 N = 16384 184 and
+    // 185 us, 20000 251 and 189, 50021 1350 and 239.  In two dimensions where
+    // the context has a surrogate, for its checks (FP32 N = 20000 88 and 98 us,
+    // 24000 115 and 98, 2^16 629 and 107; FP64 N = 2^16 1834 and 276); without
+    // one the pair kernels stay there, as the exact method that the surrogate's
+    // gain is held against
     c->grid_ok = c->has_pair && !c->kpair && c->sys.size() == 1 && cfg->targets_per_lane == 0 && cfg->sources_per_item == 0 &&
                  cfg->pair_scheme == 0 && cfg->jside_band_groups == 0 &&
-                 ((c->d == 3 && c->sys[0].N >= 24000) || (c->d == 2 && c->sys[0].N >= 32768));
+                 ((c->d == 3 && c->sys[0].N >= 20000) || (c->d == 2 && c->sys[0].N >= 24000));
     for (int attempt = 0; attempt < 2; ++attempt) {
         std::vector<int64_t> Ns;
         for (auto& S : c->sys) Ns.push_back(S.N);
