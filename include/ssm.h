@@ -147,8 +147,8 @@ typedef struct {
                                   are taken */
     int32_t graphs;            /* nonzero: each tick replays a HIP graph captured once per tick
                                   phase (tick % (h_max/h_min)); not used while profiling or with
-                                  the surrogate enabled.  0: contexts by modes, and network ticks
-                                  of the surrogate in residual mode, still launch 4, 8 or 16 ticks of
+                                  the surrogate enabled.  0: contexts by modes or without a pair
+                                  term, and network ticks of the surrogate in residual mode, still launch 4, 8 or 16 ticks of
                                   an ssm_step call as one graph once the context has taken 64, unless
                                   the caller is capturing the stream */
     /* Coefficient extensions (zero: off), see "Coefficients" above. */

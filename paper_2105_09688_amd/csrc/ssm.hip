@@ -1073,7 +1073,9 @@ static ssm_status replay_ticks(ssm_ctx* c, int64_t n, hipGraphExec_t ex)
 // about 14 us and 0.2 us a node (measured: 8 nodes 1.7 us each, 32 nodes 0.4).
 // So from 4 ticks on, in whole periods of the step sizes, for contexts that
 // have taken kGraphAfter ticks (a graph takes some 100 us to make, which short
-// runs would not get back).  The network ticks up to the next check likewise,
+// runs would not get back).  Contexts without a pair term are alike, with two
+// or three launches a tick (Ginzburg-Landau version 2, 2 x 5000, FP64, 24
+// ticks: 345 us and 240, three contexts in turn 315 and 91).  The network ticks up to the next check likewise,
 // five launches each, while what they carry in their arguments stays: no fitted
 // gains (residual mode), with residuals or without.  -1: launch by launch.
 // One check and 15 network ticks, N = 2^16, three contexts in turn: 472 us and 317
@@ -1089,7 +1091,7 @@ static int graph_choice(ssm_ctx* c, int64_t n)
         for (int k = 0; k < c->d; ++k)
             if (c->surr_gain[k] != 1.0) return -1;
         n = std::min(n, c->surr_check_every - since);
-    } else if (!c->modes) {
+    } else if (!c->modes && c->has_pair) {
         return -1;
     }
     // a caller that captures the context's stream gets the launches

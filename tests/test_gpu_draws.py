@@ -37,6 +37,24 @@ def test_increments_of_large_systems(N):
         assert np.max(np.abs(s.state(0)[:, at] - ref)) <= 1e-13
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32_kahan"])
+@pytest.mark.parametrize("kind", ["free", "mean", "two sizes"])
+def test_many_ticks_of_a_call_equal_single_ones(kind, precision):
+    """Without a pair term a call's ticks leave as graphs too, past a context's first 64."""
+    from paper_2105_09688_amd.ssm import SSM
+    h = 2.0 ** -7
+    w = W.ginzburg_landau(version=2, h_fine=h / 4) if kind == "mean" else W.ou(x0_std=0.5, h=h, h_fine=h / 4)
+    w = W.with_systems(w, [(2500, 0, h), (3001, 1, 2 * h if kind == "two sizes" else h)])
+    w["T"] = 128 * h
+    out = []
+    for plan in ((70, 31, 27), (1,) * 128):
+        with SSM(w, precision=precision) as s:
+            for n in plan:
+                s.step(n)
+            out.append(s.states())
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
+
+
 @pytest.mark.parametrize("rows", [64, 128, 512, 576, 1088, 2112])
 def test_gradients_of_every_remainder(torch_cuda, rows):
     from paper_2105_09688_amd.ssm import mlp_init, mlp_loss_grad
