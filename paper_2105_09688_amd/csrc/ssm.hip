@@ -315,8 +315,9 @@ struct ssm_ctx {
     std::vector<hipGraphExec_t> phase_graph;
     // graphs of several ticks of a one-dimensional context (graph_choice)
     hipGraphExec_t tick_graph[3] = {nullptr, nullptr, nullptr};
-    hipGraphExec_t net_graph[3] = {nullptr, nullptr, nullptr};  // and of several network ticks
-    bool net_graph_res = false;    // those add the residuals
+    // and of several network ticks, without and with residuals added: whether
+    // they are changes while replays of the other set are still queued
+    hipGraphExec_t net_graph[2][3] = {};
     hipStream_t cap_stream = nullptr;
     int64_t multi_ticks = 0;       // ticks launched one by one
     bool no_tick_graph = false;    // a capture failed
@@ -688,6 +689,7 @@ static void grid_for_checks(ssm_ctx* c)
 {
     if (!c->grid_ok || c->grid || c->d != 2) return;
     c->grid_ok = false;  // tried
+    (void)hipStreamSynchronize(c->stream);  // graphs of the ticks before may be queued
     c->grid = c->prec == SSM_FP64 ? grid_setup<double>(c) : grid_setup<float>(c);
     drop_graphs(c);  // their ticks do not have the grid's launches
 }
@@ -1113,14 +1115,7 @@ static ssm_status run_ticks(ssm_ctx* c, int64_t n, int64_t* done)
     const int q = graph_choice(c, n);
     if (q >= 0) {
         const bool net = c->surr_check_every > 0 && c->has_pair;
-        if (net && c->net_graph_res != c->surr_res_valid) {
-            for (auto& g : c->net_graph) {
-                if (g) (void)hipGraphExecDestroy(g);
-                g = nullptr;
-            }
-            c->net_graph_res = c->surr_res_valid;
-        }
-        hipGraphExec_t& ex = net ? c->net_graph[q] : c->tick_graph[q];
+        hipGraphExec_t& ex = net ? c->net_graph[c->surr_res_valid][q] : c->tick_graph[q];
         if (!ex && capture_ticks<T>(c, kGraphTicks[q], &ex) != SSM_OK) {
             (void)hipGetLastError();
             c->no_tick_graph = true;
@@ -1148,13 +1143,14 @@ static ssm_status run_ticks(ssm_ctx* c, int64_t n, int64_t* done)
     return replay_ticks<T>(c, 1, ex);
 }
 
+// The caller has synchronized the stream: no replay of them is queued.
 static void drop_graphs(ssm_ctx* c)
 {
     for (auto& g : c->phase_graph) {
         if (g) (void)hipGraphExecDestroy(g);
         g = nullptr;
     }
-    for (auto* set : {c->tick_graph, c->net_graph})
+    for (auto* set : {c->tick_graph, c->net_graph[0], c->net_graph[1]})
         for (int q = 0; q < 3; ++q) {
             if (set[q]) (void)hipGraphExecDestroy(set[q]);
             set[q] = nullptr;
