@@ -126,8 +126,9 @@ typedef struct {
     int32_t pair_scheme;       /* 0: default (d = 1 with none of targets_per_lane, sources_per_item,
                                   jside_band_groups and kahan_span = 1 given: by modes, below; d = 3
                                   likewise with one system of 20000 particles or more, and d = 2 with
-                                  one of 24000 or more from its first surrogate check or samples on: by
-                                  a grid, below; else symmetric where the group fits, else ordered);
+                                  one of 24000 or more from its first ssm_surrogate_enable with
+                                  check_every > 0 on: by a grid, below; else symmetric where the
+                                  group fits, else ordered);
                                   1: every ordered pair (i, j) evaluated; 2: symmetric: each unordered
                                   pair evaluated once, +q to i and -q to j (the kernel is odd).
                                   By modes: the sums over all pairs as a Fourier sum over the extent of
@@ -463,7 +464,11 @@ ssm_status ssm_surrogate_load(ssm_ctx *ctx, const float *master, int64_t n);
  *    system must step on check ticks: check_every a multiple of the ratio of
  *    the largest to the smallest step of the context.
  * Check ticks synchronize the stream.  check_every = 0 turns the surrogate
- * off.  Enabling (again) forgets the gain and the residuals. */
+ * off.  Enabling (again) forgets the gain and the residuals.  In two
+ * dimensions a context of one large system keeps the grid for its exact ticks
+ * (ssm_config.pair_scheme) from its first enabling on, also once turned off;
+ * a context resumed from its state follows it bit for bit if it has been
+ * enabled too. */
 ssm_status ssm_surrogate_enable(ssm_ctx *ctx, int32_t check_every, double tol, int32_t mode);
 
 /* Rechecks during a fallback (an extension; off by default).  With on = 1,

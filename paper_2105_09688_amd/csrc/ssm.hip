@@ -337,6 +337,8 @@ struct ssm_ctx {
     double* mode_tot = nullptr;     // [n_sys][kModeVals] (mode_totals)
     float2* rng = nullptr;          // [nblk_tot] range of the scaled positions of each block
     bool grid_ok = false;           // one large system in two or three dimensions
+    bool grid_tried = false, grid_made = false;  // its buffers
+    bool grid_asked = false;        // two dimensions: the surrogate has been turned on
     bool grid = false;              // exact ticks by the grid where the cloud fits it (ssm_grid.hpp)
     GridArgs ga{};
     void* grid_buf = nullptr;       // its buffers
@@ -683,14 +685,33 @@ static bool grid_setup(ssm_ctx* c)
            hipMemsetAsync(g.grid, 0, Win::nodes * sizeof(unsigned long long), c->stream) == hipSuccess;
 }
 
-// The grid in two dimensions, from a context's first check (or training rows)
-// on: runs without one do not pay for its buffers.  Both synchronize anyway.
-static void grid_for_checks(ssm_ctx* c)
+// The grid's buffers in two dimensions, made where they are first needed, in
+// calls that synchronize anyway: runs without a check do not pay for them.
+static bool grid_buffers(ssm_ctx* c)
 {
-    if (!c->grid_ok || c->grid || c->d != 2) return;
-    c->grid_ok = false;  // tried
+    if (c->grid_ok && !c->grid_tried) {
+        c->grid_tried = true;
+        c->grid_made = c->prec == SSM_FP64 ? grid_setup<double>(c) : grid_setup<float>(c);
+    }
+    return c->grid_made;
+}
+
+// A context of two dimensions sums its exact ticks by the grid from its first
+// ssm_surrogate_enable that turns the surrogate on.  Called before the first
+// exact tick after that (a check, a fallback after a state change, the
+// surrogate turned off), so that the way depends on how the context was
+// configured and not on which ticks were checks or where rows were sampled.
+static void grid_for_exact(ssm_ctx* c)
+{
+    if (!c->grid_asked || c->grid) return;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;  // nothing can be allocated in a caller's capture
+    if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (!grid_buffers(c)) return;
     (void)hipStreamSynchronize(c->stream);  // graphs of the ticks before may be queued
-    c->grid = c->prec == SSM_FP64 ? grid_setup<double>(c) : grid_setup<float>(c);
+    c->grid = true;
     drop_graphs(c);  // their ticks do not have the grid's launches
 }
 
@@ -698,12 +719,12 @@ static void grid_for_checks(ssm_ctx* c)
 // or (banded j-side rows) one launch per band followed by the fold of that
 // band's rows into jtot for every stepping particle.
 template <typename T>
-static ssm_status launch_pairs(ssm_ctx* c, int64_t ph)
+static ssm_status launch_pairs(ssm_ctx* c, int64_t ph, bool grid)
 {
     const int d = c->d;
     const int64_t np = c->pair_cnt[ph];
     const PairItem* items = c->dpair + c->pair_off[ph];
-    if (c->grid) {
+    if (grid) {
         ssm_status st = launch_grid<T>(c);
         if (st != SSM_OK) return st;
     }
@@ -871,8 +892,8 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
             e1 = take_event(c);
             if (e0) HIP_TRY(hipEventRecord(e0, c->stream));
         }
-        if (check) grid_for_checks(c);
-        ssm_status st = c->modes ? launch_modes<T>(c, ph, targ, tdev, false) : launch_pairs<T>(c, ph);
+        if (check) grid_for_exact(c);
+        ssm_status st = c->modes ? launch_modes<T>(c, ph, targ, tdev, false) : launch_pairs<T>(c, ph, c->grid);
         if (st != SSM_OK) return st;
         if (prof) {
             if (e1) HIP_TRY(hipEventRecord(e1, c->stream));
@@ -1557,8 +1578,8 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     // one system in three dimensions by way of a grid, from the size on where
     // that is faster.  A tick, pair kernels against grid: FP32 N = 16384 91 and
     // 105 us, 20000 119 and 106, 2^18 14.1 ms and 225 us; FP64 N = 16384 184 and
-    // 185 us, 20000 251 and 189, 50021 1350 and 239.  In two dimensions where
-    // the context has a surrogate, for its checks (FP32 N = 20000 88 and 98 us,
+    // 185 us, 20000 251 and 189, 50021 1350 and 239.  In two dimensions once
+    // the surrogate has been turned on (grid_for_exact), for its checks (FP32 N = 20000 88 and 98 us,
     // 24000 115 and 98, 2^16 629 and 107; FP64 N = 2^16 1834 and 276); without
     // one the pair kernels stay there, as the exact method that the surrogate's
     // gain is held against
@@ -1825,7 +1846,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     if (he == hipSuccess) he = hipMemsetAsync(c->ymean, 0, c->sys.size() * kMaxD * sizeof(double), c->stream);
     if (he == hipSuccess && c->small_ok && !c->solo) he = hipMemcpyAsync(c->dtiles, tiles.data(), tiles.size() * sizeof(SmallTile), hipMemcpyHostToDevice, c->stream);
     if (he == hipSuccess && c->small_ok && !c->solo) he = hipMemsetAsync(c->dbar, 0, c->sys.size() * kBarLine * sizeof(uint64_t), c->stream);
-    if (he == hipSuccess && c->grid_ok && c->d == 3) c->grid = c->prec == SSM_FP64 ? grid_setup<double>(c) : grid_setup<float>(c);
+    if (he == hipSuccess && c->d == 3) c->grid = grid_buffers(c);
     if (he == hipSuccess) he = hipStreamSynchronize(c->stream);  // host vectors go out of scope
     if (he != hipSuccess) { std::string m = hipGetErrorString(he); free_ctx(c); return fail(SSM_ERR_HIP, "upload: " + m); }
 
@@ -2074,6 +2095,7 @@ static void surrogate_invalidate(ssm_ctx* c)
 {
     c->surr_res_valid = false;
     c->surr_fallback = true;
+    grid_for_exact(c);
     for (int k = 0; k < kMaxD; ++k) c->surr_gain[k] = 1.0;
 }
 
@@ -2500,6 +2522,8 @@ extern "C" ssm_status ssm_surrogate_enable(ssm_ctx* c, int32_t check_every, doub
     c->surr_fallback = false;
     c->surr_res_valid = false;
     for (int k = 0; k < kMaxD; ++k) c->surr_gain[k] = 1.0;
+    if (check_every > 0) c->grid_asked = c->d == 2;
+    else grid_for_exact(c);
     return SSM_OK;
 }
 
@@ -2550,11 +2574,13 @@ static ssm_status launch_exact(ssm_ctx* c)
         HIP_TRY(hipGetLastError());
         return SSM_OK;
     }
-    ssm_status st = launch_pairs<T>(c, 0);
+    const bool grid = grid_buffers(c);
+    ssm_status st = launch_pairs<T>(c, 0, grid);
     if (st != SSM_OK) return st;
     SSM_DISPATCH_D(c->d, hipLaunchKernelGGL((k_combine<T, D>), dim3(nb * 4), dim3(64 * kCombineWaves), 0, c->stream, items,
                                             c->dsys, c->P, (const T*)c->Bp, (const T*)c->Bpj, (const double*)c->jtot,
                                             c->pairsum));
+    if (grid && !c->grid) hipLaunchKernelGGL(k_grid_leave, dim3(1), dim3(64), 0, c->stream, c->ga);
     HIP_TRY(hipGetLastError());
     return SSM_OK;
 }
@@ -2570,7 +2596,6 @@ extern "C" ssm_status ssm_surrogate_samples(ssm_ctx* c, int32_t sys, int64_t n, 
         st = (c->prec == SSM_FP64) ? refresh_after_small<double>(c) : refresh_after_small<float>(c);
         if (st != SSM_OK) return st;
     }
-    grid_for_checks(c);
     // exact pair sums and RFF moments of the current Y* of every system (phase-0 lists hold all)
     const int64_t nb = c->blk_cnt[0];
     const int d = c->d;

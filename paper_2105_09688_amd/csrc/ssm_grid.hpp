@@ -296,6 +296,12 @@ __global__ __launch_bounds__(kBlk) void k_grid_bin(GridArgs g, int nrange, const
         if (i0 + u * kBlk < g.N) g.key[i0 + u * kBlk] = make_int2(bin[u], place[u] + (int)hist[bin[u]]);
 }
 
+// Sums made for other uses than a tick leave no mark for the ticks after them.
+__global__ void k_grid_leave(GridArgs g)
+{
+    if (threadIdx.x == 0 && blockIdx.x == 0) g.sys->by_grid = 0;
+}
+
 // Exclusive sums of v over the block's threads; *total: their sum.
 __device__ __forceinline__ int block_scan(int v, int* wsum, int* total)
 {

@@ -159,3 +159,43 @@ def test_repeats_bit_for_bit(torch_cuda, precision):
         out.append(s.state(0))
     for x in out[1:]:
         assert np.array_equal(out[0], x)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_two_dimensions_by_configuration(torch_cuda, precision):
+    """How exact ticks are summed follows from how a context was configured: rows sampled
+    in between change nothing, nor does which ticks were checks, and a context resumed
+    from the state repeats the run bit for bit."""
+    from paper_2105_09688_amd.ssm import mlp_init
+    N = 24000
+    w = _w(N, (1.0, 1.0, 1.0), 0.6)
+    w.update(d=2, x0_mean=[0.0, 2.0], x0_std=[1.0, 0.3], sigma=dict(s0=[0.1] * 2, s1=[0.0] * 2, s2=[0.0] * 2))
+
+    def run(enabled, samples, check, resume=False):
+        with _ssm(w, precision) as s:
+            s.surrogate_load(mlp_init(2, seed=1))
+            if enabled:
+                s.surrogate_enable(check_every=check, tol=1e9, mode="residual")
+                s.surrogate_enable(check_every=0)
+            s.step(1)
+            if samples:
+                s.surrogate_samples(512, seed=3)
+            s.step(1)
+            mid = s.state(0)
+            if not resume:
+                s.step(1)
+                return s.state(0)
+        with _ssm(w, precision) as s:
+            s.surrogate_load(mlp_init(2, seed=1))
+            if enabled:
+                s.surrogate_enable(check_every=check, tol=1e9, mode="residual")
+                s.surrogate_enable(check_every=0)
+            s.set_state(0, mid, step=2)
+            s.step(1)
+            return s.state(0)
+
+    pairs, grid = run(False, False, 1), run(True, False, 1)
+    assert not np.array_equal(pairs, grid)
+    assert np.array_equal(pairs, run(False, True, 1)) and np.array_equal(grid, run(True, True, 1))
+    assert np.array_equal(grid, run(True, False, 16))
+    assert np.array_equal(pairs, run(False, True, 1, resume=True)) and np.array_equal(grid, run(True, True, 1, resume=True))
