@@ -261,14 +261,17 @@ __device__ __forceinline__ void newton_roots(const double (&nw)[P], const double
     double hi[P];
     bool act[P];
     const double alpha3 = alpha * alpha * alpha;
+    // an infinite second moment (a particle that is not finite, v_kappa > 0)
+    // makes alpha infinite, where rcp_fast has no value: the bound is 0 there
+    const double ra = alpha < 0x1.0p1000 ? rcp_fast(alpha) : 1.0 / alpha;
     bool any = false;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         // cbrt(nw / ha) < nw / alpha where alpha^3 < ha nw^2; a step of ordinary
         // size stays on the other side, without the cube root (a third of the
-        // solve's instructions)
-        hi[p] = nw[p] * rcp_fast(alpha);
-        if (live[p] && alpha3 < ha * nw2[p]) hi[p] = fmin(hi[p], cbrt(nw[p] / ha));
+        // solve's instructions); an alpha that is NaN takes the cube root
+        hi[p] = nw[p] * ra;
+        if (live[p] && !(alpha3 >= ha * nw2[p])) hi[p] = fmin(hi[p], cbrt(nw[p] / ha));
         act[p] = live[p];
         if (live[p]) s[p] = hi[p];
         any = any || act[p];
