@@ -140,12 +140,13 @@ typedef struct {
                                   By a grid: the sums over all pairs by a window function, a grid over
                                   the cloud's extent and convolutions along its axes, O(N) operations
                                   in double precision in every precision mode; error against the exact
-                                  sums 1e-15 of their size in FP64, 5e-9 in the FP32 modes (a direct
-                                  FP32 sum: 2e-8).  A cloud too wide for the grid (30 widths b_ell along
-                                  an axis or 27 along all three in FP64, 42 and 31 in the FP32 modes)
-                                  or with a non-finite particle takes the pair kernels that tick.  It holds 60 MB more
-                                  device memory (117 in FP64); without room for them the pair kernels
-                                  are taken */
+                                  sums, relative to their root mean square, 3e-16 in FP64 (sums over
+                                  pairs 2e-16 to 9e-16) and 1e-8 in the FP32 modes (direct FP32 terms
+                                  2e-8).  A cloud too wide for the grid (37 widths b_ell along an axis
+                                  or 33 along all three in FP64, 42 and 31 in the FP32 modes) or with
+                                  a non-finite particle takes the pair kernels that tick.  It holds
+                                  60 MB more device memory (134 in FP64); without room for them the
+                                  pair kernels are taken */
     int32_t graphs;            /* nonzero: each tick replays a HIP graph captured once per tick
                                   phase (tick % (h_max/h_min)); not used while profiling or with
                                   the surrogate enabled.  0: contexts by modes or without a pair

@@ -620,18 +620,18 @@ static ssm_status launch_grid(ssm_ctx* c)
     const int64_t chunks = g.N / Win::chunk + kGridBins;  // at most
     // workgroups as many as a compute unit's LDS holds at once
     const int cus = device_cus();
-    const dim3 spread((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 3 : 2) * cus));
-    const dim3 gather((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 1 : 2) * cus));
+    const dim3 spread((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 3 : 1) * cus));
+    const dim3 gather((unsigned)std::min<int64_t>(chunks, cus));
     const dim3 conv((unsigned)(4 * cus));
     hipLaunchKernelGGL(k_grid_range<T>, dim3((unsigned)nrange), dim3(kBlk), 0, c->stream, g, Ys);
     hipLaunchKernelGGL(k_grid_bin<T>, per, dim3(kBlk), 0, c->stream, g, nrange, Ys);
     hipLaunchKernelGGL(k_grid_scatter<T>, per, dim3(kBlk), 0, c->stream, g, Ys);
     hipLaunchKernelGGL(k_grid_spread<T>, spread, dim3(Win::wg), 0, c->stream, g);
-    hipLaunchKernelGGL(k_grid_conv<0>, conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
-    hipLaunchKernelGGL(k_grid_conv<1>, conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
-    hipLaunchKernelGGL(k_grid_conv<2>, conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
+    hipLaunchKernelGGL((k_grid_conv<0, Win::two>), conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
+    hipLaunchKernelGGL((k_grid_conv<1, Win::two>), conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
+    hipLaunchKernelGGL((k_grid_conv<2, Win::two>), conv, dim3(kBlk), 0, c->stream, g, Win::nodes);
     if constexpr (Win::W == 8) hipLaunchKernelGGL(k_grid_gather8, gather, dim3(Win::gather_wg), 0, c->stream, g, Win::nodes);
-    else hipLaunchKernelGGL(k_grid_gather14, gather, dim3(Win::gather_wg), 0, c->stream, g, Win::nodes);
+    else hipLaunchKernelGGL(k_grid_gather16, gather, dim3(Win::gather_wg), 0, c->stream, g, Win::nodes);
     HIP_TRY(hipGetLastError());
     return SSM_OK;
 }
@@ -648,7 +648,7 @@ static bool grid_setup(ssm_ctx* c)
     g.off = c->one.off;
     g.N = (int32_t)N;
     g.dim = c->d;
-    g.qb = std::min(Win::unit, 62 - (int)std::ceil(std::log2((double)N)));
+    g.qb = Win::two ? Win::unit : std::min(Win::unit, 62 - (int)std::ceil(std::log2((double)N)));
     g.scale = c->one.pair_scale;
     g.out = c->pairsum;
     g.sys = c->dsys;
@@ -662,7 +662,7 @@ static bool grid_setup(ssm_ctx* c)
     const size_t range = part(kGridRange * 6 * sizeof(double)), dom = part(sizeof(GridDom)),
                  count = part(kGridBins * sizeof(uint32_t)), key = part(N * sizeof(int2)), rec = part(N * sizeof(GridRec)),
                  chunks = part((N / Win::chunk + kGridBins) * sizeof(GridChunk)),
-                 grid = part(Win::nodes * sizeof(unsigned long long)), A = part(3 * Win::nodes * sizeof(double)),
+                 grid = part((Win::two ? 2 : 1) * Win::nodes * sizeof(unsigned long long)), A = part(3 * Win::nodes * sizeof(double)),
                  B = part(3 * Win::nodes * sizeof(double)), dtab = part(tab.size() * sizeof(double));
     char* base = nullptr;
     if (dev_alloc(c, (void**)&base, at) != SSM_OK) {
@@ -682,7 +682,7 @@ static bool grid_setup(ssm_ctx* c)
     g.tab = (const double*)(base + dtab);
     return hipMemcpyAsync(base + dtab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice, c->stream) == hipSuccess &&
            hipMemsetAsync(g.count, 0, kGridBins * sizeof(uint32_t), c->stream) == hipSuccess &&
-           hipMemsetAsync(g.grid, 0, Win::nodes * sizeof(unsigned long long), c->stream) == hipSuccess;
+           hipMemsetAsync(g.grid, 0, (Win::two ? 2 : 1) * Win::nodes * sizeof(unsigned long long), c->stream) == hipSuccess;
 }
 
 // The grid's buffers in two dimensions, made where they are first needed, in
@@ -1577,10 +1577,10 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
                cfg->pair_scheme == 0 && cfg->jside_band_groups == 0;
     // one system in three dimensions by way of a grid, from the size on where
     // that is faster.  A tick, pair kernels against grid: FP32 N = 16384 91 and
-    // 105 us, 20000 119 and 106, 2^18 14.1 ms and 225 us; FP64 N = 16384 184 and
-    // 185 us, 20000 251 and 189, 50021 1350 and 239.  In two dimensions once
+    // 105 us, 20000 119 and 106, 2^18 14.1 ms and 225 us; FP64 N = 20000 257 and
+    // 241 us, 24000 340 and 245, 50021 1350 and 265.  In two dimensions once
     // the surrogate has been turned on (grid_for_exact), for its checks (FP32 N = 20000 88 and 98 us,
-    // 24000 115 and 98, 2^16 629 and 107; FP64 N = 2^16 1834 and 276); without
+    // 24000 115 and 98, 2^16 629 and 107; FP64 N = 24000 276 and 193); without
     // one the pair kernels stay there, as the exact method that the surrogate's
     // gain is held against
     c->grid_ok = c->has_pair && !c->kpair && c->sys.size() == 1 && cfg->targets_per_lane == 0 && cfg->sources_per_item == 0 &&

@@ -18,12 +18,16 @@
 // of semicircle kernel", SIAM J. Sci. Comput. 41, 2019).
 //
 // Two dimensions are taken as a third coordinate of 0: that makes 8 times (FP64
-// 14 times) the nodes a particle needs, on sums that are bound by their launches.
+// 16 times) the nodes a particle needs, on sums that are bound by their launches.
 //
 // All of it is in double precision in every precision mode.  Node values are
-// added up as 64-bit integers in units of 2^-qb: integer sums do not depend on
-// their order, so runs stay bitwise reproducible with atomic additions, and
-// a resumed run equals an uninterrupted one.
+// added up as integers in units of 2^-qb: integer sums do not depend on their
+// order, so runs stay bitwise reproducible with atomic additions, and a resumed
+// run equals an uninterrupted one.  In FP64 the unit is 2^-52 at every N, and
+// the sums over the grid are in two words of 64 bits: what a unit cuts off are
+// the window's tails, the same for all particles, which the convolution
+// amplifies (with one word, 2^-46 at N = 50021 and 2^-44 at 2^18, the error was
+// 6.8e-15 and 3e-14 of the root mean square of K).
 //
 // A cloud that is too wide for the grid, or holds a particle that is not
 // finite, is summed by the pair kernels as before: k_grid_bin marks in SysDev
@@ -46,29 +50,39 @@ constexpr int kGridPer = 4;      // particles per thread of k_grid_bin and k_gri
 constexpr double kGridAlpha = 0.69314718055994530942;  // a = ln 2
 
 // Window and spacing of a precision.  Error of K against the exact sums,
-// relative to its root mean square (one dimension, normal cloud): FP64 1.1e-15,
-// FP32 modes 4.6e-9 (the direct FP32 terms carry 2e-8 and their plain sums 5e-7).
+// relative to its root mean square (normal clouds in two and three dimensions of
+// standard deviation 0.1 to 2.6, N = 20000 to 2^18, this arithmetic on the CPU):
+// FP64 1.9e-16 to 2.9e-16, sums over pairs in double there 2.5e-16 to 8.8e-16;
+// FP32 modes 4e-9 to 1e-8 (the direct FP32 terms carry 2e-8 and their plain sums
+// 5e-7).  What decides it in FP64 beside the unit: a spacing whose multiples are
+// exact, so that a particle's distance from its nodes carries no rounding of its
+// distance from the grid's corner; a window whose exponent cancels nothing and
+// has exact constants (grid_psi); and 16 nodes (14 at 0.2 with those: 3e-16 at
+// best, 5e-16 over the range, between the jump at a low window's edge and the
+// aliases of a high one; 14 without them 2.5e-15).
 template <typename T>
 struct GridWin;
 template <>
 struct GridWin<float> {
     static constexpr int W = 8;
     static constexpr double step = 0.28, beta = 2.55 * 8;
-    static constexpr int group = 8;    // lanes per particle of k_grid_gather
+    static constexpr double rate = beta * 1.44269504088896340736;  // psi = 2^(rate (sqrt(1 - z^2) - 1))
     static constexpr int chunk = 512;  // particles of a bin that a workgroup takes at a time
     static constexpr int wg = 512, gather_wg = 1024;
     static constexpr int64_t nodes = 1 << 20;
-    static constexpr int unit = 42;    // node sums in units of 2^-unit at most
+    static constexpr bool two = false;  // node sums in two words
+    static constexpr int unit = 42;     // node sums in units of 2^-unit at most
 };
 template <>
 struct GridWin<double> {
-    static constexpr int W = 14;
-    static constexpr double step = 0.2, beta = 2.6 * 14;
-    static constexpr int group = 16;
-    static constexpr int chunk = 128;
-    static constexpr int wg = 512, gather_wg = 512;
+    static constexpr int W = 16;
+    static constexpr double step = 0.25, rate = 6.875;  // psi = 2^(-rate t^2 / (8 + sqrt(64 - t^2))), t = 8 z
+    static constexpr long double beta = 55 * 0.693147180559945309417232121458176568L;
+    static constexpr int chunk = 256;
+    static constexpr int wg = 1024, gather_wg = 1024;
     static constexpr int64_t nodes = 1 << 21;
-    static constexpr int unit = 50;
+    static constexpr bool two = true;
+    static constexpr int unit = 52;
 };
 
 // The tick's grid: lowest coordinates, nodes and bins along each axis, chunks.
@@ -80,7 +94,7 @@ struct GridDom {
 };
 
 struct GridRec {      // a particle in its bin's order
-    double v[3];      // (s - lo) / step
+    double f[3];      // its first node's distance ahead, in [0, 1) of a step
     int32_t i;
     int32_t cell;     // its first node's place in the bin: x | y << 4 | z << 8
 };
@@ -101,7 +115,7 @@ struct GridArgs {
     int2* key;                      // [N] bin and place in it
     GridRec* rec;                   // [N]
     GridChunk* chunks;
-    unsigned long long* grid;       // [nodes], zero between ticks
+    unsigned long long* grid;       // [nodes] (two words: [2][nodes], kGridLow), zero between ticks
     double *A, *B;                  // [3][nodes] each
     const double* tab;              // [2][2 kGridTab]: t and t' / (2 a) at offsets -kGridTab ..
     double* out;                    // pairsum
@@ -111,7 +125,7 @@ struct GridArgs {
 // Host: t and t' / (2 a) at the grid's offsets.  Gauss-Legendre panels in long
 // double; psi's integral in z = sin(theta), where it is smooth.
 // ---------------------------------------------------------------------------
-inline std::vector<double> grid_table(int W, double step, double beta)
+inline std::vector<double> grid_table(int W, double step, long double beta)
 {
     typedef long double L;
     const L pi = 3.14159265358979323846264338327950288L, a = 0.693147180559945309417232121458176568L;
@@ -145,7 +159,7 @@ inline std::vector<double> grid_table(int W, double step, double beta)
     for (int q = 0; q < n; ++q) {  // even in theta: twice the half range
         const L th = X[q] * pi / 2, c = std::cos(th);
         zq[q] = std::sin(th) * hw;
-        pq[q] = std::exp((L)beta * (c - 1)) * c * Wt[q] * (pi / 2) * hw * 2;
+        pq[q] = std::exp(beta * (c - 1)) * c * Wt[q] * (pi / 2) * hw * 2;
     }
     std::vector<L> t(kGridTab, 0), td(kGridTab, 0);
     for (int q = 0; q < n; ++q) {
@@ -224,6 +238,19 @@ __global__ __launch_bounds__(kBlk) void k_grid_range(GridArgs g, const T* __rest
     }
 }
 
+// A coordinate's first node (ceil of its place on the grid), and how far that
+// lies ahead in steps.  With lo a multiple of a step that is a short binary
+// fraction (FP64), the node's coordinate and its distance are exact; at the
+// edges of a cell the distance may leave [0, 1) by the rounding of the place.
+template <typename T>
+__device__ __forceinline__ int grid_place(double s, double lo, double* f)
+{
+    constexpr double step = GridWin<T>::step;
+    const double v = (s - lo) * (1.0 / step), c = ceil(v);
+    *f = sizeof(T) == 8 ? (fma(c, step, lo) - s) * (1.0 / step) : c - v;
+    return (int)c;
+}
+
 // The tick's grid from the blocks' ranges: the same in every block.
 template <typename T>
 __device__ __forceinline__ GridDom grid_domain(const GridArgs& g, int nrange, double (*part)[6])
@@ -239,8 +266,10 @@ __device__ __forceinline__ GridDom grid_domain(const GridArgs& g, int nrange, do
     int64_t nodes = 1;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
+        constexpr double step = GridWin<T>::step;
         d.lo[k] = m[k];
-        const double e = ceil((-m[k + 3] - m[k]) * (1.0 / GridWin<T>::step));
+        if (sizeof(T) == 8 && fabs(m[k]) < 0x1.0p40) d.lo[k] = floor(m[k] * (1.0 / step)) * step;
+        const double e = ceil((-m[k + 3] - d.lo[k]) * (1.0 / step));
         const bool fits = e < (double)kGridAxis;  // false for NaN and infinities
         const int cells = fits ? (int)e + 1 : 1;
         if (!fits) d.use = 0;
@@ -281,7 +310,10 @@ __global__ __launch_bounds__(kBlk) void k_grid_bin(GridArgs g, int nrange, const
     for (int u = 0; u < kGridPer; ++u) {
         int c[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) c[k] = (int)ceil((s[u][k] - d.lo[k]) * (1.0 / GridWin<T>::step)) / kGridCell;
+        for (int k = 0; k < 3; ++k) {
+            double f;
+            c[k] = grid_place<T>(s[u][k], d.lo[k], &f) / kGridCell;
+        }
         bin[u] = (c[0] * d.nb[1] + c[1]) * d.nb[2] + c[2];
         if (i0 + u * kBlk < g.N) place[u] = (int)atomicAdd(&hist[bin[u]], 1u);
     }
@@ -370,24 +402,33 @@ __global__ __launch_bounds__(kBlk) void k_grid_scatter(GridArgs g, const T* __re
         if (i >= g.N) break;
         const int2 k = g.key[i];
         GridRec r;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) r.v[a] = a < g.dim ? ((double)Ys[a * g.P + g.off + i] - d.lo[a]) * (1.0 / GridWin<T>::step) : 0.0;
         r.i = i;
         r.cell = 0;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) r.cell |= ((int)ceil(r.v[a]) % kGridCell) << (4 * a);
+        for (int a = 0; a < 3; ++a) {
+            const double s = a < g.dim ? (double)Ys[a * g.P + g.off + i] : 0.0;
+            r.cell |= (grid_place<T>(s, d.lo[a], &r.f[a]) % kGridCell) << (4 * a);
+        }
         g.rec[start[k.x] + k.y] = r;
     }
 }
 
-// psi at node m of a particle's W, f in [0, 1) the first node's distance.
+// psi at node m of a particle's W, f in [0, 1) the first node's distance.  FP64:
+// sqrt(1 - z^2) - 1 as -z^2 / (1 + sqrt(1 - z^2)), whose difference would lose
+// beta roundings at the window's peak, and by t = z W / 2, so that no constant
+// is rounded: an error that all particles share is not averaged.
 template <typename T>
 __device__ __forceinline__ double grid_psi(int m, double f)
 {
     constexpr int W = GridWin<T>::W;
-    constexpr double b = GridWin<T>::beta * 1.44269504088896340736;
-    const double z = ((double)(m - W / 2) + f) * (2.0 / W);
-    return exp2_fast(fma(b, sqrt(fmax(fma(-z, z, 1.0), 0.0)), -b));
+    constexpr double rate = GridWin<T>::rate;
+    const double t = (double)(m - W / 2) + f;
+    if constexpr (sizeof(T) == 4) {
+        const double z = t * (2.0 / W);
+        return exp2_fast(fma(rate, sqrt(fmax(fma(-z, z, 1.0), 0.0)), -rate));
+    }
+    const double q = W / 2 + sqrt(fmax(fma(-t, t, W * W / 4.0), 0.0)), r = rcp_fast(q);
+    return exp2_fast(-rate * (t * t * fma(fma(-q, r, 1.0), r, r)));
 }
 
 // A bin's nodes in LDS: kGridCell + W - 1 along each axis.  W = 8: rows of 16,
@@ -412,21 +453,25 @@ __device__ __forceinline__ void grid_weights(const GridRec* __restrict__ rec, in
     constexpr int W = GridWin<T>::W;
     for (int q = t; q < n * 3 * W; q += nt) {
         const int p = q / (3 * W), r = q - p * (3 * W), a = r / W, m = r - a * W;
-        const double v = rec[p].v[a];
-        w[p * PITCH + r] = grid_psi<T>(m, ceil(v) - v);
+        w[p * PITCH + r] = grid_psi<T>(m, rec[p].f[a]);
     }
 }
 
 // ---------------------------------------------------------------------------
 // k_grid_spread: a workgroup adds a chunk's particles into its bin's nodes in
 // LDS, a wavefront one particle at a time (lanes: y and z), then into the grid.
-// A value is rounded to units of 2^-qb by adding 1.5 2^(52 - qb), whose own
-// bits are taken off again.  Bound by LDS atomics: W^3 / 64 a particle.
+// A value, at most 1, is rounded to units of 2^-qb by adding 2^(52 - qb), whose
+// own bits are taken off again.  Bound by LDS atomics: W^3 / 64 a particle.
+// Two words: the tile's sums are whole (256 particles of 2^52 units), the grid
+// takes their kGridLow lower bits and the others, 0 at most nodes, apart; neither
+// word can overflow below 2^31 particles.
 // ---------------------------------------------------------------------------
+constexpr int kGridLow = 38;
+
 template <typename T>
 __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
 {
-    constexpr int W = GridWin<T>::W, WG = GridWin<T>::wg, PB = W == 8 ? 8 : 2, Z = W == 8 ? 8 : 16, R = (W * Z + 63) / 64;
+    constexpr int W = GridWin<T>::W, WG = GridWin<T>::wg, PB = W == 8 ? 8 : 2, R = W * W / 64;
     typedef GridTile<T> Tile;
     constexpr int E = Tile::E;
     __shared__ unsigned long long tile[Tile::size];
@@ -436,7 +481,7 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
     if (!d.use) return;
     // at W = 8 the added bits stay in: a power of two, they are above bit 51, and
     // a chunk's sum of a node is below 2^51 (GridWin::unit)
-    const double magic = ldexp(W == 8 ? 1.0 : 1.5, 52 - g.qb);
+    const double magic = ldexp(1.0, 52 - g.qb);
     const unsigned long long mbits = W == 8 ? 0 : (unsigned long long)__double_as_longlong(magic);
     constexpr unsigned long long keep = W == 8 ? (1ull << 52) - 1 : ~0ull;
     double* w = wts[wave];
@@ -458,19 +503,17 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
                 int at[R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    const int y = lane / Z + 64 / Z * r, z = lane % Z;
-                    const bool in = y < W && z < W;
-                    wyz[r] = in ? w[p * 3 * W + W + y] * w[p * 3 * W + 2 * W + z] : 0.0;
-                    at[r] = Tile::at(x0, y0 + (in ? y : 0), z0 + (in ? z : 0));
+                    const int y = lane / W + 64 / W * r, z = lane % W;
+                    wyz[r] = w[p * 3 * W + W + y] * w[p * 3 * W + 2 * W + z];
+                    at[r] = Tile::at(x0, y0 + y, z0 + z);
                 }
 #pragma unroll
                 for (int x = 0; x < W; ++x) {
                     const double wx = w[p * 3 * W + x];
 #pragma unroll
                     for (int r = 0; r < R; ++r)
-                        if (Z == W || (lane / Z + 64 / Z * r < W && lane % Z < W))
-                            atomicAdd(&tile[at[r] + x * E * Tile::pitch],
-                                      (unsigned long long)__double_as_longlong(fma(wx, wyz[r], magic)) - mbits);
+                        atomicAdd(&tile[at[r] + x * E * Tile::pitch],
+                                  (unsigned long long)__double_as_longlong(fma(wx, wyz[r], magic)) - mbits);
                 }
             }
             wave_lds_fence();
@@ -481,7 +524,13 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
             const unsigned long long v = tile[Tile::at(x, y, z)] & keep;
             if (v) {  // nodes outside the grid hold nothing
                 const int64_t node = ((int64_t)(bx * kGridCell + x) * d.n[1] + by * kGridCell + y) * d.n[2] + bz * kGridCell + z;
-                atomicAdd(&g.grid[node], v);
+                if constexpr (GridWin<T>::two) {
+                    const unsigned long long low = v & ((1ull << kGridLow) - 1), high = v >> kGridLow;
+                    if (low) atomicAdd(&g.grid[node], low);
+                    if (high) atomicAdd(&g.grid[GridWin<T>::nodes + node], high);
+                } else {
+                    atomicAdd(&g.grid[node], v);
+                }
             }
         }
         __syncthreads();
@@ -503,7 +552,15 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
 // ---------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-template <int PASS>
+// A node's sum in units of 2^-qb.
+template <bool TWO>
+__device__ __forceinline__ double grid_sum(const unsigned long long* __restrict__ raw, int64_t at, int64_t nodes)
+{
+    if constexpr (TWO) return fma((double)(long long)raw[nodes + at], (double)(1ull << kGridLow), (double)(long long)raw[at]);
+    else return (double)(long long)raw[at];
+}
+
+template <int PASS, bool TWO>
 __global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
 {
     constexpr int NIN = PASS + 1, NOUT = PASS == 0 ? 2 : 3, NT = 2, U = 4;
@@ -538,7 +595,7 @@ __global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
                 const int64_t at = (int64_t)min(k, n - 1) * inner + qc;
 #pragma unroll
                 for (int f = 0; f < NIN; ++f) {
-                    if constexpr (PASS == 0) x[u][f] = (double)(long long)raw[at];
+                    if constexpr (PASS == 0) x[u][f] = grid_sum<TWO>(raw, at, nodes);
                     else x[u][f] = in[f * nodes + at];
                 }
             }
@@ -579,7 +636,10 @@ __global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
     }
     if constexpr (PASS == 1) {
         const int64_t used = (int64_t)n * inner;
-        for (int64_t q = (int64_t)blockIdx.x * kBlk + threadIdx.x; q < used; q += (int64_t)gridDim.x * kBlk) g.grid[q] = 0;
+        for (int64_t q = (int64_t)blockIdx.x * kBlk + threadIdx.x; q < used; q += (int64_t)gridDim.x * kBlk) {
+            g.grid[q] = 0;
+            if constexpr (TWO) g.grid[nodes + q] = 0;
+        }
         const int bins = d.nb[0] * d.nb[1] * d.nb[2];
         for (int q = blockIdx.x * kBlk + threadIdx.x; q < bins; q += gridDim.x * kBlk) g.count[q] = 0;
     }
@@ -666,9 +726,8 @@ __global__ __launch_bounds__(GridWin<float>::gather_wg) void k_grid_gather8(Grid
             const GridRec r = rec[min(p0 + grp, len - 1)];
             double wx[W], wy[W / 2];
             wave_lds_fence();
-            const double vxy = odd ? r.v[1] : r.v[0];
-            st[odd ? W + (z & 1) * 4 + z / 2 : z] = grid_psi<float>(z, ceil(vxy) - vxy);  // wx, then wy: even ones, odd ones
-            const double wz = grid_psi<float>(z, ceil(r.v[2]) - r.v[2]);
+            st[odd ? W + (z & 1) * 4 + z / 2 : z] = grid_psi<float>(z, odd ? r.f[1] : r.f[0]);  // wx, then wy: even ones, odd ones
+            const double wz = grid_psi<float>(z, r.f[2]);
             const int y0 = ((r.cell >> 4) & 15) + odd;
             const int base = ((r.cell & 15) * E + y0) * ROW + (((r.cell >> 8) + z) ^ ((y0 & 1) << 3));
             wave_lds_fence();
@@ -708,21 +767,24 @@ __global__ __launch_bounds__(GridWin<float>::gather_wg) void k_grid_gather8(Grid
     }
 }
 
-// W = 14: a field at a time in 74 KB, so that two workgroups share a compute
-// unit, one staging nodes while the other reads them.  A lane keeps its three
-// weights of each of its particles.  N = 50021: 122 us of a
-// 230 us tick, bound by LDS reads (60 %) and unequal chunks; one workgroup of
-// 1024 threads with the nodes read ahead 130, two fields side by side in one 147
-__global__ __launch_bounds__(GridWin<double>::gather_wg, 4) void k_grid_gather14(GridArgs g, int64_t nodes)
+// W = 16: a field at a time in 97 KB, 16 lanes a particle, one for each z.  A
+// lane keeps its three weights of each of its particles.  N = 50021: 152 us of
+// a tick with 14 nodes in two workgroups a compute unit, 238 here (one trace),
+// the tick 245 and 272.  Chunks of 128 and 64, a field's chunk as a work item of
+// its own, the next field's nodes read ahead, and 32 lanes a particle without
+// bank conflicts were all slower or the same: staging and waiting bound it.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(GridWin<double>::gather_wg) void k_grid_gather16(GridArgs g, int64_t nodes)
 {
     typedef GridWin<double> Win;
-    constexpr int W = Win::W, WG = Win::gather_wg, E = kGridCell + W - 1, SP = 2 * W + 2, Q = Win::chunk / (WG / 16);
-    __shared__ double tile[E * E * E];
+    constexpr int W = Win::W, WG = Win::gather_wg, E = GridTile<double>::E, ROW = GridTile<double>::pitch, SP = 2 * W + 2,
+                  Q = Win::chunk / (WG / 16);
+    __shared__ double tile[GridTile<double>::size];
     __shared__ double stage[WG / 64][4 * SP];
     const GridDom d = *g.dom;
     if (!d.use) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int z = lane & 15, grp = lane >> 4, zc = min(z, W - 1);
+    const int z = lane & 15, grp = lane >> 4;
     const int tx = threadIdx.x / (E * E), ty = threadIdx.x / E % E, tz = threadIdx.x % E;
     double* __restrict__ st = stage[wave] + grp * SP;
     for (int ch = blockIdx.x; ch < d.nchunks; ch += gridDim.x) {
@@ -738,8 +800,8 @@ __global__ __launch_bounds__(GridWin<double>::gather_wg, 4) void k_grid_gather14
             if (q * (WG / 16) >= len) break;
             const GridRec r = rec[min(q * (WG / 16) + grp, len - 1)];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) w[q][a] = grid_psi<double>(zc, ceil(r.v[a]) - r.v[a]);
-            base[q] = ((r.cell & 15) * E + ((r.cell >> 4) & 15)) * E + (r.cell >> 8) + zc;
+            for (int a = 0; a < 3; ++a) w[q][a] = grid_psi<double>(z, r.f[a]);
+            base[q] = ((r.cell & 15) * E + ((r.cell >> 4) & 15)) * ROW + (r.cell >> 8) + z;
         }
 #pragma unroll 1
         for (int f = 0; f < g.dim; ++f) {
@@ -747,11 +809,11 @@ __global__ __launch_bounds__(GridWin<double>::gather_wg, 4) void k_grid_gather14
             __syncthreads();
             // node t of the tile, then t + WG, ...: x, y and z move on by WG's digits
             int x = tx, y = ty, zz = tz;
-#pragma unroll 5
+#pragma unroll 6
             for (int t = threadIdx.x; t < E * E * E; t += WG) {
                 const bool in = ox + x < d.n[0] && oy + y < d.n[1] && oz + zz < d.n[2];
                 const double v = F[in ? ((ox + x) * d.n[1] + oy + y) * d.n[2] + oz + zz : 0];
-                tile[t] = in ? v : 0.0;
+                tile[(x * E + y) * ROW + zz] = in ? v : 0.0;
                 zz += WG % E;
                 y += WG / E % E + (zz >= E);
                 zz -= zz >= E ? E : 0;
@@ -764,10 +826,8 @@ __global__ __launch_bounds__(GridWin<double>::gather_wg, 4) void k_grid_gather14
                 const int p = q * (WG / 16) + grp;
                 if (q * (WG / 16) >= len) break;
                 wave_lds_fence();
-                if (z < W) {
-                    st[z] = w[q][0];
-                    st[W + z] = w[q][1];
-                }
+                st[z] = w[q][0];
+                st[W + z] = w[q][1];
                 wave_lds_fence();
                 double wy[W], acc = 0.0;
 #pragma unroll
@@ -776,10 +836,10 @@ __global__ __launch_bounds__(GridWin<double>::gather_wg, 4) void k_grid_gather14
                 for (int x = 0; x < W; ++x) {
                     double s = 0.0;
 #pragma unroll
-                    for (int y = 0; y < W; ++y) s = fma(wy[y], tile[base[q] + (x * E + y) * E], s);
+                    for (int y = 0; y < W; ++y) s = fma(wy[y], tile[base[q] + (x * E + y) * ROW], s);
                     acc = fma(st[x], s, acc);
                 }
-                acc = z < W ? acc * w[q][2] : 0.0;
+                acc *= w[q][2];
                 acc += dpp64<kDppXor1>(acc);
                 acc += dpp64<kDppXor2>(acc);
                 acc += dpp64<kDppHalfMirror>(acc);

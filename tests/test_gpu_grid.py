@@ -199,3 +199,40 @@ def test_two_dimensions_by_configuration(torch_cuda, precision):
     assert np.array_equal(pairs, run(False, True, 1)) and np.array_equal(grid, run(True, True, 1))
     assert np.array_equal(grid, run(True, False, 16))
     assert np.array_equal(pairs, run(False, True, 1, resume=True)) and np.array_equal(grid, run(True, True, 1, resume=True))
+
+
+def _rms_error(w, x0, x1, ell, targets=48):
+    """RMS error of the step's pair term over its RMS, against sums in long double."""
+    N = x0.shape[1]
+    idx = np.linspace(0, N - 1, targets).astype(int)
+    X = x0.astype(np.longdouble)
+    err = ref = 0.0
+    for i in idx:
+        z = X - X[:, i:i + 1]
+        K = (z * np.exp(-(z * z).sum(0) / (2 * np.longdouble(ell) ** 2))).sum(1) / N
+        err += float((((x1[:, i].astype(np.longdouble) - X[:, i]) / H - K) ** 2).sum())
+        ref += float((K * K).sum())
+    return np.sqrt(err / ref)
+
+
+@pytest.mark.parametrize("d,N", [(3, 20000), (3, 50021), (3, 262144), (3, 1048577), (2, 50021)])
+def test_fp64_error_does_not_grow(torch_cuda, d, N):
+    """FP64 at every size: 6e-16 by this arithmetic on the CPU (normal clouds, 2e4 to
+    2^20), 1e-16 for x_1 and x_0 in the difference, 1e-15 allowed."""
+    from paper_2105_09688_amd.ssm import mlp_init
+    w = _w(N, (1.0, 1.0, 1.0))
+    if d == 2:
+        w.update(d=2, x0_mean=[0.0] * 2, x0_std=[1.0] * 2, sigma=dict(s0=[0.0] * 2, s1=[0.0] * 2, s2=[0.0] * 2))
+    out = []
+    for kw in ({}, dict(pair_scheme="symmetric")):
+        if kw and N > 300000:
+            break
+        with _ssm(w, "fp64", **kw) as s:
+            if d == 2:
+                s.surrogate_load(mlp_init(2, seed=1))
+                s.surrogate_enable(check_every=1, tol=1e9, mode="residual")
+            x0 = s.state(0)
+            s.step(1)
+            out.append(_rms_error(w, x0, s.state(0), 0.5))
+    print(f"[gpu-grid] d={d} N={N} FP64 relative RMS error: grid, pair kernels {['%.1e' % e for e in out]}", flush=True)
+    assert out[0] <= 1e-15
