@@ -622,7 +622,7 @@ static ssm_status launch_grid(ssm_ctx* c)
     const int cus = device_cus();
     const dim3 spread((unsigned)std::min<int64_t>(chunks, (Win::W == 8 ? 3 : 1) * cus));
     const dim3 gather((unsigned)std::min<int64_t>(chunks, cus));
-    const dim3 conv((unsigned)(4 * cus));
+    const dim3 conv((unsigned)(g.nphi / (kBlk / 64)));
     hipLaunchKernelGGL(k_grid_range<T>, dim3((unsigned)nrange), dim3(kBlk), 0, c->stream, g, Ys);
     hipLaunchKernelGGL(k_grid_bin<T>, per, dim3(kBlk), 0, c->stream, g, nrange, Ys);
     hipLaunchKernelGGL(k_grid_scatter<T>, per, dim3(kBlk), 0, c->stream, g, Ys);
@@ -659,7 +659,10 @@ static bool grid_setup(ssm_ctx* c)
         at += (bytes + 255) / 256 * 256;
         return here;
     };
-    const size_t range = part(kGridRange * 6 * sizeof(double)), dom = part(sizeof(GridDom)),
+    g.kb = std::min(50, kGridK2 + 1 - (int)std::ceil(std::log2((double)N)));
+    g.k2unit = std::ldexp(1.0 / ((double)N * (double)N), g.kb);
+    g.nphi = 4 * device_cus() * (kBlk / 64);
+    const size_t range = part(kGridRange * kGridRow * sizeof(double)), phi = part(g.nphi * sizeof(double)), dom = part(sizeof(GridDom)),
                  count = part(kGridBins * sizeof(uint32_t)), key = part(N * sizeof(int2)), rec = part(N * sizeof(GridRec)),
                  chunks = part((N / Win::chunk + kGridBins) * sizeof(GridChunk)),
                  grid = part((Win::two ? 2 : 1) * Win::nodes * sizeof(unsigned long long)), A = part(3 * Win::nodes * sizeof(double)),
@@ -671,6 +674,7 @@ static bool grid_setup(ssm_ctx* c)
     }
     c->grid_buf = base;
     g.range = (double*)(base + range);
+    g.phi = (double*)(base + phi);
     g.dom = (GridDom*)(base + dom);
     g.count = (uint32_t*)(base + count);
     g.key = (int2*)(base + key);

@@ -32,6 +32,15 @@
 // A cloud that is too wide for the grid, or holds a particle that is not
 // finite, is summed by the pair kernels as before: k_grid_bin marks in SysDev
 // which of the two the tick takes, and the other's kernels return at once.
+// So is a cloud that has contracted against the kernel's width.  The grid's
+// error is a fraction of Phi (FP64 4e-17 to 1e-16, FP32 modes 2e-9 to 3e-9);
+// that of sums over pairs is one of K, and in a cluster of spread r (root mean
+// square distance from the mean, scaled) K is r Phi.  k_grid_bin leaves clouds
+// of less spread than GridWin::least to the pair kernels.  Several tight
+// clusters, or a tight one and a few particles far away, have any spread: the
+// last block of the gather compares the root mean square of K with the mean of
+// Phi (the sums of which come from the third convolution) and marks the tick as
+// the pair kernels' below the same ratio.
 #pragma once
 
 #include "ssm_kernels.hpp"
@@ -46,6 +55,7 @@ constexpr int kGridAxis = 128;   // first nodes along an axis at most: 16 bins
 constexpr int kGridBins = (kGridAxis / kGridCell) * (kGridAxis / kGridCell) * (kGridAxis / kGridCell);
 constexpr int kGridTab = 176;    // offsets of the convolution tables: kGridAxis + W - 1, rounded up to whole products
 constexpr int kGridRange = 256;  // blocks of k_grid_range at most
+constexpr int kGridRow = 10;     // a row of k_grid_range: lo[3], -hi[3], sums of s - s_0 [3] and |s - s_0|^2
 constexpr int kGridPer = 4;      // particles per thread of k_grid_bin and k_grid_scatter
 constexpr double kGridAlpha = 0.69314718055994530942;  // a = ln 2
 
@@ -72,6 +82,7 @@ struct GridWin<float> {
     static constexpr int64_t nodes = 1 << 20;
     static constexpr bool two = false;  // node sums in two words
     static constexpr int unit = 42;     // node sums in units of 2^-unit at most
+    static constexpr double least = 0.1;    // least K / Phi: an error of 2e-8 of K, a direct FP32 term's
 };
 template <>
 struct GridWin<double> {
@@ -83,6 +94,7 @@ struct GridWin<double> {
     static constexpr int64_t nodes = 1 << 21;
     static constexpr bool two = true;
     static constexpr int unit = 52;
+    static constexpr double least = 0.125;  // 3e-16 of K
 };
 
 // The tick's grid: lowest coordinates, nodes and bins along each axis, chunks.
@@ -91,6 +103,7 @@ struct GridDom {
     int32_t n[3], nb[3];
     int32_t use;      // 0: the pair kernels take the tick
     int32_t nchunks;
+    unsigned long long k2;      // kGridK2 bits: sum of |K / N|^2 in units of 2^-kb; above: blocks of the gather done
 };
 
 struct GridRec {      // a particle in its bin's order
@@ -107,8 +120,12 @@ struct GridArgs {
     int64_t P, off;                 // component stride and first slot of the system
     int32_t N, qb;                  // particles; unit 2^-qb of the node sums
     int32_t dim;                    // 3, or 2: the third coordinate is 0
+    int32_t kb;                     // unit 2^-kb of the sum of |K / N|^2
+    double k2unit;                  // 2^kb / N^2
+    int32_t nphi;                   // wavefronts of k_grid_conv
     double scale;                   // pair_scale
-    double* range;                  // [kGridRange][6]
+    double* range;                  // [kGridRange][kGridRow]
+    double* phi;                    // [nphi] parts of the sum of Phi over the particles
     GridDom* dom;
     SysDev* sys;
     uint32_t* count;                // [kGridBins], zero between ticks
@@ -190,8 +207,9 @@ inline std::vector<double> grid_table(int W, double step, long double beta)
 }
 
 // ---------------------------------------------------------------------------
-// k_grid_range: the cloud's extent, a row per block.  A coordinate that is not
-// finite leaves -infinity as its lower end.
+// k_grid_range: the cloud's extent and sums for its spread (about the first
+// particle, s_0), a row per block.  A coordinate that is not finite leaves
+// -infinity as its lower end.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double wave_min_f64(double v)
 {
@@ -200,27 +218,31 @@ __device__ __forceinline__ double wave_min_f64(double v)
     return v;
 }
 
-// lo[3], -hi[3] of a block's threads, in all of wavefront 0 .. (kBlk / 64 wavefronts)
-__device__ __forceinline__ void block_min6(double (&m)[6], double (*part)[6])
+// A row from the threads' rows, in every thread (kBlk / 64 wavefronts).
+__device__ __forceinline__ void block_row(double (&m)[kGridRow], double (*part)[kGridRow])
 {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) m[k] = wave_min_f64(m[k]);
+    for (int k = 0; k < kGridRow; ++k) m[k] = k < 6 ? wave_min_f64(m[k]) : wave_sum(m[k]);
     if (lane == 0)
 #pragma unroll
-        for (int k = 0; k < 6; ++k) part[wave][k] = m[k];
+        for (int k = 0; k < kGridRow; ++k) part[wave][k] = m[k];
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 6; ++k) m[k] = fmin(fmin(part[0][k], part[1][k]), fmin(part[2][k], part[3][k]));
+    for (int k = 0; k < kGridRow; ++k)
+        m[k] = k < 6 ? fmin(fmin(part[0][k], part[1][k]), fmin(part[2][k], part[3][k]))
+                     : (part[0][k] + part[1][k]) + (part[2][k] + part[3][k]);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kBlk) void k_grid_range(GridArgs g, const T* __restrict__ Ys)
 {
-    __shared__ double part[kBlk / 64][6];
-    double m[6];
+    __shared__ double part[kBlk / 64][kGridRow];
+    double m[kGridRow], s0[3];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) m[k] = INFINITY;
+    for (int k = 0; k < kGridRow; ++k) m[k] = k < 6 ? INFINITY : 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) s0[k] = k < g.dim ? (double)Ys[k * g.P + g.off] : 0.0;
     for (int i = blockIdx.x * kBlk + threadIdx.x; i < g.N; i += gridDim.x * kBlk)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -228,13 +250,15 @@ __global__ __launch_bounds__(kBlk) void k_grid_range(GridArgs g, const T* __rest
             const bool ok = fabs(x) < INFINITY;
             m[k] = fmin(m[k], ok ? x : -INFINITY);
             m[k + 3] = fmin(m[k + 3], ok ? -x : -INFINITY);
+            m[k + 6] += x - s0[k];
+            m[9] = fma(x - s0[k], x - s0[k], m[9]);
         }
-    block_min6(m, part);
-    if (threadIdx.x < 6) {
+    block_row(m, part);
+    if (threadIdx.x < kGridRow) {
         double v = m[0];
 #pragma unroll
-        for (int k = 1; k < 6; ++k) v = (int)threadIdx.x == k ? m[k] : v;
-        g.range[blockIdx.x * 6 + threadIdx.x] = v;
+        for (int k = 1; k < kGridRow; ++k) v = (int)threadIdx.x == k ? m[k] : v;
+        g.range[blockIdx.x * kGridRow + threadIdx.x] = v;
     }
 }
 
@@ -253,16 +277,22 @@ __device__ __forceinline__ int grid_place(double s, double lo, double* f)
 
 // The tick's grid from the blocks' ranges: the same in every block.
 template <typename T>
-__device__ __forceinline__ GridDom grid_domain(const GridArgs& g, int nrange, double (*part)[6])
+__device__ __forceinline__ GridDom grid_domain(const GridArgs& g, int nrange, double (*part)[kGridRow])
 {
     constexpr int W = GridWin<T>::W;
-    double m[6];
+    constexpr double least = GridWin<T>::least;
+    double m[kGridRow];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) m[k] = (int)threadIdx.x < nrange ? g.range[threadIdx.x * 6 + k] : INFINITY;
-    block_min6(m, part);
+    for (int k = 0; k < kGridRow; ++k)
+        m[k] = (int)threadIdx.x < nrange ? g.range[threadIdx.x * kGridRow + k] : k < 6 ? INFINITY : 0.0;
+    block_row(m, part);
     GridDom d;
     d.use = 1;
     d.nchunks = 0;
+    d.k2 = 0;
+    const double inv = 1.0 / (double)g.N;
+    const double spread2 = m[9] * inv - ((m[6] * inv) * (m[6] * inv) + (m[7] * inv) * (m[7] * inv) + (m[8] * inv) * (m[8] * inv));
+    if (!(spread2 >= least * least)) d.use = 0;  // also where it is NaN
     int64_t nodes = 1;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -288,7 +318,7 @@ __device__ __forceinline__ GridDom grid_domain(const GridArgs& g, int nrange, do
 template <typename T>
 __global__ __launch_bounds__(kBlk) void k_grid_bin(GridArgs g, int nrange, const T* __restrict__ Ys)
 {
-    __shared__ double part[kBlk / 64][6];
+    __shared__ double part[kBlk / 64][kGridRow];
     __shared__ uint32_t hist[kGridBins];
     const int i0 = blockIdx.x * (kBlk * kGridPer) + threadIdx.x;
     double s[kGridPer][3];
@@ -548,13 +578,14 @@ __global__ __launch_bounds__(GridWin<T>::wg) void k_grid_spread(GridArgs g)
 // of 4 nodes ahead, is what is left of its time.  On the vector units (4
 // outputs a thread) the three passes took 54 us at 65^3 nodes and 87 us at
 // 95^3, on it 24 and 33 us.
-// Pass 1 also clears the grid and the bins' counts for the next tick.
+// Pass 1 also clears the bins' counts for the next tick, pass 2 the grid, whose
+// product with t t t of it is the sum of Phi over the particles.
 // ---------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // A node's sum in units of 2^-qb.
 template <bool TWO>
-__device__ __forceinline__ double grid_sum(const unsigned long long* __restrict__ raw, int64_t at, int64_t nodes)
+__device__ __forceinline__ double grid_sum(const unsigned long long* raw, int64_t at, int64_t nodes)
 {
     if constexpr (TWO) return fma((double)(long long)raw[nodes + at], (double)(1ull << kGridLow), (double)(long long)raw[at]);
     else return (double)(long long)raw[at];
@@ -563,7 +594,7 @@ __device__ __forceinline__ double grid_sum(const unsigned long long* __restrict_
 template <int PASS, bool TWO>
 __global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
 {
-    constexpr int NIN = PASS + 1, NOUT = PASS == 0 ? 2 : 3, NT = 2, U = 4;
+    constexpr int NIN = PASS + 1, NOUT = PASS == 0 ? 2 : 3, NACC = PASS == 2 ? 4 : NOUT, NT = 2, U = 4;
     __shared__ double tab[4 * kGridTab];
     const GridDom d = *g.dom;
     if (!d.use) return;
@@ -576,14 +607,23 @@ __global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
     const double unit = ldexp(1.0, -g.qb);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int col = lane & 15, kk = lane >> 4;
+    double phi = 0.0;
     const int qt = (inner + 15) / 16, work = qt * ((n + 16 * NT - 1) / (16 * NT));
     for (int it = blockIdx.x * (kBlk / 64) + wave; it < work; it += gridDim.x * (kBlk / 64)) {
         const int a0 = it / qt * (16 * NT), q0 = it % qt * 16;
         const int qc = min(q0 + col, inner - 1);
         const double* t = tab + kGridTab + a0 + col - kk;
-        f64x4 acc[NOUT][NT];
+        double sum[PASS == 2 ? NT : 1][4];  // the nodes' sums, on their way meanwhile
+        if constexpr (PASS == 2) {
 #pragma unroll
-        for (int o = 0; o < NOUT; ++o)
+            for (int c = 0; c < NT; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    sum[c][r] = grid_sum<TWO>(g.grid, (int64_t)min(q0 + 4 * r + kk, inner - 1) * n + min(a0 + 16 * c + col, n - 1), nodes);
+        }
+        f64x4 acc[NACC][NT];
+#pragma unroll
+        for (int o = 0; o < NACC; ++o)
 #pragma unroll
             for (int c = 0; c < NT; ++c) acc[o][c] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
@@ -619,6 +659,7 @@ __global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
                         mul(acc[0][c], x[u][2], tv);
                         mul(acc[1][c], x[u][1], tv);
                         mul(acc[2][c], x[u][0], dv);
+                        mul(acc[3][c], x[u][0], tv);
                     }
                 }
             }
@@ -633,15 +674,72 @@ __global__ __launch_bounds__(kBlk) void k_grid_conv(GridArgs g, int64_t nodes)
                     const int q = q0 + 4 * r + kk, a = a0 + 16 * c + col;
                     if (q < inner && a < n) out[o * nodes + (int64_t)q * n + a] = PASS == 0 ? acc[o][c][r] * unit : acc[o][c][r];
                 }
+        if constexpr (PASS == 2) {
+#pragma unroll
+            for (int c = 0; c < NT; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int q = q0 + 4 * r + kk, a = a0 + 16 * c + col;
+                    if (q >= inner || a >= n) continue;
+                    const int64_t at = (int64_t)q * n + a;  // the grid's own order again; nobody else has this node
+                    phi = fma(acc[3][c][r], sum[c][r], phi);
+                    g.grid[at] = 0;
+                    if constexpr (TWO) g.grid[nodes + at] = 0;
+                }
+        }
+    }
+    if constexpr (PASS == 2) {
+        phi = wave_sum(phi);
+        if (lane == 0) g.phi[blockIdx.x * (kBlk / 64) + wave] = phi * unit;
     }
     if constexpr (PASS == 1) {
-        const int64_t used = (int64_t)n * inner;
-        for (int64_t q = (int64_t)blockIdx.x * kBlk + threadIdx.x; q < used; q += (int64_t)gridDim.x * kBlk) {
-            g.grid[q] = 0;
-            if constexpr (TWO) g.grid[nodes + q] = 0;
-        }
         const int bins = d.nb[0] * d.nb[1] * d.nb[2];
         for (int q = blockIdx.x * kBlk + threadIdx.x; q < bins; q += gridDim.x * kBlk) g.count[q] = 0;
+    }
+}
+
+// |K / N|^2 of a component in units of 2^-kb (integers: no order), K / N <= 0.52;
+// rounded as the spread rounds its values.
+__device__ __forceinline__ unsigned long long grid_k2(const GridArgs& g, double K)
+{
+    return (unsigned long long)__double_as_longlong(fma(K * K, g.k2unit, 0x1.0p52)) & ((1ull << 52) - 1);
+}
+
+// The end of the gather: the blocks' sums of grid_k2 added up, and by the last
+// of the `blocks` (< 1024) blocks the choice that the pair kernels after it read.
+// Sum and count share a word, so that one atomic and no fence orders them.
+constexpr int kGridK2 = 54;
+
+template <typename T, int WG>
+__device__ __forceinline__ void grid_judge(const GridArgs& g, unsigned long long k2, int blocks)
+{
+    __shared__ unsigned long long sums[WG / 64];
+    __shared__ double parts[WG / 64];
+    __shared__ int last;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) k2 += __shfl_xor(k2, o);
+    if (lane == 0) sums[wave] = k2;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < WG / 64; ++w) k2 += sums[w];
+        const unsigned long long was = atomicAdd(&g.dom->k2, k2 + (1ull << kGridK2));
+        last = (int)(was >> kGridK2) == blocks - 1;
+        k2 += was & ((1ull << kGridK2) - 1);
+    }
+    __syncthreads();
+    if (!last) return;
+    double p = 0.0;
+    for (int q = threadIdx.x; q < g.nphi; q += WG) p += g.phi[q];
+    p = wave_sum(p);
+    if (lane == 0) parts[wave] = p;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < WG / 64; ++w) p += parts[w];
+        const double n = (double)g.N, least = GridWin<T>::least;
+        const double kk = ldexp((double)k2, -g.kb) / n;  // mean of |K / N|^2
+        p /= n * n;                                       // mean of Phi / N
+        if (!(kk >= least * least * p * p)) g.sys->by_grid = 0;
     }
 }
 
@@ -691,6 +789,7 @@ __global__ __launch_bounds__(GridWin<float>::gather_wg) void k_grid_gather8(Grid
     const int quad = lane >> 2, odd = (quad >> 2) & 1;
     const int z = (quad & 2) * 2 + (lane & 3), grp = (__popc(quad & 7) & 1) + 2 * (lane >> 5);
     double* __restrict__ st = stage[wave] + grp * SP;
+    unsigned long long k2 = 0;
     GridNodes<W, WG, E> nd;
     double next[nd.per][3];
     GridChunk c = g.chunks[blockIdx.x];
@@ -761,10 +860,14 @@ __global__ __launch_bounds__(GridWin<float>::gather_wg) void k_grid_gather8(Grid
                 acc[k] += dpp64<kDppMirror>(acc[k]);  // the quad of the other four z
                 acc[k] += __shfl_xor(acc[k], 20);     // the other rows
             }
-            if (!odd && z < g.dim && p0 + grp < len)
-                g.out[z * g.P + g.off + r.i] = g.scale * (z == 0 ? acc[0] : z == 1 ? acc[1] : acc[2]);
+            if (!odd && z < g.dim && p0 + grp < len) {
+                const double K = z == 0 ? acc[0] : z == 1 ? acc[1] : acc[2];
+                g.out[z * g.P + g.off + r.i] = g.scale * K;
+                k2 += grid_k2(g, K);
+            }
         }
     }
+    grid_judge<float, WG>(g, k2, min((int)gridDim.x, d.nchunks));
 }
 
 // W = 16: a field at a time in 97 KB, 16 lanes a particle, one for each z.  A
@@ -782,9 +885,10 @@ __global__ __launch_bounds__(GridWin<double>::gather_wg) void k_grid_gather16(Gr
     __shared__ double tile[GridTile<double>::size];
     __shared__ double stage[WG / 64][4 * SP];
     const GridDom d = *g.dom;
-    if (!d.use) return;
+    if (!d.use || (int)blockIdx.x >= d.nchunks) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int z = lane & 15, grp = lane >> 4;
+    unsigned long long k2 = 0;
     const int tx = threadIdx.x / (E * E), ty = threadIdx.x / E % E, tz = threadIdx.x % E;
     double* __restrict__ st = stage[wave] + grp * SP;
     for (int ch = blockIdx.x; ch < d.nchunks; ch += gridDim.x) {
@@ -844,10 +948,14 @@ __global__ __launch_bounds__(GridWin<double>::gather_wg) void k_grid_gather16(Gr
                 acc += dpp64<kDppXor2>(acc);
                 acc += dpp64<kDppHalfMirror>(acc);
                 acc += dpp64<kDppMirror>(acc);
-                if (z == 0 && p < len) g.out[f * g.P + g.off + rec[p].i] = g.scale * acc;
+                if (z == 0 && p < len) {
+                    g.out[f * g.P + g.off + rec[p].i] = g.scale * acc;
+                    k2 += grid_k2(g, acc);
+                }
             }
         }
     }
+    grid_judge<double, WG>(g, k2, min((int)gridDim.x, d.nchunks));
 }
 
 }  // namespace ssm

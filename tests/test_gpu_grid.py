@@ -236,3 +236,48 @@ def test_fp64_error_does_not_grow(torch_cuda, d, N):
             out.append(_rms_error(w, x0, s.state(0), 0.5))
     print(f"[gpu-grid] d={d} N={N} FP64 relative RMS error: grid, pair kernels {['%.1e' % e for e in out]}", flush=True)
     assert out[0] <= 1e-15
+
+
+def _contracted(kind, N):
+    """Coordinates in which the grid's error, a fraction of Phi, is too large a part of K."""
+    rng = np.random.default_rng(11)
+    x = rng.normal(size=(3, N))
+    if kind == "cluster":      # one cluster of 0.034 kernel widths (scaled)
+        return 0.02 * x + np.array([[0.3], [-4.0], [1.0]])
+    x *= 1e-3
+    if kind == "two":          # two tight ones far apart
+        x[0, N // 2:] += 5.0
+    elif kind == "far":        # a tight one, and a few particles that make its spread large
+        x[1, :1000] += 2.0
+    elif kind == "near":       # two tight ones at the kernel's width: K is of its size
+        x[2, : N // 2] += 0.5
+    return x
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("kind,grid", [("cluster", False), ("two", False), ("far", False), ("near", True), ("normal", True)])
+def test_contracted_clouds(torch_cuda, precision, kind, grid):
+    """Bit for bit the pair kernels' where K is small against Phi, and not so elsewhere."""
+    N = 32768
+    w = _w(N, (1.0, 1.0, 1.0))
+    out = []
+    for kw in ({}, dict(pair_scheme="symmetric")):
+        with _ssm(w, precision, **kw) as s:
+            if kind != "normal":
+                s.set_state(0, _contracted(kind, N), step=0)
+            x0 = s.state(0)
+            s.step(1)
+            out.append(s.state(0))
+    assert np.array_equal(*out) != grid
+
+
+@pytest.mark.parametrize("std", [0.06, 0.12, 0.6])
+def test_fp64_error_of_a_contracting_cloud(torch_cuda, std):
+    """As test_fp64_error_does_not_grow: down to where the pair kernels take over 3e-16 by
+    this arithmetic on the CPU."""
+    with _ssm(_w(30000, (std,) * 3), "fp64") as s:
+        x0 = s.state(0)
+        s.step(1)
+        err = _rms_error(s, x0, s.state(0), 0.5)
+    print(f"[gpu-grid] std {std}: FP64 relative RMS error {err:.1e}", flush=True)
+    assert err <= 1e-15
