@@ -243,7 +243,8 @@ __global__ __launch_bounds__(kBlk) void k_grid_range(GridArgs g, const T* __rest
     for (int k = 0; k < kGridRow; ++k) m[k] = k < 6 ? INFINITY : 0.0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) s0[k] = k < g.dim ? (double)Ys[k * g.P + g.off] : 0.0;
-    for (int i = blockIdx.x * kBlk + threadIdx.x; i < g.N; i += gridDim.x * kBlk)
+    // in 64 bits: with up to 2^31 - 1 particles the index past the last one is not an int
+    for (int64_t i = (int64_t)blockIdx.x * kBlk + threadIdx.x; i < g.N; i += (int64_t)gridDim.x * kBlk)
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             const double x = k < g.dim ? (double)Ys[k * g.P + g.off + i] : 0.0;
@@ -311,6 +312,14 @@ __device__ __forceinline__ GridDom grid_domain(const GridArgs& g, int nrange, do
     return d;
 }
 
+// First of a thread's kGridPer particles, kBlk apart, in k_grid_bin and k_grid_scatter.
+__host__ __device__ constexpr int64_t grid_first(uint32_t block, uint32_t thread)
+{
+    return (int64_t)block * (kBlk * kGridPer) + thread;
+}
+// the last block of the largest system: none of its threads' places wraps around
+static_assert(grid_first(0x7ffffffeu / (kBlk * kGridPer), kBlk - 1) + (kGridPer - 1) * kBlk == 0x7fffffff, "");
+
 // ---------------------------------------------------------------------------
 // k_grid_bin: the particles' bins and their places in them.  A block counts
 // 1024 particles in LDS and takes its places in each bin with one addition.
@@ -320,12 +329,12 @@ __global__ __launch_bounds__(kBlk) void k_grid_bin(GridArgs g, int nrange, const
 {
     __shared__ double part[kBlk / 64][kGridRow];
     __shared__ uint32_t hist[kGridBins];
-    const int i0 = blockIdx.x * (kBlk * kGridPer) + threadIdx.x;
+    const int64_t i0 = grid_first(blockIdx.x, threadIdx.x);
     double s[kGridPer][3];
 #pragma unroll
     for (int u = 0; u < kGridPer; ++u)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) s[u][k] = k < g.dim ? (double)Ys[k * g.P + g.off + min(i0 + u * kBlk, g.N - 1)] : 0.0;
+        for (int k = 0; k < 3; ++k) s[u][k] = k < g.dim ? (double)Ys[k * g.P + g.off + min(i0 + u * kBlk, (int64_t)g.N - 1)] : 0.0;
     const GridDom d = grid_domain<T>(g, nrange, part);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *g.dom = d;
@@ -425,14 +434,14 @@ __global__ __launch_bounds__(kBlk) void k_grid_scatter(GridArgs g, const T* __re
         if (threadIdx.x == 0) g.dom->nchunks = total;
     }
     __syncthreads();
-    const int i0 = blockIdx.x * (kBlk * kGridPer) + threadIdx.x;
+    const int64_t i0 = grid_first(blockIdx.x, threadIdx.x);
 #pragma unroll
     for (int u = 0; u < kGridPer; ++u) {
-        const int i = i0 + u * kBlk;
+        const int64_t i = i0 + u * kBlk;
         if (i >= g.N) break;
         const int2 k = g.key[i];
         GridRec r;
-        r.i = i;
+        r.i = (int32_t)i;
         r.cell = 0;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
