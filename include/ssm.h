@@ -124,7 +124,8 @@ typedef struct {
                                   scheme, >= 64) or a range against a 4-block target group
                                   (symmetric, rounded up to a multiple of 16) */
     int32_t pair_scheme;       /* 0: default (d = 1 with none of targets_per_lane, sources_per_item,
-                                  jside_band_groups and kahan_span = 1 given: by modes, below; d = 3
+                                  jside_band_groups and kahan_span = 1 given, and the cloud not drawn
+                                  too wide: by modes, below; d = 3
                                   likewise with one system of 20000 particles or more, and d = 2 with
                                   one of 24000 or more from its first ssm_surrogate_enable with
                                   check_every > 0 on: by a grid, below; else symmetric where the
@@ -134,9 +135,14 @@ typedef struct {
                                   By modes: the sums over all pairs as a Fourier sum over the extent of
                                   the system's cloud, O(N) operations in double precision in every
                                   precision mode, images and truncation below the rounding of the pair
-                                  sums; a cloud too wide for its particle count (about 170 widths b_ell
-                                  for N up to 1000, 700 from N = 4096 on) or with a non-finite particle
-                                  is summed over its ordered pairs that tick.
+                                  sums.  Its time grows with the cloud's extent: a context whose x0_std
+                                  makes that slower than the pair kernels (an extent of 65 widths
+                                  b_ell at N = 1000 in FP64, 150 at 4096, 640 from 2^16 on; in the
+                                  FP32 modes 15, 55 and 800) keeps
+                                  those, whatever its cloud becomes.  A cloud that becomes too wide
+                                  later, or has a non-finite particle, is summed over its ordered pairs
+                                  that tick, two to four times slower than by the pair kernels (up to 2048
+                                  particles, in one workgroup, up to 20 times).
                                   By a grid: the sums over all pairs by a window function, a grid over
                                   the cloud's extent and convolutions along its axes, O(N) operations
                                   in double precision in every precision mode; error against the exact

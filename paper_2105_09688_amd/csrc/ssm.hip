@@ -335,6 +335,7 @@ struct ssm_ctx {
     ModeDom* dom = nullptr;         // [n_sys] the tick's domains
     double* mode_part = nullptr;    // [kModeVals / 16][mode_rows][16] (mode_at)
     double* mode_tot = nullptr;     // [n_sys][kModeVals] (mode_totals)
+    int direct_Q = 1;               // shares of the sources of direct sums
     float2* rng = nullptr;          // [nblk_tot] range of the scaled positions of each block
     bool grid_ok = false;           // one large system in two or three dimensions
     bool grid_tried = false, grid_made = false;  // its buffers
@@ -823,20 +824,22 @@ static ssm_status launch_window(ssm_ctx* c, int64_t t0, const int64_t* tdev)
     return SSM_OK;
 }
 
+static DirectRows direct_rows(const ssm_ctx* c) { return DirectRows{c->mode_part, kBlk * c->mode_P, c->direct_Q}; }
+
 // The tick's mode sums (d = 1): the partial rows, with the Brownian sums and
 // the means of mu^Y in the same launch, and their totals.
 template <typename T>
 static ssm_status launch_modes(ssm_ctx* c, int64_t ph, int64_t targ, const int64_t* tdev, bool sums_only)
 {
     const BlkItem* items = c->dblk + c->blk_off[ph];
-    const int nm = (int)c->pair_cnt[ph];
+    const int nm = (int)c->pair_cnt[ph], Q = c->direct_Q;
     const int n_main = nm + (sums_only ? 0 : (int)(c->blk_cnt[ph] * c->bm_lanes[ph]));
     const YMeanJob job{c->dsys_list + c->sys_list_off[ph],
                        c->needs_ybar && !sums_only ? (int)c->sys_list_cnt[ph] : 0, c->psumY, c->nblk_tot, c->ymean};
 #define SSM_MODES(PV, LPV, ONE)                                                                                        \
-    hipLaunchKernelGGL((k_modes<T, PV, LPV, ONE>), dim3((unsigned)(n_main + job.n)), dim3(kBlk), 0, c->stream, nm, n_main,  \
+    hipLaunchKernelGGL((k_modes<T, PV, LPV, ONE>), dim3((unsigned)(n_main + job.n + nm * (Q - 1))), dim3(kBlk), 0, c->stream, nm, Q, n_main,  \
                        c->one, (const ModeItem*)c->dmitems + c->pair_off[ph], items, c->dsys, c->coef, c->P, (const T*)c->Ys,  \
-                       (const float2*)c->rng, c->dom, c->mode_part, c->mode_rows, c->pairsum, targ, tdev,               \
+                       (const float2*)c->rng, c->dom, c->mode_part, c->mode_rows, targ, tdev,               \
                        (const double*)c->win, c->dW, job)
 #define SSM_MODES_LP(LPV)                                 \
     do {                                                  \
@@ -921,7 +924,7 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
 #define SSM_UPDATE_MODES(TOT, ONE, part)                                                                              \
     hipLaunchKernelGGL((k_update_modes<T, TOT, ONE>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, c->one, items,      \
                        c->dsys, c->coef, c->P, targ, tdev, X, Y, Ys, (const ModeDom*)c->dom, (const double*)(part),      \
-                       c->mode_rows, c->pairsum, (const double*)c->dW, (const double*)c->ymean, c->psumX, c->psumY,      \
+                       c->mode_rows, direct_rows(c), c->pairsum, (const double*)c->dW, (const double*)c->ymean, c->psumX, c->psumY,      \
                        c->nblk_tot, c->dflags, c->dnmax, c->rng)
             if (c->mode_totals) SSM_UPDATE_MODES(true, false, c->mode_tot);
             else if (c->sys.size() > 1) SSM_UPDATE_MODES(false, false, c->mode_part);
@@ -1244,7 +1247,7 @@ static int device_cus()
 // (3.93e13 lane-slots/s, about 90 % issued), 2d + 1 slots per unordered pair
 // (FP64: about 2d + 20).  Small case, FP32: 9.2 against 17.4 (measured 8.9
 // and 18.2); FP64: 19.4 against 33 (18.8 and 31.7).
-static bool small_preferred(const ssm_ctx* c)
+static void small_estimate(const ssm_ctx* c, double* pers_us, double* multi_us)
 {
     const bool f64 = c->prec == SSM_FP64;
     const double d = (double)c->d;
@@ -1258,7 +1261,58 @@ static bool small_preferred(const ssm_ctx* c)
         pers += maxN * (3.0 * d + 2.0 + (f64 ? 16.0 : 0.0)) / 1850.0;
         multi += 0.5 * sumN2 * (f64 ? 2.0 * d + 20.0 : 2.0 * d + 1.0) / 3.5e7;
     }
+    *pers_us = pers;
+    *multi_us = multi;
+}
+
+static bool small_preferred(const ssm_ctx* c)
+{
+    double pers = 0.0, multi = 0.0;
+    small_estimate(c, &pers, &multi);
     return pers < multi;
+}
+
+// Whether the mode sums are the faster for a one-dimensional context as it is
+// drawn.  The modes grow with the cloud's extent in kernel widths; by the
+// configuration, so that the way does not depend on the state and a resumed run
+// follows, that is the range of N normal draws of x0_std (Y* is no wider while
+// v pulls inward).  Tick times in microseconds, fits to one context's ticks from
+// N = 300 to 131072 and 11 to 800 modes M, both precisions within 15 %:
+//   one workgroup a system  3.4 + 0.0016 N + M (0.06 + 6.6e-5 N)
+//   two launches a tick     9 + 8e-5 N + 0.11 M (longer past 2^18 particles)
+//   pair kernels            FP64 30 + 2.9e-7 N^2, FP32 15 + 8.2e-8 N^2
+//   tiled kernel            small_estimate
+// FP32 N = 2048: 31 us at 100 modes against 12; N = 8191: 76 at 600 against 23;
+// N = 2^16: 92 at 650 against 369.
+static bool modes_pay(const ssm_ctx* c, const ssm_config* cfg, double coord_scale)
+{
+    const bool f64 = c->prec == SSM_FP64;
+    double top = 0.0, sum = 0.0, sum2 = 0.0;
+    int64_t ntiles = 0;
+    for (auto& S : c->sys) {
+        ntiles += (S.N + kSmallTile - 1) / kSmallTile;
+        top = std::max(top, (double)S.N);
+        sum += (double)S.N / (double)S.stride;
+        sum2 += (double)S.N * (double)S.N / (double)S.stride;
+    }
+    const double t = std::sqrt(2.0 * std::log(std::max(top, 2.0)));
+    const double z = std::max(0.0, t - (std::log(0.5 * t * t) + 2.531) / (2.0 * t));  // expected largest of N normals
+    const ModeLimits lim = mode_limits(f64);
+    const double m = lim.kmax / kTwoPi * (2.0 * z * std::fabs(cfg->x0_std[0]) * coord_scale + lim.gap);
+    const double M = std::ceil(m / kModeChunk) * kModeChunk;
+    const bool solo = cfg->persistent == 0 && top <= kSoloMax;
+    const double solos = std::max(1.0, (double)c->sys.size() / 256.0);
+    const double cap = solo ? solo_cap((int32_t)top, f64) : mode_cap((int32_t)top, f64);
+    if (!(m <= 0.9 * cap)) return false;  // a NaN too
+    const double by_modes = solo ? solos * (3.4 + 0.0016 * top + M * (0.06 + 6.6e-5 * top))
+                                 : 9.0 + 8e-5 * sum + 0.11 * M * std::max(1.0, sum / 262144.0);
+    double pers = 0.0, multi = 0.0;
+    small_estimate(c, &pers, &multi);
+    const double by_pairs = f64 ? 30.0 + 2.9e-7 * sum2 : 15.0 + 8.2e-8 * sum2;
+    const bool tiled = cfg->persistent >= 0 && pers < multi;
+    if (by_modes <= by_pairs && (!tiled || by_modes <= pers)) return true;
+    const bool tiled_ok = tiled && ntiles <= device_cus() && small_ineligible(c, ntiles).empty();
+    return by_modes <= (tiled_ok ? pers : by_pairs);
 }
 
 static bool small_usable(const ssm_ctx* c)
@@ -1579,6 +1633,7 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     // that both are the launches' latency
     c->modes = c->d == 1 && c->has_pair && !c->kpair && cfg->targets_per_lane == 0 && cfg->sources_per_item == 0 &&
                cfg->pair_scheme == 0 && cfg->jside_band_groups == 0;
+    if (c->modes) c->modes = modes_pay(c, cfg, cf.coord_scale);  // clouds drawn wide keep the pair kernels
     // one system in three dimensions by way of a grid, from the size on where
     // that is faster.  A tick, pair kernels against grid: FP32 N = 16384 91 and
     // 105 us, 20000 119 and 106, 2^18 14.1 ms and 225 us; FP64 N = 20000 257 and
@@ -1711,6 +1766,12 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         // every block of the update adds its system's rows; past 2^17 rows read
         // in a tick one launch more that adds them once is cheaper
         c->mode_totals = reads > 2 * 65536;
+        // direct sums on two workgroups a compute unit while the rows alone are
+        // fewer than the compute units (FP32 N = 16384 57 us with eight shares, 120
+        // with four).  From 256 rows on one share: two or four make them faster too
+        // (N = 2^16 FP32 1.62 ms, 0.66 with two; FP64 2.95 and 2.65), but their
+        // blocks cost every tick by modes 0.4 of 7 us
+        c->direct_Q = c->mode_rows < 256 ? (int)std::min<int64_t>(512 / c->mode_rows, 8 / c->mode_P) : 1;
     }
 
     // work lists per phase
@@ -2571,10 +2632,10 @@ static ssm_status launch_exact(ssm_ctx* c)
         if (st != SSM_OK) return st;
         if (c->mode_totals)
             hipLaunchKernelGGL((k_mode_eval<T, true>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,
-                               (const ModeDom*)c->dom, (const double*)c->mode_tot, c->mode_rows, c->pairsum);
+                               (const ModeDom*)c->dom, (const double*)c->mode_tot, c->mode_rows, direct_rows(c), c->pairsum);
         else
             hipLaunchKernelGGL((k_mode_eval<T, false>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,
-                               (const ModeDom*)c->dom, (const double*)c->mode_part, c->mode_rows, c->pairsum);
+                               (const ModeDom*)c->dom, (const double*)c->mode_part, c->mode_rows, direct_rows(c), c->pairsum);
         HIP_TRY(hipGetLastError());
         return SSM_OK;
     }

@@ -15,10 +15,14 @@
 // M = kmax L / (2 pi), in place of N^2 / 2 exponentials.  All of it runs in
 // double precision in every precision mode.
 //
-// A cloud that is too wide for its particle count (mode_domain), or holds a
-// particle that is not finite, is summed directly in place of its modes
-// (mode_direct): every ordered pair, as the small-system kernel does, so NaN
-// and infinities spread as they do there.
+// The modes grow with the cloud's extent, and a context whose cloud is drawn too
+// wide for them keeps the pair kernels (modes_pay in ssm.hip).  A cloud that
+// becomes too wide for its particle count later (mode_cap), or holds a particle
+// that is not finite, is summed directly in place of its modes (mode_direct):
+// every ordered pair, as the small-system kernel does, so NaN and infinities
+// spread as they do there; further blocks of k_modes, which return at once
+// otherwise, take shares of the sources where the rows alone leave compute units
+// idle.
 //
 // An exact tick is two launches: k_modes (the sums' partial rows; the Brownian
 // increments and the means of mu^Y, which do not depend on them, in further
@@ -73,19 +77,26 @@ struct ModeDom {
     int32_t M, pad;
 };
 
-// The domain of the cloud between lo and hi.  The modes' cost per particle is
-// about 12 M double operations against 3 N (FP32) to 12 N (FP64) issue slots
-// of direct sums, and N / 4 keeps a wide cloud of few particles on the
-// cheaper side; below 64 modes they always are, or both are nothing beside
-// the tick's latency.
-__device__ __forceinline__ ModeDom mode_domain(double lo, double hi, int32_t N, bool fp64)
+// Most modes that k_modes takes for a system of N particles; beyond, its direct
+// sums are the cheaper: a mode costs 0.11 us of a tick and those take, FP64 and
+// FP32, 21 and 15 us at N = 300, 38 and 27 at 4096, 66 and 42 at 8191, 190 and 57
+// at 16384, beside 9 us of both.
+__host__ __device__ constexpr int mode_cap(int32_t N, bool fp64)
+{
+    const float m = fp64 ? 190.0f + 5.5e-6f * (float)N * (float)N : 145.0f + 1.4e-6f * (float)N * (float)N;
+    const float few = N > 64 ? (float)N : 64.0f, top = m < few ? m : few;
+    return top < (float)kModeCap ? (int)top : kModeCap;
+}
+
+// The domain of the cloud between lo and hi, of at most `cap` modes.
+__device__ __forceinline__ ModeDom mode_domain(double lo, double hi, int cap, bool fp64)
 {
     const ModeLimits lim = mode_limits(fp64);
     const double L = (hi - lo) + lim.gap;
     const double m = ceil(lim.kmax / kTwoPi * L);
     ModeDom d{0.5 * (lo + hi), 1.0 / L, 0, 0};
     // an infinite range, or one that overflows, fails the comparison
-    if (m <= (double)min(kModeCap, max(64, N / 4))) d.M = ((int)m + kModeChunk - 1) / kModeChunk * kModeChunk;
+    if (m <= (double)cap) d.M = ((int)m + kModeChunk - 1) / kModeChunk * kModeChunk;
     return d;
 }
 
@@ -103,7 +114,7 @@ __device__ __forceinline__ ModeDom system_domain(const SysDev& S, const float2* 
     __syncthreads();
     lo = fminf(fminf(red[0].x, red[1].x), fminf(red[2].x, red[3].x));
     hi = fmaxf(fmaxf(red[0].y, red[1].y), fmaxf(red[2].y, red[3].y));
-    return mode_domain((double)lo, (double)hi, S.N, fp64);
+    return mode_domain((double)lo, (double)hi, mode_cap(S.N, fp64), fp64);
 }
 
 // cos and sin of 2 pi t for |t| <= 1/2: quadrant k = rint(4 t), the rest by
@@ -173,19 +184,21 @@ __device__ __forceinline__ void horner(double& pr, double& pi, double zr, double
     pr = t;
 }
 
-// The direct sum of the thread's target ys over all sources of its system, in
-// tiles of kDirectTile staged in LDS (compensated within a tile in FP32, the
-// tiles' sums added in double).
+// The direct sum of the thread's target ys over share q of Q of its system's
+// sources, in tiles of kDirectTile staged in LDS (compensated within a tile in
+// FP32, the tiles' sums added in double).
 constexpr int kDirectTile = 1024;
 
 template <typename T>
-__device__ __forceinline__ double mode_direct(const SysDev& S, const T* __restrict__ Ys, T ys, T* src)
+__device__ __forceinline__ double mode_direct(const SysDev& S, const T* __restrict__ Ys, T ys, int q, int Q, T* src)
 {
     double tot = 0.0;
-    for (int j0 = 0; j0 < S.N; j0 += kDirectTile) {
-        const int n = min(kDirectTile, S.N - j0);
+    const int64_t len = ((int64_t)S.N + Q * kBlk - 1) / (Q * kBlk) * kBlk;
+    const int64_t j1 = min((q + 1) * len, (int64_t)S.N);
+    for (int64_t j0 = q * len; j0 < j1; j0 += kDirectTile) {
+        const int n = (int)min((int64_t)kDirectTile, j1 - j0);
         __syncthreads();
-        for (int q = threadIdx.x; q < n; q += kBlk) src[q] = Ys[S.off + j0 + q];
+        for (int p = threadIdx.x; p < n; p += kBlk) src[p] = Ys[S.off + j0 + p];
         __syncthreads();
         const T yi[1] = {ys};
         T out[1];
@@ -201,7 +214,9 @@ __device__ __forceinline__ double mode_direct(const SysDev& S, const T* __restri
 // enough for the 64 modes that almost every cloud stays below; rows 16 doubles
 // further apart than that, so that two of them meet no bank twice), added in
 // a fixed order.  A system without modes gets its particles' direct sums here
-// instead, in pairsum: the kernel that evaluates also moves the particles.
+// instead, each of the Q blocks of a row its share of the sources, in the row's
+// own place (value q 256 P + j for particle j; Q P <= 8, so that they fit): the
+// kernel that evaluates also moves the particles.
 // ---------------------------------------------------------------------------
 constexpr int kRowVals = 128;
 constexpr int kModeRowsLds = kBlk / 16;  // rows of 16 lanes in a block
@@ -209,7 +224,7 @@ constexpr int kModeRowsLds = kBlk / 16;  // rows of 16 lanes in a block
 template <typename T, int P>
 __device__ __forceinline__ void mode_block(const ModeItem& it, const SysDev& S, const T* __restrict__ Ys,
                                            const float2* __restrict__ rng, ModeDom* __restrict__ dom,
-                                           double* __restrict__ part, int64_t nrows_tot, double* __restrict__ pairsum)
+                                           double* __restrict__ part, int64_t nrows_tot, int q, int Q)
 {
     __shared__ __align__(32) double rows[kModeRowsLds][kRowVals + 16];
     static_assert(sizeof(rows) >= kDirectTile * sizeof(T), "the direct sums stage their sources there");
@@ -222,17 +237,18 @@ __device__ __forceinline__ void mode_block(const ModeItem& it, const SysDev& S, 
         s[p] = Ys[S.off + it.i0 + j];
     }
     const ModeDom d = system_domain(S, rng, sizeof(T) == 8, red);
-    if (it.row == S.mode_row0 && threadIdx.x == 0) dom[it.sys] = d;
+    if (q == 0 && it.row == S.mode_row0 && threadIdx.x == 0) dom[it.sys] = d;
     if (d.M == 0) {  // block-uniform
 #pragma unroll 1
         for (int p = 0; p < P; ++p) {
             const int j = p * kBlk + (int)threadIdx.x;
             const T ys = j < it.n ? Ys[S.off + it.i0 + j] : (T)0;
-            const double K = mode_direct(S, Ys, ys, reinterpret_cast<T*>(&rows[0][0]));
-            if (j < it.n) pairsum[S.off + it.i0 + j] = K * S.pair_scale;
+            const double K = mode_direct(S, Ys, ys, q, Q, reinterpret_cast<T*>(&rows[0][0]));
+            if (j < it.n) part[mode_at(it.row, q * kBlk * P + j, nrows_tot)] = K;
         }
         return;
     }
+    if (q > 0) return;
     double zr[P], zi[P], wr[P], wi[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
@@ -257,25 +273,27 @@ __device__ __forceinline__ void mode_block(const ModeItem& it, const SysDev& S, 
     }
 }
 
-// n_modes blocks of mode sums, then (up to n_main) the Brownian sums, then
-// job.n blocks of system means.
+// n_modes blocks of mode sums, then (up to n_main) the Brownian sums, then job.n
+// blocks of system means, then n_modes (Q - 1) for the further shares of direct
+// sums.
 template <typename T, int P, int LP, bool ONE>
-__global__ __launch_bounds__(kBlk) void k_modes(int n_modes, int n_main, SysDev one, const ModeItem* __restrict__ mitems,
+__global__ __launch_bounds__(kBlk) void k_modes(int n_modes, int Q, int n_main, SysDev one, const ModeItem* __restrict__ mitems,
                                                 const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
                                                 Coef cf, int64_t Pn, const T* __restrict__ Ys,
                                                 const float2* __restrict__ rng, ModeDom* __restrict__ dom,
                                                 double* __restrict__ part, int64_t nrows_tot,
-                                                double* __restrict__ pairsum, int64_t tick_arg, const int64_t* __restrict__ tick_dev,
+                                                int64_t tick_arg, const int64_t* __restrict__ tick_dev,
                                                 const double* __restrict__ win, double* __restrict__ dW, YMeanJob job)
 {
-    if ((int)blockIdx.x < n_modes) {
+    const int more = (int)blockIdx.x - (n_main + job.n);
+    if ((int)blockIdx.x < n_modes || more >= 0) {
+        const int q = more >= 0 ? 1 + more / n_modes : 0, row = more >= 0 ? more % n_modes : (int)blockIdx.x;
         if constexpr (ONE) {
-            const int i0 = (int)blockIdx.x * kBlk * P;
-            mode_block<T, P>(ModeItem{0, (int)blockIdx.x, i0, min(kBlk * P, one.N - i0)}, one, Ys, rng, dom, part,
-                             nrows_tot, pairsum);
+            const int i0 = row * kBlk * P;
+            mode_block<T, P>(ModeItem{0, row, i0, min(kBlk * P, one.N - i0)}, one, Ys, rng, dom, part, nrows_tot, q, Q);
         } else {
-            const ModeItem it = mitems[blockIdx.x];
-            mode_block<T, P>(it, sys[it.sys], Ys, rng, dom, part, nrows_tot, pairsum);
+            const ModeItem it = mitems[row];
+            mode_block<T, P>(it, sys[it.sys], Ys, rng, dom, part, nrows_tot, q, Q);
         }
     } else if ((int)blockIdx.x < n_main)
         brownian_block<1, LP, (sizeof(T) == 4)>(blockIdx.x - n_modes, items, sys, cf, Pn, tick_arg, tick_dev, win, dW);
@@ -417,10 +435,27 @@ struct ModeLds {
     double stage[TOTALS ? 1 : kBlk / 16][kCoefVals];
 };
 
+// Where the direct sums of a context lie: its partial rows, of `per` particles,
+// Q shares each.
+struct DirectRows {
+    const double* part;
+    int per, Q;
+};
+
+// The scaled pair term of particle i of a system without modes: the shares added up.
+__device__ __forceinline__ double direct_pair(const DirectRows& dr, const SysDev& S, int i, int64_t nrows_tot)
+{
+    const int row = i / dr.per, j = i - row * dr.per;
+    double K = 0.0;
+    for (int q = 0; q < dr.Q; ++q) K += dr.part[mode_at(S.mode_row0 + row, q * dr.per + j, nrows_tot)];
+    return K * S.pair_scale;
+}
+
 template <typename T, bool TOTALS>
 __device__ __forceinline__ double mode_pair(const BlkItem it, const SysDev& S, const T* __restrict__ Ys,
                                             const ModeDom* __restrict__ dom, const double* __restrict__ part,
-                                            int64_t nrows_tot, double* __restrict__ pairsum, ModeLds<TOTALS>& lds)
+                                            int64_t nrows_tot, const DirectRows& dr,
+                                            double* __restrict__ pairsum, ModeLds<TOTALS>& lds)
 {
     const int i = it.blk * kBlk + threadIdx.x;
     const int64_t at = S.off + min(i, S.N - 1);
@@ -430,7 +465,11 @@ __device__ __forceinline__ double mode_pair(const BlkItem it, const SysDev& S, c
     if constexpr (TOTALS) {
         const double* row = part + (int64_t)it.sys * kModeVals;
         double a = row[threadIdx.x];
-        if (d.M == 0) return pairsum[at];  // block-uniform
+        if (d.M == 0) {  // block-uniform
+            const double K = direct_pair(dr, S, min(i, S.N - 1), nrows_tot);
+            if (i < S.N) pairsum[at] = K;
+            return K;
+        }
         for (int v = threadIdx.x; v < 2 * d.M; v += kBlk) {
             if (v >= kBlk) a = row[v];
             mode_coef(d, v, a, lds.g);
@@ -439,7 +478,11 @@ __device__ __forceinline__ double mode_pair(const BlkItem it, const SysDev& S, c
         __syncthreads();
     } else {
         const RowBatch first = row_batch(part, nrows_tot, S, 0, threadIdx.x >> 4);
-        if (d.M == 0) return pairsum[at];
+        if (d.M == 0) {
+            const double K = direct_pair(dr, S, min(i, S.N - 1), nrows_tot);
+            if (i < S.N) pairsum[at] = K;
+            return K;
+        }
         sincos_turn(((double)ys - d.c) * d.inv_L, &zi, &zr);
         mode_coefs(d, part, nrows_tot, S, first, lds.g, lds.stage);
     }
@@ -462,6 +505,7 @@ __global__ __launch_bounds__(kBlk) void k_update_modes(SysDev one, const BlkItem
                                                        const int64_t* __restrict__ tick_dev, T* __restrict__ X,
                                                        T* __restrict__ Y, T* Ys, const ModeDom* __restrict__ dom,
                                                        const double* __restrict__ part, int64_t nrows_tot,
+                                                       DirectRows dr,
                                                        double* __restrict__ pairsum, const double* __restrict__ dWbuf,
                                                        const double* __restrict__ ymean, double* __restrict__ psumX,
                                                        double* __restrict__ psumY, int64_t nblk_tot, Flags* flags,
@@ -474,7 +518,7 @@ __global__ __launch_bounds__(kBlk) void k_update_modes(SysDev one, const BlkItem
     const int i = it.blk * kBlk + threadIdx.x;
     const UpdateIn<1> u = load_update<T, 1>(it.sys, S.off + min(i, S.N - 1), P, Y, dWbuf, ymean);
     touch_coefs(cf);
-    const double pair[1] = {mode_pair<T, TOTALS>(it, S, Ys, dom, part, nrows_tot, pairsum, lds)};
+    const double pair[1] = {mode_pair<T, TOTALS>(it, S, Ys, dom, part, nrows_tot, dr, pairsum, lds)};
     const int64_t n = step_of(tick_of(tick_dev, tick_arg), S.stride);
     update_block<T, 1>(it, S, cf, P, n, pair, u, X, Y, Ys, psumX, psumY, nblk_tot, flags, nmax, rng, red);
 }
@@ -484,11 +528,12 @@ template <typename T, bool TOTALS>
 __global__ __launch_bounds__(kBlk) void k_mode_eval(const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
                                                     const T* __restrict__ Ys, const ModeDom* __restrict__ dom,
                                                     const double* __restrict__ part, int64_t nrows_tot,
+                                                    DirectRows dr,
                                                     double* __restrict__ pairsum)
 {
     __shared__ __align__(16) ModeLds<TOTALS> lds;
     const BlkItem it = items[blockIdx.x];
-    (void)mode_pair<T, TOTALS>(it, sys[it.sys], Ys, dom, part, nrows_tot, pairsum, lds);
+    (void)mode_pair<T, TOTALS>(it, sys[it.sys], Ys, dom, part, nrows_tot, dr, pairsum, lds);
 }
 
 }  // namespace ssm
