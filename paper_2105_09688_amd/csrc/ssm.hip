@@ -330,6 +330,7 @@ struct ssm_ctx {
     bool modes = false;             // exact ticks use them in place of the pair kernels
     int mode_P = 1;                 // particles per thread of a partial row
     int64_t mode_rows = 0;          // partial rows of all systems
+    bool mode_wide = false;         // FP64, drawn wide: its powers are anchored (kModePlain)
     bool mode_totals = false;       // the rows are added up by k_mode_total
     ModeItem* dmitems = nullptr;    // per phase (pair_off / pair_cnt)
     ModeDom* dom = nullptr;         // [n_sys] the tick's domains
@@ -836,11 +837,16 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, int64_t targ, const int64
     const int n_main = nm + (sums_only ? 0 : (int)(c->blk_cnt[ph] * c->bm_lanes[ph]));
     const YMeanJob job{c->dsys_list + c->sys_list_off[ph],
                        c->needs_ybar && !sums_only ? (int)c->sys_list_cnt[ph] : 0, c->psumY, c->nblk_tot, c->ymean};
-#define SSM_MODES(PV, LPV, ONE)                                                                                        \
-    hipLaunchKernelGGL((k_modes<T, PV, LPV, ONE>), dim3((unsigned)(n_main + job.n + nm * (Q - 1))), dim3(kBlk), 0, c->stream, nm, Q, n_main,  \
+#define SSM_MODES_K(KERNEL)                                                                                            \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)(n_main + job.n + nm * (Q - 1))), dim3(kBlk), 0, c->stream, nm, Q, n_main,  \
                        c->one, (const ModeItem*)c->dmitems + c->pair_off[ph], items, c->dsys, c->coef, c->P, (const T*)c->Ys,  \
                        (const float2*)c->rng, c->dom, c->mode_part, c->mode_rows, targ, tdev,               \
                        (const double*)c->win, c->dW, job)
+#define SSM_MODES(PV, LPV, ONE)                                                            \
+    do {                                                                                   \
+        if (c->mode_wide) { SSM_MODES_K((k_modes<T, PV, LPV, ONE, sizeof(T) == 8>)); }     \
+        else { SSM_MODES_K((k_modes<T, PV, LPV, ONE, false>)); }                           \
+    } while (0)
 #define SSM_MODES_LP(LPV)                                 \
     do {                                                  \
         if (c->mode_P == 4) { SSM_MODES(4, LPV, false); } \
@@ -856,6 +862,7 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, int64_t targ, const int64
     }
 #undef SSM_MODES_LP
 #undef SSM_MODES
+#undef SSM_MODES_K
     HIP_TRY(hipGetLastError());
     if (c->mode_totals) {
         hipLaunchKernelGGL(k_mode_total, dim3((unsigned)c->sys_list_cnt[ph], 4), dim3(kBlk), 0, c->stream,
@@ -921,8 +928,13 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
         }
         const BlkItem* items = c->dblk + c->blk_off[ph];
         if (c->modes && run_exact) {
-#define SSM_UPDATE_MODES(TOT, ONE, part)                                                                              \
-    hipLaunchKernelGGL((k_update_modes<T, TOT, ONE>), dim3((unsigned)nb), dim3(kBlk), 0, c->stream, c->one, items,      \
+#define SSM_UPDATE_MODES(TOT, ONE, part)                                                                               \
+    do {                                                                                                               \
+        if (c->mode_wide) { SSM_UPDATE_MODES_K((k_update_modes<T, TOT, ONE, sizeof(T) == 8>), part); }                 \
+        else { SSM_UPDATE_MODES_K((k_update_modes<T, TOT, ONE, false>), part); }                                       \
+    } while (0)
+#define SSM_UPDATE_MODES_K(KERNEL, part)                                                                              \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)nb), dim3(kBlk), 0, c->stream, c->one, items,      \
                        c->dsys, c->coef, c->P, targ, tdev, X, Y, Ys, (const ModeDom*)c->dom, (const double*)(part),      \
                        c->mode_rows, direct_rows(c), c->pairsum, (const double*)c->dW, (const double*)c->ymean, c->psumX, c->psumY,      \
                        c->nblk_tot, c->dflags, c->dnmax, c->rng)
@@ -930,6 +942,7 @@ static ssm_status launch_tick(ssm_ctx* c, const int64_t* tdev, int64_t off)
             else if (c->sys.size() > 1) SSM_UPDATE_MODES(false, false, c->mode_part);
             else SSM_UPDATE_MODES(false, true, c->mode_part);
 #undef SSM_UPDATE_MODES
+#undef SSM_UPDATE_MODES_K
             HIP_TRY(hipGetLastError());
         } else {
             // Brownian sums of the step, and on exact ticks the combine of the pair
@@ -1272,7 +1285,7 @@ static bool small_preferred(const ssm_ctx* c)
     return pers < multi;
 }
 
-// Whether the mode sums are the faster for a one-dimensional context as it is
+// Whether (and how: mode_wide) the mode sums are the faster for a one-dimensional context as it is
 // drawn.  The modes grow with the cloud's extent in kernel widths; by the
 // configuration, so that the way does not depend on the state and a resumed run
 // follows, that is the range of N normal draws of x0_std (Y* is no wider while
@@ -1284,7 +1297,7 @@ static bool small_preferred(const ssm_ctx* c)
 //   tiled kernel            small_estimate
 // FP32 N = 2048: 31 us at 100 modes against 12; N = 8191: 76 at 600 against 23;
 // N = 2^16: 92 at 650 against 369.
-static bool modes_pay(const ssm_ctx* c, const ssm_config* cfg, double coord_scale)
+static bool modes_pay(ssm_ctx* c, const ssm_config* cfg, double coord_scale)
 {
     const bool f64 = c->prec == SSM_FP64;
     double top = 0.0, sum = 0.0, sum2 = 0.0;
@@ -1300,6 +1313,7 @@ static bool modes_pay(const ssm_ctx* c, const ssm_config* cfg, double coord_scal
     const ModeLimits lim = mode_limits(f64);
     const double m = lim.kmax / kTwoPi * (2.0 * z * std::fabs(cfg->x0_std[0]) * coord_scale + lim.gap);
     const double M = std::ceil(m / kModeChunk) * kModeChunk;
+    c->mode_wide = f64 && M > 0.5 * kModePlain;
     const bool solo = cfg->persistent == 0 && top <= kSoloMax;
     const double solos = std::max(1.0, (double)c->sys.size() / 256.0);
     const double cap = solo ? solo_cap((int32_t)top, f64) : mode_cap((int32_t)top, f64);
@@ -1356,15 +1370,16 @@ static ssm_status launch_solo(ssm_ctx* c, int64_t n)
     for (auto& S : c->sys) top = std::max(top, S.N);
     // the fewest threads of up to four particles: each wavefront's reductions
     // then serve 256 particles
-#define SSM_SOLO(PAIR)                                                                                           \
+#define SSM_SOLO(PAIR, WIDE)                                                                                     \
     do {                                                                                                         \
-        if (top <= 256) hipLaunchKernelGGL((k_solo<T, PAIR, 256, 1>), g, dim3(256), 0, c->stream, a);            \
-        else if (top <= 512) hipLaunchKernelGGL((k_solo<T, PAIR, 256, 2>), g, dim3(256), 0, c->stream, a);       \
-        else if (top <= 1024) hipLaunchKernelGGL((k_solo<T, PAIR, 256, 4>), g, dim3(256), 0, c->stream, a);      \
-        else hipLaunchKernelGGL((k_solo<T, PAIR, 512, 4>), g, dim3(512), 0, c->stream, a);                       \
+        if (top <= 256) hipLaunchKernelGGL((k_solo<T, PAIR, 256, 1, WIDE>), g, dim3(256), 0, c->stream, a);      \
+        else if (top <= 512) hipLaunchKernelGGL((k_solo<T, PAIR, 256, 2, WIDE>), g, dim3(256), 0, c->stream, a); \
+        else if (top <= 1024) hipLaunchKernelGGL((k_solo<T, PAIR, 256, 4, WIDE>), g, dim3(256), 0, c->stream, a); \
+        else hipLaunchKernelGGL((k_solo<T, PAIR, 512, 4, WIDE>), g, dim3(512), 0, c->stream, a);                 \
     } while (0)
-    if (c->has_pair) SSM_SOLO(true);
-    else SSM_SOLO(false);
+    if (!c->has_pair) SSM_SOLO(false, false);
+    else if (c->mode_wide) SSM_SOLO(true, (sizeof(T) == 8));
+    else SSM_SOLO(true, false);
 #undef SSM_SOLO
     HIP_TRY(hipGetLastError());
     return SSM_OK;
@@ -2631,10 +2646,10 @@ static ssm_status launch_exact(ssm_ctx* c)
         ssm_status st = launch_modes<T>(c, 0, c->tick, nullptr, true);
         if (st != SSM_OK) return st;
         if (c->mode_totals)
-            hipLaunchKernelGGL((k_mode_eval<T, true>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,
+            hipLaunchKernelGGL((k_mode_eval<T, true, sizeof(T) == 8>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,
                                (const ModeDom*)c->dom, (const double*)c->mode_tot, c->mode_rows, direct_rows(c), c->pairsum);
         else
-            hipLaunchKernelGGL((k_mode_eval<T, false>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,
+            hipLaunchKernelGGL((k_mode_eval<T, false, sizeof(T) == 8>), dim3(nb), dim3(kBlk), 0, c->stream, items, c->dsys, (const T*)c->Ys,
                                (const ModeDom*)c->dom, (const double*)c->mode_part, c->mode_rows, direct_rows(c), c->pairsum);
         HIP_TRY(hipGetLastError());
         return SSM_OK;

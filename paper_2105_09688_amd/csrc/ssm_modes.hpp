@@ -145,6 +145,34 @@ __device__ __forceinline__ void sincos_turn(double t, double* sn, double* cs)
     *cs = ((q + 1) & 2) ? -b : b;
 }
 
+// A particle's place on the domain in turns, hi + lo: the phase of mode m is m
+// times that, exact to the roundings of the last product.
+struct Turn {
+    double hi, lo;
+};
+
+__device__ __forceinline__ Turn mode_turn(double s, const ModeDom& d)
+{
+    const double x = s - d.c, b = x - s, xl = (s - (x - b)) - (d.c + b);  // x + xl = s - c
+    const double t = x * d.inv_L;
+    return Turn{t, fma(x, d.inv_L, -t) + xl * d.inv_L};
+}
+
+// e^(2 pi i m t).  The powers of a particle's e^(2 pi i t) by repeated products
+// carry its rounding m times: FP64 clouds of more than kModePlain modes take
+// every kModeAnchor-th power from here, in the sums and in the evaluation
+// (relative RMS error at 536 modes 5.5e-15 without, 6.4e-16 with, sums over
+// pairs 2.2e-16; at 80 modes 2e-16 in either case).  Only in the kernels of
+// contexts whose cloud is drawn wider than half of that (WIDE): their code costs
+// a tick of narrow ones 0.4 of 7 us.
+constexpr int kModePlain = 64, kModeAnchor = 16;
+
+__device__ __forceinline__ void mode_power(const Turn& t, int m, double* im, double* re)
+{
+    const double k = (double)m;
+    sincos_turn(fma(k, t.lo, fma(k, t.hi, -rint(k * t.hi))), im, re);
+}
+
 // (re, im) = (re, im) z
 __device__ __forceinline__ void rotate(double& re, double& im, double zr, double zi)
 {
@@ -174,6 +202,33 @@ __device__ __forceinline__ double mode_chunk(double (&wr)[P], double (&wi)[P], c
         for (int p = 0; p < P; ++p) rotate(wr[p], wi[p], zr[p], zi[p]);
     }
     return row_scatter(acc);
+}
+
+// The modes from value v0 on up to v1 (kModeChunk values of a pair of 16) of a
+// block's particles into their rows of lanes.  ANCHOR: with the powers of
+// mode_power; `in(p)` says whether the thread has a particle p, place(p) where.
+template <int P, bool ANCHOR, typename Row, typename In, typename Place>
+__device__ __forceinline__ void mode_values(int v0, int v1, const ModeDom& d, double (&wr)[P], double (&wi)[P],
+                                            const double (&zr)[P], const double (&zi)[P], Row&& row, In&& in, Place&& place)
+{
+    for (int v = v0; v < v1; v += 2 * kModeChunk) {
+        if constexpr (ANCHOR) {
+            if (v > 0 && v % (2 * kModeAnchor) == 0) {
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+                    if (in(p)) mode_power(mode_turn(place(p), d), v / 2 + 1, &wi[p], &wr[p]);
+            }
+        }
+        row(v - v0 + (threadIdx.x & 15)) = mode_chunk<P>(wr, wi, zr, zi);
+    }
+}
+
+// Whether a system takes the anchored forms.
+template <typename T, bool WIDE>
+__device__ __forceinline__ bool mode_anchored(const ModeDom& d)
+{
+    static_assert(!WIDE || sizeof(T) == 8, "FP32 modes: the plain powers are exact enough");
+    return WIDE && d.M > kModePlain;
 }
 
 // p = p z + g
@@ -221,7 +276,7 @@ __device__ __forceinline__ double mode_direct(const SysDev& S, const T* __restri
 constexpr int kRowVals = 128;
 constexpr int kModeRowsLds = kBlk / 16;  // rows of 16 lanes in a block
 
-template <typename T, int P>
+template <typename T, int P, bool WIDE>
 __device__ __forceinline__ void mode_block(const ModeItem& it, const SysDev& S, const T* __restrict__ Ys,
                                            const float2* __restrict__ rng, ModeDom* __restrict__ dom,
                                            double* __restrict__ part, int64_t nrows_tot, int q, int Q)
@@ -253,15 +308,18 @@ __device__ __forceinline__ void mode_block(const ModeItem& it, const SysDev& S, 
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const bool valid = p * kBlk + (int)threadIdx.x < it.n;
-        sincos_turn(((double)s[p] - d.c) * d.inv_L, &zi[p], &zr[p]);
+        if (mode_anchored<T, WIDE>(d)) mode_power(mode_turn((double)s[p], d), 1, &zi[p], &zr[p]);
+        else sincos_turn(((double)s[p] - d.c) * d.inv_L, &zi[p], &zr[p]);
         wr[p] = valid ? zr[p] : 0.0;
         wi[p] = valid ? zi[p] : 0.0;
     }
     for (int v0 = 0; v0 < 2 * d.M; v0 += kRowVals) {
         const int v1 = min(v0 + kRowVals, 2 * d.M);
-        for (int v = v0; v < v1; v += 2 * kModeChunk) {
-            rows[threadIdx.x >> 4][v - v0 + (threadIdx.x & 15)] = mode_chunk<P>(wr, wi, zr, zi);
-        }
+        auto row = [&](int v) -> double& { return rows[threadIdx.x >> 4][v]; };
+        auto in = [&](int p) { return p * kBlk + (int)threadIdx.x < it.n; };
+        auto place = [&](int p) { return (double)s[p]; };
+        if (mode_anchored<T, WIDE>(d)) mode_values<P, WIDE>(v0, v1, d, wr, wi, zr, zi, row, in, place);
+        else mode_values<P, false>(v0, v1, d, wr, wi, zr, zi, row, in, place);
         __syncthreads();
         for (int v = threadIdx.x; v < v1 - v0; v += kBlk) {
             double t = 0.0;
@@ -276,7 +334,7 @@ __device__ __forceinline__ void mode_block(const ModeItem& it, const SysDev& S, 
 // n_modes blocks of mode sums, then (up to n_main) the Brownian sums, then job.n
 // blocks of system means, then n_modes (Q - 1) for the further shares of direct
 // sums.
-template <typename T, int P, int LP, bool ONE>
+template <typename T, int P, int LP, bool ONE, bool WIDE>
 __global__ __launch_bounds__(kBlk) void k_modes(int n_modes, int Q, int n_main, SysDev one, const ModeItem* __restrict__ mitems,
                                                 const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
                                                 Coef cf, int64_t Pn, const T* __restrict__ Ys,
@@ -290,10 +348,10 @@ __global__ __launch_bounds__(kBlk) void k_modes(int n_modes, int Q, int n_main, 
         const int q = more >= 0 ? 1 + more / n_modes : 0, row = more >= 0 ? more % n_modes : (int)blockIdx.x;
         if constexpr (ONE) {
             const int i0 = row * kBlk * P;
-            mode_block<T, P>(ModeItem{0, row, i0, min(kBlk * P, one.N - i0)}, one, Ys, rng, dom, part, nrows_tot, q, Q);
+            mode_block<T, P, WIDE>(ModeItem{0, row, i0, min(kBlk * P, one.N - i0)}, one, Ys, rng, dom, part, nrows_tot, q, Q);
         } else {
             const ModeItem it = mitems[row];
-            mode_block<T, P>(it, sys[it.sys], Ys, rng, dom, part, nrows_tot, q, Q);
+            mode_block<T, P, WIDE>(it, sys[it.sys], Ys, rng, dom, part, nrows_tot, q, Q);
         }
     } else if ((int)blockIdx.x < n_main)
         brownian_block<1, LP, (sizeof(T) == 4)>(blockIdx.x - n_modes, items, sys, cf, Pn, tick_arg, tick_dev, win, dW);
@@ -415,13 +473,51 @@ __device__ __forceinline__ void mode_coefs(const ModeDom& d, const double* __res
     }
 }
 
-// sum_m Re(g_m z^m) by Horner's rule.
-__device__ __forceinline__ double mode_eval(int M, const double2* g, double zr, double zi)
+// sum_m Re(g_m z^m) of P particles by Horner's rule; mode_eval_anchored: in
+// pieces that begin at the powers of mode_power.
+template <int P>
+__device__ __forceinline__ void mode_eval(int M, const double2* g, const double (&zr)[P], const double (&zi)[P], double (&K)[P])
 {
-    double pr = 0.0, pi = 0.0;
-#pragma unroll 8
-    for (int m = M - 1; m >= 0; --m) horner(pr, pi, zr, zi, g[m]);
-    return fma(pr, zr, -pi * zi);
+    double pr[P], pi[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) pr[p] = pi[p] = 0.0;
+    constexpr int kUnrolled = P == 1 ? 8 : 4;
+#pragma unroll kUnrolled
+    for (int m = M - 1; m >= 0; --m) {
+        const double2 gm = g[m];
+#pragma unroll
+        for (int p = 0; p < P; ++p) horner(pr[p], pi[p], zr[p], zi[p], gm);
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) K[p] = fma(pr[p], zr[p], -pi[p] * zi[p]);
+}
+
+template <int P>
+__device__ __forceinline__ void mode_eval_anchored(const ModeDom& d, const double2* g, const double (&s)[P],
+                                                   double (&K)[P])
+{
+    double zr[P], zi[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        mode_power(mode_turn(s[p], d), 1, &zi[p], &zr[p]);
+        K[p] = 0.0;
+    }
+    for (int a = 0; a < d.M; a += kModeAnchor) {
+        double pr[P], pi[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) pr[p] = pi[p] = 0.0;
+        for (int m = min(a + kModeAnchor, d.M) - 1; m >= a; --m) {
+            const double2 gm = g[m];
+#pragma unroll
+            for (int p = 0; p < P; ++p) horner(pr[p], pi[p], zr[p], zi[p], gm);
+        }
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            double wr, wi;
+            mode_power(mode_turn(s[p], d), a + 1, &wi, &wr);
+            K[p] += fma(pr[p], wr, -pi[p] * wi);
+        }
+    }
 }
 
 // The scaled pair term of one block's particles (each thread its own), from
@@ -451,7 +547,7 @@ __device__ __forceinline__ double direct_pair(const DirectRows& dr, const SysDev
     return K * S.pair_scale;
 }
 
-template <typename T, bool TOTALS>
+template <typename T, bool TOTALS, bool WIDE>
 __device__ __forceinline__ double mode_pair(const BlkItem it, const SysDev& S, const T* __restrict__ Ys,
                                             const ModeDom* __restrict__ dom, const double* __restrict__ part,
                                             int64_t nrows_tot, const DirectRows& dr,
@@ -486,7 +582,11 @@ __device__ __forceinline__ double mode_pair(const BlkItem it, const SysDev& S, c
         sincos_turn(((double)ys - d.c) * d.inv_L, &zi, &zr);
         mode_coefs(d, part, nrows_tot, S, first, lds.g, lds.stage);
     }
-    const double K = mode_eval(d.M, lds.g, zr, zi) * S.pair_scale;
+    const double z0[1] = {zr}, z1[1] = {zi}, s0[1] = {(double)ys};
+    double k0[1];
+    if (mode_anchored<T, WIDE>(d)) mode_eval_anchored<1>(d, lds.g, s0, k0);
+    else mode_eval<1>(d.M, lds.g, z0, z1, k0);
+    const double K = k0[0] * S.pair_scale;
     if (i < S.N) pairsum[at] = K;
     return K;
 }
@@ -499,7 +599,7 @@ __device__ __forceinline__ double mode_pair(const BlkItem it, const SysDev& S, c
 // its own clock it took 15500 cycles, of which 7700 until the rows had
 // arrived, in six waits one after the other; 2700 in the implicit solve; 1100
 // in the block's reductions.  Every load is issued before the first wait now.
-template <typename T, bool TOTALS, bool ONE>
+template <typename T, bool TOTALS, bool ONE, bool WIDE>
 __global__ __launch_bounds__(kBlk) void k_update_modes(SysDev one, const BlkItem* __restrict__ items,
                                                        const SysDev* __restrict__ sys, Coef cf, int64_t P, int64_t tick_arg,
                                                        const int64_t* __restrict__ tick_dev, T* __restrict__ X,
@@ -518,13 +618,13 @@ __global__ __launch_bounds__(kBlk) void k_update_modes(SysDev one, const BlkItem
     const int i = it.blk * kBlk + threadIdx.x;
     const UpdateIn<1> u = load_update<T, 1>(it.sys, S.off + min(i, S.N - 1), P, Y, dWbuf, ymean);
     touch_coefs(cf);
-    const double pair[1] = {mode_pair<T, TOTALS>(it, S, Ys, dom, part, nrows_tot, dr, pairsum, lds)};
+    const double pair[1] = {mode_pair<T, TOTALS, WIDE>(it, S, Ys, dom, part, nrows_tot, dr, pairsum, lds)};
     const int64_t n = step_of(tick_of(tick_dev, tick_arg), S.stride);
     update_block<T, 1>(it, S, cf, P, n, pair, u, X, Y, Ys, psumX, psumY, nblk_tot, flags, nmax, rng, red);
 }
 
 // k_mode_eval: the pair term alone into pairsum (the training sampler).
-template <typename T, bool TOTALS>
+template <typename T, bool TOTALS, bool WIDE>
 __global__ __launch_bounds__(kBlk) void k_mode_eval(const BlkItem* __restrict__ items, const SysDev* __restrict__ sys,
                                                     const T* __restrict__ Ys, const ModeDom* __restrict__ dom,
                                                     const double* __restrict__ part, int64_t nrows_tot,
@@ -533,7 +633,7 @@ __global__ __launch_bounds__(kBlk) void k_mode_eval(const BlkItem* __restrict__ 
 {
     __shared__ __align__(16) ModeLds<TOTALS> lds;
     const BlkItem it = items[blockIdx.x];
-    (void)mode_pair<T, TOTALS>(it, sys[it.sys], Ys, dom, part, nrows_tot, dr, pairsum, lds);
+    (void)mode_pair<T, TOTALS, WIDE>(it, sys[it.sys], Ys, dom, part, nrows_tot, dr, pairsum, lds);
 }
 
 }  // namespace ssm

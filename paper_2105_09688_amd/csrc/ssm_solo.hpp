@@ -109,7 +109,7 @@ __device__ __forceinline__ int solo_solve(const SysDev& S, const Coef& cf, const
     return top;
 }
 
-template <typename T, bool PAIR, int WG, int P>
+template <typename T, bool PAIR, int WG, int P, bool WIDE>
 __global__ __launch_bounds__(WG) void k_solo(SoloArgs<T> a)
 {
     constexpr int kRows = WG / 16, kW = WG / 64;
@@ -222,14 +222,18 @@ __global__ __launch_bounds__(WG) void k_solo(SoloArgs<T> a)
                 double zr[P], zi[P], wr[P], wi[P];
 #pragma unroll
                 for (int p = 0; p < P; ++p) {
-                    sincos_turn((ys[p] - d.c) * d.inv_L, &zi[p], &zr[p]);
+                    if (mode_anchored<T, WIDE>(d)) mode_power(mode_turn(ys[p], d), 1, &zi[p], &zr[p]);
+                    else sincos_turn((ys[p] - d.c) * d.inv_L, &zi[p], &zr[p]);
                     wr[p] = valid[p] ? zr[p] : 0.0;
                     wi[p] = valid[p] ? zi[p] : 0.0;
                 }
                 for (int v0 = 0; v0 < 2 * d.M; v0 += kRowVals) {
                     const int v1 = min(v0 + kRowVals, 2 * d.M);
-                    for (int v = v0; v < v1; v += 2 * kModeChunk)
-                        rows[threadIdx.x >> 4][v - v0 + (threadIdx.x & 15)] = mode_chunk<P>(wr, wi, zr, zi);
+                    auto row = [&](int v) -> double& { return rows[threadIdx.x >> 4][v]; };
+                    auto in = [&](int p) { return valid[p]; };
+                    auto place = [&](int p) { return ys[p]; };
+                    if (mode_anchored<T, WIDE>(d)) mode_values<P, WIDE>(v0, v1, d, wr, wi, zr, zi, row, in, place);
+                    else mode_values<P, false>(v0, v1, d, wr, wi, zr, zi, row, in, place);
                     __syncthreads();
                     for (int v = threadIdx.x; v < v1 - v0; v += WG) {
                         double t = 0.0;
@@ -240,17 +244,10 @@ __global__ __launch_bounds__(WG) void k_solo(SoloArgs<T> a)
                     __syncthreads();
                 }
                 // 3. evaluated, all of the thread's particles by the same coefficients
-                double pr[P], pi[P];
+                if (mode_anchored<T, WIDE>(d)) mode_eval_anchored<P>(d, g, ys, pair);
+                else mode_eval<P>(d.M, g, zr, zi, pair);
 #pragma unroll
-                for (int p = 0; p < P; ++p) pr[p] = pi[p] = 0.0;
-#pragma unroll 4
-                for (int m = d.M - 1; m >= 0; --m) {
-                    const double2 gm = g[m];
-#pragma unroll
-                    for (int p = 0; p < P; ++p) horner(pr[p], pi[p], zr[p], zi[p], gm);
-                }
-#pragma unroll
-                for (int p = 0; p < P; ++p) pair[p] = fma(pr[p], zr[p], -pi[p] * zi[p]) * S.pair_scale;
+                for (int p = 0; p < P; ++p) pair[p] *= S.pair_scale;
             } else {
                 // direct sums over the positions in LDS
                 T* src = reinterpret_cast<T*>(&rows[0][0]);
