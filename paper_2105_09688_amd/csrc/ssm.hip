@@ -334,8 +334,9 @@ struct ssm_ctx {
     bool mode_totals = false;       // the rows are added up by k_mode_total
     ModeItem* dmitems = nullptr;    // per phase (pair_off / pair_cnt)
     ModeDom* dom = nullptr;         // [n_sys] the tick's domains
-    double* mode_part = nullptr;    // [kModeVals / 16][mode_rows][16] (mode_at)
-    double* mode_tot = nullptr;     // [n_sys][kModeVals] (mode_totals)
+    int mode_vals = kModeVals;      // values of a partial row
+    double* mode_part = nullptr;    // [mode_vals / 16][mode_rows][16] (mode_at)
+    double* mode_tot = nullptr;     // [n_sys][mode_vals] (mode_totals)
     int direct_Q = 1;               // shares of the sources of direct sums
     float2* rng = nullptr;          // [nblk_tot] range of the scaled positions of each block
     bool grid_ok = false;           // one large system in two or three dimensions
@@ -825,7 +826,7 @@ static ssm_status launch_window(ssm_ctx* c, int64_t t0, const int64_t* tdev)
     return SSM_OK;
 }
 
-static DirectRows direct_rows(const ssm_ctx* c) { return DirectRows{c->mode_part, kBlk * c->mode_P, c->direct_Q}; }
+static DirectRows direct_rows(const ssm_ctx* c) { return DirectRows{c->mode_part, kBlk * c->mode_P, c->direct_Q, c->mode_vals}; }
 
 // The tick's mode sums (d = 1): the partial rows, with the Brownian sums and
 // the means of mu^Y in the same launch, and their totals.
@@ -840,7 +841,7 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, int64_t targ, const int64
 #define SSM_MODES_K(KERNEL)                                                                                            \
     hipLaunchKernelGGL(KERNEL, dim3((unsigned)(n_main + job.n + nm * (Q - 1))), dim3(kBlk), 0, c->stream, nm, Q, n_main,  \
                        c->one, (const ModeItem*)c->dmitems + c->pair_off[ph], items, c->dsys, c->coef, c->P, (const T*)c->Ys,  \
-                       (const float2*)c->rng, c->dom, c->mode_part, c->mode_rows, targ, tdev,               \
+                       (const float2*)c->rng, c->dom, c->mode_part, c->mode_rows, c->pairsum, targ, tdev,               \
                        (const double*)c->win, c->dW, job)
 #define SSM_MODES(PV, LPV, ONE)                                                            \
     do {                                                                                   \
@@ -867,7 +868,7 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, int64_t targ, const int64
     if (c->mode_totals) {
         hipLaunchKernelGGL(k_mode_total, dim3((unsigned)c->sys_list_cnt[ph], 4), dim3(kBlk), 0, c->stream,
                            c->dsys_list + c->sys_list_off[ph], c->dsys, (const ModeDom*)c->dom,
-                           (const double*)c->mode_part, c->mode_rows, c->mode_tot);
+                           (const double*)c->mode_part, c->mode_rows, c->mode_vals, c->mode_tot);
         HIP_TRY(hipGetLastError());
     }
     return SSM_OK;
@@ -1290,21 +1291,26 @@ static bool small_preferred(const ssm_ctx* c)
 // configuration, so that the way does not depend on the state and a resumed run
 // follows, that is the range of N normal draws of x0_std (Y* is no wider while
 // v pulls inward).  Tick times in microseconds, fits to one context's ticks from
-// N = 300 to 131072 and 11 to 800 modes M, both precisions within 15 %:
-//   one workgroup a system  3.4 + 0.0016 N + M (0.06 + 6.6e-5 N)
-//   two launches a tick     9 + 8e-5 N + 0.11 M (longer past 2^18 particles)
-//   pair kernels            FP64 30 + 2.9e-7 N^2, FP32 15 + 8.2e-8 N^2
+// N = 300 to 131072 and 11 to 800 modes M, and to 64 to 20000 systems of 50 to
+// 2000 particles, mostly within 20 %:
+//   one workgroup a system  3.4 + 0.0016 N + M (0.06 + 6.6e-5 N), and a system
+//                           (0.005 + 3.2e-5 N) (0.6 + 0.025 M)
+//   two launches a tick     9 + 0.11 M (longer past 2^18 particles), a system
+//                           0.015 + 8e-5 N
+//   pair kernels            FP64 30, a system 0.007 + 1.4e-4 N + 2.9e-7 N^2
+//                           FP32 15, a system 0.005 + 7e-5 N + 8.2e-8 N^2
 //   tiled kernel            small_estimate
 // FP32 N = 2048: 31 us at 100 modes against 12; N = 8191: 76 at 600 against 23;
 // N = 2^16: 92 at 650 against 369.
 static bool modes_pay(ssm_ctx* c, const ssm_config* cfg, double coord_scale)
 {
     const bool f64 = c->prec == SSM_FP64;
-    double top = 0.0, sum = 0.0, sum2 = 0.0;
+    double top = 0.0, num = 0.0, sum = 0.0, sum2 = 0.0;  // of a tick
     int64_t ntiles = 0;
     for (auto& S : c->sys) {
         ntiles += (S.N + kSmallTile - 1) / kSmallTile;
         top = std::max(top, (double)S.N);
+        num += 1.0 / (double)S.stride;
         sum += (double)S.N / (double)S.stride;
         sum2 += (double)S.N * (double)S.N / (double)S.stride;
     }
@@ -1315,14 +1321,15 @@ static bool modes_pay(ssm_ctx* c, const ssm_config* cfg, double coord_scale)
     const double M = std::ceil(m / kModeChunk) * kModeChunk;
     c->mode_wide = f64 && M > 0.5 * kModePlain;
     const bool solo = cfg->persistent == 0 && top <= kSoloMax;
-    const double solos = std::max(1.0, (double)c->sys.size() / 256.0);
     const double cap = solo ? solo_cap((int32_t)top, f64) : mode_cap((int32_t)top, f64);
     if (!(m <= 0.9 * cap)) return false;  // a NaN too
-    const double by_modes = solo ? solos * (3.4 + 0.0016 * top + M * (0.06 + 6.6e-5 * top))
-                                 : 9.0 + 8e-5 * sum + 0.11 * M * std::max(1.0, sum / 262144.0);
+    const double by_modes = solo ? 3.4 + 0.0016 * top + M * (0.06 + 6.6e-5 * top) +
+                                       (c->sys.size() > 1 ? (0.005 * num + 3.2e-5 * sum) * (0.6 + 0.025 * M) : 0.0)
+                                 : 9.0 + 0.015 * num + 8e-5 * sum + 0.11 * M * std::max(1.0, sum / 262144.0);
     double pers = 0.0, multi = 0.0;
     small_estimate(c, &pers, &multi);
-    const double by_pairs = f64 ? 30.0 + 2.9e-7 * sum2 : 15.0 + 8.2e-8 * sum2;
+    const double by_pairs = f64 ? 30.0 + 0.007 * num + 1.4e-4 * sum + 2.9e-7 * sum2
+                                : 15.0 + 0.005 * num + 7e-5 * sum + 8.2e-8 * sum2;
     const bool tiled = cfg->persistent >= 0 && pers < multi;
     if (by_modes <= by_pairs && (!tiled || by_modes <= pers)) return true;
     const bool tiled_ok = tiled && ntiles <= device_cus() && small_ineligible(c, ntiles).empty();
@@ -1754,8 +1761,12 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
                 (void)hipGetLastError();
                 khz = 100000;  // the 100 MHz counter of gfx9
             }
-            // a launch's increments in 24 MiB (at least 16 ticks of them)
-            c->solo_ticks = std::min<int64_t>(std::max<int64_t>(((int64_t)24 << 20) / (8 * c->P), 16), kSmallTicksPerLaunch);
+            // a launch's increments in 24 MiB, in up to 64 for 16 ticks of them, and
+            // two ticks at least (20000 systems of 50, FP32: 123 us a tick with 16 in a
+            // launch, 180 with one; sixteen took 640 MB there)
+            const int64_t per_tick = 8 * c->P;
+            c->solo_ticks = std::max(((int64_t)24 << 20) / per_tick, std::min<int64_t>(16, ((int64_t)64 << 20) / per_tick));
+            c->solo_ticks = std::min(std::max<int64_t>(c->solo_ticks, 2), kSmallTicksPerLaunch);
             c->solo_ticks = std::min(c->solo_ticks, c->ticks_total);
             c->small_wait_limit = (int64_t)khz * 1000 * 4;  // 4 s per barrier wait
             if (const char* env = std::getenv("SSM_PERSISTENT_WAIT_US")) {
@@ -1787,6 +1798,15 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         // (N = 2^16 FP32 1.62 ms, 0.66 with two; FP64 2.95 and 2.65), but their
         // blocks cost every tick by modes 0.4 of 7 us
         c->direct_Q = c->mode_rows < 256 ? (int)std::min<int64_t>(512 / c->mode_rows, 8 / c->mode_P) : 1;
+        // a row holds the modes of the largest system or the shares of a row's
+        // direct sums, in whole rounds of mode_coefs (64) and of the totals' reader (256); with
+        // kModeVals each, many small systems took 16 KB more than their particles
+        c->mode_vals = kBlk;
+        for (auto& S : c->sys) {
+            const int per = kBlk * c->mode_P, direct = c->direct_Q > 1 ? c->direct_Q * per : 0;
+            c->mode_vals = std::max(c->mode_vals, std::max(direct, mode_vals((int32_t)S.N, c->prec == SSM_FP64)));
+        }
+        c->mode_vals = (c->mode_vals + 63) / 64 * 64;
     }
 
     // work lists per phase
@@ -1884,8 +1904,8 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     if (c->modes) {
         ALLOC(c->dmitems, mitems.size() * sizeof(ModeItem));
         ALLOC(c->dom, c->sys.size() * sizeof(ModeDom));
-        ALLOC(c->mode_part, (size_t)c->mode_rows * kModeVals * sizeof(double));
-        if (c->mode_totals) ALLOC(c->mode_tot, c->sys.size() * kModeVals * sizeof(double));
+        ALLOC(c->mode_part, (size_t)c->mode_rows * c->mode_vals * sizeof(double));
+        if (c->mode_totals) ALLOC(c->mode_tot, c->sys.size() * c->mode_vals * sizeof(double));
         ALLOC(c->rng, (size_t)c->nblk_tot * sizeof(float2));
     }
     ALLOC(c->dblk, blks.size() * sizeof(BlkItem));

@@ -41,7 +41,7 @@ namespace ssm {
 
 constexpr int kModeChunk = 8;                  // modes between reductions over a wavefront
 constexpr int kModeCap = 1024;                 // modes of a system at most
-constexpr int kModeVals = 2 * kModeCap;        // values of a partial row: per chunk C_m x 8, S_m x 8
+constexpr int kModeVals = 2 * kModeCap;        // values of a partial row at most: per chunk C_m x 8, S_m x 8
 constexpr double kModeAlpha = 0.69314718055994530942;  // a = ln 2
 constexpr double kTwoPi = 6.283185307179586476925286766559;
 
@@ -269,9 +269,9 @@ __device__ __forceinline__ double mode_direct(const SysDev& S, const T* __restri
 // enough for the 64 modes that almost every cloud stays below; rows 16 doubles
 // further apart than that, so that two of them meet no bank twice), added in
 // a fixed order.  A system without modes gets its particles' direct sums here
-// instead, each of the Q blocks of a row its share of the sources, in the row's
-// own place (value q 256 P + j for particle j; Q P <= 8, so that they fit): the
-// kernel that evaluates also moves the particles.
+// instead, in pairsum, or, each of Q > 1 blocks of a row its share of the
+// sources, in the row's own place (value q 256 P + j for particle j; Q P <= 8, so
+// that they fit): the kernel that evaluates also moves the particles.
 // ---------------------------------------------------------------------------
 constexpr int kRowVals = 128;
 constexpr int kModeRowsLds = kBlk / 16;  // rows of 16 lanes in a block
@@ -279,7 +279,8 @@ constexpr int kModeRowsLds = kBlk / 16;  // rows of 16 lanes in a block
 template <typename T, int P, bool WIDE>
 __device__ __forceinline__ void mode_block(const ModeItem& it, const SysDev& S, const T* __restrict__ Ys,
                                            const float2* __restrict__ rng, ModeDom* __restrict__ dom,
-                                           double* __restrict__ part, int64_t nrows_tot, int q, int Q)
+                                           double* __restrict__ part, int64_t nrows_tot, int q, int Q,
+                                           double* __restrict__ pairsum)
 {
     __shared__ __align__(32) double rows[kModeRowsLds][kRowVals + 16];
     static_assert(sizeof(rows) >= kDirectTile * sizeof(T), "the direct sums stage their sources there");
@@ -299,7 +300,9 @@ __device__ __forceinline__ void mode_block(const ModeItem& it, const SysDev& S, 
             const int j = p * kBlk + (int)threadIdx.x;
             const T ys = j < it.n ? Ys[S.off + it.i0 + j] : (T)0;
             const double K = mode_direct(S, Ys, ys, q, Q, reinterpret_cast<T*>(&rows[0][0]));
-            if (j < it.n) part[mode_at(it.row, q * kBlk * P + j, nrows_tot)] = K;
+            if (j >= it.n) continue;
+            if (Q == 1) pairsum[S.off + it.i0 + j] = K * S.pair_scale;
+            else part[mode_at(it.row, q * kBlk * P + j, nrows_tot)] = K;
         }
         return;
     }
@@ -340,18 +343,19 @@ __global__ __launch_bounds__(kBlk) void k_modes(int n_modes, int Q, int n_main, 
                                                 Coef cf, int64_t Pn, const T* __restrict__ Ys,
                                                 const float2* __restrict__ rng, ModeDom* __restrict__ dom,
                                                 double* __restrict__ part, int64_t nrows_tot,
-                                                int64_t tick_arg, const int64_t* __restrict__ tick_dev,
-                                                const double* __restrict__ win, double* __restrict__ dW, YMeanJob job)
+                                                double* __restrict__ pairsum, int64_t tick_arg,
+                                                const int64_t* __restrict__ tick_dev, const double* __restrict__ win,
+                                                double* __restrict__ dW, YMeanJob job)
 {
     const int more = (int)blockIdx.x - (n_main + job.n);
     if ((int)blockIdx.x < n_modes || more >= 0) {
         const int q = more >= 0 ? 1 + more / n_modes : 0, row = more >= 0 ? more % n_modes : (int)blockIdx.x;
         if constexpr (ONE) {
             const int i0 = row * kBlk * P;
-            mode_block<T, P, WIDE>(ModeItem{0, row, i0, min(kBlk * P, one.N - i0)}, one, Ys, rng, dom, part, nrows_tot, q, Q);
+            mode_block<T, P, WIDE>(ModeItem{0, row, i0, min(kBlk * P, one.N - i0)}, one, Ys, rng, dom, part, nrows_tot, q, Q, pairsum);
         } else {
             const ModeItem it = mitems[row];
-            mode_block<T, P, WIDE>(it, sys[it.sys], Ys, rng, dom, part, nrows_tot, q, Q);
+            mode_block<T, P, WIDE>(it, sys[it.sys], Ys, rng, dom, part, nrows_tot, q, Q, pairsum);
         }
     } else if ((int)blockIdx.x < n_main)
         brownian_block<1, LP, (sizeof(T) == 4)>(blockIdx.x - n_modes, items, sys, cf, Pn, tick_arg, tick_dev, win, dW);
@@ -394,12 +398,12 @@ __device__ __forceinline__ void add_batch(const RowBatch& b, int r0, int nrows, 
 }
 
 // k_mode_total: the rows of each listed system added up once, into one row of
-// `tot` per system, 16 values at a time by 16 threads each.  Launched where
+// `tot` per system (`vals` apart), 16 values at a time by 16 threads each.  Launched where
 // the blocks of k_update_modes would together read many more rows than the
 // systems have.
 __global__ __launch_bounds__(kBlk) void k_mode_total(const int32_t* __restrict__ sys_list, const SysDev* __restrict__ sys,
                                                      const ModeDom* __restrict__ dom, const double* __restrict__ part,
-                                                     int64_t nrows_tot, double* __restrict__ tot)
+                                                     int64_t nrows_tot, int vals, double* __restrict__ tot)
 {
     __shared__ double stage[kBlk / 16][16];
     const int s = sys_list[blockIdx.x];
@@ -424,7 +428,7 @@ __global__ __launch_bounds__(kBlk) void k_mode_total(const int32_t* __restrict__
             double t = 0.0;
 #pragma unroll
             for (int u = 0; u < kBlk / 16; ++u) t += stage[u][l];
-            tot[(int64_t)s * kModeVals + v0 + l] = t;
+            tot[(int64_t)s * vals + v0 + l] = t;
         }
         __syncthreads();
     }
@@ -531,12 +535,18 @@ struct ModeLds {
     double stage[TOTALS ? 1 : kBlk / 16][kCoefVals];
 };
 
-// Where the direct sums of a context lie: its partial rows, of `per` particles,
-// Q shares each.
+// Where the shares of direct sums of a context lie: its partial rows, of `per`
+// particles, Q > 1 shares each; `vals` values from one row of totals to the next.
 struct DirectRows {
     const double* part;
-    int per, Q;
+    int per, Q, vals;
 };
+
+// Values of a partial row that hold the sums of a system of N particles.
+__host__ __device__ constexpr int mode_vals(int32_t N, bool fp64)
+{
+    return (mode_cap(N, fp64) + kModeChunk - 1) / kModeChunk * 2 * kModeChunk;
+}
 
 // The scaled pair term of particle i of a system without modes: the shares added up.
 __device__ __forceinline__ double direct_pair(const DirectRows& dr, const SysDev& S, int i, int64_t nrows_tot)
@@ -559,13 +569,9 @@ __device__ __forceinline__ double mode_pair(const BlkItem it, const SysDev& S, c
     const T ys = Ys[at];
     double zr, zi;
     if constexpr (TOTALS) {
-        const double* row = part + (int64_t)it.sys * kModeVals;
+        const double* row = part + (int64_t)it.sys * dr.vals;
         double a = row[threadIdx.x];
-        if (d.M == 0) {  // block-uniform
-            const double K = direct_pair(dr, S, min(i, S.N - 1), nrows_tot);
-            if (i < S.N) pairsum[at] = K;
-            return K;
-        }
+        if (d.M == 0) return pairsum[at];  // block-uniform; contexts with totals have Q = 1
         for (int v = threadIdx.x; v < 2 * d.M; v += kBlk) {
             if (v >= kBlk) a = row[v];
             mode_coef(d, v, a, lds.g);
@@ -575,6 +581,7 @@ __device__ __forceinline__ double mode_pair(const BlkItem it, const SysDev& S, c
     } else {
         const RowBatch first = row_batch(part, nrows_tot, S, 0, threadIdx.x >> 4);
         if (d.M == 0) {
+            if (dr.Q == 1) return pairsum[at];
             const double K = direct_pair(dr, S, min(i, S.N - 1), nrows_tot);
             if (i < S.N) pairsum[at] = K;
             return K;
