@@ -7,14 +7,17 @@ workload shape, precision and GPU architecture ($SSM_TUNE_CACHE, default
 ~/.cache/ssm_tune.json).  Results do not depend on the tiling beyond
 floating-point summation order (tested), so any cached choice is safe.
 
-The tuner chooses among tilings of the pair kernels.  In one dimension a
-context with no tiling given sums the interaction by its modes and beats all
-of them; tiling arguments bring the pair kernels back.
+A tiling asks for the pair kernels, and a context without one may have faster
+ways (modes in one dimension, the grid, one launch for small systems).  So the
+best tiling is timed against a context without any: the choice's "kwargs" are
+what to pass to SSM, empty where no tiling is the faster, beside the best tiling
+of the pair kernels itself.
 """
 from __future__ import annotations
 
 import json
 import os
+import time
 
 from .ssm import SSM
 
@@ -73,9 +76,24 @@ def measure(workload: dict, precision: str, cand: dict, stream=None, steps: int 
     return (i["pair_ms"] + i["update_ms"]) / max(1, i["pair_launches"])
 
 
+def tick_ms(workload: dict, precision: str, stream=None, steps: int = 24, **tiling) -> float:
+    """Time (ms) of a tick of a context with `tiling`, as a program steps it."""
+    with SSM(workload, precision=precision, stream=stream, **tiling) as s:
+        n = max(1, min(steps, (s.info()["ticks_total"] - 1) // 2))
+        best = float("inf")
+        for _ in range(2):  # the first call makes what the second one reuses
+            t = time.perf_counter()
+            s.step(n)
+            s.sync()
+            best = min(best, (time.perf_counter() - t) * 1e3 / n)
+    return best
+
+
 def autotune(workload: dict, precision: str = "fp32_kahan", stream=None, steps: int = 24,
              use_cache: bool = True, verbose: bool = False) -> dict:
-    """Best tiling for `workload`: {"targets_per_lane", "sources_per_item", "pair_scheme"}."""
+    """Best tiling of the pair kernels for `workload` ("targets_per_lane", "sources_per_item",
+    "pair_scheme", "tick_ms") and what to pass to SSM ("kwargs": that tiling, or nothing where a context
+    without one is the faster; "default_tick_ms", "tiled_tick_ms": both as timed)."""
     key = _key(workload, precision)
     path = _cache_path()
     cache = {}
@@ -85,7 +103,7 @@ def autotune(workload: dict, precision: str = "fp32_kahan", stream=None, steps: 
                 cache = json.load(fh)
         except (OSError, ValueError):
             cache = {}
-        if key in cache:
+        if "kwargs" in cache.get(key, {}):  # older entries do not know the default's time
             return cache[key]
     best, best_ms = None, float("inf")
     for cand in candidates(workload["d"], precision):
@@ -96,6 +114,10 @@ def autotune(workload: dict, precision: str = "fp32_kahan", stream=None, steps: 
             best_ms, best = ms, cand
     choice = {"targets_per_lane": best["targets_per_lane"], "sources_per_item": best["sources_per_item"],
               "pair_scheme": best["pair_scheme"], "tick_ms": best_ms}
+    tiling = {k: choice[k] for k in ("targets_per_lane", "sources_per_item", "pair_scheme")}
+    choice["default_tick_ms"] = tick_ms(workload, precision, stream=stream, steps=steps)
+    choice["tiled_tick_ms"] = tick_ms(workload, precision, stream=stream, steps=steps, **tiling)
+    choice["kwargs"] = tiling if choice["tiled_tick_ms"] < choice["default_tick_ms"] else {}
     cache[key] = choice
     try:
         os.makedirs(os.path.dirname(path), exist_ok=True)
