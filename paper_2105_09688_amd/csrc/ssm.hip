@@ -835,11 +835,11 @@ static ssm_status launch_modes(ssm_ctx* c, int64_t ph, int64_t targ, const int64
 {
     const BlkItem* items = c->dblk + c->blk_off[ph];
     const int nm = (int)c->pair_cnt[ph], Q = c->direct_Q;
-    const int n_main = nm + (sums_only ? 0 : (int)(c->blk_cnt[ph] * c->bm_lanes[ph]));
+    const int n_main = nm * Q + (sums_only ? 0 : (int)(c->blk_cnt[ph] * c->bm_lanes[ph]));
     const YMeanJob job{c->dsys_list + c->sys_list_off[ph],
                        c->needs_ybar && !sums_only ? (int)c->sys_list_cnt[ph] : 0, c->psumY, c->nblk_tot, c->ymean};
 #define SSM_MODES_K(KERNEL)                                                                                            \
-    hipLaunchKernelGGL(KERNEL, dim3((unsigned)(n_main + job.n + nm * (Q - 1))), dim3(kBlk), 0, c->stream, nm, Q, n_main,  \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)(n_main + job.n)), dim3(kBlk), 0, c->stream, nm, Q, n_main,  \
                        c->one, (const ModeItem*)c->dmitems + c->pair_off[ph], items, c->dsys, c->coef, c->P, (const T*)c->Ys,  \
                        (const float2*)c->rng, c->dom, c->mode_part, c->mode_rows, c->pairsum, targ, tdev,               \
                        (const double*)c->win, c->dW, job)
@@ -1658,10 +1658,10 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
     if (c->modes) c->modes = modes_pay(c, cfg, cf.coord_scale);  // clouds drawn wide keep the pair kernels
     // one system in three dimensions by way of a grid, from the size on where
     // that is faster.  A tick, pair kernels against grid: FP32 N = 16384 91 and
-    // 105 us, 20000 119 and 106, 2^18 14.1 ms and 225 us; FP64 N = 20000 257 and
-    // 241 us, 24000 340 and 245, 50021 1350 and 265.  In two dimensions once
+    // 105 us, 20000 119 and 111, 2^18 14.1 ms and 229 us; FP64 N = 20000 259 and
+    // 249 us, 24000 334 and 251, 50021 1340 and 272.  In two dimensions once
     // the surrogate has been turned on (grid_for_exact), for its checks (FP32 N = 20000 88 and 98 us,
-    // 24000 115 and 98, 2^16 629 and 107; FP64 N = 24000 276 and 193); without
+    // 24000 116 and 102, 2^16 630 and 112; FP64 N = 24000 272 and 197); without
     // one the pair kernels stay there, as the exact method that the surrogate's
     // gain is held against
     c->grid_ok = c->has_pair && !c->kpair && c->sys.size() == 1 && cfg->targets_per_lane == 0 && cfg->sources_per_item == 0 &&

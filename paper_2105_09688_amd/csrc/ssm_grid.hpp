@@ -880,11 +880,11 @@ __global__ __launch_bounds__(GridWin<float>::gather_wg) void k_grid_gather8(Grid
 }
 
 // W = 16: a field at a time in 97 KB, 16 lanes a particle, one for each z.  A
-// lane keeps its three weights of each of its particles.  N = 50021: 152 us of
-// a tick with 14 nodes in two workgroups a compute unit, 238 here (one trace),
-// the tick 245 and 272.  Chunks of 128 and 64, a field's chunk as a work item of
-// its own, the next field's nodes read ahead, and 32 lanes a particle without
-// bank conflicts were all slower or the same: staging and waiting bound it.
+// lane keeps its three weights of each of its particles.  N = 50021: 231 us of a
+// tick of 280; with 14 nodes and two workgroups a compute unit 152 of 250 (same
+// trace).  Chunks of 128 and 64, a field's chunk as a work item of its own, the
+// next field's nodes read ahead, and 32 lanes a particle without bank conflicts
+// were all slower or the same: staging and waiting bound it.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(GridWin<double>::gather_wg) void k_grid_gather16(GridArgs g, int64_t nodes)
 {
