@@ -75,7 +75,7 @@ def test_no_slower_than_the_pair_kernels(n_sys, N, precision):
             s.step(72)
             s.sync()
             best = 1.0
-            for _ in range(3):
+            for _ in range(6):
                 t = time.perf_counter()
                 s.step(16)
                 s.sync()
