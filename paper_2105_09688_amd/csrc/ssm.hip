@@ -1794,9 +1794,10 @@ extern "C" ssm_status ssm_init(const ssm_config* cfg, ssm_ctx** out)
         c->mode_totals = reads > 2 * 65536;
         // direct sums on two workgroups a compute unit while the rows alone are
         // fewer than the compute units (FP32 N = 16384 57 us with eight shares, 120
-        // with four).  From 256 rows on one share: two or four make them faster too
-        // (N = 2^16 FP32 1.62 ms, 0.66 with two; FP64 2.95 and 2.65), but their
-        // blocks cost every tick by modes 0.4 of 7 us
+        // with four; a tick by modes 13.6 at N = 8191, 13.3 with one share).  From
+        // 256 rows on one share: two or four make them faster too (N = 2^16 FP32
+        // 1.62 ms, 0.66 with two; FP64 2.95 and 2.65), but their blocks cost every
+        // tick by modes 0.4 of 7 us
         c->direct_Q = c->mode_rows < 256 ? (int)std::min<int64_t>(512 / c->mode_rows, 8 / c->mode_P) : 1;
         // a row holds the modes of the largest system or the shares of a row's
         // direct sums, in whole rounds of mode_coefs (64) and of the totals' reader (256); with
